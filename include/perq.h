@@ -338,8 +338,8 @@ perq_status_t perq_quant_error(const float* y, int64_t T, int32_t d, const uint8
  *   a_codes  device, uint8 [T, d/2], 16-byte aligned;   a_scales  device, float [T]
  *   w_codes  device, uint8 [N, d/2], 16-byte aligned;   w_scales  device, float [N]
  *   out      device, float [T, ldo], ldo >= N
- * The integer sums are exact; the two multiplications are fp32, left to right.  A plain integer
- * kernel for checking the layout end to end, not a tuned GEMM.  T == 0 or N == 0 does nothing.
+ * The integer sums are exact; the two multiplications are fp32, left to right.  Runs on the int8
+ * matrix instruction (nibbles unpacked in registers).  T == 0 or N == 0 does nothing.
  */
 perq_status_t perq_w4a4_gemm_ref(const uint8_t* a_codes, const float* a_scales, int64_t T,
                                  const uint8_t* w_codes, const float* w_scales, int32_t N, int32_t d,
@@ -356,8 +356,8 @@ perq_status_t perq_w4a4_gemm_ref(const uint8_t* a_codes, const float* a_scales, 
  *   out      device, float [T, ldo], ldo >= N
  * Runs on gfx950's scaled matrix instruction (v_mfma_scale_f32_32x32x64_f8f6f4, fp4 x fp4), which
  * takes a 32-group of packed codes and its scale byte exactly as the fused path writes them: the
- * products are exact, the sums are fp32 in the unit's own order.  A checker of the layout, not a
- * tuned GEMM.  d % 32 == 0; T == 0 or N == 0 does nothing.
+ * products are exact, the sums are fp32 in an order of the kernel's own that depends on the sizes only.
+ * d % 32 == 0; T == 0 or N == 0 does nothing.
  */
 perq_status_t perq_w4a4_mxfp4_gemm_ref(const uint8_t* a_codes, const uint8_t* a_scales, int64_t T,
                                        const uint8_t* w_codes, const uint8_t* w_scales, int32_t N, int32_t d,

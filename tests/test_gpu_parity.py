@@ -452,6 +452,40 @@ def test_w4a4_mxfp4_gemm_on_the_scaled_matrix_unit(T, N, d, b):
     assert np.corrcoef(out.ravel(), (X @ Wt.T).ravel())[0, 1] > 0.97
 
 
+# every branch of the products' choice of tile, each at ragged edges of rows, columns and contraction
+@pytest.mark.parametrize("T,N,d", [(1, 1, 32), (3, 70, 96),                          # one stage, one wave per tile
+                                   (33, 70, 128), (5, 3, 1056), (64, 130, 4096),      # few tiles: contraction cut among waves
+                                   (31, 65, 8224),                                    # the same sizes, long rows
+                                   (513, 700, 1024), (449, 577, 2880),                # 64 x 64 tiles
+                                   (1540, 1537, 1312), (1700, 1300, 544),             # 128 x 128
+                                   (2177, 2177, 416), (2060, 2177, 2080)])            # 128 x 128 twice a CU; 128 x 256
+@pytest.mark.parametrize("fmt", ["int4", "mxfp4"])
+def test_w4a4_products_over_tiles_and_remainders(T, N, d, fmt):
+    torch = _torch()
+    print(f"[case] product {fmt} T={T} N={N} d={d}", flush=True)
+    rng = np.random.default_rng(T + 3 * N + d)
+    codes = lambda n: rng.integers(0, 256, size=(n, d // 2), dtype=np.uint8)           # all sixteen codes, -8 among them
+    nib = lambda c: np.stack([c & 15, c >> 4], axis=2).reshape(c.shape[0], d)
+    ca, cw = codes(T), codes(N)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    out = torch.full((T, N + 3), 7.5, device="cuda")                                  # rows further apart than they are wide
+    if fmt == "int4":
+        sa, sw = (rng.uniform(0.01, 2.0, size=n).astype(np.float32) for n in (T, N))
+        binding.perq_w4a4_gemm_ref(dev(ca), dev(sa), dev(cw), dev(sw), out=out[:, :N])
+        val = lambda c: ((nib(c).astype(np.int64) ^ 8) - 8).astype(np.float64)
+        acc = val(ca) @ val(cw).T                                                     # exact: below 2^53
+        want = (acc.astype(np.float32) * sa[:, None] * sw[None, :]).astype(np.float32)  # (the sums are below 2^24)
+        assert np.array_equal(out[:, :N].cpu().numpy(), want)
+    else:
+        ea, ew = (rng.integers(110, 140, size=(n, d // 32), dtype=np.uint8) for n in (T, N))
+        binding.perq_w4a4_mxfp4_gemm_ref(dev(ca), dev(ea), dev(cw), dev(ew), out=out[:, :N])
+        a, w = orc.dequant_mxfp4(nib(ca), ea), orc.dequant_mxfp4(nib(cw), ew)
+        got = out[:, :N].cpu().numpy().astype(np.float64)
+        # exact products; d fp32 additions, each off by at most 2^-24 of the sum of magnitudes
+        assert np.all(np.abs(got - a @ w.T) <= d * 2.0 ** -24 * (np.abs(a) @ np.abs(w).T))
+    assert bool((out[:, N:] == 7.5).all())
+
+
 def test_w4a4_gemm_argument_checks():
     torch = _torch()
     a = torch.zeros((4, 16), dtype=torch.uint8, device="cuda")
