@@ -118,9 +118,9 @@ perq_status_t dispatch(const ApplyParams& p, int out_kind, perq_algo_t algo, hip
     }
     switch (algo) {
         case PERQ_ALGO_AUTO:
-            // The matrix-core kernel wins wherever its 4096-wide wave tiles are filled (measured:
-            // rocprofv3 summaries under profiles/); b > 4096 on rows of 8192, 16384 or 32768 goes to the
-            // chunked matrix-core kernel; other narrow rows and odd widths take the butterflies.
+            // The matrix-core kernel wins where its 4096-wide wave tiles are filled and the launch is long
+            // enough for its set-up (mfma_preferred); b > 4096 on rows of 8192, 16384 or 32768 goes to the
+            // chunked matrix-core kernel; the rest takes the butterflies.
             if (chunked_pow2_supports(p)) e = launch_npo2_32(p, out_kind, stream);
             else e = mfma_preferred(p, out_kind) ? launch_mfma(p, out_kind, stream) : launch_butterfly(p, out_kind, stream);
             break;
@@ -175,7 +175,7 @@ perq_status_t quant_entry(const uint16_t* x_bf16, int64_t T, int32_t d, int64_t 
     // 8192: + 1 - 1.5 %), so those stay in the fixed layout (layout::placement_applies, which the
     // tables follow).
     if (prepared != nullptr && perm != nullptr && algo == PERQ_ALGO_AUTO && d >= 4096 && d % 512 == 0 && is_pow2(b) &&
-        b >= 16 && b <= 4096 && mfma_supports(p)) {
+        b >= 16 && b <= 4096 && mfma_preferred(p, out_kind)) {
         // [int32 place of the channel of every position][uint16 granule of every slot][uint16 lane tables]
         const int32_t* places = static_cast<const int32_t*>(prepared);
         if (layout::placement_applies(d)) {

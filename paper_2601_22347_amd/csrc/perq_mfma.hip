@@ -1297,11 +1297,42 @@ static bool folds(const ApplyParams& p, int out_kind) {
            p.T >= kTile / p.d;
 }
 
+// Which of the two general kernels takes a call.  The choice must not depend on whether a permutation
+// came with its prepared form (the outputs of the two calls agree bit for bit).  Every line was measured
+// on both sides, launches back to back on one GPU, butterfly / this kernel in us (with a permutation:
+// the prepared form where there is one):
+//   Rows of 2560, 3072, 3584 fill 5/8 of a wave tile and more.  T = 32768, d = 3072, b = 128, INT4: 74 / 44
+//     (P = I), 83 / 51 (permutation); T = 4001 with a permutation, asymmetric INT4: 14.7 / 13.0.  Narrower
+//     rows that cannot be folded leave too much of the tile empty (d = 2048, b = 128: 39 / 37, d = 1024:
+//     21 / 31), but for the large blocks of d = 2048 on long launches (T = 32768, b = 2048: 59 / 47).
+//   Few rows: this kernel's set-up (operand tables, two staging buffers) is not paid back.
+//     P = I, T = 16: d = 4096, b = 128 3.8 / 4.7; d = 8192, b = 32 3.9 / 5.8; d = 8192, b = 4096 5.6 / 9.0.
+//       The two meet at 2^22 elements (d = 4096, b = 128, T = 1024: 5.1 / 5.2; T = 2048: 7.1 / 6.5), for
+//       b <= 32, with five stages fewer in the butterflies, and for b >= 1024, whose operand addresses cost
+//       this kernel 3 us, at 2^23 (d = 4096, b = 16: T = 2048 5.8 / 6.1, T = 8192 17.8 / 16.2; d = 8192,
+//       b = 4096: T = 1024 10.8 / 11.1, T = 2048 20.8 / 16.4).
+//     With a permutation: d = 8192, b = 32, T = 16 5.2 / 7.2, T = 256 5.2 / 7.1, T = 1024 9.4 / 8.9;
+//       d = 14336, b = 128, T = 256 7.6 / 8.6, T = 1024 17.5 / 13.7: the line is 2^22 elements.  The tile of
+//       d = 4096 and of folded rows builds its operand table once for four waves: T = 512, b = 64 5.3 / 5.7,
+//       T = 1024 7.0 / 5.8, and for b >= 1024 it is always ahead (T = 16, b = 4096: 6.5 / 6.3).  b >= 1024 on
+//       wider rows: d = 6144, b = 2048, T = 256 6.0 / 7.7, T = 512 8.0 / 7.7; d = 16384, b = 4096 9.2 / 9.0.
+//       Rows wider than 16384 need workgroups of 1024 lanes there: T = 16, d = 28672 11.8 / 9.1.
 bool mfma_preferred(const ApplyParams& p, int out_kind) {
     if (!mfma_supports(p)) return false;
-    if (p.d >= kTile) return true;            // its 4096-wide wave tiles are filled
-    // folded narrow rows: ahead from b = 128 on, and for any b once the launch is long
-    return folds(p, out_kind) && (p.b >= 128 || p.T * (int64_t)p.d >= ((int64_t)1 << 26));
+    const int64_t n = p.T * (int64_t)p.d;
+    const bool folded = folds(p, out_kind), large = p.b >= 1024;
+    if (folded) {
+        if (p.b < 128 && n < ((int64_t)1 << 26)) return false;      // folded narrow rows: ahead from b = 128 on, and for any b once the launch is long
+    } else if (p.d < 2560) {
+        if (!(p.d == 2048 && large && n >= ((int64_t)1 << 25))) return false;
+    }
+    if (p.perm == nullptr) return n >= ((int64_t)1 << (p.b <= 32 || large ? 23 : 22));
+    if (folded || p.d == kTile) return large || n > ((int64_t)1 << 21);
+    // (no prepared form below 4096: every launch builds the table; T = 4096, d = 3072, b = 16 10.9 / 12.3,
+    //  T = 8192 18.5 / 16.9; b = 128, T = 2048 9.7 / 10.0, T = 4096 13.6 / 12.4)
+    if (p.d < kTile) return n >= ((int64_t)1 << (p.b <= 32 ? 24 : 23));
+    if (p.d > 16384) return true;
+    return large ? p.d > 8192 || n > ((int64_t)1 << 21) : n >= ((int64_t)1 << 22);
 }
 
 hipError_t launch_mfma(const ApplyParams& p0, int out_kind, hipStream_t stream) {

@@ -379,6 +379,27 @@ def test_int4_asym_offset_rows(d, b, algo):
     assert np.all(c[T - 1] == 0) and s[T - 1] == 0 and z[T - 1] == 0            # constant row
 
 
+# ---- the line between the two general kernels: calls on either side of it -------------------------
+@pytest.mark.parametrize("d,b,rows,with_perm", [(3072, 64, 1366, False), (2560, 512, 1639, False), (3584, 16, 2341, False),
+                                                (3072, 128, 2731, True), (4096, 128, 1024, False), (4096, 64, 513, True),
+                                                (8192, 128, 512, True), (6144, 2048, 342, True), (5120, 1024, 1639, False)])
+@pytest.mark.parametrize("fmt", ["int4", "mxfp4", "int4_asym"])
+def test_few_rows_and_many_take_either_kernel(d, b, rows, with_perm, fmt):
+    rng = np.random.default_rng(d + b + rows)
+    x_bits = synth.f64_to_bf16_bits(rng.standard_t(4, size=(rows, d)))
+    perm = rng.permutation(d).astype(np.int32) if with_perm else None
+    for T in (rows - 1, rows):
+        assert_parity(x_bits[:T], perm, b, fmt, ldx=d + 24 if T == rows else None, label="few or many rows")
+    if with_perm and d >= 4096:          # the prepared form goes where the plain call goes
+        torch = _torch()
+        pt, place = torch.from_numpy(perm).cuda(), binding.placement_to_device(binding.perq_perm_prepare(perm, b)[0])
+        for T in (rows - 1, rows):
+            x = binding.bits_to_device(x_bits[:T])
+            for p, q in zip(binding.perq_permute_rotate_quant(x, pt, b, fmt),
+                            binding.perq_permute_rotate_quant(x, pt, b, fmt, placement=place)):
+                assert torch.equal(p, q)
+
+
 # ---- the codes consumed: W4A4 product with P and the rotation merged into the weights -----------
 @pytest.mark.parametrize("T,N,d,b", [(70, 50, 256, 32), (33, 130, 4096, 128), (5, 3, 1024, 1024),
                                      # rotations that are not symmetric matrices (base 12) or not powers of two
