@@ -174,12 +174,27 @@ butterfly_kernel(ApplyParams p, BflyGeom g) {
 
         // ---- epilogue -------------------------------------------------------------------------
         if constexpr (OUT == OUT_F32) {
-            if (live) {
-                float4* yo = reinterpret_cast<float4*>(p.y + row * (int64_t)d + 32 * t);
+#pragma unroll
+            for (int i = 0; i < 32; ++i) v[i] *= p.rsqrt_b;
+            float* yo = p.y + row * (int64_t)d;
+            if ((g.nt & 3) == 0) {             // a quad of lanes lies in one row (and is active as a whole)
+                quad_transpose16(v);
+                quad_transpose16(v + 16);
+                if (live) {
+                    const int q = t & 3;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) {
+                            const float* w = v + 16 * j + 4 * u;
+                            *reinterpret_cast<float4*>(yo + 32 * (t - q + u) + 16 * j + 4 * q) = make_float4(w[0], w[1], w[2], w[3]);
+                        }
+                    }
+                }
+            } else if (live) {
 #pragma unroll
                 for (int j = 0; j < 8; ++j)
-                    yo[j] = make_float4(v[4 * j] * p.rsqrt_b, v[4 * j + 1] * p.rsqrt_b,
-                                        v[4 * j + 2] * p.rsqrt_b, v[4 * j + 3] * p.rsqrt_b);
+                    reinterpret_cast<float4*>(yo + 32 * t)[j] = make_float4(v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]);
             }
         } else if constexpr (OUT == OUT_DIAG) {
             // per token: ||x||_inf, ||x||_1, largest block l1 of the permuted row, ||y||_inf

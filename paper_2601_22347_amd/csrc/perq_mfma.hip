@@ -664,14 +664,24 @@ mfma_kernel(ApplyParams p, MfmaGeom g) {
         //      or the 16 outputs from hk_run(q) on of every accumulator tile q (high-K mode) -------
         if constexpr (OUT == OUT_F32) {
             PERQ_GATHER_STEPS(kG0, 9);
+            // (the runs of a quad's four lanes; whole quads are in the row or past it only for d % 512 == 0,
+            //  so every run is tested)
+            const int cc = c & 3;
 #pragma unroll
             for (int q = 0; q < kQ; ++q) {
-                if (row_live && qvalid[q]) {
-                    float4* yo = reinterpret_cast<float4*>(p.y + row * (int64_t)d + tile_base + (kHighK ? hk_run(q) : sbq(q) * 32 + 16 * h));
+                float* w = v + q * 16;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        yo[j] = make_float4(v[q * 16 + 4 * j] * p.rsqrt_b, v[q * 16 + 4 * j + 1] * p.rsqrt_b,
-                                            v[q * 16 + 4 * j + 2] * p.rsqrt_b, v[q * 16 + 4 * j + 3] * p.rsqrt_b);
+                for (int r = 0; r < 16; ++r) w[r] *= p.rsqrt_b;
+                quad_transpose16(w);
+                if (row_live) {
+                    const int own = kHighK ? hk_run(q) : sbq(q) * 32 + 16 * h;
+                    float* yo = p.y + row * (int64_t)d + tile_base + 4 * cc;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const int at = own + (t - cc) * (kHighK ? 16 : 128);        // first position of lane t's run
+                        if (at < tile_len)
+                            *reinterpret_cast<float4*>(yo + at) = make_float4(w[4 * t], w[4 * t + 1], w[4 * t + 2], w[4 * t + 3]);
+                    }
                 }
             }
         } else {

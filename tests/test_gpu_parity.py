@@ -379,6 +379,30 @@ def test_int4_asym_offset_rows(d, b, algo):
     assert np.all(c[T - 1] == 0) and s[T - 1] == 0 and z[T - 1] == 0            # constant row
 
 
+# ---- fp32 output: stored by quads of lanes; rows of fewer than four lanes, of a multiple and not ------
+@pytest.mark.parametrize("d,b", [(32, 32), (64, 16), (96, 32), (128, 64), (160, 32), (352, 32), (512, 256), (1536, 512),
+                                 (4096, 128), (4608, 512), (8192, 4096), (14336, 2048), (10240, 1024)])
+@pytest.mark.parametrize("algo", ["butterfly", "mfma"])
+def test_f32_output_fills_its_rows_and_nothing_else(d, b, algo):
+    torch = _torch()
+    if algo == "mfma" and not mfma_covers(d, b):
+        return
+    print(f"[case] f32 rows d={d} b={b} algo={algo}", flush=True)
+    rng = np.random.default_rng(d + b)
+    for T in (1, 5):
+        x_bits = synth.f64_to_bf16_bits(rng.standard_normal((T, d)))
+        perm = rng.permutation(d).astype(np.int32)
+        buf = torch.full((T * d + 64,), 7.5, device="cuda")
+        binding.perq_permute_rotate_f32(binding.bits_to_device(x_bits), torch.from_numpy(perm).cuda(), b,
+                                        y=buf[:T * d].view(T, d), algo=algo)
+        X = orc.bf16_bits_to_f64(x_bits)
+        want = orc.block_hadamard(orc.permute_channels(X, perm), b)
+        got = buf[:T * d].view(T, d).cpu().numpy().astype(np.float64)
+        # log2(b) + 1 fp32 roundings of values no larger than the row's l1 norm over sqrt(b)
+        assert np.all(np.abs(got - want) <= 1e-5 * np.linalg.norm(X, axis=1, keepdims=True))
+        assert bool((buf[T * d:] == 7.5).all())
+
+
 # ---- the line between the two general kernels: calls on either side of it -------------------------
 @pytest.mark.parametrize("d,b,rows,with_perm", [(3072, 64, 1366, False), (2560, 512, 1639, False), (3584, 16, 2341, False),
                                                 (3072, 128, 2731, True), (4096, 128, 1024, False), (4096, 64, 513, True),
