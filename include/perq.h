@@ -92,10 +92,10 @@ const char* perq_status_string(perq_status_t status);
  *   out_mean   device, float [d]
  *   workspace  device, at least perq_colabs_mean_workspace_bytes(M, d) bytes, 16-byte aligned
  *
- * Two deterministic passes (row-slice partial sums in fp32, then a fixed-order reduction);
- * the result does not depend on scheduling.  M == 0 is INVALID_ARG (the mean is undefined).
- * Accuracy: a partial sum adds at most r - 1 non-negative fp32 terms, r = rows per slice =
- * max(8, ceil(M / floor(512 / ceil(d / 2048)))), and the second pass works in double, so
+ * Deterministic (row-slice partial sums in fp32, then a fixed-order reduction; up to 128 rows in one
+ * pass): the result does not depend on scheduling.  M == 0 is INVALID_ARG (the mean is undefined).
+ * Accuracy: a sum adds at most r - 1 non-negative fp32 terms,
+ * r = max(8, ceil(M / floor(512 / ceil(d / 2048)))), and the rest works in double, so
  * |out_mean[i] - a_i| < (r + 1) 2^-24 a_i  (r <= 32 for M <= 4096: below 2.0e-6 relative).
  */
 size_t perq_colabs_mean_workspace_bytes(int64_t M, int32_t d);

@@ -2,23 +2,37 @@
 // same two passes with max in place of + give max_k |x[k,i]|, the statistic of the "absmax" and
 // ZigZag permutations of the ablation (Appendix C).
 //
-// Pass 1: the M rows are cut into S slices; workgroup (column tile, slice) adds |x| over its
-// rows, each lane owning 8 adjacent columns (one 16-byte bf16 load per row), and writes fp32
-// partial sums part[slice][column].  Pass 2: one lane per column adds the S partials in slice
-// order (in double) and divides by M.  No atomics: the result is independent of scheduling.
-// Rounding: at most rows_per_slice - 1 fp32 additions of non-negative terms per partial, so the
-// relative error of a_i is below (rows_per_slice + 1) * 2^-24.
+// Pass 1: the M rows are cut into S slices; workgroup (column tile, slice) adds |x| over its rows:
+// 32 lanes own 8 adjacent columns each (one 16-byte bf16 load per row), the eight groups of 32 take
+// every eighth row, and their sums meet in LDS (in double).  It writes one fp32 partial sum per column
+// and slice.  Pass 2: one lane per column adds the S partials in slice order (in double) and divides by
+// M; up to 128 rows are a single slice and there is no second launch.  No
+// atomics: the result is independent of scheduling.
+// Rounding: at most rows_per_slice / 8 - 1 fp32 additions of non-negative terms per sum and one rounding
+// of the partial, so the relative error of a_i is below (rows_per_slice / 8 + 2) * 2^-24.
+//   Bound by reading x, small inputs by the two launches.  Eight row groups a workgroup instead of one
+// (2048 columns each) make the partials an eighth as large (a quarter of the input at M <= 1024 before).
+// Launches back to back: M = 16, d = 4096 4.1 -> 2.3 us, M = 500, d = 14336 9.3 -> 7.9, M = 2048, d = 4096
+// 9.1 -> 7.8, M = 4096, d = 8192 (cache resident) 13.7 -> 13.9, M = d = 32768 369 -> 322.
 #include "perq.h"
 #include "perq_launch.h"
 
 #include <mutex>
+#include <type_traits>
 
 namespace perq {
 namespace {
 
 constexpr int kColsPerLane = 8;
 constexpr int kThreads = 256;
-constexpr int kTileCols = kColsPerLane * kThreads;   // 2048
+constexpr int kGroups = 8;                                    // row groups of a workgroup
+constexpr int kTileCols = kColsPerLane * kThreads / kGroups;  // 256
+static_assert(kTileCols == kThreads, "one lane per column adds the groups");
+
+constexpr int kOneSlice = 128;                                // up to here a second launch costs more than the rows
+// Inputs past the last-level cache are read with streaming loads (M = 32768, d = 4096: 50.4 -> 45.4 us);
+// smaller ones may be in it already and should stay (M = 4096, d = 8192 again and again: 13.9 against 15.2).
+constexpr int64_t kStreamBytes = (int64_t)256 << 20;
 
 struct ColabsPlan {
     int col_tiles;
@@ -28,29 +42,30 @@ struct ColabsPlan {
 
 ColabsPlan colabs_plan(int64_t M, int32_t d) {
     ColabsPlan pl;
-    pl.col_tiles = (d + kTileCols - 1) / kTileCols;
-    int64_t want = 512 / pl.col_tiles;           // ~2 workgroups per CU: longer row loops, small partials
+    pl.col_tiles = (int)(((int64_t)d + kTileCols - 1) / kTileCols);
+    int64_t want = 512 / pl.col_tiles;           // ~2 workgroups per CU (1024: M = 32768, d = 4096 50.4 -> 51.9 us)
     if (want < 1) want = 1;
     int64_t rps = (M + want - 1) / want;
-    if (rps < 8) rps = 8;                        // at least a few rows per lane
+    if (rps < 64) rps = 64;                      // at least a few rows per lane
+    if (M <= kOneSlice) rps = kOneSlice;
     pl.rows_per_slice = (int)rps;
     pl.slices = (int)((M + rps - 1) / rps);
     return pl;
 }
 
-template <bool MAXSTAT>
+// FINAL: the only slice; the result itself is written (m_rows: rows to divide by).  STREAM: streaming loads.
+template <bool MAXSTAT, bool FINAL, bool STREAM>
 __global__ void __launch_bounds__(kThreads)
 colabs_partial_kernel(const uint16_t* __restrict__ x, int64_t M, int32_t d, int64_t ldx,
-                      int rows_per_slice, float* __restrict__ part) {
-    const int col = blockIdx.x * kTileCols + threadIdx.x * kColsPerLane;
-    if (col >= d) return;
+                      int rows_per_slice, float* __restrict__ part, float m_rows) {
+    typedef typename std::conditional<FINAL && !MAXSTAT, double, float>::type sum_t;
+    __shared__ sum_t red[kGroups][kTileCols];
+    const int cl = threadIdx.x % (kThreads / kGroups), group = threadIdx.x / (kThreads / kGroups);
+    const int64_t col0 = (int64_t)blockIdx.x * kTileCols, col = col0 + cl * kColsPerLane;
     const int64_t r0 = (int64_t)blockIdx.y * rows_per_slice;
     const int64_t r1 = r0 + rows_per_slice < M ? r0 + rows_per_slice : M;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    const uint16_t* px = x + col;
-#pragma unroll 4
-    for (int64_t r = r0; r < r1; ++r) {
-        const uint4 w = *reinterpret_cast<const uint4*>(px + r * ldx);
+    auto add = [&](const uint4& w) {
         const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -58,10 +73,47 @@ colabs_partial_kernel(const uint16_t* __restrict__ x, int64_t M, int32_t d, int6
             acc[2 * q] = MAXSTAT ? fmaxf(acc[2 * q], lo) : acc[2 * q] + lo;
             acc[2 * q + 1] = MAXSTAT ? fmaxf(acc[2 * q + 1], hi) : acc[2 * q + 1] + hi;
         }
+    };
+    sum_t total[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (col < d) {
+        const uint16_t* px = x + col;
+        if constexpr (FINAL) {
+            // eight rows at a time, all requested together, their sums added up in double
+            for (int64_t base = r0 + group; base < r1; base += 8 * kGroups) {
+                uint4 w[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    w[i] = base + i * kGroups < r1 ? *reinterpret_cast<const uint4*>(px + (base + i * kGroups) * ldx) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) add(w[i]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    total[e] = MAXSTAT ? (sum_t)acc[e] : total[e] + acc[e];
+                    if constexpr (!MAXSTAT) acc[e] = 0.0f;
+                }
+            }
+        } else {
+#pragma unroll 8
+            for (int64_t r = r0 + group; r < r1; r += kGroups)
+                add(STREAM ? load_stream16(px + r * ldx) : *reinterpret_cast<const uint4*>(px + r * ldx));
+#pragma unroll
+            for (int e = 0; e < 8; ++e) total[e] = acc[e];
+        }
     }
-    float4* out = reinterpret_cast<float4*>(part + (int64_t)blockIdx.y * d + col);
-    out[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    out[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) red[group][cl * kColsPerLane + e] = total[e];
+    __syncthreads();
+    const int64_t c = col0 + threadIdx.x;
+    if (c < d) {
+        double t = red[0][threadIdx.x];
+#pragma unroll
+        for (int g = 1; g < kGroups; ++g) {
+            const double v = red[g][threadIdx.x];
+            t = MAXSTAT ? (v > t ? v : t) : t + v;
+        }
+        if constexpr (FINAL) part[c] = MAXSTAT ? (float)t : (float)(t / (double)m_rows);
+        else part[(int64_t)blockIdx.y * d + c] = (float)t;
+    }
 }
 
 // Pass 2: 32 columns per workgroup, 8 lanes per column.  Lane j of a column adds slices
@@ -124,8 +176,13 @@ perq_status_t colabs_launch(const uint16_t* x_bf16, int64_t M, int32_t d, int64_
                             void* hip_stream) {
     const ColabsPlan pl = colabs_plan(M, d);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    hipLaunchKernelGGL(colabs_partial_kernel<MAXSTAT>, dim3(pl.col_tiles, pl.slices), dim3(kThreads), 0, stream, x_bf16,
-                       M, d, ldx, pl.rows_per_slice, part);
+    if (pl.slices == 1) {
+        hipLaunchKernelGGL((colabs_partial_kernel<MAXSTAT, true, false>), dim3(pl.col_tiles), dim3(kThreads), 0, stream, x_bf16,
+                           M, d, ldx, pl.rows_per_slice, out, (float)M);
+        return hipGetLastError() == hipSuccess ? PERQ_OK : PERQ_ERR_LAUNCH;
+    }
+    auto kern = M * (int64_t)d * 2 >= kStreamBytes ? colabs_partial_kernel<MAXSTAT, false, true> : colabs_partial_kernel<MAXSTAT, false, false>;
+    hipLaunchKernelGGL(kern, dim3(pl.col_tiles, pl.slices), dim3(kThreads), 0, stream, x_bf16, M, d, ldx, pl.rows_per_slice, part, 0.0f);
     if (hipGetLastError() != hipSuccess) return PERQ_ERR_LAUNCH;
     hipLaunchKernelGGL(colabs_finish_kernel<MAXSTAT>, dim3((d + kFinishCols - 1) / kFinishCols), dim3(kThreads), 0,
                        stream, part, pl.slices, d, (float)M, out);

@@ -541,6 +541,30 @@ def test_w4a4_gemm_argument_checks():
         binding.perq_w4a4_gemm_ref(a, s, torch.zeros((4, 8), dtype=torch.uint8, device="cuda"), s)
 
 
+# one slice or several, column tiles of 256 and their remainders, streaming loads from 256 MiB on
+@pytest.mark.parametrize("M,d", [(1, 8), (7, 248), (64, 256), (65, 264), (127, 2056), (128, 14336), (129, 520), (577, 4096),
+                                 (1030, 8), (33, 40000), (2049, 65536)])
+def test_statistics_over_slices_and_column_tiles(M, d):
+    torch = _torch()
+    print(f"[case] statistics M={M} d={d}", flush=True)
+    rng = np.random.default_rng(M + d)
+    bits = synth.f64_to_bf16_bits(rng.standard_normal((min(M, 600), d)) * np.exp(rng.uniform(-2, 2, size=(1, d))))
+    bits = np.tile(bits, (-(-M // bits.shape[0]), 1))[:M]
+    wide = torch.full((M, d + 16), 1.0e4, dtype=torch.bfloat16, device="cuda")       # strided rows, loud padding
+    wide[:, :d] = binding.bits_to_device(bits)
+    out = torch.full((d + 8,), -1.0, device="cuda")
+    a = np.zeros(d)
+    top = np.zeros(d)
+    for r in range(0, M, 600):
+        x = np.abs(orc.bf16_bits_to_f64(bits[r:r + 600]))
+        a, top = a + x.sum(axis=0) / M, np.maximum(top, x.max(axis=0))
+    got = binding.perq_colabs_mean(wide[:, :d], out=out[:d]).cpu().numpy().astype(np.float64)
+    r = max(8, -(-M // max(1, 512 // -(-d // 2048))))                                # the documented bound
+    assert np.all(np.abs(got - a) <= (r + 1) * 2.0 ** -24 * a)
+    assert np.array_equal(binding.perq_colabs_absmax(wide[:, :d], out=out[:d]).cpu().numpy().astype(np.float64), top)
+    assert bool((out[d:] == -1.0).all())
+
+
 # ---- ablation permutations and the per-token diagnostics (Appendix C; Section 3) ------------------
 def test_colabs_absmax_is_exact():
     wl = synth.llama1b_down()
