@@ -56,7 +56,7 @@ struct MfmaGeom {
     int tiles_per_row;   // power of two >= ceil(d / 4096)
     int rows;            // rows per workgroup iteration = waves / tiles_per_row
     int nload;           // direct-to-LDS load instructions per lane per iteration
-    uint32_t row_bytes;  // d * 2
+    uint32_t row_bytes;  // bytes of a staged row: d * 2, rounded up to the 1 KiB of a load instruction
     uint32_t ctr_set;    // which set of ticket counters this launch draws from
     uint32_t dynamic;    // 1: units dealt at run time through the ticket counters; 0: fixed stride
     uint32_t fold_mask;  // rows folded into 4096-wide ones: width of a real row - 1; else all ones
@@ -326,7 +326,7 @@ mfma_kernel(ApplyParams p, MfmaGeom g) {
         return 16 * (q * 32 + c) + 2048 * h;
     };
 
-    const uint32_t gpr = (uint32_t)d >> 3;                    // granules per row (multiple of 64)
+    const uint32_t gpr = (uint32_t)d >> 3;                    // granules per row (a multiple of 4)
     // Where a granule of the row sits in its staging buffer: the fixed swizzle, or the placement the
     // caller prepared for this permutation (perq_perm_prepare).  In that case p.perm holds, per
     // position, the channel's place in the staged row (slot * 8 + channel % 8) instead of the channel,
@@ -361,13 +361,22 @@ mfma_kernel(ApplyParams p, MfmaGeom g) {
             ok = in_row < gpr;
         } else {
             const uint32_t s0 = (uint32_t)(k * NWAVES + wave) * 64u;
-            rslot = s0 / gpr;
-            in_row = s0 - rslot * gpr;
+            const uint32_t slots = g.row_bytes >> 4;            // gpr, rounded up
+            rslot = s0 / slots;
+            in_row = s0 - rslot * slots;
             ok = rslot < (uint32_t)g.rows;
         }
         ok = ok && k < g.nload;
         ld_lane_off[k] = (ok ? granule_at(in_row + (uint32_t)lane) : 0u) * 16u + rslot * (uint32_t)(p.ldx * 2);
         if (ok) (rslot == 0 ? mask_row0 : mask_row1) |= 1u << k;
+    }
+    // (slots past the end of a row of d % 512 != 0 repeat its last granule; nothing reads them)
+    if ((gpr & 63u) != 0) {
+#pragma unroll
+        for (int k = 0; k < kMaxLoad; ++k) {
+            const uint32_t last = (gpr - 1u) * 16u + (((mask_row1 >> k) & 1u) != 0 ? (uint32_t)(p.ldx * 2) : 0u);
+            ld_lane_off[k] = ld_lane_off[k] < last ? ld_lane_off[k] : last;
+        }
     }
     const unsigned char* xbytes = reinterpret_cast<const unsigned char*>(p.x);
     const int64_t ldx_bytes = p.ldx * 2;
@@ -858,7 +867,13 @@ mfma_kernel(ApplyParams p, MfmaGeom g) {
                 if constexpr (OUT == OUT_MXFP4) {
                     uint8_t* srow = static_cast<uint8_t*>(p.scales) + row * (int64_t)(d >> 5) + (tile_base >> 5);
                     if constexpr (!kHighK) {
-                        if (h == 0 && qvalid[0]) *reinterpret_cast<uint32_t*>(srow + c * kQ) = ebytes;
+                        if ((d & 127) == 0) {
+                            if (h == 0 && qvalid[0]) *reinterpret_cast<uint32_t*>(srow + c * kQ) = ebytes;
+                        } else if (h == 0) {
+#pragma unroll
+                            for (int q = 0; q < kQ; ++q)
+                                if (qvalid[q]) srow[c * kQ + q] = (uint8_t)(ebytes >> (8 * q));
+                        }
                     } else {
 #pragma unroll
                         for (int q = 0; q < kQ; ++q)
@@ -1215,10 +1230,9 @@ hipError_t launch_mfma_st(const ApplyParams& p, uint32_t fold_mask, hipStream_t 
     g.tiles_per_row = 1;
     while (g.tiles_per_row < tiles) g.tiles_per_row <<= 1;
     g.rows = NWAVES / g.tiles_per_row;
-    g.row_bytes = (uint32_t)p.d * 2u;
+    g.row_bytes = ((uint32_t)p.d * 2u + 1023u) & ~1023u;
     const uint32_t stage_bytes = (uint32_t)g.rows * g.row_bytes;
-    const uint32_t gpr = (uint32_t)p.d / 8u;
-    g.nload = g.tiles_per_row == 1 ? (int)(gpr / 64u)
+    g.nload = g.tiles_per_row == 1 ? (int)(g.row_bytes / 1024u)
                                    : (int)((stage_bytes / 16u + NWAVES * 64u - 1u) / (NWAVES * 64u));
     const uint32_t lds_bytes = 65536u;                  // dynamic part: the staging buffers (incl. the zero slot)
     g.ctr_set = 0;
@@ -1291,6 +1305,18 @@ bool mfma_supports(const ApplyParams& p) {
     return p.b <= kTile && p.d % 512 == 0 && p.d <= 32768 && p.T < ((int64_t)1 << 31) && p.ldx < ((int64_t)1 << 30);
 }
 
+// Widths that are no multiple of a load instruction's 512 elements: their rows are staged at a pitch of
+// whole instructions.  AUTO only (the explicit choice keeps to the widths above); b <= 256 by divisibility.
+// The rows of a staging buffer must leave its last 16 bytes alone, the zeros that lanes past the end of the
+// row read.
+static bool mfma_takes_ragged(const ApplyParams& p) {
+    if (p.d % 512 == 0 || p.d < 2560 || p.d > 32768 || p.b > 256 || p.T >= ((int64_t)1 << 31) || p.ldx >= ((int64_t)1 << 30)) return false;
+    const int waves = p.d > 4 * kTile ? 8 : 4, tiles = (p.d + kTile - 1) / kTile;
+    int per_row = 1;
+    while (per_row < tiles) per_row <<= 1;
+    return (waves / per_row) * ((p.d * 2 + 1023) / 1024 * 1024) < waves * 8192;
+}
+
 // Narrow rows stored back to back can be folded into 4096-wide ones (a wave's tile is 4096 wide
 // whatever d is): blocks and 32-groups do not straddle rows, and codes, e8m0 bytes and fp32 outputs
 // of consecutive rows are contiguous, so only the operand addresses through `perm` know about it.
@@ -1328,7 +1354,8 @@ static bool folds(const ApplyParams& p, int out_kind) {
 //       wider rows: d = 6144, b = 2048, T = 256 6.0 / 7.7, T = 512 8.0 / 7.7; d = 16384, b = 4096 9.2 / 9.0.
 //       Rows wider than 16384 need workgroups of 1024 lanes there: T = 16, d = 28672 11.8 / 9.1.
 bool mfma_preferred(const ApplyParams& p, int out_kind) {
-    if (!mfma_supports(p)) return false;
+    const bool ragged = mfma_takes_ragged(p);
+    if (!mfma_supports(p) && !ragged) return false;
     const int64_t n = p.T * (int64_t)p.d;
     const bool folded = folds(p, out_kind), large = p.b >= 1024;
     if (folded) {
@@ -1336,11 +1363,26 @@ bool mfma_preferred(const ApplyParams& p, int out_kind) {
     } else if (p.d < 2560) {
         if (!(p.d == 2048 && large && n >= ((int64_t)1 << 25))) return false;
     }
-    if (p.perm == nullptr) return n >= ((int64_t)1 << (p.b <= 32 || large ? 23 : 22));
+    const bool two_tiles = p.d > kTile && p.d <= 2 * kTile;
+    if (p.perm == nullptr) {
+        if (large) return n >= ((int64_t)1 << 23);
+        if (ragged && two_tiles) return n >= ((int64_t)3 << (p.b <= 32 ? 23 : 22));
+        // Ragged rows of more tiles: b = 32, d = 11008, T = 762 7.2 / 7.8, T = 1524 12.6 / 11.7; d = 15904, T = 527
+        // 7.4 / 8.4, T = 1054 11.6 / 12.1; b = 128, d = 11008, T = 381 6.7 / 6.8, T = 762 8.7 / 8.3.
+        return n >= ((int64_t)1 << ((p.b <= 32 ? 23 : 22) + (ragged && p.d > kTile)));
+    }
     if (folded || p.d == kTile) return large || n > ((int64_t)1 << 21);
     // (no prepared form below 4096: every launch builds the table; T = 4096, d = 3072, b = 16 10.9 / 12.3,
-    //  T = 8192 18.5 / 16.9; b = 128, T = 2048 9.7 / 10.0, T = 4096 13.6 / 12.4)
+    //  T = 8192 18.5 / 16.9; b = 128, T = 2048 9.7 / 10.0, T = 4096 13.6 / 12.4;
+    //  ragged: d = 2880, b = 32, T = 5825 16.2 / 15.3, T = 32768 with MXFP4 and b = 64 69.1 / 51.2; T = 2912 11.4 / 10.9;
+    //  P = I, b = 32, T = 5832 12.2 / 10.5, T = 32768 56.8 / 41.2)
     if (p.d < kTile) return n >= ((int64_t)1 << (p.b <= 32 ? 24 : 23));
+    // Ragged rows, with a permutation: two tiles, b = 16, d = 5152, T = 6512 23.6 / 25.2, b = 32, T = 16384 64.5 / 57.3;
+    // b = 256, d = 7424, T = 2259 18.6 / 17.7, T = 4519 31.5 / 26.2.  Three and four: b = 16, d = 15904, T = 1054
+    // 17.2 / 18.3, T = 2109 27.0 / 24.8; d = 11008, b = 256, T = 762 16.1 / 16.3, T = 16384 212 / 116; b = 128,
+    // T = 1524 24.5 / 19.6.  More: b = 32, d = 17440, T = 480 16.6 / 16.2, T = 961 27.3 / 22.2; b = 128, d = 28800,
+    // T = 291 24.7 / 18.3.
+    if (ragged) return n >= ((int64_t)1 << ((p.b <= 32 ? 24 : 23) + (p.d <= 2 * kTile ? 2 : p.d <= 4 * kTile ? 1 : 0)));
     if (p.d > 16384) return true;
     return large ? p.d > 8192 || n > ((int64_t)1 << 21) : n >= ((int64_t)1 << 22);
 }

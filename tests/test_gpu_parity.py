@@ -424,6 +424,35 @@ def test_few_rows_and_many_take_either_kernel(d, b, rows, with_perm, fmt):
                 assert torch.equal(p, q)
 
 
+# ---- rows that are no multiple of a load instruction: staged at a pitch of whole instructions ----------
+# AUTO takes the matrix-core kernel for every such width from 2^26 elements on.  The rows repeat with a
+# period of 32, and a row's output does not depend on its place: the first 32 go to the oracle, the others
+# have to equal them bit for bit.
+@pytest.mark.parametrize("d,b,with_perm", [
+    (2592, 32, True), (2880, 64, True), (2880, 32, False), (3040, 16, True), (3552, 32, True),   # a row per wave
+    (5152, 32, True), (7648, 16, False), (7424, 256, True),                                       # two rows a group
+    (11008, 256, True), (11008, 64, False), (15904, 32, True),                                    # one row, four tiles
+    (17440, 32, True), (28800, 128, True), (31776, 16, True),                                     # eight waves
+    (4064, 32, True), (8160, 32, True), (16352, 16, False), (32736, 32, True)])                   # no room for the zeros: butterflies
+@pytest.mark.parametrize("fmt", ["int4", "mxfp4", "int4_asym", "fp4_token"])
+def test_ragged_rows_in_bulk(d, b, with_perm, fmt):
+    torch = _torch()
+    rng = np.random.default_rng(d + b)
+    few = synth.f64_to_bf16_bits(rng.standard_t(4, size=(32, d)))
+    T = (1 << 26) // d + 3
+    perm = rng.permutation(d).astype(np.int32) if with_perm else None
+    pt = None if perm is None else torch.from_numpy(perm).cuda()
+    x = torch.zeros((T, d + 8), dtype=torch.bfloat16, device="cuda")[:, :d]
+    x.copy_(binding.bits_to_device(few).repeat(T // 32 + 1, 1)[:T])
+    print(f"[case] ragged rows T={T} d={d} b={b} fmt={fmt} perm={with_perm}", flush=True)
+    codes, scales = binding.perq_permute_rotate_quant(x, pt, b, fmt)
+    y = binding.perq_permute_rotate_f32(x, pt, b)
+    for out in (codes, scales, y):
+        assert torch.equal(out, out[:32].repeat(T // 32 + 1, *[1] * (out.dim() - 1))[:T])
+    rep = parity.compare_apply(few, perm, b, fmt, codes[:32].cpu().numpy(), scales[:32].cpu().numpy(), y[:32].cpu().numpy())
+    assert rep.ok(), (rep.summary(), rep.notes[:5])
+
+
 # ---- the codes consumed: W4A4 product with P and the rotation merged into the weights -----------
 @pytest.mark.parametrize("T,N,d,b", [(70, 50, 256, 32), (33, 130, 4096, 128), (5, 3, 1024, 1024),
                                      # rotations that are not symmetric matrices (base 12) or not powers of two
