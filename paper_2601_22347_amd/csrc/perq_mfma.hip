@@ -1347,8 +1347,10 @@ static bool folds(const ApplyParams& p, int out_kind) {
 //       b <= 32, with five stages fewer in the butterflies, and for b >= 1024, whose operand addresses cost
 //       this kernel 3 us, at 2^23 (d = 4096, b = 16: T = 2048 5.8 / 6.1, T = 8192 17.8 / 16.2; d = 8192,
 //       b = 4096: T = 1024 10.8 / 11.1, T = 2048 20.8 / 16.4).
-//     With a permutation: d = 8192, b = 32, T = 16 5.2 / 7.2, T = 256 5.2 / 7.1, T = 1024 9.4 / 8.9;
-//       d = 14336, b = 128, T = 256 7.6 / 8.6, T = 1024 17.5 / 13.7: the line is 2^22 elements.  The tile of
+//     With a permutation: d = 8192, b = 32, T = 16 5.2 / 7.2, T = 256 5.2 / 7.1; d = 14336, b = 128, T = 256
+//       7.6 / 8.6, T = 1024 17.5 / 13.7: the line is 2^22 elements.  On rows of two tiles it is 2^24 for b <= 32
+//       (d = 8192, T = 1025 9.9 / 9.8 prepared, 13.4 as given; T = 2049 14.6 / 13.9, 16.4; d = 6144, T = 2731
+//       14.1 / 15.3, 17.7) and 2^23 above (b = 128: d = 8192, T = 513 8.2 / 8.4, 11.9; T = 1025 10.9 / 10.3, 13.6).  The tile of
 //       d = 4096 and of folded rows builds its operand table once for four waves: T = 512, b = 64 5.3 / 5.7,
 //       T = 1024 7.0 / 5.8, and for b >= 1024 it is always ahead (T = 16, b = 4096: 6.5 / 6.3).  b >= 1024 on
 //       wider rows: d = 6144, b = 2048, T = 256 6.0 / 7.7, T = 512 8.0 / 7.7; d = 16384, b = 4096 9.2 / 9.0.
@@ -1366,7 +1368,9 @@ bool mfma_preferred(const ApplyParams& p, int out_kind) {
     const bool two_tiles = p.d > kTile && p.d <= 2 * kTile;
     if (p.perm == nullptr) {
         if (large) return n >= ((int64_t)1 << 23);
-        if (ragged && two_tiles) return n >= ((int64_t)3 << (p.b <= 32 ? 23 : 22));
+        // Two tiles: b = 32, d = 5120, T = 1639 6.8 / 8.6, T = 3277 11.9 / 11.8, T = 6554 20.7 / 18.4; d = 8192, T = 1025
+        // 6.5 / 7.5, T = 2049 10.9 / 11.2, T = 4097 18.6 / 18.6.  b = 128: T = 1639 8.8 / 9.7, T = 3277 14.6 / 13.2.
+        if (two_tiles) return n >= ((int64_t)3 << (p.b <= 32 ? 23 : 22));
         // Ragged rows of more tiles: b = 32, d = 11008, T = 762 7.2 / 7.8, T = 1524 12.6 / 11.7; d = 15904, T = 527
         // 7.4 / 8.4, T = 1054 11.6 / 12.1; b = 128, d = 11008, T = 381 6.7 / 6.8, T = 762 8.7 / 8.3.
         return n >= ((int64_t)1 << ((p.b <= 32 ? 23 : 22) + (ragged && p.d > kTile)));
@@ -1384,7 +1388,8 @@ bool mfma_preferred(const ApplyParams& p, int out_kind) {
     // T = 291 24.7 / 18.3.
     if (ragged) return n >= ((int64_t)1 << ((p.b <= 32 ? 24 : 23) + (p.d <= 2 * kTile ? 2 : p.d <= 4 * kTile ? 1 : 0)));
     if (p.d > 16384) return true;
-    return large ? p.d > 8192 || n > ((int64_t)1 << 21) : n >= ((int64_t)1 << 22);
+    if (large) return p.d > 2 * kTile || n > ((int64_t)1 << 21);
+    return n >= ((int64_t)1 << (two_tiles ? (p.b <= 32 ? 24 : 23) : 22));
 }
 
 hipError_t launch_mfma(const ApplyParams& p0, int out_kind, hipStream_t stream) {

@@ -406,7 +406,9 @@ def test_f32_output_fills_its_rows_and_nothing_else(d, b, algo):
 # ---- the line between the two general kernels: calls on either side of it -------------------------
 @pytest.mark.parametrize("d,b,rows,with_perm", [(3072, 64, 1366, False), (2560, 512, 1639, False), (3584, 16, 2341, False),
                                                 (3072, 128, 2731, True), (4096, 128, 1024, False), (4096, 64, 513, True),
-                                                (8192, 128, 512, True), (6144, 2048, 342, True), (5120, 1024, 1639, False)])
+                                                (8192, 128, 1024, True), (6144, 2048, 342, True), (5120, 1024, 1639, False),
+                                                (10240, 64, 410, True), (5120, 32, 3277, True), (5120, 32, 4916, False),
+                                                (8192, 256, 1536, False)])
 @pytest.mark.parametrize("fmt", ["int4", "mxfp4", "int4_asym"])
 def test_few_rows_and_many_take_either_kernel(d, b, rows, with_perm, fmt):
     rng = np.random.default_rng(d + b + rows)
