@@ -1361,7 +1361,18 @@ bool mfma_preferred(const ApplyParams& p, int out_kind) {
     const int64_t n = p.T * (int64_t)p.d;
     const bool folded = folds(p, out_kind), large = p.b >= 1024;
     if (folded) {
-        if (p.b < 128 && n < ((int64_t)1 << 26)) return false;      // folded narrow rows: ahead from b = 128 on, and for any b once the launch is long
+        // Folded narrow rows.  For b <= 32 the butterflies' five stages cost no more than this kernel's products
+        // (d = 2048, T = 16384 17.6 / 17.2, with a permutation and MXFP4 20.3 / 20.5; T = 32768 31.9 / 30.4, 37.2 / 34.4).
+        // b = 64: d = 2048, T = 8192 11.8 / 10.3, permutation, d = 1024, T = 16384 13.2 / 13.6, T = 32768 22.7 / 21.0; d = 512,
+        // T = 65536 20.4 / 17.1.  b >= 128, P = I: d = 1024, T = 4096 5.3 / 5.6, T = 16384 13.0 / 11.1.
+        // Rows left over take a second launch of 4 us, 6 us with a permutation: d = 1024, T = 16385, b = 64 11.8 / 14.1,
+        // T = 65537 36.4 / 34.5; b = 128, T = 8193 7.3 / 10.8, T = 32769 21.6 / 21.5; permutation, T = 4097 7.8 / 13.1,
+        // T = 32769 25.2 / 27.9.
+        if (p.T % (kTile / p.d) != 0 && !large)
+            return n >= (p.b <= 32 ? (int64_t)1 << 27 : p.perm == nullptr ? (int64_t)3 << 24 : (int64_t)1 << 26);
+        if (p.b <= 32) return n >= ((int64_t)1 << 26);
+        if (p.b == 64) return n >= (p.perm == nullptr ? (int64_t)1 << 24 : (int64_t)3 << 23);
+        if (p.perm == nullptr && !large) return n >= ((int64_t)3 << 21);
     } else if (p.d < 2560) {
         if (!(p.d == 2048 && large && n >= ((int64_t)1 << 25))) return false;
     }
