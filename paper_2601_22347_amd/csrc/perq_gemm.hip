@@ -263,17 +263,20 @@ gemm_tile_kernel(GemmParams p) {
     Raw r0, r1;
     Ops u0, u1;
     Scales cur, nxt;
-    auto advance = [&](int S, auto j_const, auto inner_const) {
+    auto advance = [&](int S, auto j_const, auto inner_const, auto tail_const) {
         constexpr int j = decltype(j_const)::value;
+        constexpr bool tail = decltype(tail_const)::value;
         // requested after the next stage's codes: those of NBUF - 2 stages, and the scales if stage 0 of a
-        // superstage is among the last NBUF - 1 (vmcnt: a six-bit count in bits 3:0 and 15:14)
-        constexpr int n = (NBUF - 2) * kLoads + (MX && j > 0 && j < NBUF ? kSc : 0);
+        // superstage is among the last NBUF - 1 (vmcnt: a six-bit count in bits 3:0 and 15:14).  Nothing
+        // follows a tail: scales requested there would be unused, and loads that the compiler takes out
+        // must not be counted.
+        constexpr int n = (NBUF - 2) * kLoads + (MX && !tail && j > 0 && j < NBUF ? kSc : 0);
         static_assert(n < 64, "");
         __builtin_amdgcn_s_waitcnt(0x0F70 | (n & 15) | ((n >> 4) << 14));
         workgroup_barrier_lds();
         request_codes(S, std::integral_constant<int, j + NBUF>{}, inner_const);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (j == 0) request_scales(S + 1, nxt, inner_const);
+        if constexpr (j == 0 && !tail) request_scales(S + 1, nxt, inner_const);
         __builtin_amdgcn_sched_barrier(0);
     };
     // One stage.  INT4: the codes of a step are read two steps ahead of its products and unpacked while
@@ -294,7 +297,7 @@ gemm_tile_kernel(GemmParams p) {
             }
             auto step = [&](auto kc_const, Raw& now, Raw& next) {
                 constexpr int kc = decltype(kc_const)::value;
-                if constexpr (kc == 3) advance(S, j_const, inner_const);
+                if constexpr (kc == 3) advance(S, j_const, inner_const, tail_const);
                 read(j, kc + 1, next);
                 __builtin_amdgcn_sched_barrier(0);
                 multiply_mx(kc_const, now, sw, tail ? live(j, kc) : -1);
@@ -307,7 +310,7 @@ gemm_tile_kernel(GemmParams p) {
         } else {
             auto step = [&](auto kc_const, const Ops& now, Ops& next, const Raw& raw_next, Raw& raw) {
                 constexpr int kc = decltype(kc_const)::value;
-                if constexpr (kc == 2) advance(S, j_const, inner_const);
+                if constexpr (kc == 2) advance(S, j_const, inner_const, tail_const);
                 read(j, kc + 2, raw);
                 // (the step after the last one of a tail is never multiplied)
                 unpack(raw_next, next, tail ? live(j + ((kc + 1) >> 2), (kc + 1) & 3) : -1);
