@@ -563,6 +563,25 @@ def test_w4a4_products_over_tiles_and_remainders(T, N, d, fmt):
     assert bool((out[:, N:] == 7.5).all())
 
 
+# ---- rows that end in several stages of a partial superstage: the waits count the loads that are there ----
+@pytest.mark.parametrize("T,N,d", [(449, 577, 2880), (513, 700, 1312), (1540, 1537, 800), (2177, 2177, 2016)])
+@pytest.mark.parametrize("fmt", ["int4", "mxfp4"])
+def test_w4a4_products_repeat_bit_for_bit(T, N, d, fmt):
+    torch = _torch()
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    ca, cw = (torch.randint(0, 256, (n, d // 2), dtype=torch.uint8, device="cuda", generator=g) for n in (T, N))
+    if fmt == "int4":
+        sa, sw = (torch.rand(n, device="cuda", generator=g) + 0.1 for n in (T, N))
+        call = binding.perq_w4a4_gemm_ref
+    else:
+        sa, sw = (torch.randint(120, 131, (n, d // 32), dtype=torch.uint8, device="cuda", generator=g) for n in (T, N))
+        call = binding.perq_w4a4_mxfp4_gemm_ref
+    first = call(ca, sa, cw, sw)
+    for _ in range(50):
+        ca = ca.clone()                 # from memory again, not from the caches
+        assert torch.equal(call(ca, sa, cw, sw), first)
+
+
 def test_w4a4_gemm_argument_checks():
     torch = _torch()
     a = torch.zeros((4, 16), dtype=torch.uint8, device="cuda")
