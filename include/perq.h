@@ -92,11 +92,11 @@ const char* perq_status_string(perq_status_t status);
  *   out_mean   device, float [d]
  *   workspace  device, at least perq_colabs_mean_workspace_bytes(M, d) bytes, 16-byte aligned
  *
- * Deterministic (row-slice partial sums in fp32, then a fixed-order reduction; up to 128 rows in one
- * pass): the result does not depend on scheduling.  M == 0 is INVALID_ARG (the mean is undefined).
- * Accuracy: a sum adds at most r - 1 non-negative fp32 terms,
- * r = max(8, ceil(M / floor(512 / ceil(d / 2048)))), and the rest works in double, so
- * |out_mean[i] - a_i| < (r + 1) 2^-24 a_i  (r <= 32 for M <= 4096: below 2.0e-6 relative).
+ * Deterministic (fp32 sums over runs of rows, everything after them in double and in a fixed order; up
+ * to 128 rows in one pass): the result does not depend on scheduling.  M == 0 is INVALID_ARG (the mean is
+ * undefined).  Accuracy: an fp32 sum takes in at most r non-negative terms,
+ * r = max(8, ceil(M / floor(512 / ceil(d / 2048)))) (512 / ... at least 1), so
+ * |out_mean[i] - a_i| < (r + 1) 2^-24 a_i  (M <= 4096, d <= 8192: r <= 32, below 2.0e-6 relative).
  */
 size_t perq_colabs_mean_workspace_bytes(int64_t M, int32_t d);
 perq_status_t perq_colabs_mean(const uint16_t* x_bf16, int64_t M, int32_t d, int64_t ldx,

@@ -4,14 +4,15 @@
 //
 // Pass 1: the M rows are cut into S slices; workgroup (column tile, slice) adds |x| over its rows:
 // 32 lanes own 8 adjacent columns each (one 16-byte bf16 load per row), the eight groups of 32 take
-// every eighth row, and their sums meet in LDS (in double).  It writes one fp32 partial sum per column
-// and slice.  Pass 2: one lane per column adds the S partials in slice order (in double) and divides by
+// every eighth row, and their sums meet in LDS (in double).  It writes one partial sum per column
+// and slice, in double.  Pass 2: one lane per column adds the S partials in slice order and divides by
 // M; up to 128 rows are a single slice and there is no second launch.  No
 // atomics: the result is independent of scheduling.
-// Rounding: at most rows_per_slice / 8 - 1 fp32 additions of non-negative terms per sum and one rounding
-// of the partial, so the relative error of a_i is below (rows_per_slice / 8 + 2) * 2^-24.
+// Rounding: fp32 is used inside a run of at most max_run(M, d) rows of one lane only, so a run's sum is off
+// by less than max_run(M, d) - 1 roundings of non-negative terms, and the mean is rounded once more: the
+// relative error of a_i is below (max_run(M, d) + 1) * 2^-24.
 //   Bound by reading x, small inputs by the two launches.  Eight row groups a workgroup instead of one
-// (2048 columns each) make the partials an eighth as large (a quarter of the input at M <= 1024 before).
+// (2048 columns each) make the partials a quarter as large (a quarter of the input at M <= 1024 before).
 // Launches back to back: M = 16, d = 4096 4.1 -> 2.3 us, M = 500, d = 14336 9.3 -> 7.9, M = 2048, d = 4096
 // 9.1 -> 7.8, M = 4096, d = 8192 (cache resident) 13.7 -> 13.9, M = d = 32768 369 -> 322.
 #include "perq.h"
@@ -40,25 +41,38 @@ struct ColabsPlan {
     int rows_per_slice;
 };
 
+// Rows that one fp32 sum may take in (the bound that perq.h states).
+int64_t max_run(int64_t M, int32_t d) {
+    const int64_t tiles = ((int64_t)d + 2047) / 2048, slices = tiles < 512 ? 512 / tiles : 1;
+    const int64_t run = (M + slices - 1) / slices;
+    return run < 8 ? 8 : run;
+}
+
 ColabsPlan colabs_plan(int64_t M, int32_t d) {
     ColabsPlan pl;
     pl.col_tiles = (int)(((int64_t)d + kTileCols - 1) / kTileCols);
-    int64_t want = 512 / pl.col_tiles;           // ~2 workgroups per CU (1024: M = 32768, d = 4096 50.4 -> 51.9 us)
+    const int64_t run = max_run(M, d);
+    // 2 workgroups per CU, or 4 where the slices of 2 would be longer than `run` allows (M = 40000, d = 28672: 4
+    // slices 334 us, 9 330; 5, which would do and leave the CUs uneven shares, 384)
+    int64_t want = 512 / pl.col_tiles;
+    if (want == 0 || M > want * kGroups * run) want = 1024 / pl.col_tiles;
+    const int64_t most = (M + run - 1) / run / 2;       // no more bytes of partials than a float per run
+    if (want > most) want = most;
     if (want < 1) want = 1;
     int64_t rps = (M + want - 1) / want;
-    if (rps < 64) rps = 64;                      // at least a few rows per lane
+    if (rps < 8 * kGroups) rps = 8 * kGroups;           // at least a few rows per lane
     if (M <= kOneSlice) rps = kOneSlice;
     pl.rows_per_slice = (int)rps;
     pl.slices = (int)((M + rps - 1) / rps);
     return pl;
 }
 
-// FINAL: the only slice; the result itself is written (m_rows: rows to divide by).  STREAM: streaming loads.
-template <bool MAXSTAT, bool FINAL, bool STREAM>
+// FEW: the only slice, which writes the result (m_rows: rows to divide by).  STREAM: streaming loads.
+template <bool MAXSTAT, bool FEW, bool STREAM>
 __global__ void __launch_bounds__(kThreads)
-colabs_partial_kernel(const uint16_t* __restrict__ x, int64_t M, int32_t d, int64_t ldx,
-                      int rows_per_slice, float* __restrict__ part, float m_rows) {
-    typedef typename std::conditional<FINAL && !MAXSTAT, double, float>::type sum_t;
+colabs_partial_kernel(const uint16_t* __restrict__ x, int64_t M, int32_t d, int64_t ldx, int rows_per_slice,
+                      double* __restrict__ part, float* __restrict__ out, float m_rows) {
+    typedef typename std::conditional<MAXSTAT, float, double>::type sum_t;
     __shared__ sum_t red[kGroups][kTileCols];
     const int cl = threadIdx.x % (kThreads / kGroups), group = threadIdx.x / (kThreads / kGroups);
     const int64_t col0 = (int64_t)blockIdx.x * kTileCols, col = col0 + cl * kColsPerLane;
@@ -77,7 +91,7 @@ colabs_partial_kernel(const uint16_t* __restrict__ x, int64_t M, int32_t d, int6
     sum_t total[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (col < d) {
         const uint16_t* px = x + col;
-        if constexpr (FINAL) {
+        if constexpr (FEW) {
             // eight rows at a time, all requested together, their sums added up in double
             for (int64_t base = r0 + group; base < r1; base += 8 * kGroups) {
                 uint4 w[8];
@@ -111,19 +125,19 @@ colabs_partial_kernel(const uint16_t* __restrict__ x, int64_t M, int32_t d, int6
             const double v = red[g][threadIdx.x];
             t = MAXSTAT ? (v > t ? v : t) : t + v;
         }
-        if constexpr (FINAL) part[c] = MAXSTAT ? (float)t : (float)(t / (double)m_rows);
-        else part[(int64_t)blockIdx.y * d + c] = (float)t;
+        if constexpr (FEW) out[c] = MAXSTAT ? (float)t : (float)(t / (double)m_rows);
+        else part[(int64_t)blockIdx.y * d + c] = t;
     }
 }
 
 // Pass 2: 32 columns per workgroup, 8 lanes per column.  Lane j of a column adds slices
-// j, j+8, ... in double; the 8 sub-sums are then added in lane order.  Fixed order throughout.
+// j, j+8, ...; the 8 sub-sums are then added in lane order.  Fixed order throughout.
 constexpr int kFinishCols = 32;
 constexpr int kFinishWays = kThreads / kFinishCols;   // 8
 
 template <bool MAXSTAT>
 __global__ void __launch_bounds__(kThreads)
-colabs_finish_kernel(const float* __restrict__ part, int slices, int32_t d, float m_rows,
+colabs_finish_kernel(const double* __restrict__ part, int slices, int32_t d, float m_rows,
                      float* __restrict__ out) {
     __shared__ double red[kFinishWays][kFinishCols];
     const int cl = threadIdx.x % kFinishCols, way = threadIdx.x / kFinishCols;
@@ -132,7 +146,7 @@ colabs_finish_kernel(const float* __restrict__ part, int slices, int32_t d, floa
     if (col < d) {
 #pragma unroll 8
         for (int k = way; k < slices; k += kFinishWays) {
-            const double v = (double)part[(int64_t)k * d + col];
+            const double v = part[(int64_t)k * d + col];
             s = MAXSTAT ? (v > s ? v : s) : s + v;
         }
     }
@@ -152,14 +166,15 @@ colabs_finish_kernel(const float* __restrict__ part, int slices, int32_t d, floa
 extern "C" size_t perq_colabs_mean_workspace_bytes(int64_t M, int32_t d) {
     if (M <= 0 || d <= 0) return 0;
     const perq::ColabsPlan pl = perq::colabs_plan(M, d);
-    return (size_t)pl.slices * (size_t)d * sizeof(float);
+    // (a single slice writes the result itself; callers provide a row of floats all the same)
+    return pl.slices == 1 ? (size_t)d * sizeof(float) : (size_t)pl.slices * (size_t)d * sizeof(double);
 }
 
 // Partial sums of perq_colabs_mean_static, for callers that cannot hand over device memory of their
 // own.  In host code this name only stands for the array: its device address is looked up once per
 // device (scratch_of_current_device) and that pointer is what kernels are given.
 constexpr size_t kStaticScratchBytes = (size_t)4 << 20;
-static __device__ __align__(256) float scratch[kStaticScratchBytes / sizeof(float)];
+static __device__ __align__(256) double scratch[kStaticScratchBytes / sizeof(double)];
 
 namespace perq {
 namespace {
@@ -172,18 +187,17 @@ perq_status_t colabs_check(const uint16_t* x_bf16, int64_t M, int32_t d, int64_t
 }
 
 template <bool MAXSTAT>
-perq_status_t colabs_launch(const uint16_t* x_bf16, int64_t M, int32_t d, int64_t ldx, float* out, float* part,
+perq_status_t colabs_launch(const uint16_t* x_bf16, int64_t M, int32_t d, int64_t ldx, float* out, double* part,
                             void* hip_stream) {
     const ColabsPlan pl = colabs_plan(M, d);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (pl.slices == 1) {
-        hipLaunchKernelGGL((colabs_partial_kernel<MAXSTAT, true, false>), dim3(pl.col_tiles), dim3(kThreads), 0, stream, x_bf16,
-                           M, d, ldx, pl.rows_per_slice, out, (float)M);
-        return hipGetLastError() == hipSuccess ? PERQ_OK : PERQ_ERR_LAUNCH;
-    }
-    auto kern = M * (int64_t)d * 2 >= kStreamBytes ? colabs_partial_kernel<MAXSTAT, false, true> : colabs_partial_kernel<MAXSTAT, false, false>;
-    hipLaunchKernelGGL(kern, dim3(pl.col_tiles, pl.slices), dim3(kThreads), 0, stream, x_bf16, M, d, ldx, pl.rows_per_slice, part, 0.0f);
+    auto kern = pl.slices == 1                          ? colabs_partial_kernel<MAXSTAT, true, false>
+                : M * (int64_t)d * 2 >= kStreamBytes ? colabs_partial_kernel<MAXSTAT, false, true>
+                                                     : colabs_partial_kernel<MAXSTAT, false, false>;
+    hipLaunchKernelGGL(kern, dim3(pl.col_tiles, pl.slices), dim3(kThreads), 0, stream, x_bf16, M, d, ldx, pl.rows_per_slice,
+                       part, out, (float)M);
     if (hipGetLastError() != hipSuccess) return PERQ_ERR_LAUNCH;
+    if (pl.slices == 1) return PERQ_OK;
     hipLaunchKernelGGL(colabs_finish_kernel<MAXSTAT>, dim3((d + kFinishCols - 1) / kFinishCols), dim3(kThreads), 0,
                        stream, part, pl.slices, d, (float)M, out);
     if (hipGetLastError() != hipSuccess) return PERQ_ERR_LAUNCH;
@@ -198,14 +212,14 @@ perq_status_t colabs_stat(const uint16_t* x_bf16, int64_t M, int32_t d, int64_t 
     const size_t need = perq_colabs_mean_workspace_bytes(M, d);
     if (workspace == nullptr || workspace_bytes < need) return PERQ_ERR_INVALID_ARG;
     if ((reinterpret_cast<uintptr_t>(workspace) & 15u) != 0) return PERQ_ERR_INVALID_ARG;
-    return colabs_launch<MAXSTAT>(x_bf16, M, d, ldx, out, static_cast<float*>(workspace), hip_stream);
+    return colabs_launch<MAXSTAT>(x_bf16, M, d, ldx, out, static_cast<double*>(workspace), hip_stream);
 }
 
 // Device address of `scratch` on the current device: every device holds its own copy of the array
 // at an address of its own, looked up at the first call with that device current.
-perq_status_t scratch_of_current_device(float** out) {
+perq_status_t scratch_of_current_device(double** out) {
     static std::mutex mu;
-    static float* known[64] = {};
+    static double* known[64] = {};
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return PERQ_ERR_LAUNCH;
     std::lock_guard<std::mutex> lock(mu);
@@ -215,7 +229,7 @@ perq_status_t scratch_of_current_device(float** out) {
             (void)hipGetLastError();
             return PERQ_ERR_LAUNCH;
         }
-        known[dev] = static_cast<float*>(ptr);
+        known[dev] = static_cast<double*>(ptr);
     }
     *out = known[dev];
     return PERQ_OK;
@@ -240,7 +254,7 @@ extern "C" perq_status_t perq_colabs_mean_static(const uint16_t* x_bf16, int64_t
     const perq_status_t st = perq::colabs_check(x_bf16, M, d, ldx, out_mean);
     if (st != PERQ_OK) return st;
     if (perq_colabs_mean_workspace_bytes(M, d) > kStaticScratchBytes) return PERQ_ERR_UNSUPPORTED;
-    float* part = nullptr;
+    double* part = nullptr;
     const perq_status_t sp = perq::scratch_of_current_device(&part);
     if (sp != PERQ_OK) return sp;
     return perq::colabs_launch<false>(x_bf16, M, d, ldx, out_mean, part, hip_stream);

@@ -616,6 +616,33 @@ def test_statistics_over_slices_and_column_tiles(M, d):
     assert bool((out[d:] == -1.0).all())
 
 
+# A fp32 sum that starts with a 1 loses every later value below half its last place, so rows of ones that are followed
+# by rows of such values show how many rows a sum takes in: the documented number r at most, also where the
+# widths do not divide evenly.
+@pytest.mark.parametrize("M,d", [(4096, 28672), (32768, 28672), (4096, 43776), (4096, 8192), (33333, 256)])
+def test_mean_of_rows_that_one_sum_would_lose(M, d):
+    torch = _torch()
+    r = max(8, -(-M // max(1, 512 // -(-d // 2048))))
+    for step in (-(-M // max(1, 512 // -(-d // 256))), 8 * r, r):
+        print(f"[case] statistics M={M} d={d} ones every {step} rows", flush=True)
+        v = torch.full((M,), 2.0 ** -24 * (1 - 2.0 ** -8), dtype=torch.bfloat16)
+        v[(torch.arange(M) % step) < 8] = 1.0
+        x = v.cuda()[:, None].expand(M, d).contiguous()
+        a = float(v.double().mean())
+        got = binding.perq_colabs_mean(x).double()
+        assert float((got - a).abs().max()) <= (r + 1) * 2.0 ** -24 * a
+        assert bool((binding.perq_colabs_absmax(x) == 1.0).all())
+
+
+def test_mean_of_values_near_the_top_of_the_range():
+    """Sums of r rows fit fp32 here, sums of more do not."""
+    torch = _torch()
+    for M, d in ((1024, 256), (4096, 520), (130, 8192)):
+        x = torch.full((M, d), 3.0e37, dtype=torch.bfloat16, device="cuda")
+        got = binding.perq_colabs_mean(x).double()
+        assert bool(((got - x[0].double()).abs() <= 9 * 2.0 ** -24 * x[0].double()).all()), (M, d)
+
+
 # ---- ablation permutations and the per-token diagnostics (Appendix C; Section 3) ------------------
 def test_colabs_absmax_is_exact():
     wl = synth.llama1b_down()

@@ -66,6 +66,17 @@ def test_greedy_rejects_bad_arguments(lib):
     assert lib.perq_massdiff_perm(pa, 64, 16, pp) == binding.PERQ_ERR_INVALID_ARG
 
 
+def test_statistics_workspace_is_no_larger_than_a_float_per_run_of_rows(lib):
+    """A float per column and run of r rows (r as documented), and never more than the static array holds."""
+    rng = np.random.default_rng(5)
+    widths = [8 * k for k in range(1, 700)] + [8 * int(k) for k in rng.integers(700, 131072, size=700)] + [1 << 20]
+    for d in widths:
+        for M in [1, 9, 128, 129, 193, 1000, 4096, 33333, 10 ** 7, int(rng.integers(129, 10 ** 6))]:
+            r = max(8, -(-M // max(1, 512 // -(-d // 2048))))
+            need = lib.perq_colabs_mean_workspace_bytes(M, d)
+            assert 4 * d <= need <= min(4 * d * -(-M // r), 4 << 20), (M, d)
+
+
 def test_perm_validate():
     assert binding.perq_perm_validate(np.arange(100)[::-1])
     assert not binding.perq_perm_validate(np.array([0, 1, 1, 3]))
