@@ -6,8 +6,8 @@
 // 32 lanes own 8 adjacent columns each (one 16-byte bf16 load per row), the eight groups of 32 take
 // every eighth row, and their sums meet in LDS (in double).  It writes one partial sum per column
 // and slice, in double.  Pass 2: one lane per column adds the S partials in slice order and divides by
-// M; up to 128 rows are a single slice and there is no second launch.  No
-// atomics: the result is independent of scheduling.
+// M; a single slice (up to 128 rows, or d > 131072) writes the means itself and there is no second launch.
+// No atomics: the result is independent of scheduling.
 // Rounding: fp32 is used inside a run of at most max_run(M, d) rows of one lane only, so a run's sum is off
 // by less than max_run(M, d) - 1 roundings of non-negative terms, and the mean is rounded once more: the
 // relative error of a_i is below (max_run(M, d) + 1) * 2^-24.
@@ -30,7 +30,9 @@ constexpr int kGroups = 8;                                    // row groups of a
 constexpr int kTileCols = kColsPerLane * kThreads / kGroups;  // 256
 static_assert(kTileCols == kThreads, "one lane per column adds the groups");
 
-constexpr int kOneSlice = 128;                                // up to here a second launch costs more than the rows
+// Up to here a second launch costs more than the rows.  Their loads are all requested together; more rows take
+// the loop, also where x is so wide that they are one slice (M = 4096, d = 200000: 261 against 299 us).
+constexpr int kOneSlice = 128;
 // Inputs past the last-level cache are read with streaming loads (M = 32768, d = 4096: 50.4 -> 45.4 us);
 // smaller ones may be in it already and should stay (M = 4096, d = 8192 again and again: 13.9 against 15.2).
 constexpr int64_t kStreamBytes = (int64_t)256 << 20;
@@ -67,7 +69,8 @@ ColabsPlan colabs_plan(int64_t M, int32_t d) {
     return pl;
 }
 
-// FEW: the only slice, which writes the result (m_rows: rows to divide by).  STREAM: streaming loads.
+// FEW: at most kOneSlice rows.  STREAM: streaming loads.  part == nullptr: the only slice, which writes the
+// result (m_rows: rows to divide by).
 template <bool MAXSTAT, bool FEW, bool STREAM>
 __global__ void __launch_bounds__(kThreads)
 colabs_partial_kernel(const uint16_t* __restrict__ x, int64_t M, int32_t d, int64_t ldx, int rows_per_slice,
@@ -125,7 +128,7 @@ colabs_partial_kernel(const uint16_t* __restrict__ x, int64_t M, int32_t d, int6
             const double v = red[g][threadIdx.x];
             t = MAXSTAT ? (v > t ? v : t) : t + v;
         }
-        if constexpr (FEW) out[c] = MAXSTAT ? (float)t : (float)(t / (double)m_rows);
+        if (FEW || part == nullptr) out[c] = MAXSTAT ? (float)t : (float)(t / (double)m_rows);
         else part[(int64_t)blockIdx.y * d + c] = t;
     }
 }
@@ -191,11 +194,11 @@ perq_status_t colabs_launch(const uint16_t* x_bf16, int64_t M, int32_t d, int64_
                             void* hip_stream) {
     const ColabsPlan pl = colabs_plan(M, d);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    auto kern = pl.slices == 1                          ? colabs_partial_kernel<MAXSTAT, true, false>
+    auto kern = M <= kOneSlice                          ? colabs_partial_kernel<MAXSTAT, true, false>
                 : M * (int64_t)d * 2 >= kStreamBytes ? colabs_partial_kernel<MAXSTAT, false, true>
                                                      : colabs_partial_kernel<MAXSTAT, false, false>;
     hipLaunchKernelGGL(kern, dim3(pl.col_tiles, pl.slices), dim3(kThreads), 0, stream, x_bf16, M, d, ldx, pl.rows_per_slice,
-                       part, out, (float)M);
+                       pl.slices == 1 ? nullptr : part, out, (float)M);
     if (hipGetLastError() != hipSuccess) return PERQ_ERR_LAUNCH;
     if (pl.slices == 1) return PERQ_OK;
     hipLaunchKernelGGL(colabs_finish_kernel<MAXSTAT>, dim3((d + kFinishCols - 1) / kFinishCols), dim3(kThreads), 0,

@@ -619,7 +619,7 @@ def test_statistics_over_slices_and_column_tiles(M, d):
 # A fp32 sum that starts with a 1 loses every later value below half its last place, so rows of ones that are followed
 # by rows of such values show how many rows a sum takes in: the documented number r at most, also where the
 # widths do not divide evenly.
-@pytest.mark.parametrize("M,d", [(4096, 28672), (32768, 28672), (4096, 43776), (4096, 8192), (33333, 256)])
+@pytest.mark.parametrize("M,d", [(4096, 28672), (32768, 28672), (4096, 43776), (4096, 8192), (33333, 256), (1000, 140000)])
 def test_mean_of_rows_that_one_sum_would_lose(M, d):
     torch = _torch()
     r = max(8, -(-M // max(1, 512 // -(-d // 2048))))
