@@ -82,12 +82,6 @@ __device__ __forceinline__ uint32_t scale_dword(const uint8_t* row, uint32_t at,
     __builtin_memcpy(&v, row + from, 4);             // (rows of scales need not be aligned)
     return v >> (8u * ((at - from) & 3u));
 }
-// rows of fewer than four scale bytes (d < 128): one stage
-__device__ __forceinline__ uint32_t scale_bytes(const uint8_t* row, uint32_t at, uint32_t nb) {
-    uint32_t v = 0;
-    for (uint32_t k = 0; k < 4u; ++k) v |= (uint32_t)row[at + k < nb ? at + k : nb - 1u] << (8u * k);
-    return v;
-}
 
 // Tile of this workgroup.  Workgroups go round-robin to the 8 XCDs, each with an L2 of its own: XCD x
 // gets a contiguous share of the tiles in an order that walks columns of 8 tiles, so that its rows of
@@ -434,8 +428,8 @@ gemm_skinny_kernel(GemmParams p) {
             const uint8_t* ws = static_cast<const uint8_t*>(p.w_scales) + (int64_t)n * nb;
             uint32_t at = 8u * (uint32_t)s + 4u * (uint32_t)h;
             at = at < nb ? at : nb - 1u;
-            sa = nb < 4u ? scale_bytes(as, at, nb) : scale_dword(as, at, nb);
-            sw = nb < 4u ? scale_bytes(ws, at, nb) : scale_dword(ws, at, nb);
+            sa = scale_dword(as, at, nb);
+            sw = scale_dword(ws, at, nb);
         }
 #pragma unroll
         for (int kc = 0; kc < 4; ++kc) {
@@ -483,6 +477,55 @@ gemm_skinny_kernel(GemmParams p) {
     }
 }
 
+// ---- rows of up to four granules (d <= 128): one 32 x 32 tile per wave, nothing but its operands -----
+// Bound by the store.  Half-wave h takes granules h and 2 + h.
+template <bool MX>
+__global__ void __launch_bounds__(64)
+gemm_short_kernel(GemmParams p) {
+    const int lane = threadIdx.x, i = lane & 31, h = lane >> 5;
+    uint32_t tt, tn;
+    tile_of_block(p, tt, tn);
+    const int64_t t0 = (int64_t)tt * 32, t = t0 + i < p.T ? t0 + i : p.T - 1;
+    const int32_t n0 = (int32_t)tn * 32, n = n0 + i < p.N ? n0 + i : p.N - 1;
+    const uint32_t row_bytes = (uint32_t)p.d >> 1, granules = row_bytes >> 4;
+    acc_t<MX> acc = {};
+    v4i_t a[2], w[2];
+    uint32_t sa[2] = {0, 0}, sw[2] = {0, 0};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const uint32_t g = 2u * k + (uint32_t)h, gc = g < granules ? g : granules - 1u;
+        a[k] = *reinterpret_cast<const v4i_t*>(p.a_codes + t * row_bytes + 16u * gc);
+        w[k] = *reinterpret_cast<const v4i_t*>(p.w_codes + (int64_t)n * row_bytes + 16u * gc);
+        if constexpr (MX) {
+            sa[k] = static_cast<const uint8_t*>(p.a_scales)[t * granules + gc];
+            sw[k] = static_cast<const uint8_t*>(p.w_scales)[(int64_t)n * granules + gc];
+        }
+        if (g >= granules) a[k] = v4i_t{0, 0, 0, 0};
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        if (2u * k >= granules) break;
+        if constexpr (MX) {
+            acc = mx_product<0>(a[k], w[k], acc, sa[k], sw[k]);
+        } else {
+            const int mk = (int)kHighNibbles;
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(high_codes(a[k], mk), high_codes(w[k], mk), acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(low_codes(a[k], mk), low_codes(w[k], mk), acc, 0, 0, 0);
+        }
+    }
+    const float step_w = MX ? 1.0f : static_cast<const float*>(p.w_scales)[n];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const int64_t row = t0 + 8 * (j >> 2) + 4 * h + (j & 3);
+        if (row < p.T && n0 + i < p.N) {
+            float v;
+            if constexpr (MX) v = acc[j];
+            else v = (float)acc[j] * 0x1p-8f * static_cast<const float*>(p.a_scales)[row] * step_w;
+            p.out[row * p.ldo + n0 + i] = v;
+        }
+    }
+}
+
 template <bool MX, int MT, int NT, int WM, int WN, int NBUF, int WGS>
 hipError_t launch_tile(GemmParams p, hipStream_t stream) {
     constexpr uint32_t lds_bytes = (uint32_t)(32 * MT * WM + 32 * NT * WN) * (kStageBytes * NBUF + (MX ? 0u : 4u));
@@ -496,6 +539,14 @@ hipError_t launch_tile(GemmParams p, hipStream_t stream) {
     return hipGetLastError();
 }
 
+template <bool MX>
+hipError_t launch_short(GemmParams p, hipStream_t stream) {
+    p.tiles_t = (uint32_t)((p.T + 31) / 32);
+    p.tiles_n = (uint32_t)(((int64_t)p.N + 31) / 32);
+    hipLaunchKernelGGL(gemm_short_kernel<MX>, dim3(p.tiles_t * p.tiles_n), dim3(64), 0, stream, p);
+    return hipGetLastError();
+}
+
 template <bool MX, int KW>
 hipError_t launch_skinny(GemmParams p, hipStream_t stream) {
     p.tiles_t = (uint32_t)((p.T + 31) / 32);
@@ -506,7 +557,10 @@ hipError_t launch_skinny(GemmParams p, hipStream_t stream) {
 
 // The largest tile that still gives the 256 CUs work; every line below was measured on both sides, one
 // GPU, launches back to back, INT4 / MXFP4 us (T, N, d):
-//   d < 128: one stage; a row has fewer scale bytes than the tile kernel loads at once.
+//   d < 128, MXFP4 also d = 128: no staging and no cut of the contraction, one wave per 32 x 32 tile.
+//     (4096, 4096, 64) 14.7 / 12.2 against 19.1 / 15.6 with a trip of the tile through LDS, (16384, 512, 64)
+//     9.3 / 7.5 against 12.4 / 10.6.  At d = 128 against the tiles below: (4096, 4096) 15.9 / 13.2 against 16.3 /
+//     14.4, (16384, 512) 9.9 / 8.7 against 9.4 / 9.0, (300, 14336) 7.7 / 6.7 against 8.2 / 7.6.
 //   up to 256 tiles of 32 x 32: the contraction cut among 8 waves.  INT4 (64, 4096, 4096) 6.0 against
 //     8.2 with 64 x 64 tiles, (64, 300, 28672) 26 against 41; twice the tiles (100, 4096, 4096) 9.9
 //     against 8.7.  MXFP4 has half the products per granule: 6.7 against 7.0, and from d = 8192 on it
@@ -522,7 +576,7 @@ hipError_t launch_skinny(GemmParams p, hipStream_t stream) {
 template <bool MX>
 hipError_t launch_gemm(const GemmParams& p, hipStream_t stream) {
     auto tiles = [&](int64_t m, int64_t n) { return ((p.T + m - 1) / m) * (((int64_t)p.N + n - 1) / n); };
-    if (p.d < 128) return launch_skinny<MX, 1>(p, stream);
+    if (p.d <= (MX ? 128 : 96)) return launch_short<MX>(p, stream);
     if (tiles(32, 32) <= 256 && !(MX && p.d >= 8192)) return launch_skinny<MX, 8>(p, stream);
     if (tiles(128, 128) <= 144) return launch_tile<MX, 1, 1, 2, 2, 4, 2>(p, stream);
     if (tiles(128, 128) > 256 && p.d >= 2048) return launch_tile<MX, 2, 2, 2, 4, 2, 1>(p, stream);
