@@ -339,7 +339,8 @@ perq_status_t perq_quant_error(const float* y, int64_t T, int32_t d, const uint8
  *   w_codes  device, uint8 [N, d/2], 16-byte aligned;   w_scales  device, float [N]
  *   out      device, float [T, ldo], ldo >= N
  * The integer sums are exact; the two multiplications are fp32, left to right.  Runs on the int8
- * matrix instruction (nibbles unpacked in registers).  T == 0 or N == 0 does nothing.
+ * matrix instruction (nibbles unpacked in registers).  T up to 4194240, UNSUPPORTED beyond; T == 0 or
+ * N == 0 does nothing.
  */
 perq_status_t perq_w4a4_gemm_ref(const uint8_t* a_codes, const float* a_scales, int64_t T,
                                  const uint8_t* w_codes, const float* w_scales, int32_t N, int32_t d,
@@ -357,7 +358,7 @@ perq_status_t perq_w4a4_gemm_ref(const uint8_t* a_codes, const float* a_scales, 
  * Runs on gfx950's scaled matrix instruction (v_mfma_scale_f32_32x32x64_f8f6f4, fp4 x fp4), which
  * takes a 32-group of packed codes and its scale byte exactly as the fused path writes them: the
  * products are exact, the sums are fp32 in an order of the kernel's own that depends on the sizes only.
- * d % 32 == 0; T == 0 or N == 0 does nothing.
+ * d % 32 == 0; T up to 2097120, UNSUPPORTED beyond; T == 0 or N == 0 does nothing.
  */
 perq_status_t perq_w4a4_mxfp4_gemm_ref(const uint8_t* a_codes, const uint8_t* a_scales, int64_t T,
                                        const uint8_t* w_codes, const uint8_t* w_scales, int32_t N, int32_t d,

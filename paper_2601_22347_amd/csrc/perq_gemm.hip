@@ -530,7 +530,7 @@ template <bool MX, int MT, int NT, int WM, int WN, int NBUF, int WGS>
 hipError_t launch_tile(GemmParams p, hipStream_t stream) {
     constexpr uint32_t lds_bytes = (uint32_t)(32 * MT * WM + 32 * NT * WN) * (kStageBytes * NBUF + (MX ? 0u : 4u));
     p.tiles_t = (uint32_t)((p.T + 32 * MT * WM - 1) / (32 * MT * WM));
-    p.tiles_n = (uint32_t)((p.N + 32 * NT * WN - 1) / (32 * NT * WN));
+    p.tiles_n = (uint32_t)(((int64_t)p.N + 32 * NT * WN - 1) / (32 * NT * WN));
     auto kern = gemm_tile_kernel<MX, MT, NT, WM, WN, NBUF, WGS>;
     int per_cu = 0;      // (raises the kernel's limit of dynamic LDS)
     const hipError_t e = resident_blocks(reinterpret_cast<const void*>(kern), 64 * WM * WN, lds_bytes, &per_cu);
@@ -539,12 +539,34 @@ hipError_t launch_tile(GemmParams p, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// Rows of one launch of the kernel for short rows.  A grid takes less than 2^32 lanes, 64 to a tile of 32 x 32
+// outputs: 2^36 outputs are more than that (and fit the card's memory).  The other kernels have a lane
+// per 64 outputs, or few tiles.
+constexpr int64_t rows_of_a_short_launch(int64_t tiles_n) {
+    const int64_t most = ((int64_t)1 << 26) - 1;
+    return 32 * (most / tiles_n > 0 ? most / tiles_n : 1);
+}
+static_assert(rows_of_a_short_launch(1) == 32 * (((int64_t)1 << 26) - 1), "one column of tiles: any T that is accepted");
+static_assert(rows_of_a_short_launch(33000 / 32 + 1) < 2097120, "T = 2097120, N = 33000 (277 GB of output) takes two launches");
+static_assert(rows_of_a_short_launch(33000 / 32 + 1) / 32 * (33000 / 32 + 1) * 64 < ((int64_t)1 << 32), "that fit");
+static_assert(rows_of_a_short_launch(32768 / 32) >= 2097120, "T = 2097120, N = 32768 takes one");
+
 template <bool MX>
-hipError_t launch_short(GemmParams p, hipStream_t stream) {
-    p.tiles_t = (uint32_t)((p.T + 31) / 32);
+hipError_t launch_short(const GemmParams& all, hipStream_t stream) {
+    GemmParams p = all;
     p.tiles_n = (uint32_t)(((int64_t)p.N + 31) / 32);
-    hipLaunchKernelGGL(gemm_short_kernel<MX>, dim3(p.tiles_t * p.tiles_n), dim3(64), 0, stream, p);
-    return hipGetLastError();
+    const int64_t rows = rows_of_a_short_launch(p.tiles_n), row_bytes = all.d >> 1, scale_bytes = MX ? all.d >> 5 : 4;
+    for (int64_t t = 0; t < all.T; t += rows) {
+        p.T = all.T - t < rows ? all.T - t : rows;
+        p.a_codes = all.a_codes + t * row_bytes;
+        p.a_scales = static_cast<const uint8_t*>(all.a_scales) + t * scale_bytes;
+        p.out = all.out + t * all.ldo;
+        p.tiles_t = (uint32_t)((p.T + 31) / 32);
+        hipLaunchKernelGGL(gemm_short_kernel<MX>, dim3(p.tiles_t * p.tiles_n), dim3(64), 0, stream, p);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <bool MX, int KW>
@@ -599,7 +621,7 @@ extern "C" perq_status_t perq_w4a4_mxfp4_gemm_ref(const uint8_t* a_codes, const 
     if (((reinterpret_cast<uintptr_t>(a_codes) | reinterpret_cast<uintptr_t>(w_codes)) & 15u) != 0 ||
         (reinterpret_cast<uintptr_t>(out) & 3u) != 0)
         return PERQ_ERR_UNSUPPORTED;
-    if ((T + 31) / 32 > 65535) return PERQ_ERR_UNSUPPORTED;          // one launch, no splitting of T here
+    if ((T + 31) / 32 > 65535) return PERQ_ERR_UNSUPPORTED;          // the documented reach
     const perq::GemmParams p = {a_codes, a_scales, w_codes, w_scales, out, T, ldo, N, d, 0, 0};
     return perq::launch_gemm<true>(p, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? PERQ_OK : PERQ_ERR_LAUNCH;
 }
@@ -614,7 +636,7 @@ extern "C" perq_status_t perq_w4a4_gemm_ref(const uint8_t* a_codes, const float*
     if (((reinterpret_cast<uintptr_t>(a_codes) | reinterpret_cast<uintptr_t>(w_codes)) & 15u) != 0 ||
         ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales) | reinterpret_cast<uintptr_t>(out)) & 3u) != 0)
         return PERQ_ERR_UNSUPPORTED;
-    if ((T + 63) / 64 > 65535) return PERQ_ERR_UNSUPPORTED;          // one launch, no splitting of T here
+    if ((T + 63) / 64 > 65535) return PERQ_ERR_UNSUPPORTED;          // the documented reach
     const perq::GemmParams p = {a_codes, a_scales, w_codes, w_scales, out, T, ldo, N, d, 0, 0};
     return perq::launch_gemm<false>(p, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? PERQ_OK : PERQ_ERR_LAUNCH;
 }
