@@ -55,6 +55,46 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def _device_assembly(src: str) -> str:
+    import tempfile
+    with tempfile.TemporaryDirectory() as tmp:
+        asm = os.path.join(tmp, os.path.splitext(src)[0] + ".s")
+        flags = [f for f in HIP_FLAGS if f != "-fPIC"]
+        cmd = [hipcc(), *flags, "--offload-device-only", "-S", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+               "-x", "hip", os.path.join(CSRC, src), "-o", asm]
+        res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        if res.returncode != 0:
+            raise RuntimeError(f"hipcc failed:\n{res.stdout}")
+        return open(asm).read()
+
+
+def check_product_waits() -> int:
+    """Compiler check for the counted waits of the products' tile kernels (perq_gemm.hip), about six seconds.
+
+    A stage begins with a wait that lets the loads of the stages behind it be on their way, and requests one
+    more stage.  The waits may count loads into LDS only, and every one of those has to be there: one wait of
+    NBUF - 1 stages, then a wait of NBUF - 2 stages and a stage of loads each.  Returns the number of
+    kernel variants checked; raises on a mismatch."""
+    import re
+    text = _device_assembly("perq_gemm.hip")
+    checked = 0
+    for m in re.finditer(r"\n(_ZN4perq\S*gemm_tile_kernelILb\dELi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)\S*): +; @", text):
+        mt, nt, wm, wn, nbuf = (int(v) for v in m.groups()[1:])
+        loads = 4 * (mt * wm + nt * wn) // (wm * wn)                 # of a wave and stage
+        body = text[m.end():text.index(".Lfunc_end", m.end())].split("\n")
+        issued = sum("buffer_load_dwordx4" in l and " lds" in l for l in body)
+        waits = [int(re.search(r"vmcnt\((\d+)\)", l).group(1)) for i, l in enumerate(body)
+                 if "vmcnt(" in l and any("s_barrier" in k for k in body[i + 1:i + 5])]
+        stages = len(waits) - 1
+        if stages < 12 or sorted(waits) != sorted([loads * (nbuf - 1)] + [loads * (nbuf - 2)] * stages) or \
+                issued != loads * (nbuf + stages):
+            raise RuntimeError(f"{m.group(1)}: {loads} loads a stage, {issued} in all, waits {waits}")
+        checked += 1
+    if checked == 0:
+        raise RuntimeError("no tile kernel found")
+    return checked
+
+
 def check_table_reads() -> int:
     """Compiler check for the prepared-form reads of the matrix-core kernel (perq_mfma.hip).
 
@@ -65,16 +105,7 @@ def check_table_reads() -> int:
     the tuples handed back are the ones the loads were given.  Returns the number of variants checked;
     raises on a mismatch.  Run after a compiler upgrade: `python -m paper_2601_22347_amd.build --check-table-reads`."""
     import re
-    import tempfile
-    with tempfile.TemporaryDirectory() as tmp:
-        asm = os.path.join(tmp, "perq_mfma.s")
-        flags = [f for f in HIP_FLAGS if f != "-fPIC"]
-        cmd = [hipcc(), *flags, "--offload-device-only", "-S", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-               "-x", "hip", os.path.join(CSRC, "perq_mfma.hip"), "-o", asm]
-        res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-        if res.returncode != 0:
-            raise RuntimeError(f"hipcc failed:\n{res.stdout}")
-        text = open(asm).read()
+    text = _device_assembly("perq_mfma.hip")
     checked = 0
     for m in re.finditer(r"\n(_ZN4perq\S*mfma_kernel\S*): +; @", text):
         body = text[m.end():text.index("s_endpgm", m.end())].split("\n")

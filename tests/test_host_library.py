@@ -66,6 +66,11 @@ def test_greedy_rejects_bad_arguments(lib):
     assert lib.perq_massdiff_perm(pa, 64, 16, pp) == binding.PERQ_ERR_INVALID_ARG
 
 
+def test_counted_waits_of_the_products_count_loads_that_are_there():
+    from paper_2601_22347_amd import build
+    assert build.check_product_waits() >= 7                           # tile shapes of both formats
+
+
 def test_statistics_workspace_is_no_larger_than_a_float_per_run_of_rows(lib):
     """A float per column and run of r rows (r as documented), and never more than the static array holds."""
     rng = np.random.default_rng(5)
