@@ -71,7 +71,12 @@ typedef enum {
 /* Which rotation kernel runs.  AUTO picks the fastest one that covers the shape (block sizes that
  * are not powers of two, and powers of two above 4096 on rows of 8192, 16384 or 32768, have a
  * matrix-core kernel of their own that only AUTO selects); the explicit values exist so that the
- * two general kernels can be compared with each other and each checked alone. */
+ * two general kernels can be compared with each other and each checked alone.
+ *   AUTO decides between the two general kernels by T, d, ldx, b, the format and whether a permutation is
+ * given (not by its prepared form).  They add in different orders, both in fp32: the last bits of a step, and
+ * with them a code next to a rounding boundary, can differ between calls that AUTO sends to different
+ * kernels, for instance between a row in a batch of 16 and the same row in a batch of 4096.  With an
+ * explicit kernel a row's output depends on that row alone, bit for bit. */
 typedef enum {
     PERQ_ALGO_AUTO = 0,
     PERQ_ALGO_BUTTERFLY = 1,  /* register / cross-lane / LDS radix-2 butterflies; every shape with a

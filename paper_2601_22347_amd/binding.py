@@ -342,7 +342,8 @@ def alloc_outputs(T: int, d: int, fmt: str, device):
 def perq_permute_rotate_quant(x, perm, b: int, fmt: str, codes=None, scales=None, stream=None,
                               algo: str = "auto", placement=None):
     """x: CUDA bf16 [T, d]; perm: CUDA int32 [d] or None; placement: CUDA uint8 copy of what
-    perq_perm_prepare wrote for perm, or None.  Returns (codes, scales) tensors."""
+    perq_perm_prepare wrote for perm, or None.  Returns (codes, scales) tensors.
+    algo "auto" goes by T too; with "mfma" or "butterfly" a row's bits do not depend on the rows beside it."""
     T, d, ldx = _check_x(x)
     if codes is None or scales is None:
         codes, scales = alloc_outputs(T, d, fmt, x.device)

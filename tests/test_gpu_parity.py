@@ -427,6 +427,25 @@ def test_few_rows_and_many_take_either_kernel(d, b, rows, with_perm, fmt):
                 assert torch.equal(p, q)
 
 
+# ---- a kernel chosen by the caller: a row's bits do not depend on how many rows come with it ------------
+@pytest.mark.parametrize("d,b", [(1024, 64), (2048, 2048), (3072, 32), (4096, 128), (4096, 4096), (8192, 32), (14336, 512), (20480, 16)])
+@pytest.mark.parametrize("algo", ["butterfly", "mfma"])
+def test_rows_alone_and_among_others(d, b, algo):
+    torch = _torch()
+    rng = np.random.default_rng(d + b)
+    few = binding.bits_to_device(synth.f64_to_bf16_bits(rng.standard_t(4, size=(67, d))))
+    many = few.repeat((1 << 24) // d // 67 + 2, 1)
+    for perm in (None, torch.from_numpy(rng.permutation(d).astype(np.int32)).cuda()):
+        print(f"[case] few and many rows d={d} b={b} algo={algo}", flush=True)
+        for fmt in ("int4", "mxfp4", "int4_asym", "fp4_token"):
+            want = binding.perq_permute_rotate_quant(many, perm, b, fmt, algo=algo)
+            for T in (1, 7, 67):
+                for got, full in zip(binding.perq_permute_rotate_quant(few[:T], perm, b, fmt, algo=algo), want):
+                    assert torch.equal(got, full[:T]) and torch.equal(got, full[67:67 + T]), (T, fmt)
+        y = binding.perq_permute_rotate_f32(many, perm, b, algo=algo)
+        assert torch.equal(binding.perq_permute_rotate_f32(few, perm, b, algo=algo), y[:67])
+
+
 # ---- rows that are no multiple of a load instruction: staged at a pitch of whole instructions ----------
 # AUTO takes the matrix-core kernel for every such width from 2^26 elements on.  The rows repeat with a
 # period of 32, and a row's output does not depend on its place: the first 32 go to the oracle, the others
