@@ -720,6 +720,12 @@ def test_calibrated_permutations_ranked_by_the_bound():
 
 
 # ---- the fused call with a placement prepared for the permutation -------------------------------------
+def _in_bulk(x):
+    """x over and over, 2^24 elements and more: with a permutation and d >= 4096 the matrix-core kernel takes so
+    many whatever b is, and reads the prepared form."""
+    return x.repeat((1 << 24) // x.numel() + 1, 1)
+
+
 @pytest.mark.parametrize("T,d,b,fmt", [(300, 4096, 128, "int4"), (4200, 4096, 128, "int4"), (300, 4096, 4096, "int4"),
                                        (2100, 8192, 32, "mxfp4"), (1030, 14336, 128, "int4"), (1030, 14336, 2048, "int4_asym"),
                                        (270, 14336, 512, "fp4_token"), (530, 20480, 1024, "int4"), (600, 12288, 64, "mxfp4"),
@@ -744,15 +750,23 @@ def test_prepared_placement_gives_the_plain_call_bit_for_bit(T, d, b, fmt):
     rows = min(T, 128)
     got = binding.perq_permute_rotate_quant(x, perm_t, b, fmt, placement=binding.placement_to_device(table))
     torch.cuda.synchronize()
-    assert torch.equal(got[0], plain[0]) and torch.equal(got[1], plain[1])
+    assert torch.equal(got[0], plain[0]) and torch.equal(got[1], plain[1])          # (few rows: the form may be ignored)
+    # many rows: the kernel that reads the form, against the same kernel chosen without one
+    bulk = _in_bulk(x)
+    want = binding.perq_permute_rotate_quant(bulk, perm_t, b, fmt, algo="mfma")
+    got = binding.perq_permute_rotate_quant(bulk, perm_t, b, fmt, placement=binding.placement_to_device(table))
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    # ... and it does read it: the form of another permutation gives other codes
+    other = binding.placement_to_device(binding.perq_perm_prepare(np.roll(perm, 1), b)[0])
+    assert not torch.equal(binding.perq_permute_rotate_quant(bulk, perm_t, b, fmt, placement=other)[0], want[0])
     # a random valid form: the 8 pieces of every 128-byte line shuffled
     G = d // 8
     slot_of = np.concatenate([8 * w + rng.permutation(8) for w in range(G // 8)]).astype(np.int64)
     rnd = prepared_form.assemble(perm, slot_of)
     assert binding.perq_perm_prepared_validate(rnd, perm)
-    got = binding.perq_permute_rotate_quant(x, perm_t, b, fmt, placement=binding.placement_to_device(rnd))
+    got = binding.perq_permute_rotate_quant(bulk, perm_t, b, fmt, placement=binding.placement_to_device(rnd))
     torch.cuda.synchronize()
-    assert torch.equal(got[0], plain[0]) and torch.equal(got[1], plain[1])
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
     # and against the oracle
     rep = parity.compare_apply(x_bits[:rows], perm, b, fmt, got[0][:rows].cpu().numpy(), got[1][:rows].cpu().numpy())
     assert rep.ok(), (rep.summary(), rep.notes[:5])
@@ -760,7 +774,8 @@ def test_prepared_placement_gives_the_plain_call_bit_for_bit(T, d, b, fmt):
 
 def test_prepared_form_on_seeded_random_shapes():
     """Forty seeded shapes (row widths in steps of 512 from 4096 to 32768, every block size that divides
-    them, every format, 1 to 300 rows): the prepared call equals the plain call bit for bit."""
+    them, every format, 1 to 300 rows, alone and over and over until the matrix-core kernel takes them): the
+    prepared call equals the plain call and that kernel without the form, bit for bit."""
     torch = _torch()
     rng = np.random.default_rng(20260)
     fmts = ["int4", "mxfp4", "int4_asym", "fp4_token"]
@@ -779,6 +794,10 @@ def test_prepared_form_on_seeded_random_shapes():
         got = binding.perq_permute_rotate_quant(x, perm_t, b, fmt, placement=form)
         torch.cuda.synchronize()
         assert torch.equal(got[0], plain[0]) and torch.equal(got[1], plain[1]), (T, d, b, fmt)
+        bulk = _in_bulk(x)
+        want = binding.perq_permute_rotate_quant(bulk, perm_t, b, fmt, algo="mfma")
+        got = binding.perq_permute_rotate_quant(bulk, perm_t, b, fmt, placement=form)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), (bulk.shape[0], d, b, fmt)
 
 
 def test_prepared_placement_is_ignored_where_no_such_gather_runs():
@@ -890,14 +909,17 @@ def test_prepared_form_and_chunked_kernel_in_a_graph():
     torch = _torch()
     rng = np.random.default_rng(321)
     st = torch.cuda.Stream()
-    for T, d, b, fmt, prepared in ((700, 8192, 64, "int4", True), (300, 14336, 2048, "int4_asym", True),
+    for T, d, b, fmt, prepared in ((1100, 8192, 64, "int4", True), (300, 14336, 2048, "int4_asym", True),
                                    (500, 12288, 12288, "int4", False), (260, 16384, 8192, "mxfp4", False)):
         print(f"[case] graph T={T} d={d} b={b} fmt={fmt} prepared={prepared}", flush=True)
         x = binding.bits_to_device(synth.f64_to_bf16_bits(rng.standard_t(4, size=(T, d))))
         perm_np = rng.permutation(d).astype(np.int32) if prepared else None
         perm = torch.from_numpy(perm_np).cuda() if prepared else None
         form = binding.placement_to_device(binding.perq_perm_prepare(perm_np, b)[0]) if prepared else None
-        ref = binding.perq_permute_rotate_quant(x, perm, b, fmt)
+        ref = binding.perq_permute_rotate_quant(x, perm, b, fmt, algo="mfma" if prepared else "auto")
+        if prepared:          # the form is read
+            other = binding.placement_to_device(binding.perq_perm_prepare(np.roll(perm_np, 1), b)[0])
+            assert not torch.equal(binding.perq_permute_rotate_quant(x, perm, b, fmt, placement=other)[0], ref[0])
         codes, scales = binding.alloc_outputs(T, d, fmt, x.device)
         torch.cuda.synchronize()
         g = torch.cuda.CUDAGraph()
