@@ -549,12 +549,15 @@ def test_w4a4_mxfp4_gemm_on_the_scaled_matrix_unit(T, N, d, b):
 
 
 # every branch of the products' choice of tile, each at ragged edges of rows, columns and contraction
-@pytest.mark.parametrize("T,N,d", [(1, 1, 32), (3, 70, 96),                          # one stage, one wave per tile
+# (rows of a superstage of 1024 codes or less never reach the loop over whole superstages: every tile shape that
+# runs it is here with several of them, with rows that end there and rows that go on for one, two or four stages)
+@pytest.mark.parametrize("T,N,d", [(1, 1, 32), (3, 70, 96), (515, 700, 64), (515, 700, 96), (515, 700, 128),     # one wave per tile
                                    (33, 70, 128), (5, 3, 1056), (64, 130, 4096),      # few tiles: contraction cut among waves
                                    (31, 65, 8224),                                    # the same sizes, long rows
-                                   (513, 700, 1024), (449, 577, 2880),                # 64 x 64 tiles
-                                   (1540, 1537, 1312), (1700, 1300, 544),             # 128 x 128
-                                   (2177, 2177, 416), (2060, 2177, 2080)])            # 128 x 128 twice a CU; 128 x 256
+                                   (513, 700, 1024), (449, 577, 2880), (449, 577, 4096),                # 64 x 64 tiles
+                                   (1540, 1537, 1312), (1700, 1300, 544), (1540, 1537, 2880), (1540, 1537, 3328), (1540, 1537, 4096),  # 128 x 128
+                                   (2177, 2177, 416), (2177, 2177, 2016), (2060, 2177, 2080),      # 128 x 128 twice a CU; 128 x 256
+                                   (2060, 2177, 2880), (2060, 2177, 3328), (2060, 2177, 4096)])
 @pytest.mark.parametrize("fmt", ["int4", "mxfp4"])
 def test_w4a4_products_over_tiles_and_remainders(T, N, d, fmt):
     torch = _torch()
@@ -583,7 +586,8 @@ def test_w4a4_products_over_tiles_and_remainders(T, N, d, fmt):
 
 
 # ---- rows that end in several stages of a partial superstage: the waits count the loads that are there ----
-@pytest.mark.parametrize("T,N,d", [(449, 577, 2880), (513, 700, 1312), (1540, 1537, 800), (2177, 2177, 2016)])
+@pytest.mark.parametrize("T,N,d", [(449, 577, 2880), (513, 700, 1312), (1540, 1537, 800), (2177, 2177, 2016),
+                                   (1540, 1537, 2880), (1540, 1537, 4096), (2060, 2177, 2880), (2060, 2177, 4096)])
 @pytest.mark.parametrize("fmt", ["int4", "mxfp4"])
 def test_w4a4_products_repeat_bit_for_bit(T, N, d, fmt):
     torch = _torch()
@@ -596,8 +600,9 @@ def test_w4a4_products_repeat_bit_for_bit(T, N, d, fmt):
         sa, sw = (torch.randint(120, 131, (n, d // 32), dtype=torch.uint8, device="cuda", generator=g) for n in (T, N))
         call = binding.perq_w4a4_mxfp4_gemm_ref
     first = call(ca, sa, cw, sw)
-    for _ in range(50):
-        ca = ca.clone()                 # from memory again, not from the caches
+    flush = torch.empty(512 << 20, dtype=torch.uint8, device="cuda")
+    for k in range(50):
+        flush.fill_(k)                  # twice the last-level cache: the operands come from memory
         assert torch.equal(call(ca, sa, cw, sw), first)
 
 
