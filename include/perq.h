@@ -111,12 +111,12 @@ perq_status_t perq_colabs_mean(const uint16_t* x_bf16, int64_t M, int32_t d, int
 /*
  * perq_colabs_mean for callers that cannot allocate device memory or hand any over: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same kernels, same result
- * bit for bit; the partial sums live in a 4 MiB array that is part of the library's code object
+ * bit for bit; the partial sums live in a 2 MiB array that is part of the library's code object
  * (one copy per device, held until the process ends) instead of a caller's workspace.  The call
  * itself allocates and frees nothing.  The very first call on a device looks up the array's
  * address there; make that call outside a capture.
- *   Limit: perq_colabs_mean_workspace_bytes(M, d) <= 4 MiB, which holds for every M when
- *   d <= 1048576; beyond it PERQ_ERR_UNSUPPORTED.  Other arguments and errors as perq_colabs_mean.
+ *   Limit: d <= 1048576, any M; beyond it PERQ_ERR_UNSUPPORTED.  Other arguments and errors as
+ *   perq_colabs_mean.
  *   All calls on one device share the array: two calls that overlap there (different streams, or
  *   graph replays side by side) race and give undefined means; calls on one stream are safe.
  *   Nothing needs clearing between calls (the first pass overwrites every partial the second reads).

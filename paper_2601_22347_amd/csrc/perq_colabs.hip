@@ -37,6 +37,8 @@ constexpr int kOneSlice = 128;
 // smaller ones may be in it already and should stay (M = 4096, d = 8192 again and again: 13.9 against 15.2).
 constexpr int64_t kStreamBytes = (int64_t)256 << 20;
 
+constexpr int kMostBlocks = 1024;                             // workgroups of a first pass of several slices
+
 struct ColabsPlan {
     int col_tiles;
     int slices;
@@ -56,8 +58,8 @@ ColabsPlan colabs_plan(int64_t M, int32_t d) {
     const int64_t run = max_run(M, d);
     // 2 workgroups per CU, or 4 where the slices of 2 would be longer than `run` allows (M = 40000, d = 28672: 4
     // slices 334 us, 9 330; 5, which would do and leave the CUs uneven shares, 384)
-    int64_t want = 512 / pl.col_tiles;
-    if (want == 0 || M > want * kGroups * run) want = 1024 / pl.col_tiles;
+    int64_t want = kMostBlocks / 2 / pl.col_tiles;
+    if (want == 0 || M > want * kGroups * run) want = kMostBlocks / pl.col_tiles;
     const int64_t most = (M + run - 1) / run / 2;       // no more bytes of partials than a float per run
     if (want > most) want = most;
     if (want < 1) want = 1;
@@ -176,8 +178,9 @@ extern "C" size_t perq_colabs_mean_workspace_bytes(int64_t M, int32_t d) {
 // Partial sums of perq_colabs_mean_static, for callers that cannot hand over device memory of their
 // own.  In host code this name only stands for the array: its device address is looked up once per
 // device (scratch_of_current_device) and that pointer is what kernels are given.
-constexpr size_t kStaticScratchBytes = (size_t)4 << 20;
-static __device__ __align__(256) double scratch[kStaticScratchBytes / sizeof(double)];
+// Several slices never have more columns in all than kMostBlocks tiles.
+static __device__ __align__(256) double scratch[perq::kMostBlocks * perq::kTileCols];
+constexpr int32_t kStaticMostColumns = 1 << 20;
 
 namespace perq {
 namespace {
@@ -256,7 +259,7 @@ extern "C" perq_status_t perq_colabs_mean_static(const uint16_t* x_bf16, int64_t
                                                  float* out_mean, void* hip_stream) {
     const perq_status_t st = perq::colabs_check(x_bf16, M, d, ldx, out_mean);
     if (st != PERQ_OK) return st;
-    if (perq_colabs_mean_workspace_bytes(M, d) > kStaticScratchBytes) return PERQ_ERR_UNSUPPORTED;
+    if (d > kStaticMostColumns) return PERQ_ERR_UNSUPPORTED;
     double* part = nullptr;
     const perq_status_t sp = perq::scratch_of_current_device(&part);
     if (sp != PERQ_OK) return sp;

@@ -1,4 +1,5 @@
-// Matrix-core kernel for X -> quantize(XP R~), b <= 4096, d a multiple of 512.
+// Matrix-core kernel for X -> quantize(XP R~), b <= 4096, d a multiple of 512; under AUTO also other d from 2560
+// on, b <= 256 (rows staged at a pitch of whole load instructions).
 //
 // The low five index bits of the rotation are one dense product on the MFMA unit; what is left
 // (b > 32) are a few +-1 butterflies on the accumulators.

@@ -23,9 +23,10 @@ def test_static_scratch_entry_point_matches_the_workspace_one():
     lib = binding.load()
     stream = torch.cuda.current_stream()
     sp = ctypes.c_void_p(stream.cuda_stream)
-    # the second input is smaller in both directions: fewer slices, narrower rows; the third is the
-    # largest the array holds for its width (32 slices of 32768 columns = 4 MiB)
-    for seed, (M, d) in enumerate([(4096, 8192), (777, 2048), (260, 32768)]):
+    # the second input is smaller in both directions: fewer slices, narrower rows; the last needs the most
+    # partial sums of all (11 slices of 23808 columns in double, 2048 bytes short of the 2 MiB array)
+    assert lib.perq_colabs_mean_workspace_bytes(2000, 23808) == (2 << 20) - 2048
+    for seed, (M, d) in enumerate([(4096, 8192), (777, 2048), (260, 32768), (2000, 23808)]):
         print(f"[case] perq_colabs_mean_static M={M} d={d}", flush=True)
         bits = _rows(seed, M, d)
         x = binding.bits_to_device(bits)
@@ -57,7 +58,8 @@ def test_static_scratch_entry_point_rejects_what_it_cannot_hold():
     assert lib.perq_colabs_mean_static(fake, 0, 256, 256, fake, None) == INV
     assert lib.perq_colabs_mean_static(fake, 4, 256, 128, fake, None) == INV
     assert lib.perq_colabs_mean_static(fake, 4, 252, 256, fake, None) == UNS
-    # wider than the array's limit (one slice of 2^21 columns needs 8 MiB of partial sums)
+    # wider than the documented limit
     assert lib.perq_colabs_mean_workspace_bytes(16, 1 << 21) > (4 << 20)
     assert lib.perq_colabs_mean_static(fake, 16, 1 << 21, 1 << 21, fake, None) == UNS
+    assert lib.perq_colabs_mean_static(fake, 16, (1 << 20) + 8, (1 << 20) + 8, fake, None) == UNS
     assert torch.cuda.is_available()
