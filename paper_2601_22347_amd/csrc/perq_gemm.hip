@@ -578,31 +578,38 @@ hipError_t launch_skinny(GemmParams p, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// The largest tile that still gives the 256 CUs work; every line below was measured on both sides, one
-// GPU, launches back to back, INT4 / MXFP4 us (T, N, d):
+// Which kernel and tile.  Measured on both sides of every line, one GPU, launches back to back, INT4 / MXFP4
+// us (T, N, d), the kernel that is taken first:
 //   d < 128, MXFP4 also d = 128: no staging and no cut of the contraction, one wave per 32 x 32 tile.
 //     (4096, 4096, 64) 14.7 / 12.2 against 19.1 / 15.6 with a trip of the tile through LDS, (16384, 512, 64)
 //     9.3 / 7.5 against 12.4 / 10.6.  At d = 128 against the tiles below: (4096, 4096) 15.9 / 13.2 against 16.3 /
 //     14.4, (16384, 512) 9.9 / 8.7 against 9.4 / 9.0, (300, 14336) 7.7 / 6.7 against 8.2 / 7.6.
-//   up to 256 tiles of 32 x 32: the contraction cut among 8 waves.  INT4 (64, 4096, 4096) 6.0 against
-//     8.2 with 64 x 64 tiles, (64, 300, 28672) 26 against 41; twice the tiles (100, 4096, 4096) 9.9
-//     against 8.7.  MXFP4 has half the products per granule: 6.7 against 7.0, and from d = 8192 on it
-//     loses ((64, 300, 28672) 32 against 25, (32, 4096, 14336) 19 against 16).
-//   up to 144 tiles of 128 x 128: 64 x 64 tiles.  (512, 4096, 4096) 13.0 / 15.1 against 16.2 / 15.0;
-//     at 256 tiles (1024, 4096, 4096) 24.0 / 27.0 against 18.9 / 20.0.
-//   more than 256 tiles of 128 x 128 and d >= 2048: 128 x 256, a sixth less to load per product.
-//     (2048, 4096, 4096) 30.2 / 32.4 against 35.9 / 37.5; (4096, 4096, 512) 20.2 / 24.5 against
-//     19.4 / 21.7; at 256 tiles (1024, 4096, 4096) 25 / 26 against 18.9 / 20.
-//   MXFP4 with at most one 128 x 128 tile per CU: four stages in LDS instead of two and a second
-//     workgroup that would not come, (2048, 2048, 8192) 32.6 against 34.4, (1024, 4096, 14336) 49 against
-//     57; INT4, whose stages take twice as long, is faster with two (32.4 against 35.2).
+//   up to 256 tiles of 32 x 32: the contraction cut among 8 waves, against 64 x 64 tiles.  256 tiles:
+//     (64, 4096, 4096) 7.0 / 6.9 against 8.2 / 7.0, d = 6144 7.8 / 8.7 against 10.9 / 8.5, d = 8192 10.8 / 10.9 against
+//     13.7 / 10.0 (MXFP4 has half the products per granule: not from d = 8192 on).  258 tiles: (96, 2752, 4096)
+//     9.3 / 10.8 against 8.8 / 7.1.
+//   up to 128 tiles of 128 x 128: 64 x 64 tiles, which two workgroups a CU hold at once up to there, against
+//     128 x 128.  (512, 4096, 4096) 12.6 / 15.0 against 16.3 / 15.3, d = 1024 7.3 / 8.6 against 7.6 / 9.3; the other way
+//     round with 130 tiles, (640, 3328, 4096) 16.5 / 15.5 against 17.9 / 20.7.
+//   more than 256 tiles of 128 x 128: 128 x 256, a sixth less to load per product, for long rows, and only if the
+//     rounds of 256 such tiles are full (or there is one: then a CU has two 128 x 128 tiles or one of these).
+//     (4096, 4096): d = 2048 36.2 / 38.8 with 128 x 128 against 36.1 / 42.4, d = 2880 49.7 / 52.4 against 48.1 / 51.3,
+//     d = 4096 61.0 / 61.5 against 57.0 / 62.5, d = 5120 72.7 / 76.1 against 68.1 / 73.0, d = 8192 110 / 110 against 102 / 103.
+//     Rounds that are not full: (3000, 3500, 4096) 42.3 / 46.4 with 128 x 128 against 50.0 / 57.2, d = 8192 76.0 / 80.6
+//     against 90.1 / 95.3; (2048, 14336, 4096), three and a half, 104 / 106 against 104 / 116.  One round: (2048, 4096,
+//     4096) 29.9 / 33.0 against 29.8 / 33.0, (2177, 2177, 8192) 45.2 / 47.6 against 43.3 / 47.7.
+//   MXFP4 with at most one 128 x 128 tile per CU: four stages in LDS instead of two and a second workgroup that
+//     would not come, (2048, 2048, 4096) 19.5 against 20.6, (1280, 1664, 4096) 16.1 against 17.0, (1536, 1536, 1024) 9.6
+//     against 9.5; INT4, whose stages take twice as long, is faster with two.
 template <bool MX>
 hipError_t launch_gemm(const GemmParams& p, hipStream_t stream) {
     auto tiles = [&](int64_t m, int64_t n) { return ((p.T + m - 1) / m) * (((int64_t)p.N + n - 1) / n); };
     if (p.d <= (MX ? 128 : 96)) return launch_short<MX>(p, stream);
     if (tiles(32, 32) <= 256 && !(MX && p.d >= 8192)) return launch_skinny<MX, 8>(p, stream);
-    if (tiles(128, 128) <= 144) return launch_tile<MX, 1, 1, 2, 2, 4, 2>(p, stream);
-    if (tiles(128, 128) > 256 && p.d >= 2048) return launch_tile<MX, 2, 2, 2, 4, 2, 1>(p, stream);
+    if (tiles(128, 128) <= 128) return launch_tile<MX, 1, 1, 2, 2, 4, 2>(p, stream);
+    const int64_t wide = tiles(128, 256), rounds = (wide + 255) / 256;
+    if (tiles(128, 128) > 256 && p.d >= (MX ? 5120 : 2880) && (rounds == 1 || 16 * wide >= 15 * 256 * rounds))
+        return launch_tile<MX, 2, 2, 2, 4, 2, 1>(p, stream);
     if constexpr (MX) {
         if (tiles(128, 128) <= 256) return launch_tile<MX, 2, 2, 2, 2, 4, 1>(p, stream);
     }

@@ -557,7 +557,8 @@ def test_w4a4_mxfp4_gemm_on_the_scaled_matrix_unit(T, N, d, b):
                                    (513, 700, 1024), (449, 577, 2880), (449, 577, 4096),                # 64 x 64 tiles
                                    (1540, 1537, 1312), (1700, 1300, 544), (1540, 1537, 2880), (1540, 1537, 3328), (1540, 1537, 4096),  # 128 x 128
                                    (2177, 2177, 416), (2177, 2177, 2016), (2060, 2177, 2080),      # 128 x 128 twice a CU; 128 x 256
-                                   (2060, 2177, 2880), (2060, 2177, 3328), (2060, 2177, 4096)])
+                                   (2060, 2177, 2880), (2060, 2177, 3328), (2060, 2177, 4096),
+                                   (2060, 2177, 5152), (2060, 2177, 6016), (2060, 2177, 6144), (2690, 3330, 2912)])
 @pytest.mark.parametrize("fmt", ["int4", "mxfp4"])
 def test_w4a4_products_over_tiles_and_remainders(T, N, d, fmt):
     torch = _torch()
@@ -587,7 +588,8 @@ def test_w4a4_products_over_tiles_and_remainders(T, N, d, fmt):
 
 # ---- rows that end in several stages of a partial superstage: the waits count the loads that are there ----
 @pytest.mark.parametrize("T,N,d", [(449, 577, 2880), (513, 700, 1312), (1540, 1537, 800), (2177, 2177, 2016),
-                                   (1540, 1537, 2880), (1540, 1537, 4096), (2060, 2177, 2880), (2060, 2177, 4096)])
+                                   (1540, 1537, 2880), (1540, 1537, 4096), (2060, 2177, 2880), (2060, 2177, 4096),
+                                   (2060, 2177, 6016), (2060, 2177, 6144)])
 @pytest.mark.parametrize("fmt", ["int4", "mxfp4"])
 def test_w4a4_products_repeat_bit_for_bit(T, N, d, fmt):
     torch = _torch()
