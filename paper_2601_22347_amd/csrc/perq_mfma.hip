@@ -1334,75 +1334,79 @@ static bool folds(const ApplyParams& p, int out_kind) {
            p.T >= kTile / p.d;
 }
 
-// Which of the two general kernels takes a call.  The choice must not depend on whether a permutation
-// came with its prepared form (the outputs of the two calls agree bit for bit).  Every line was measured
-// on both sides, launches back to back on one GPU, butterfly / this kernel in us (with a permutation:
-// the prepared form where there is one):
-//   Rows of 2560, 3072, 3584 fill 5/8 of a wave tile and more.  T = 32768, d = 3072, b = 128, INT4: 74 / 44
-//     (P = I), 83 / 51 (permutation); T = 4001 with a permutation, asymmetric INT4: 14.7 / 13.0.  Narrower
-//     rows that cannot be folded leave too much of the tile empty (d = 2048, b = 128: 39 / 37, d = 1024:
-//     21 / 31), but for the large blocks of d = 2048 on long launches (T = 32768, b = 2048: 59 / 47).
-//   Few rows: this kernel's set-up (operand tables, two staging buffers) is not paid back.
-//     P = I, T = 16: d = 4096, b = 128 3.8 / 4.7; d = 8192, b = 32 3.9 / 5.8; d = 8192, b = 4096 5.6 / 9.0.
-//       The two meet at 2^22 elements (d = 4096, b = 128, T = 1024: 5.1 / 5.2; T = 2048: 7.1 / 6.5), for
-//       b <= 32, with five stages fewer in the butterflies, and for b >= 1024, whose operand addresses cost
-//       this kernel 3 us, at 2^23 (d = 4096, b = 16: T = 2048 5.8 / 6.1, T = 8192 17.8 / 16.2; d = 8192,
-//       b = 4096: T = 1024 10.8 / 11.1, T = 2048 20.8 / 16.4).
-//     With a permutation: d = 8192, b = 32, T = 16 5.2 / 7.2, T = 256 5.2 / 7.1; d = 14336, b = 128, T = 256
-//       7.6 / 8.6, T = 1024 17.5 / 13.7: the line is 2^22 elements.  On rows of two tiles it is 2^24 for b <= 32
-//       (d = 8192, T = 1025 9.9 / 9.8 prepared, 13.4 as given; T = 2049 14.6 / 13.9, 16.4; d = 6144, T = 2731
-//       14.1 / 15.3, 17.7) and 2^23 above (b = 128: d = 8192, T = 513 8.2 / 8.4, 11.9; T = 1025 10.9 / 10.3, 13.6).  The tile of
-//       d = 4096 and of folded rows builds its operand table once for four waves: T = 512, b = 64 5.3 / 5.7,
-//       T = 1024 7.0 / 5.8, and for b >= 1024 it is always ahead (T = 16, b = 4096: 6.5 / 6.3).  b >= 1024 on
-//       wider rows: d = 6144, b = 2048, T = 256 6.0 / 7.7, T = 512 8.0 / 7.7; d = 16384, b = 4096 9.2 / 9.0.
-//       Rows wider than 16384 need workgroups of 1024 lanes there: T = 16, d = 28672 11.8 / 9.1.
-bool mfma_preferred(const ApplyParams& p, int out_kind) {
-    const bool ragged = mfma_takes_ragged(p);
-    if (!mfma_supports(p) && !ragged) return false;
-    const int64_t n = p.T * (int64_t)p.d;
-    const bool folded = folds(p, out_kind), large = p.b >= 1024;
-    if (folded) {
-        // Folded narrow rows.  For b <= 32 the butterflies' five stages cost no more than this kernel's products
-        // (d = 2048, T = 16384 17.6 / 17.2, with a permutation and MXFP4 20.3 / 20.5; T = 32768 31.9 / 30.4, 37.2 / 34.4).
-        // b = 64: d = 2048, T = 8192 11.8 / 10.3, permutation, d = 1024, T = 16384 13.2 / 13.6, T = 32768 22.7 / 21.0; d = 512,
-        // T = 65536 20.4 / 17.1.  b >= 128, P = I: d = 1024, T = 4096 5.3 / 5.6, T = 16384 13.0 / 11.1.
+// Which of the two general kernels takes a call: the number of elements from which on it is this one (0: always).
+// The choice must not depend on whether a permutation came with its prepared form (the outputs of the two calls
+// agree bit for bit), so where the form matters the line is that of the prepared call, and calls with the
+// permutation as given, whose table every launch builds, are ahead on the butterflies for some way past it.
+// Figures: launches back to back on one GPU, butterfly / this kernel (/ as given) in us, INT4 where no format is
+// named.  What decides: this kernel's set-up (operand tables, two staging buffers) is paid back by long launches
+// only; for b <= 32 the butterflies have five stages fewer; for b >= 1024 its operand addresses cost 3 us.
+constexpr int64_t kNever = INT64_MAX;
+static int64_t mfma_line(const ApplyParams& p, int out_kind) {
+    const bool ragged = mfma_takes_ragged(p), perm = p.perm != nullptr, folded = folds(p, out_kind);
+    const bool small = p.b <= 32, large = p.b >= 1024;
+    auto exp2 = [](int k) { return (int64_t)1 << k; };
+    if (!mfma_supports(p) && !ragged) return kNever;
+
+    if (folded) {           // rows of 512, 1024, 2048
         // Rows left over take a second launch of 4 us, 6 us with a permutation: d = 1024, T = 16385, b = 64 11.8 / 14.1,
         // T = 65537 36.4 / 34.5; b = 128, T = 8193 7.3 / 10.8, T = 32769 21.6 / 21.5; permutation, T = 4097 7.8 / 13.1,
         // T = 32769 25.2 / 27.9.
-        if (p.T % (kTile / p.d) != 0 && !large)
-            return n >= (p.b <= 32 ? (int64_t)1 << 27 : p.perm == nullptr ? (int64_t)3 << 24 : (int64_t)1 << 26);
-        if (p.b <= 32) return n >= ((int64_t)1 << 26);
-        if (p.b == 64) return n >= (p.perm == nullptr ? (int64_t)1 << 24 : (int64_t)3 << 23);
-        if (p.perm == nullptr && !large) return n >= ((int64_t)3 << 21);
-    } else if (p.d < 2560) {
-        if (!(p.d == 2048 && large && n >= ((int64_t)1 << 25))) return false;
+        if (p.T % (kTile / p.d) != 0 && !large) return small ? exp2(27) : perm ? exp2(26) : 3 * exp2(24);
+        // d = 2048, T = 16384 17.6 / 17.2, with a permutation and MXFP4 20.3 / 20.5; T = 32768 31.9 / 30.4, 37.2 / 34.4
+        if (small) return exp2(26);
+        // d = 2048, T = 8192 11.8 / 10.3; permutation, d = 1024, T = 16384 13.2 / 13.6, T = 32768 22.7 / 21.0; d = 512,
+        // T = 65536 20.4 / 17.1
+        if (p.b == 64) return perm ? 3 * exp2(23) : exp2(24);
+        // P = I: d = 1024, T = 4096 5.3 / 5.6, T = 16384 13.0 / 11.1
+        if (!perm) return large ? exp2(23) : 3 * exp2(21);
+        // a permutation: the table is built once for four waves, as at d = 4096
+        return large ? 0 : exp2(21) + 1;
     }
-    const bool two_tiles = p.d > kTile && p.d <= 2 * kTile;
-    if (p.perm == nullptr) {
-        if (large) return n >= ((int64_t)1 << 23);
-        // Two tiles: b = 32, d = 5120, T = 1639 6.8 / 8.6, T = 3277 11.9 / 11.8, T = 6554 20.7 / 18.4; d = 8192, T = 1025
-        // 6.5 / 7.5, T = 2049 10.9 / 11.2, T = 4097 18.6 / 18.6.  b = 128: T = 1639 8.8 / 9.7, T = 3277 14.6 / 13.2.
-        if (two_tiles) return n >= ((int64_t)3 << (p.b <= 32 ? 23 : 22));
+    // Narrow rows that cannot be folded leave too much of the tile empty (d = 2048, b = 128: 39 / 37, d = 1024:
+    // 21 / 31), but for the large blocks of d = 2048 (T = 32768, b = 2048: 59 / 47).
+    if (p.d < 2560) return p.d == 2048 && large ? exp2(25) : kNever;
+
+    const bool one_tile = p.d <= kTile, two_tiles = p.d > kTile && p.d <= 2 * kTile;
+    if (!perm) {
+        // d = 8192, b = 4096: T = 16 5.6 / 9.0, T = 1024 10.8 / 11.1, T = 2048 20.8 / 16.4
+        if (large) return exp2(23);
+        // Two tiles: b = 32, d = 5120, T = 1639 6.8 / 8.6, T = 3277 11.9 / 11.8, T = 4916 14.7 / 14.3; d = 8192, T = 1025
+        // 6.5 / 7.5, T = 2049 10.9 / 11.2, T = 4097 18.6 / 18.6 (MXFP4, T = 3072 11.2 / 12.9, T = 4096 14.9 / 15.9: the
+        // butterflies keep a group's maximum in the lane).  b = 128: T = 1639 8.8 / 9.7, T = 3277 14.6 / 13.2.
+        if (two_tiles) return 3 * exp2(small ? 23 : 22);
         // Ragged rows of more tiles: b = 32, d = 11008, T = 762 7.2 / 7.8, T = 1524 12.6 / 11.7; d = 15904, T = 527
         // 7.4 / 8.4, T = 1054 11.6 / 12.1; b = 128, d = 11008, T = 381 6.7 / 6.8, T = 762 8.7 / 8.3.
-        return n >= ((int64_t)1 << ((p.b <= 32 ? 23 : 22) + (ragged && p.d > kTile)));
+        if (ragged && !one_tile) return exp2(small ? 24 : 23);
+        // d = 4096, b = 128, T = 16 3.8 / 4.7, T = 1024 5.1 / 5.2, T = 2048 7.1 / 6.5; b = 16, T = 2048 5.8 / 6.1, T = 8192
+        // 17.8 / 16.2; d = 3072, b = 128, T = 32768 74 / 44; d = 2880, b = 32, T = 5832 12.2 / 10.5, T = 32768 56.8 / 41.2
+        return exp2(small ? 23 : 22);
     }
-    if (folded || p.d == kTile) return large || n > ((int64_t)1 << 21);
-    // (no prepared form below 4096: every launch builds the table; T = 4096, d = 3072, b = 16 10.9 / 12.3,
-    //  T = 8192 18.5 / 16.9; b = 128, T = 2048 9.7 / 10.0, T = 4096 13.6 / 12.4;
-    //  ragged: d = 2880, b = 32, T = 5825 16.2 / 15.3, T = 32768 with MXFP4 and b = 64 69.1 / 51.2; T = 2912 11.4 / 10.9;
-    //  P = I, b = 32, T = 5832 12.2 / 10.5, T = 32768 56.8 / 41.2)
-    if (p.d < kTile) return n >= ((int64_t)1 << (p.b <= 32 ? 24 : 23));
-    // Ragged rows, with a permutation: two tiles, b = 16, d = 5152, T = 6512 23.6 / 25.2, b = 32, T = 16384 64.5 / 57.3;
-    // b = 256, d = 7424, T = 2259 18.6 / 17.7, T = 4519 31.5 / 26.2.  Three and four: b = 16, d = 15904, T = 1054
-    // 17.2 / 18.3, T = 2109 27.0 / 24.8; d = 11008, b = 256, T = 762 16.1 / 16.3, T = 16384 212 / 116; b = 128,
-    // T = 1524 24.5 / 19.6.  More: b = 32, d = 17440, T = 480 16.6 / 16.2, T = 961 27.3 / 22.2; b = 128, d = 28800,
-    // T = 291 24.7 / 18.3.
-    if (ragged) return n >= ((int64_t)1 << ((p.b <= 32 ? 24 : 23) + (p.d <= 2 * kTile ? 2 : p.d <= 4 * kTile ? 1 : 0)));
-    if (p.d > 16384) return true;
-    if (large) return p.d > 2 * kTile || n > ((int64_t)1 << 21);
-    return n >= ((int64_t)1 << (two_tiles ? (p.b <= 32 ? 24 : 23) : 22));
+    // T = 512, b = 64 5.3 / 5.7, T = 1024 7.0 / 5.8; b = 4096, T = 16 6.5 / 6.3
+    if (p.d == kTile) return large ? 0 : exp2(21) + 1;
+    // No prepared form: T = 4096, d = 3072, b = 16 10.9 / 12.3, T = 8192 18.5 / 16.9; b = 128, T = 2048 9.7 / 10.0, T = 4096
+    // 13.6 / 12.4, T = 32768 83 / 51; asymmetric INT4, T = 4001 14.7 / 13.0.  Ragged: d = 2880, b = 32, T = 2912 11.4 / 10.9,
+    // T = 5825 16.2 / 15.3; b = 64, MXFP4, T = 32768 69.1 / 51.2
+    if (one_tile) return exp2(small ? 24 : 23);
+    // Ragged, no prepared form.  Two tiles: b = 16, d = 5152, T = 6512 23.6 / 25.2, b = 32, T = 16384 64.5 / 57.3; b = 256,
+    // d = 7424, T = 2259 18.6 / 17.7, T = 4519 31.5 / 26.2.  Three and four: b = 16, d = 15904, T = 1054 17.2 / 18.3, T = 2109
+    // 27.0 / 24.8; d = 11008, b = 256, T = 762 16.1 / 16.3, T = 16384 212 / 116; b = 128, T = 1524 24.5 / 19.6.  More:
+    // b = 32, d = 17440, T = 480 16.6 / 16.2, T = 961 27.3 / 22.2; b = 128, d = 28800, T = 291 24.7 / 18.3.
+    if (ragged) return exp2((small ? 24 : 23) + (two_tiles ? 2 : p.d <= 4 * kTile ? 1 : 0));
+    // butterflies of workgroups of 1024 lanes: T = 16, d = 28672 11.8 / 9.1
+    if (p.d > 4 * kTile) return 0;
+    // d = 6144, b = 2048, T = 256 6.0 / 7.7, T = 512 8.0 / 7.7; d = 16384, b = 4096 9.2 / 9.0
+    if (large) return two_tiles ? exp2(21) + 1 : 0;
+    // Two tiles, prepared / as given.  b = 128: d = 8192, T = 513 8.2 / 8.4 / 11.9, T = 1025 10.9 / 10.3 / 13.6.  b = 32: d = 8192,
+    // T = 1025 9.9 / 9.8 / 13.4, T = 2049 14.6 / 13.9 / 16.4; d = 7168, T = 2341 14.6 / 13.1 / 15.5; narrower rows leave
+    // more of the second tile empty, d = 6144, T = 2731 13.8 / 14.5 / 16.8, T = 4096 17.7 / 17.7 / 20.0, d = 5120,
+    // T = 3277 14.3 / 14.4 / 17.7, T = 4916 19.4 / 19.2 / 21.8.
+    if (two_tiles) return small ? (p.d <= 6144 ? 3 * exp2(23) : exp2(24)) : exp2(23);
+    // d = 14336, b = 128, T = 256 7.6 / 8.6, T = 1024 17.5 / 13.7
+    return exp2(22);
 }
+
+bool mfma_preferred(const ApplyParams& p, int out_kind) { return p.T * (int64_t)p.d >= mfma_line(p, out_kind); }
 
 hipError_t launch_mfma(const ApplyParams& p0, int out_kind, hipStream_t stream) {
     ApplyParams p = p0;

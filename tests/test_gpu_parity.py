@@ -408,6 +408,7 @@ def test_f32_output_fills_its_rows_and_nothing_else(d, b, algo):
                                                 (3072, 128, 2731, True), (4096, 128, 1024, False), (4096, 64, 513, True),
                                                 (8192, 128, 1024, True), (6144, 2048, 342, True), (5120, 1024, 1639, False),
                                                 (10240, 64, 410, True), (5120, 32, 3277, True), (5120, 32, 4916, False),
+                                                (5120, 32, 4916, True), (7168, 16, 2341, True),
                                                 (8192, 256, 1536, False), (512, 128, 4352, True), (2048, 64, 8192, False),
                                                 (1024, 128, 6144, False), (1024, 512, 2056, True)])
 @pytest.mark.parametrize("fmt", ["int4", "mxfp4", "int4_asym"])
@@ -728,9 +729,9 @@ def test_calibrated_permutations_ranked_by_the_bound():
 
 # ---- the fused call with a placement prepared for the permutation -------------------------------------
 def _in_bulk(x):
-    """x over and over, 2^24 elements and more: with a permutation and d >= 4096 the matrix-core kernel takes so
+    """x over and over, 2^25 elements and more: with a permutation and d >= 4096 the matrix-core kernel takes so
     many whatever b is, and reads the prepared form."""
-    return x.repeat((1 << 24) // x.numel() + 1, 1)
+    return x.repeat((1 << 25) // x.numel() + 1, 1)
 
 
 @pytest.mark.parametrize("T,d,b,fmt", [(300, 4096, 128, "int4"), (4200, 4096, 128, "int4"), (300, 4096, 4096, "int4"),
