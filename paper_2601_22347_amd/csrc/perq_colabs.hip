@@ -13,8 +13,8 @@
 // relative error of a_i is below (max_run(M, d) + 1) * 2^-24.
 //   Bound by reading x, small inputs by the two launches.  Eight row groups a workgroup instead of one
 // (2048 columns each) make the partials a quarter as large (a quarter of the input at M <= 1024 before).
-// Launches back to back: M = 16, d = 4096 4.1 -> 2.3 us, M = 500, d = 14336 9.3 -> 7.9, M = 2048, d = 4096
-// 9.1 -> 7.8, M = 4096, d = 8192 (cache resident) 13.7 -> 13.9, M = d = 32768 369 -> 322.
+// Launches back to back: M = 16, d = 4096 4.1 -> 2.5 us, M = 500, d = 14336 7.8 -> 5.6, M = 2048, d = 4096
+// 7.2 -> 5.4, M = 4096, d = 8192 (cache resident) 13.6 -> 13.7, M = d = 32768 369 -> 319.
 #include "perq.h"
 #include "perq_launch.h"
 
@@ -33,8 +33,9 @@ static_assert(kTileCols == kThreads, "one lane per column adds the groups");
 // Up to here a second launch costs more than the rows.  Their loads are all requested together; more rows take
 // the loop, also where x is so wide that they are one slice (M = 4096, d = 200000: 261 against 299 us).
 constexpr int kOneSlice = 128;
-// Inputs past the last-level cache are read with streaming loads (M = 32768, d = 4096: 50.4 -> 45.4 us);
-// smaller ones may be in it already and should stay (M = 4096, d = 8192 again and again: 13.9 against 15.2).
+// Inputs past the last-level cache are read with streaming loads (M = 32768, d = 4096, three inputs in turn
+// 49.8 -> 44.8 us; M = d = 32768 352 -> 319); smaller ones may be in it already and should stay (M = 4096, d = 28672
+// again and again: 36.1 against 38.8).
 constexpr int64_t kStreamBytes = (int64_t)256 << 20;
 
 constexpr int kMostBlocks = 1024;                             // workgroups of a first pass of several slices
@@ -56,8 +57,9 @@ ColabsPlan colabs_plan(int64_t M, int32_t d) {
     ColabsPlan pl;
     pl.col_tiles = (int)(((int64_t)d + kTileCols - 1) / kTileCols);
     const int64_t run = max_run(M, d);
-    // 2 workgroups per CU, or 4 where the slices of 2 would be longer than `run` allows (M = 40000, d = 28672: 4
-    // slices 334 us, 9 330; 5, which would do and leave the CUs uneven shares, 384)
+    // 2 workgroups per CU (4: M = 32768, d = 4096 44.2 -> 46.3 us), or 4 where the slices of 2 would be longer than
+    // `run` allows (M = 40000, d = 28672: 4 slices 334 us, 9 330; 5, which would do and leave the CUs uneven
+    // shares, 384)
     int64_t want = kMostBlocks / 2 / pl.col_tiles;
     if (want == 0 || M > want * kGroups * run) want = kMostBlocks / pl.col_tiles;
     const int64_t most = (M + run - 1) / run / 2;       // no more bytes of partials than a float per run
@@ -135,10 +137,11 @@ colabs_partial_kernel(const uint16_t* __restrict__ x, int64_t M, int32_t d, int6
     }
 }
 
-// Pass 2: 32 columns per workgroup, 8 lanes per column.  Lane j of a column adds slices
-// j, j+8, ...; the 8 sub-sums are then added in lane order.  Fixed order throughout.
-constexpr int kFinishCols = 32;
-constexpr int kFinishWays = kThreads / kFinishCols;   // 8
+// Pass 2: 16 columns per workgroup, 16 lanes per column.  Lane j of a column adds slices
+// j, j+16, ...; the 16 sub-sums are then added in lane order.  Fixed order throughout.  Bound by latency: with 32
+// columns M = 2048, d = 4096 5.9 us instead of 5.4, M = 4096, d = 8192 14.0 instead of 13.9.
+constexpr int kFinishCols = 16;
+constexpr int kFinishWays = kThreads / kFinishCols;   // 16
 
 template <bool MAXSTAT>
 __global__ void __launch_bounds__(kThreads)

@@ -146,7 +146,7 @@ __device__ __forceinline__ void lane_stage(float (&v)[N], float sgn) {
 // 4 x 4 transposition of 16-byte groups inside every quad of lanes: lane q holds groups 0 .. 3 of its own
 // run; afterwards group t is group q of lane t's run.  Stored as group t at 16 q bytes into lane t's run, a
 // quad writes 64 consecutive bytes per instruction where its lanes would write 16 bytes at a pitch
-// (fp32 output, T = 2048, d = 8192, b = 32: 33.3 -> 23.6 us with a permutation, 28.7 -> 18.1 with P = I).
+// (fp32 output, T = 2048, d = 8192, b = 32: 32.1 -> 22.2 us with a permutation, 28.5 -> 18.7 with P = I).
 __device__ __forceinline__ void quad_transpose16(float* v) {
     const int q = (int)threadIdx.x & 3;
     // the lane with the lower number keeps lo and receives the partner's lo in hi's place

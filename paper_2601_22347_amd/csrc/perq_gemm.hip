@@ -1,9 +1,12 @@
 // Consumers of the packed codes: out = A W^T for two operands in the layout the fused path writes,
 // symmetric INT4 (one fp32 step per row) or MXFP4 (one e8m0 byte per 32 codes).
 //
-// Measured, T = 2048, N = d = 4096, INT4: 577 -> 30 us (2.3 POP/s; 8 codes per v_dot8_i32_i4 and no LDS
-// before); T = N = 2048, d = 8192, MXFP4: 229 -> 33 us (2.1 PFLOP/s; one 32 x 32 tile per wave, both
-// operands from memory for every product before).  The matrix unit alone would take 16 and 8 us.
+// Measured, T = 2048, N = d = 4096, INT4: 576 -> 30 - 32 us (2.2 POP/s; 8 codes per v_dot8_i32_i4 and no
+// LDS before); T = N = 2048, d = 8192, MXFP4: 229 -> 32 - 34 us (2.1 PFLOP/s; one 32 x 32 tile per wave, both
+// operands from memory for every product before).  The matrix unit alone would take 16 and 8 us.  Counters
+// (profiles/products_w4a4.txt): INT4 keeps it 59 % busy and the vector ALU, which unpacks the nibbles, 61 %.  MXFP4
+// keeps neither it (24 %) nor LDS (24 %) busy: a CU holds four waves of that tile, one a SIMD, and a wave issues
+// its loads, its LDS reads and its products one after the other with nothing beside it.
 //
 // With P and the block rotation merged into the weights (Remark "Merging Permutations", Section 4:
 // W~ = R~^T P^T W), the product of the two quantized operands stands for X W.

@@ -8,8 +8,8 @@
 // scheduling.  Sums are fp32.
 //   Bound by reading y (4 bytes an element): a thread takes four elements at a time, one 16-byte load of
 // y and two bytes of codes, and the sums of a wave meet in registers.  Against two elements a time, one
-// byte of codes per load and a tree of eight barriers through LDS: T = 2048, d = 8192, INT4 13.2 -> 12.4 us,
-// MXFP4 14.0 -> 12.4; T = 512, d = 14336 12.7 -> 7.0; T = 16, d = 4096 3.7 -> 2.4.
+// byte of codes per load and a tree of eight barriers through LDS: T = 2048, d = 8192, INT4 13.1 -> 12.2 us,
+// MXFP4 13.6 -> 12.3; T = 512, d = 14336 12.0 -> 4.8; T = 16, d = 4096 3.6 -> 2.3.
 #include "perq.h"
 #include "perq_device.h"
 #include "perq_launch.h"
