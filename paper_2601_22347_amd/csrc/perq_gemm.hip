@@ -407,7 +407,9 @@ gemm_tile_kernel(GemmParams p) {
 
 // ---- few rows: one 32 x 32 tile per workgroup, the contraction cut among its KW waves --------------
 // Bound by the latency of the loads: nothing is used twice, so the granules go straight to registers,
-// wave k takes the stages k, k + KW, ... and the partial tiles are added in LDS in wave order.
+// wave k takes the stages k, k + KW, ... and the partial tiles are added in LDS in wave order.  A stage's loads are
+// all issued before its first product (left to itself the compiler puts some behind it: (64, 4096, 8000) INT4
+// 10.4 -> 7.8 us, MXFP4 8.8 -> 8.1).
 template <bool MX, int KW>
 __global__ void __launch_bounds__(64 * KW)
 gemm_skinny_kernel(GemmParams p) {
@@ -423,7 +425,6 @@ gemm_skinny_kernel(GemmParams p) {
     const uint8_t* ac = p.a_codes + t * row_bytes;
     const uint8_t* wc = p.w_codes + (int64_t)n * row_bytes;
     acc_t<MX> acc = {};
-#pragma unroll 2
     for (int s = wave; s < stages; s += KW) {
         v4i_t a[4], w[4];
         uint32_t sa = 0, sw = 0;
@@ -442,6 +443,7 @@ gemm_skinny_kernel(GemmParams p) {
             w[kc] = *reinterpret_cast<const v4i_t*>(wc + 16u * gc);
             if (g >= granules) a[kc] = v4i_t{0, 0, 0, 0};
         }
+        __builtin_amdgcn_sched_barrier(0);
         if constexpr (MX) {
             acc = mx_product<0>(a[0], w[0], acc, sa, sw);
             acc = mx_product<1>(a[1], w[1], acc, sa, sw);
@@ -588,9 +590,9 @@ hipError_t launch_skinny(GemmParams p, hipStream_t stream) {
 //     9.3 / 7.5 against 12.4 / 10.6.  At d = 128 against the tiles below: (4096, 4096) 15.9 / 13.2 against 16.3 /
 //     14.4, (16384, 512) 9.9 / 8.7 against 9.4 / 9.0, (300, 14336) 7.7 / 6.7 against 8.2 / 7.6.
 //   up to 256 tiles of 32 x 32: the contraction cut among 8 waves, against 64 x 64 tiles.  256 tiles:
-//     (64, 4096, 4096) 7.0 / 6.9 against 8.2 / 7.0, d = 6144 7.8 / 8.7 against 10.9 / 8.5, d = 8192 10.8 / 10.9 against
-//     13.7 / 10.0 (MXFP4 has half the products per granule: not from d = 8192 on).  258 tiles: (96, 2752, 4096)
-//     9.3 / 10.8 against 8.8 / 7.1.
+//     (64, 4096, 4096) 7.2 / 6.8 against 8.2 / 7.0, d = 6144 7.6 / 8.6 against 10.9 / 8.4, d = 8192 9.4 / 10.8 against
+//     13.8 / 9.9 (MXFP4 has half the products per granule: not from d = 8192 on).  258 tiles: (96, 2752, 4096)
+//     9.3 / 10.7 against 8.8 / 7.1.
 //   up to 128 tiles of 128 x 128: 64 x 64 tiles, which two workgroups a CU hold at once up to there, against
 //     128 x 128.  (512, 4096, 4096) 12.6 / 15.0 against 16.3 / 15.3, d = 1024 7.3 / 8.6 against 7.6 / 9.3; the other way
 //     round with 130 tiles, (640, 3328, 4096) 16.5 / 15.5 against 17.9 / 20.7.

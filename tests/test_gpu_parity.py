@@ -848,6 +848,26 @@ def test_quant_error_against_oracle_and_worst_case_bound(d, b):
             assert np.all(got[:, 0] <= math.sqrt(d) / 14.0 * got[:, 2] * (1 + 1e-5))
 
 
+def test_quant_error_of_codes_scales_and_rows_that_are_not_aligned():
+    """Codes and e8m0 bytes at odd addresses, y at 8 modulo 16: what the entry point takes beside the aligned case."""
+    torch = _torch()
+    g = torch.Generator(device="cuda").manual_seed(4)
+    for T, d in ((5, 32), (9, 96), (70, 4128)):
+        y = torch.randn((T, d), device="cuda", generator=g)
+        for fmt in ("int4", "mxfp4", "int4_asym", "fp4_token"):
+            print(f"[case] quant error, not aligned T={T} d={d} fmt={fmt}", flush=True)
+            codes, scales = binding.alloc_outputs(T, d, fmt, "cuda")
+            codes.random_(0, 256, generator=g)
+            if fmt == "mxfp4":
+                scales.random_(100, 140, generator=g)
+            else:
+                scales.uniform_(0.1, 2.0, generator=g)
+            want = binding.perq_quant_error(y, codes, scales, fmt)
+            off = lambda t, k: torch.empty(t.numel() + k, dtype=t.dtype, device="cuda")[k:].view(t.shape).copy_(t)
+            got = binding.perq_quant_error(off(y, 2), off(codes, 1), off(scales, 1) if fmt != "int4_asym" else scales, fmt)
+            assert torch.equal(got, want)
+
+
 # ---- the ticket counters under concurrency and graph replay ------------------------------------------
 def test_run_time_schedule_on_two_streams_and_in_a_graph():
     """Every stream has a counter set of its own, so launches that overlap on two streams never draw
