@@ -36,7 +36,10 @@ struct BflyGeom {
     uint32_t red_off;    // byte offset of the reduction scratch in LDS
 };
 
-template <int OUT, bool PERM, int MAXT>
+// fp32 output is stored by quads of lanes where a row is a multiple of four lanes.  Workgroups of 1024 lanes have 128
+// registers, which both forms of the store in one kernel overflow (d = 17440, T = 9 with a permutation 8.5 -> 9.3 us):
+// there QUADS says which one it is; the others decide at run time.
+template <int OUT, bool PERM, int MAXT, bool QUADS = false>
 __global__ void __launch_bounds__(MAXT)
 butterfly_kernel(ApplyParams p, BflyGeom g) {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -177,7 +180,7 @@ butterfly_kernel(ApplyParams p, BflyGeom g) {
 #pragma unroll
             for (int i = 0; i < 32; ++i) v[i] *= p.rsqrt_b;
             float* yo = p.y + row * (int64_t)d;
-            if ((g.nt & 3) == 0) {             // a quad of lanes lies in one row (and is active as a whole)
+            if (MAXT > 512 ? QUADS : (g.nt & 3) == 0) {      // a quad of lanes lies in one row (and is active as a whole)
                 quad_transpose16(v);
                 quad_transpose16(v + 16);
                 if (live) {
@@ -360,6 +363,10 @@ hipError_t launch_butterfly_out(const ApplyParams& p, hipStream_t stream) {
     auto kern = threads <= 256   ? (p.perm ? butterfly_kernel<OUT, true, 256> : butterfly_kernel<OUT, false, 256>)
                 : threads <= 512 ? (p.perm ? butterfly_kernel<OUT, true, 512> : butterfly_kernel<OUT, false, 512>)
                                  : (p.perm ? butterfly_kernel<OUT, true, 1024> : butterfly_kernel<OUT, false, 1024>);
+    if constexpr (OUT == OUT_F32) {
+        if (threads > 512 && (g.nt & 3) == 0)
+            kern = p.perm ? butterfly_kernel<OUT, true, 1024, true> : butterfly_kernel<OUT, false, 1024, true>;
+    }
     // Persistent grid: as many workgroups as the device keeps resident, each walking the rows.
     int per_cu = 0;
     const hipError_t oe = resident_blocks(reinterpret_cast<const void*>(kern), threads, lds_bytes, &per_cu);
