@@ -121,7 +121,7 @@ def _check(status: int, where: str) -> None:
 
 
 # A call on a small batch is over on the device in 3 - 6 us and the HIP launch itself takes 3.6 us of
-# host time, so what is done here per call counts (a call for 16 rows: 12.6 -> 9.2 us): pointers go to
+# host time, so what is done here per call counts (a call for 16 rows: 12.6 -> 9.4 us): pointers go to
 # ctypes as plain integers, and the current stream is asked for as a raw handle (0.4 us; building a
 # torch.cuda.Stream object for it 3.0 us).
 _raw_stream = None

@@ -73,17 +73,29 @@ ColabsPlan colabs_plan(int64_t M, int32_t d) {
     return pl;
 }
 
-// FEW: at most kOneSlice rows.  STREAM: streaming loads.  part == nullptr: the only slice, which writes the
-// result (m_rows: rows to divide by).
+// FEW: at most kOneSlice rows, workgroup = column tile.  STREAM: streaming loads.  part == nullptr: the only slice,
+// which writes the result (m_rows: rows to divide by).
+//   blocks: 0, or their number where rows are no multiple of 128 bytes.  Neighbours along a row then share a cache
+// line.  Workgroups go round-robin to the 8 XCDs, each with an L2 of its own, so XCD x gets a contiguous share of
+// the (slice, tile) pairs, tiles along the row first, and reads such a line once: M = 4045, d = 11096 19.4 -> 16.9 us,
+// M = 40000, d = 8200 120 -> 107.  Rows of whole lines have nothing to share (M = 40000, d = 4096 52.8 -> 51.7, but
+// d = 14336 168 -> 177).
 template <bool MAXSTAT, bool FEW, bool STREAM>
 __global__ void __launch_bounds__(kThreads)
 colabs_partial_kernel(const uint16_t* __restrict__ x, int64_t M, int32_t d, int64_t ldx, int rows_per_slice,
-                      double* __restrict__ part, float* __restrict__ out, float m_rows) {
+                      uint32_t tiles, uint32_t blocks, double* __restrict__ part, float* __restrict__ out, float m_rows) {
     typedef typename std::conditional<MAXSTAT, float, double>::type sum_t;
     __shared__ sum_t red[kGroups][kTileCols];
     const int cl = threadIdx.x % (kThreads / kGroups), group = threadIdx.x / (kThreads / kGroups);
-    const int64_t col0 = (int64_t)blockIdx.x * kTileCols, col = col0 + cl * kColsPerLane;
-    const int64_t r0 = (int64_t)blockIdx.y * rows_per_slice;
+    uint32_t tile = blockIdx.x, slice = 0;
+    if constexpr (!FEW) {
+        const uint32_t xcd = blockIdx.x & 7u, share = blocks >> 3, more = blocks & 7u;
+        const uint32_t pair = blocks == 0 ? blockIdx.x : xcd * share + (xcd < more ? xcd : more) + (blockIdx.x >> 3);
+        slice = pair / tiles;
+        tile = pair - slice * tiles;
+    }
+    const int64_t col0 = (int64_t)tile * kTileCols, col = col0 + cl * kColsPerLane;
+    const int64_t r0 = (int64_t)slice * rows_per_slice;
     const int64_t r1 = r0 + rows_per_slice < M ? r0 + rows_per_slice : M;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     auto add = [&](const uint4& w) {
@@ -133,7 +145,7 @@ colabs_partial_kernel(const uint16_t* __restrict__ x, int64_t M, int32_t d, int6
             t = MAXSTAT ? (v > t ? v : t) : t + v;
         }
         if (FEW || part == nullptr) out[c] = MAXSTAT ? (float)t : (float)(t / (double)m_rows);
-        else part[(int64_t)blockIdx.y * d + c] = t;
+        else part[(int64_t)slice * d + c] = t;
     }
 }
 
@@ -203,8 +215,9 @@ perq_status_t colabs_launch(const uint16_t* x_bf16, int64_t M, int32_t d, int64_
     auto kern = M <= kOneSlice                          ? colabs_partial_kernel<MAXSTAT, true, false>
                 : M * (int64_t)d * 2 >= kStreamBytes ? colabs_partial_kernel<MAXSTAT, false, true>
                                                      : colabs_partial_kernel<MAXSTAT, false, false>;
-    hipLaunchKernelGGL(kern, dim3(pl.col_tiles, pl.slices), dim3(kThreads), 0, stream, x_bf16, M, d, ldx, pl.rows_per_slice,
-                       pl.slices == 1 ? nullptr : part, out, (float)M);
+    const uint32_t tiles = (uint32_t)pl.col_tiles, blocks = tiles * (uint32_t)pl.slices;
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), 0, stream, x_bf16, M, d, ldx, pl.rows_per_slice, tiles,
+                       ldx % 64 != 0 ? blocks : 0u, pl.slices == 1 ? nullptr : part, out, (float)M);
     if (hipGetLastError() != hipSuccess) return PERQ_ERR_LAUNCH;
     if (pl.slices == 1) return PERQ_OK;
     hipLaunchKernelGGL(colabs_finish_kernel<MAXSTAT>, dim3((d + kFinishCols - 1) / kFinishCols), dim3(kThreads), 0,
