@@ -78,16 +78,18 @@ def check_product_waits() -> int:
     import re
     text = _device_assembly("perq_gemm.hip")
     checked = 0
-    for m in re.finditer(r"\n(_ZN4perq\S*gemm_tile_kernelILb\dELi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)\S*): +; @", text):
-        mt, nt, wm, wn, nbuf = (int(v) for v in m.groups()[1:])
+    for m in re.finditer(r"\n(_ZN4perq\S*gemm_tile_kernelILb(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)ELi\dELb(\d)\S*): +; @", text):
+        mx, mt, nt, wm, wn, nbuf, dwords = (int(v) for v in m.groups()[1:])
         loads = 4 * (mt * wm + nt * wn) // (wm * wn)                 # of a wave and stage
+        # scale bytes, loaded before the first stage and once in the loop over whole superstages; not counted by the waits
+        scales = 2 * -(-(mt * wm + nt * wn) // (wm * wn)) if mx and dwords else 0
         body = text[m.end():text.index(".Lfunc_end", m.end())].split("\n")
         issued = sum("buffer_load_dwordx4" in l and " lds" in l for l in body)
         waits = [int(re.search(r"vmcnt\((\d+)\)", l).group(1)) for i, l in enumerate(body)
                  if "vmcnt(" in l and any("s_barrier" in k for k in body[i + 1:i + 5])]
         stages = len(waits) - 1
         if stages < 12 or sorted(waits) != sorted([loads * (nbuf - 1)] + [loads * (nbuf - 2)] * stages) or \
-                issued != loads * (nbuf + stages):
+                issued != loads * (nbuf + stages) + scales:
             raise RuntimeError(f"{m.group(1)}: {loads} loads a stage, {issued} in all, waits {waits}")
         checked += 1
     if checked == 0:

@@ -1,12 +1,12 @@
 // Consumers of the packed codes: out = A W^T for two operands in the layout the fused path writes,
 // symmetric INT4 (one fp32 step per row) or MXFP4 (one e8m0 byte per 32 codes).
 //
-// Measured, T = 2048, N = d = 4096, INT4: 576 -> 30 - 32 us (2.2 POP/s; 8 codes per v_dot8_i32_i4 and no
-// LDS before); T = N = 2048, d = 8192, MXFP4: 229 -> 32 - 34 us (2.1 PFLOP/s; one 32 x 32 tile per wave, both
-// operands from memory for every product before).  The matrix unit alone would take 16 and 8 us.  Counters
-// (profiles/products_w4a4.txt): INT4 keeps it 59 % busy and the vector ALU, which unpacks the nibbles, 61 %.  MXFP4
-// keeps neither it (24 %) nor LDS (24 %) busy: a CU holds four waves of that tile, one a SIMD, and a wave issues
-// its loads, its LDS reads and its products one after the other with nothing beside it.
+// Measured, T = 2048, N = d = 4096, INT4: 29.8 us; T = N = 2048, d = 8192, MXFP4: 23.9 us.  What bounds both is what the
+// matrix unit draws: with random codes, registers only and nothing else running, it delivers 3.6 POP/s (int8) and 6.0
+// PFLOP/s (fp4) on the whole chip, with zeros 4.7 and 9.4, and one workgroup alone runs its stages 1.4 times as fast
+// as 256 do.  LDS is next: a 128 x 128 stage of MXFP4 moves 96 KiB in and out of it, 0.34 us at 128 bytes a clock, where
+// the products take 0.36; loads from L2 alone 0.31.  Products of 16 x 16 (8 - 12 % more from the unit alone) gave
+// nothing in INT4 and cost MXFP4 18 %: eight scale reads from LDS a stage instead of four.
 //
 // With P and the block rotation merged into the weights (Remark "Merging Permutations", Section 4:
 // W~ = R~^T P^T W), the product of the two quantized operands stands for X W.
@@ -51,6 +51,7 @@ struct GemmParams {
     int64_t T, ldo;
     int32_t N, d;
     uint32_t tiles_t, tiles_n;
+    int32_t stream_out;        // the tile kernels store their output with the streaming policy
 };
 
 __device__ __forceinline__ v4i_t high_codes(v4i_t w, int mask) { return w & mask; }
@@ -101,21 +102,23 @@ __device__ __forceinline__ void tile_of_block(const GemmParams& p, uint32_t& tt,
 
 // ---- tiles of 32 MT WM rows x 32 NT WN columns, WM x WN waves, operands staged in LDS --------------
 // Stages go global -> LDS directly; NBUF stages are kept.  Place p of a row's 128-byte line holds
-// granule p ^ (r & 7) of the stage, so that the 32 rows a fragment read touches spread over all banks.
-//   Four stages make a superstage of 32 granules.  MXFP4: in stage j half-wave h takes granules
-// 16 h + 4 j + kc of the superstage, so that the scales of a lane's row for all four stages are 16
-// consecutive bytes, one load; a load of a dword per row and stage took a third of the kernel's time
-// (a load instruction that touches 32 rows occupies the address unit for as long as a product lasts).
-template <bool MX, int MT, int NT, int WM, int WN, int NBUF, int WGS>
+// granule p ^ ((r >> 1) & 7) of the stage: 16 rows a fragment read touches lie in 16 different places of the 64 banks.
+//   Four stages make a superstage of 32 granules.  MXFP4: the 32 scale bytes that a row has in a superstage come into
+// LDS as well, 1 KiB a load for 32 rows, and a lane picks the dword of each stage from there.  Loads of scales
+// straight to the lanes that use them went to every row once per wave, and to spare some of them a stage took two halves
+// of lines, which costs L2 twice the requests.  T = N = 2048, d = 8192 32.1 -> 23.9 us.
+template <bool MX, int MT, int NT, int WM, int WN, int NBUF, int WGS, bool DWORDS>
 __global__ void __launch_bounds__(64 * WM * WN, WGS* WM* WN / 4)
 gemm_tile_kernel(GemmParams p) {
     constexpr int kWaves = WM * WN, kBM = 32 * MT * WM, kBN = 32 * NT * WN;
     constexpr int kLoadA = kBM / 8 / kWaves, kLoadW = kBN / 8 / kWaves, kLoads = kLoadA + kLoadW;
     constexpr int kSc = MX ? MT + NT : 1;
-    constexpr uint32_t kBuf = (uint32_t)(kBM + kBN) * kStageBytes;
+    constexpr int kScaleLoads = MX ? (kBM + kBN + 32 * kWaves - 1) / (32 * kWaves) : 1;      // of a wave and superstage
+    constexpr uint32_t kBuf = (uint32_t)(kBM + kBN) * kStageBytes, kScaleBuf = (uint32_t)(kScaleLoads * kWaves) * 1024u;
     static_assert(kLoadA * 8 * kWaves == kBM && kLoadW * 8 * kWaves == kBN, "every wave loads whole pieces");
     static_assert(NBUF == 2 || NBUF == 4, "stage j of a superstage lies in buffer j % NBUF");
     extern __shared__ __align__(16) unsigned char lds[];
+    const unsigned char* const scale_bytes_lds = lds + NBUF * kBuf;               // MXFP4: scale bytes of two superstages and of the partial one
     float* const scales_lds = reinterpret_cast<float*>(lds + NBUF * kBuf);        // INT4: steps of the rows, then of the columns
 
     const int lane = threadIdx.x & 63, i = lane & 31, h = lane >> 5;
@@ -140,9 +143,7 @@ gemm_tile_kernel(GemmParams p) {
     }
 
     // One load instruction fills 8 rows of a stage: lane l brings the granule of place l & 7 of row l >> 3.
-    const uint32_t row8 = (uint32_t)lane >> 3, slot = ((uint32_t)lane & 7u) ^ row8;
-    const uint32_t gran = MX ? 16u * (slot >> 2) + (slot & 3u) : slot;              // + 4 j (MXFP4) or 8 j in stage j
-    constexpr uint32_t kPerStage = MX ? 4u : 8u;
+    const uint32_t row8 = (uint32_t)lane >> 3, gran = ((uint32_t)lane & 7u) ^ ((row8 >> 1) + 4u * ((uint32_t)wave & 1u));
     const rsrc_t abuf = buffer_of(p.a_codes + t0 * row_bytes, (last_t + 1u) * row_bytes);
     const rsrc_t wbuf = buffer_of(p.w_codes + (int64_t)n0 * row_bytes, (last_n + 1u) * row_bytes);
     uint32_t off[kLoads];
@@ -161,58 +162,97 @@ gemm_tile_kernel(GemmParams p) {
         constexpr int jj = decltype(j_const)::value, j = jj & 3;
         constexpr bool inner = decltype(inner_const)::value;
         S += jj >> 2;
-        const uint32_t g = gran + kPerStage * j, top = S < whole ? 31u : (rest != 0u ? rest - 1u : 0u);
+        const uint32_t g = gran + 8u * j, top = S < whole ? 31u : (rest != 0u ? rest - 1u : 0u);
         const uint32_t more = 16u * ((g < top ? g : top) - gran) + 512u * (uint32_t)S;
         const uint32_t keep = S < whole || (S == whole && rest != 0u) ? 0xFFFFFFFFu : 0u;
 #pragma unroll
         for (int k = 0; k < kLoads; ++k) {
             unsigned char* to = lds + (j % NBUF) * kBuf + (uint32_t)((k < kLoadA ? k * kWaves : kBM / 8 + (k - kLoadA) * kWaves) + wave) * 1024u;
-            if constexpr (inner) load_to_lds16(k < kLoadA ? abuf : wbuf, off[k], 512u * (uint32_t)S + 16u * kPerStage * j, to);
+            if constexpr (inner) load_to_lds16(k < kLoadA ? abuf : wbuf, off[k], 512u * (uint32_t)S + 128u * j, to);
             else load_to_lds16(k < kLoadA ? abuf : wbuf, (off[k] + more) & keep, 0u, to);
         }
     };
 
-    // ---- MXFP4: scale bytes of this lane's rows and columns, a superstage at a time -----------------
+    // ---- MXFP4: scale bytes, 32 of every row and superstage, into LDS ---------------------------------
+    // Lane l of piece q brings 16 bytes of row 32 q + (l >> 1): chunk (l & 1) ^ ((row >> 3) & 1) of its two.  Loads into
+    // LDS, which ask for rows of whole dwords (DWORDS); through registers where the rows are not, and for the
+    // superstage that the row's end cuts.
     const int wm = wave / WN, wn = wave % WN;
     const uint32_t nb = (uint32_t)p.d >> 5;
-    const uint8_t* asc = static_cast<const uint8_t*>(p.a_scales) + (MX ? t0 * nb : 0);
-    const uint8_t* wsc = static_cast<const uint8_t*>(p.w_scales) + (MX ? (int64_t)n0 * nb : 0);
-    uint32_t soff[kSc];
+    const uint8_t* const a_bytes = static_cast<const uint8_t*>(p.a_scales) + (MX ? t0 * nb : 0);
+    const uint8_t* const w_bytes = static_cast<const uint8_t*>(p.w_scales) + (MX ? (int64_t)n0 * nb : 0);
+    const rsrc_t a_sbuf = buffer_of(a_bytes, (last_t + 1u) * nb), w_sbuf = buffer_of(w_bytes, (last_n + 1u) * nb);
+    uint32_t soff[kScaleLoads];
     if constexpr (MX) {
 #pragma unroll
-        for (int m = 0; m < MT + NT; ++m) {
-            const uint32_t r = (uint32_t)(m < MT ? (wm * MT + m) * 32 + i : (wn * NT + m - MT) * 32 + i);
-            const uint32_t last = m < MT ? last_t : last_n;
-            soff[m] = (r < last ? r : last) * nb;
+        for (int k = 0; k < kScaleLoads; ++k) {
+            const uint32_t row = (uint32_t)(k * kWaves + wave) * 32u + ((uint32_t)lane >> 1);
+            const uint32_t r = row < (uint32_t)kBM ? row : row - kBM, last = row < (uint32_t)kBM ? last_t : last_n;
+            soff[k] = (r < last ? r : last) * nb;
         }
     }
-    struct Scales { uint32_t w[kSc][4]; };
-    // the four bytes of stage j of a partial superstage end with the row: where fewer are left, the
-    // row's last four are loaded and shifted at use
-    auto partial_at = [&](int j) { return 32u * (uint32_t)whole + 16u * (uint32_t)h + 4u * (uint32_t)j; };
-    auto request_scales = [&](int S, Scales& to, auto inner_const) {
+    const uint32_t chunk = 16u * (((uint32_t)lane & 1u) ^ (((uint32_t)lane >> 4) & 1u));      // (row >> 3 is lane >> 4 here)
+    auto of_a = [&](int k) { return (k * kWaves + wave) * 32 < kBM; };
+    auto piece_at = [&](int buffer, int k) { return NBUF * kBuf + (uint32_t)buffer * kScaleBuf + (uint32_t)(k * kWaves + wave) * 1024u; };
+    struct Quad { uint32_t w[4]; } sreg[kScaleLoads], rest_sreg[kScaleLoads];
+    auto request_scales = [&](int S) {
         if constexpr (MX) {
 #pragma unroll
-            for (int m = 0; m < MT + NT; ++m) {
-                const uint8_t* from = (m < MT ? asc : wsc);
-                const uint32_t at = 32u * (uint32_t)S + 16u * (uint32_t)h;
-                if constexpr (decltype(inner_const)::value) {
-                    __builtin_memcpy(to.w[m], from + (soff[m] + at), 16);
-                } else {
+            for (int k = 0; k < kScaleLoads; ++k) {
+                if constexpr (DWORDS) load_to_lds16(of_a(k) ? a_sbuf : w_sbuf, soff[k] + chunk, 32u * (uint32_t)S, lds + piece_at(S & 1, k));
+                else __builtin_memcpy(sreg[k].w, (of_a(k) ? a_bytes : w_bytes) + (soff[k] + chunk + 32u * (uint32_t)S), 16);
+            }
+        }
+    };
+    auto keep_scales = [&](int buffer, const Quad (&from)[kScaleLoads]) {
 #pragma unroll
-                    for (uint32_t j = 0; j < 4; ++j)
-                        __builtin_memcpy(&to.w[m][j], from + (soff[m] + (at + 4u * j < nb - 4u ? at + 4u * j : nb - 4u)), 4);
-                }
+        for (int k = 0; k < kScaleLoads; ++k) {
+            const v4i_t v = {(int)from[k].w[0], (int)from[k].w[1], (int)from[k].w[2], (int)from[k].w[3]};
+            const uint32_t to = piece_at(buffer, k) + 16u * (uint32_t)lane;
+            // (an instruction: ahead of an LDS store that it knows, the compiler waits for every load into LDS)
+            asm volatile("ds_write_b128 %0, %1" ::"v"(to), "v"(v) : "memory");
+        }
+    };
+    // The partial superstage: dword q of a chunk; one that the row's end cuts is the row's last four bytes, shifted.
+    auto rest_at = [&](uint32_t q) { return 32u * (uint32_t)whole + chunk + 4u * q; };
+    auto request_rest_scales = [&]() {
+#pragma unroll
+        for (int k = 0; k < kScaleLoads; ++k) {
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q)
+                __builtin_memcpy(&rest_sreg[k].w[q], (of_a(k) ? a_bytes : w_bytes) + (soff[k] + (rest_at(q) < nb - 4u ? rest_at(q) : nb - 4u)), 4);
+        }
+    };
+    auto keep_rest_scales = [&]() {
+#pragma unroll
+        for (int k = 0; k < kScaleLoads; ++k) {
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q) rest_sreg[k].w[q] >>= rest_at(q) < nb - 4u ? 0u : 8u * ((rest_at(q) - (nb - 4u)) & 3u);
+        }
+        keep_scales(2, rest_sreg);
+    };
+    // the four scale bytes of this lane's granules in each stage of superstage S
+    struct Scales { uint32_t w[kSc][4]; };
+    auto read_scales = [&](int buffer, Scales& to) {
+        if constexpr (MX) {
+            const unsigned char* base = scale_bytes_lds + (uint32_t)buffer * kScaleBuf + (uint32_t)i * 32u + 4u * (uint32_t)h;
+            const uint32_t flip = 16u * (((uint32_t)i >> 3) & 1u);
+#pragma unroll
+            for (int m = 0; m < MT + NT; ++m) {
+                const uint32_t row0 = (uint32_t)(m < MT ? (wm * MT + m) * 32 : kBM + (wn * NT + m - MT) * 32);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) to.w[m][j] = *reinterpret_cast<const uint32_t*>(base + row0 * 32u + ((uint32_t)(16 * (j >> 1)) ^ flip) + 8 * (j & 1));
             }
         }
     };
 
+    constexpr bool kEarly = !MX && MT * NT == 1;
     acc_t<MX> acc[MT][NT] = {};
     // byte offset of this lane's fragment rows inside a buffer; place of its granule in the line in step kc
     const uint32_t fa = (uint32_t)((wm * MT) * 32 + i) * kStageBytes, fw = (uint32_t)(kBM + (wn * NT) * 32 + i) * kStageBytes;
     uint32_t place[4];
 #pragma unroll
-    for (int kc = 0; kc < 4; ++kc) place[kc] = ((uint32_t)(4 * h + kc) ^ ((uint32_t)lane & 7u)) * 16u;
+    for (int kc = 0; kc < 4; ++kc) place[kc] = ((uint32_t)(4 * h + kc) ^ (((uint32_t)i >> 1) & 7u)) * 16u;
     struct Raw { v4i_t a[MT], w[NT]; };
     struct Ops { v4i_t ah[MT], al[MT], wh[NT], wl[NT]; };
     // step 0 .. 3: stage j; 4, 5: the first steps of the stage after it
@@ -224,7 +264,7 @@ gemm_tile_kernel(GemmParams p) {
         for (int n = 0; n < NT; ++n) f.w[n] = *reinterpret_cast<const v4i_t*>(base + fw + n * 32 * kStageBytes);
     };
     // -1, or 0 where the granule of stage j, step kc lies past the end of the row: the codes of A count as zero
-    auto live = [&](int j, int kc) { return (MX ? 16u * (uint32_t)h + 4u * (uint32_t)j : 8u * (uint32_t)j + 4u * (uint32_t)h) + (uint32_t)kc < rest ? -1 : 0; };
+    auto live = [&](int j, int kc) { return 8u * (uint32_t)j + 4u * (uint32_t)h + (uint32_t)kc < rest ? -1 : 0; };
     auto unpack = [&](const Raw& f, Ops& o, int keep) {
         const int am = (int)kHighNibbles & keep;
 #pragma unroll
@@ -260,9 +300,7 @@ gemm_tile_kernel(GemmParams p) {
     Raw r0, r1;
     Ops u0, u1;
     Scales cur, nxt;
-    auto advance = [&](int S, auto j_const, auto inner_const, auto tail_const) {
-        constexpr int j = decltype(j_const)::value;
-        constexpr bool tail = decltype(tail_const)::value;
+    auto advance = [&]() {
         // requested after the next stage's codes: those of NBUF - 2 stages (vmcnt: a six-bit count in bits 3:0
         // and 15:14).  Scales may have been requested among them and are not counted: those are loads like any
         // other, which the compiler takes out where nothing uses them, and a count of loads that are not there
@@ -272,33 +310,35 @@ gemm_tile_kernel(GemmParams p) {
         static_assert(n < 64, "");
         __builtin_amdgcn_s_waitcnt(0x0F70 | (n & 15) | ((n >> 4) << 14));
         workgroup_barrier_lds();
-        request_codes(S, std::integral_constant<int, j + NBUF>{}, inner_const);
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (j == 0 && !tail) request_scales(S + 1, nxt, inner_const);
-        __builtin_amdgcn_sched_barrier(0);
     };
     // One stage.  INT4: the codes of a step are read two steps ahead of its products and unpacked while
     // the products of the step before run, a few vector instructions to a product (a wave issues in
     // order).  MXFP4: they are read one step ahead.
     auto stage = [&](int S, auto j_const, auto inner_const, auto tail_const) {
         constexpr int j = decltype(j_const)::value;
-        constexpr bool tail = decltype(tail_const)::value;
+        constexpr bool tail = decltype(tail_const)::value, inner = decltype(inner_const)::value;
         if constexpr (MX) {
             uint32_t sw[kSc];
 #pragma unroll
-            for (int m = 0; m < kSc; ++m) {
-                sw[m] = cur.w[m][j];
-                if constexpr (tail) {
-                    const uint32_t at = partial_at(j);
-                    sw[m] >>= at > nb - 4u ? 8u * ((at - (nb - 4u)) & 3u) : 0u;
-                }
-            }
+            for (int m = 0; m < kSc; ++m) sw[m] = cur.w[m][j];
             auto step = [&](auto kc_const, Raw& now, Raw& next) {
                 constexpr int kc = decltype(kc_const)::value;
-                if constexpr (kc == 3) advance(S, j_const, inner_const, tail_const);
+                constexpr bool kScalesNow = kc == 1 && j == 0 && inner;
+                if constexpr (kc == 3) advance();
                 read(j, kc + 1, next);
+                if constexpr (kc == 3 && j == 3 && !tail) read_scales(inner ? (S + 1) & 1 : 2, nxt);
+                if constexpr (!DWORDS && kc == 1 && j == 3 && inner) keep_scales((S + 1) & 1, sreg);
                 __builtin_amdgcn_sched_barrier(0);
+                if constexpr (kc == 3) request_codes(S, std::integral_constant<int, j + NBUF>{}, inner_const);
+                if constexpr (kScalesNow) request_scales(S + 1);
                 multiply_mx(kc_const, now, sw, tail ? live(j, kc) : -1);
+                if constexpr (kc == 3 || kScalesNow) {
+#pragma unroll
+                    for (int q = 0; q < MT * NT; ++q) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                  // one product
+                        __builtin_amdgcn_sched_group_barrier(0x020, kc == 3 ? (kLoads + MT * NT - 1) / (MT * NT) : 1, 0);  // and its share of the loads
+                    }
+                }
                 __builtin_amdgcn_sched_barrier(0);
             };
             step(std::integral_constant<int, 0>{}, r0, r1);
@@ -308,16 +348,22 @@ gemm_tile_kernel(GemmParams p) {
         } else {
             auto step = [&](auto kc_const, const Ops& now, Ops& next, const Raw& raw_next, Raw& raw) {
                 constexpr int kc = decltype(kc_const)::value;
-                if constexpr (kc == 2) advance(S, j_const, inner_const, tail_const);
+                if constexpr (kc == 2) advance();
+                if constexpr (kc == 2 && kEarly) {
+                    request_codes(S, std::integral_constant<int, j + NBUF>{}, inner_const);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
                 read(j, kc + 2, raw);
                 // (the step after the last one of a tail is never multiplied)
                 unpack(raw_next, next, tail ? live(j + ((kc + 1) >> 2), (kc + 1) & 3) : -1);
+                if constexpr (kc == 2 && !kEarly) request_codes(S, std::integral_constant<int, j + NBUF>{}, inner_const);
                 multiply_i8(now);
                 __builtin_amdgcn_sched_group_barrier(0x100, MT + NT, 0);                      // the reads
 #pragma unroll
                 for (int q = 0; q < 2 * MT * NT; ++q) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                        // one product
                     __builtin_amdgcn_sched_group_barrier(0x002, (12 * (MT + NT) + 2 * MT * NT - 1) / (2 * MT * NT), 0);
+                    if constexpr (kc == 2 && !kEarly) __builtin_amdgcn_sched_group_barrier(0x020, (kLoads + 2 * MT * NT - 1) / (2 * MT * NT), 0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             };
@@ -327,7 +373,10 @@ gemm_tile_kernel(GemmParams p) {
             step(std::integral_constant<int, 3>{}, u1, u0, r0, r1);
         }
     };
-    request_scales(0, cur, std::false_type{});
+    if constexpr (MX) {
+        if (rest != 0u) request_rest_scales();
+        if (whole > 0) request_scales(0);
+    }
     __builtin_amdgcn_sched_barrier(0);
     request_codes(0, std::integral_constant<int, 0>{}, std::false_type{});
     __builtin_amdgcn_sched_barrier(0);
@@ -341,9 +390,14 @@ gemm_tile_kernel(GemmParams p) {
     }
     {
         constexpr int n = (NBUF - 1) * kLoads;
+        if constexpr (MX) {
+            if (!DWORDS && whole > 0) keep_scales(0, sreg);
+            if (rest != 0u) keep_rest_scales();
+        }
         __builtin_amdgcn_s_waitcnt(0x0F70 | (n & 15) | ((n >> 4) << 14));
         workgroup_barrier_lds();
         read(0, 0, r0);
+        read_scales(whole > 0 ? 0 : 2, cur);
         if constexpr (!MX) {
             read(0, 1, r1);
             unpack(r0, u0, whole > 0 ? -1 : live(0, 0));
@@ -366,7 +420,7 @@ gemm_tile_kernel(GemmParams p) {
 #pragma unroll
             for (int m = 0; m < MT; ++m) { u0.ah[m] &= keep; u0.al[m] &= keep; }
         }
-        constexpr uint32_t kFrom = MX ? 4u : 8u;        // stage j holds something if rest > kFrom j
+        constexpr uint32_t kFrom = 8u;        // stage j holds something if rest > kFrom j
         stage(S, std::integral_constant<int, 0>{}, std::false_type{}, std::true_type{});
         if (rest > kFrom) stage(S, std::integral_constant<int, 1>{}, std::false_type{}, std::true_type{});
         if (rest > 2u * kFrom) stage(S, std::integral_constant<int, 2>{}, std::false_type{}, std::true_type{});
@@ -375,8 +429,8 @@ gemm_tile_kernel(GemmParams p) {
     // no load may be on its way into LDS that another workgroup owns by then
     __builtin_amdgcn_s_waitcnt(0x0F70);
 
-    auto store = [&](auto inner_const) {
-        constexpr bool inner = decltype(inner_const)::value;
+    auto store = [&](auto inner_const, auto whole_lines_const) {
+        constexpr bool inner = decltype(inner_const)::value, whole_lines = decltype(whole_lines_const)::value;
 #pragma unroll
         for (int m = 0; m < MT; ++m) {
             const uint32_t rt = (uint32_t)((wm * MT + m) * 32 + 4 * h);            // row of accumulator 0 in the tile
@@ -395,14 +449,25 @@ gemm_tile_kernel(GemmParams p) {
                         float v;
                         if constexpr (MX) v = acc[m][n][4 * q + k];
                         else v = (float)acc[m][n][4 * q + k] * 0x1p-8f * sq[k] * scales_lds[kBM + c];      // (the sum is below 2^24: exact)
-                        if (inner || (rt + 8 * q + k <= last_t && c <= last_n)) row[n * 32] = v;
+                        if constexpr (whole_lines) __builtin_nontemporal_store(v, row + n * 32);
+                        else if (inner || (rt + 8 * q + k <= last_t && c <= last_n)) row[n * 32] = v;
                     }
                 }
             }
         }
     };
-    if (last_t + 1u == (uint32_t)kBM && last_n + 1u == (uint32_t)kBN) store(std::true_type{});
-    else store(std::false_type{});
+    if (last_t + 1u == (uint32_t)kBM && last_n + 1u == (uint32_t)kBN) {
+        if (p.stream_out) {
+            // (the empty statements keep the compiler from making one store of the two, without the policy)
+            asm volatile("" ::: "memory");
+            store(std::true_type{}, std::true_type{});
+            asm volatile("" ::: "memory");
+        } else {
+            store(std::true_type{}, std::false_type{});
+        }
+    } else {
+        store(std::false_type{}, std::false_type{});
+    }
 }
 
 // ---- few rows: one 32 x 32 tile per workgroup, the contraction cut among its KW waves --------------
@@ -532,17 +597,33 @@ gemm_short_kernel(GemmParams p) {
     }
 }
 
-template <bool MX, int MT, int NT, int WM, int WN, int NBUF, int WGS>
-hipError_t launch_tile(GemmParams p, hipStream_t stream) {
-    constexpr uint32_t lds_bytes = (uint32_t)(32 * MT * WM + 32 * NT * WN) * (kStageBytes * NBUF + (MX ? 0u : 4u));
+template <bool MX, int MT, int NT, int WM, int WN, int NBUF, int WGS, bool DWORDS>
+hipError_t launch_tile_as(GemmParams p, hipStream_t stream) {
+    constexpr uint32_t lds_bytes = (uint32_t)(32 * MT * WM + 32 * NT * WN) * (kStageBytes * NBUF + (MX ? 0u : 4u)) +
+                                    (MX ? 3u * 1024u * WM * WN * ((MT * WM + NT * WN + WM * WN - 1) / (WM * WN)) : 0u);
+    static_assert(WGS * lds_bytes <= 160u * 1024u, "LDS of a CU");
     p.tiles_t = (uint32_t)((p.T + 32 * MT * WM - 1) / (32 * MT * WM));
     p.tiles_n = (uint32_t)(((int64_t)p.N + 32 * NT * WN - 1) / (32 * NT * WN));
-    auto kern = gemm_tile_kernel<MX, MT, NT, WM, WN, NBUF, WGS>;
+    // Whole lines of the output are stored with the streaming policy: all workgroups of a round store at the same time, and
+    // what stays in L2 is written back at the end of the launch.  INT4 / MXFP4 (2048, 4096, 2048) 22.0 / 20.9 -> 18.8 / 15.2,
+    // (2048, 14336, 4096) 112 / 111 -> 103 / 84, (2048, 2048, 1024) 9.5 / 8.8 -> 8.3 / 7.6.  Lines that two rows share:
+    // (3000, 3500, 1024) 20.0 / 19.3 -> 22.9 / 22.2, so those keep the plain store.
+    p.stream_out = p.ldo % 32 == 0 && (reinterpret_cast<uintptr_t>(p.out) & 127u) == 0;
+    auto kern = gemm_tile_kernel<MX, MT, NT, WM, WN, NBUF, WGS, DWORDS>;
     int per_cu = 0;      // (raises the kernel's limit of dynamic LDS)
     const hipError_t e = resident_blocks(reinterpret_cast<const void*>(kern), 64 * WM * WN, lds_bytes, &per_cu);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(p.tiles_t * p.tiles_n), dim3(64 * WM * WN), lds_bytes, stream, p);
     return hipGetLastError();
+}
+
+template <bool MX, int MT, int NT, int WM, int WN, int NBUF, int WGS>
+hipError_t launch_tile(const GemmParams& p, hipStream_t stream) {
+    if constexpr (MX) {
+        if (p.d % 128 != 0 || ((reinterpret_cast<uintptr_t>(p.a_scales) | reinterpret_cast<uintptr_t>(p.w_scales)) & 3u) != 0)
+            return launch_tile_as<MX, MT, NT, WM, WN, NBUF, WGS, false>(p, stream);
+    }
+    return launch_tile_as<MX, MT, NT, WM, WN, NBUF, WGS, true>(p, stream);
 }
 
 // Rows of one launch of the kernel for short rows.  A grid takes less than 2^32 lanes, 64 to a tile of 32 x 32
@@ -583,42 +664,40 @@ hipError_t launch_skinny(GemmParams p, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// Which kernel and tile.  Measured on both sides of every line, one GPU, launches back to back, INT4 / MXFP4
-// us (T, N, d), the kernel that is taken first:
+// Which kernel and tile.  Measured on both sides of every line, one GPU, launches back to back, us (T, N, d), the
+// kernel that is taken first:
 //   d < 128, MXFP4 also d = 128: no staging and no cut of the contraction, one wave per 32 x 32 tile.
-//     (4096, 4096, 64) 14.7 / 12.2 against 19.1 / 15.6 with a trip of the tile through LDS, (16384, 512, 64)
-//     9.3 / 7.5 against 12.4 / 10.6.  At d = 128 against the tiles below: (4096, 4096) 15.9 / 13.2 against 16.3 /
-//     14.4, (16384, 512) 9.9 / 8.7 against 9.4 / 9.0, (300, 14336) 7.7 / 6.7 against 8.2 / 7.6.
-//   up to 256 tiles of 32 x 32: the contraction cut among 8 waves, against 64 x 64 tiles.  256 tiles:
-//     (64, 4096, 4096) 7.2 / 6.8 against 8.2 / 7.0, d = 6144 7.6 / 8.6 against 10.9 / 8.4, d = 8192 9.4 / 10.8 against
-//     13.8 / 9.9 (MXFP4 has half the products per granule: not from d = 8192 on).  258 tiles: (96, 2752, 4096)
-//     9.3 / 10.7 against 8.8 / 7.1.
+//     INT4 / MXFP4 (4096, 4096, 64) 14.7 / 12.2 against 19.1 / 15.6 with a trip of the tile through LDS.  At d = 128
+//     against the tiles below: (4096, 4096) 15.9 / 13.2 against 16.3 / 14.4, (300, 14336) 7.7 / 6.7 against 8.2 / 7.6.
+//   up to 256 tiles of 32 x 32: the contraction cut among 8 waves, against 64 x 64 tiles.
+//     INT4: (64, 4096, 4096) 5.9 against 8.1, d = 8192 9.9 against 14.1; 258 tiles: (96, 2752, 4096) 9.4 against 8.7.
+//     MXFP4, where the address unit takes a load of this kernel row by row: up to 16 rows, (1, 4096, 4096) 4.7 against
+//     5.6, (8, 4096, 4096) 5.0 against 5.5, (16, 4096, 4096) 5.6 against 5.6, (24, 4096, 4096) 6.0 against 5.6, (64, 4096, 4096)
+//     6.6 against 5.3; d = 8192 (16, 4096) 9.1 against 8.5.  Up to 32 rows for d <= 2048: (32, 2048, 2048) 4.3 against 4.5.
+//     Rows of scale bytes that are no whole dwords: (64, 4096, 2880) 4.3 against 5.4, (128, 2048, 2880) 4.4 against 5.5.
 //   up to 128 tiles of 128 x 128: 64 x 64 tiles, which two workgroups a CU hold at once up to there, against
-//     128 x 128.  (512, 4096, 4096) 12.6 / 15.0 against 16.3 / 15.3, d = 1024 7.3 / 8.6 against 7.6 / 9.3; the other way
-//     round with 130 tiles, (640, 3328, 4096) 16.5 / 15.5 against 17.9 / 20.7.
-//   more than 256 tiles of 128 x 128: 128 x 256, a sixth less to load per product, for long rows, and only if the
-//     rounds of 256 such tiles are full (or there is one: then a CU has two 128 x 128 tiles or one of these).
-//     (4096, 4096): d = 2048 36.2 / 38.8 with 128 x 128 against 36.1 / 42.4, d = 2880 49.7 / 52.4 against 48.1 / 51.3,
-//     d = 4096 61.0 / 61.5 against 57.0 / 62.5, d = 5120 72.7 / 76.1 against 68.1 / 73.0, d = 8192 110 / 110 against 102 / 103.
-//     Rounds that are not full: (3000, 3500, 4096) 42.3 / 46.4 with 128 x 128 against 50.0 / 57.2, d = 8192 76.0 / 80.6
-//     against 90.1 / 95.3; (2048, 14336, 4096), three and a half, 104 / 106 against 104 / 116.  One round: (2048, 4096,
-//     4096) 29.9 / 33.0 against 29.8 / 33.0, (2177, 2177, 8192) 45.2 / 47.6 against 43.3 / 47.7.
-//   MXFP4 with at most one 128 x 128 tile per CU: four stages in LDS instead of two and a second workgroup that
-//     would not come, (2048, 2048, 4096) 19.5 against 20.6, (1280, 1664, 4096) 16.1 against 17.0, (1536, 1536, 1024) 9.6
-//     against 9.5; INT4, whose stages take twice as long, is faster with two.
+//     128 x 128.  INT4 / MXFP4 (512, 4096, 4096) 13.7 / 10.7 against 15.5 / 12.5, d = 1024 6.2 / 5.4 against 7.3 / 6.5; the
+//     other way round with 130 tiles, (640, 3328, 4096) 15.5 / 12.1 against 19.1 / 13.7.
+//   more than 256 tiles of 128 x 128: 128 x 256, a sixth less to load per product.
+//     MXFP4: (2048, 4096), one round of them for two of 128 x 128, d = 1024 11.2 against 14.1, d = 2048 15.2 against 18.8,
+//     d = 4096 23.5 against 30; (4096, 6144, 2048) 43 against 55, (2048, 14336, 4096) 84 against 88, (4096, 4096, 2048)
+//     36.6 against 34.9; rounds that are not full: (3000, 3500, 2880) 38.5 against 39.6, d = 8192 69 against 67.
+//     INT4, which has two workgroups of 128 x 128 a CU and loads less per product: only where some CUs have one of those
+//     and some two.  (2048, 2560, 4096) 23.4 against 25.3, (2177, 2177, 8192) 42.7 against 45.6, (2048, 3072, 8192) 43.7
+//     against 46.1, d = 4096 25.2 against 25.5, d = 2048 16.1 against 15.6; (2048, 4096, 4096) 31.0 against 29.8,
+//     (2048, 14336, 4096) 108 against 103, (4096, 4096, 8192) 103 against 105.
+//   128 x 128: MXFP4 four stages in LDS and one workgroup a CU, against two stages (2048, 2048, 8192) 23.9 against
+//     27.8; INT4, whose stages take twice as long, two and two workgroups, (2048, 2048, 8192) 30.6 against 33.0.
 template <bool MX>
 hipError_t launch_gemm(const GemmParams& p, hipStream_t stream) {
     auto tiles = [&](int64_t m, int64_t n) { return ((p.T + m - 1) / m) * (((int64_t)p.N + n - 1) / n); };
     if (p.d <= (MX ? 128 : 96)) return launch_short<MX>(p, stream);
-    if (tiles(32, 32) <= 256 && !(MX && p.d >= 8192)) return launch_skinny<MX, 8>(p, stream);
+    const bool few_rows = !MX || (p.d < 8192 && (p.T <= 16 || (p.T <= 32 && p.d <= 2048) || p.d % 128 != 0));
+    if (tiles(32, 32) <= 256 && few_rows) return launch_skinny<MX, 8>(p, stream);
     if (tiles(128, 128) <= 128) return launch_tile<MX, 1, 1, 2, 2, 4, 2>(p, stream);
-    const int64_t wide = tiles(128, 256), rounds = (wide + 255) / 256;
-    if (tiles(128, 128) > 256 && p.d >= (MX ? 5120 : 2880) && (rounds == 1 || 16 * wide >= 15 * 256 * rounds))
-        return launch_tile<MX, 2, 2, 2, 4, 2, 1>(p, stream);
-    if constexpr (MX) {
-        if (tiles(128, 128) <= 256) return launch_tile<MX, 2, 2, 2, 2, 4, 1>(p, stream);
-    }
-    return launch_tile<MX, 2, 2, 2, 2, 2, 2>(p, stream);
+    if (tiles(128, 128) > 256 && (MX || (tiles(128, 128) <= 384 && p.d >= 2880))) return launch_tile<MX, 2, 2, 2, 4, 2, 1>(p, stream);
+    if constexpr (MX) return launch_tile<MX, 2, 2, 2, 2, 4, 1>(p, stream);
+    else return launch_tile<MX, 2, 2, 2, 2, 2, 2>(p, stream);
 }
 
 }  // namespace
@@ -635,7 +714,7 @@ extern "C" perq_status_t perq_w4a4_mxfp4_gemm_ref(const uint8_t* a_codes, const 
         (reinterpret_cast<uintptr_t>(out) & 3u) != 0)
         return PERQ_ERR_UNSUPPORTED;
     if ((T + 31) / 32 > 65535) return PERQ_ERR_UNSUPPORTED;          // the documented reach
-    const perq::GemmParams p = {a_codes, a_scales, w_codes, w_scales, out, T, ldo, N, d, 0, 0};
+    const perq::GemmParams p = {a_codes, a_scales, w_codes, w_scales, out, T, ldo, N, d, 0, 0, 0};
     return perq::launch_gemm<true>(p, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? PERQ_OK : PERQ_ERR_LAUNCH;
 }
 
@@ -650,6 +729,6 @@ extern "C" perq_status_t perq_w4a4_gemm_ref(const uint8_t* a_codes, const float*
         ((reinterpret_cast<uintptr_t>(a_scales) | reinterpret_cast<uintptr_t>(w_scales) | reinterpret_cast<uintptr_t>(out)) & 3u) != 0)
         return PERQ_ERR_UNSUPPORTED;
     if ((T + 63) / 64 > 65535) return PERQ_ERR_UNSUPPORTED;          // the documented reach
-    const perq::GemmParams p = {a_codes, a_scales, w_codes, w_scales, out, T, ldo, N, d, 0, 0};
+    const perq::GemmParams p = {a_codes, a_scales, w_codes, w_scales, out, T, ldo, N, d, 0, 0, 0};
     return perq::launch_gemm<false>(p, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? PERQ_OK : PERQ_ERR_LAUNCH;
 }

@@ -609,6 +609,33 @@ def test_w4a4_products_repeat_bit_for_bit(T, N, d, fmt):
         assert torch.equal(call(ca, sa, cw, sw), first)
 
 
+@pytest.mark.parametrize("T,N,d", [(300, 640, 1152), (300, 640, 2944), (1024, 1408, 1024), (1024, 1408, 4224), (2176, 2304, 2176),
+                                   (2176, 2304, 3072)])
+def test_w4a4_mxfp4_scale_bytes_at_any_address(T, N, d):
+    """Scale bytes at an odd address go through registers, at a dword into LDS directly: the same sums, bit for bit.
+    Output rows of whole 128-byte lines and others are stored differently: the same values."""
+    torch = _torch()
+    print(f"[case] scale bytes T={T} N={N} d={d}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    ca, cw = (torch.randint(0, 256, (n, d // 2), dtype=torch.uint8, device="cuda", generator=g) for n in (T, N))
+    ea, ew = (torch.randint(110, 140, (n, d // 32), dtype=torch.uint8, device="cuda", generator=g) for n in (T, N))
+    want = binding.perq_w4a4_mxfp4_gemm_ref(ca, ea, cw, ew)
+
+    def at(t, shift):
+        room = torch.zeros(t.numel() + 16, dtype=torch.uint8, device="cuda")
+        room[shift:shift + t.numel()] = t.flatten()
+        return room[shift:shift + t.numel()].view(t.shape)
+    for sa, sw in ((1, 0), (0, 2), (3, 3), (4, 8)):
+        assert torch.equal(binding.perq_w4a4_mxfp4_gemm_ref(ca, at(ea, sa), cw, at(ew, sw)), want)
+    out = torch.full((T, N + 5), 7.5, device="cuda")
+    binding.perq_w4a4_mxfp4_gemm_ref(ca, ea, cw, ew, out=out[:, :N])
+    assert torch.equal(out[:, :N], want) and bool((out[:, N:] == 7.5).all())
+    a, w = (orc.dequant_mxfp4(np.stack([c & 15, c >> 4], axis=2).reshape(len(c), d), e)
+            for c, e in ((ca[:64].cpu().numpy(), ea[:64].cpu().numpy()), (cw.cpu().numpy(), ew.cpu().numpy())))
+    # exact products; d fp32 additions, each off by at most 2^-24 of the sum of magnitudes
+    assert np.all(np.abs(want[:64].cpu().numpy().astype(np.float64) - a @ w.T) <= d * 2.0 ** -24 * (np.abs(a) @ np.abs(w).T))
+
+
 def test_w4a4_gemm_argument_checks():
     torch = _torch()
     a = torch.zeros((4, 16), dtype=torch.uint8, device="cuda")
