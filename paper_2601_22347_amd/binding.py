@@ -1,4 +1,5 @@
-"""ctypes binding of libperq.so -- argument marshalling only; every step runs in the library.
+"""Python binding of libperq.so (ctypes, and an extension module for the device calls) -- argument marshalling
+only; every step runs in the library.
 
 Function names and argument order mirror include/perq.h.  Device buffers are PyTorch tensors
 (PyTorch is used for device memory and streams, nothing else); host buffers are NumPy arrays.
@@ -121,9 +122,32 @@ def _check(status: int, where: str) -> None:
 
 
 # A call on a small batch is over on the device in 3 - 6 us and the HIP launch itself takes 3.6 us of
-# host time, so what is done here per call counts (a call for 16 rows: 12.6 -> 9.4 us): pointers go to
-# ctypes as plain integers, and the current stream is asked for as a raw handle (0.4 us; building a
-# torch.cuda.Stream object for it 3.0 us).
+# host time, so what is done on the host per call counts: the device entry points that allocate their
+# outputs are functions of an extension module (csrc/perq_torch.cpp), which does what is between the
+# arguments and the library call in compiled code.
+_module = None
+
+
+def _native():
+    global _module
+    if _module is None:
+        import importlib
+
+        import torch  # noqa: F401  (the module links against it)
+        load()
+        from . import build as _build
+        if not os.path.exists(_build.MODULE):
+            _build.build_module()
+        _module = importlib.import_module("._perq_torch", __package__)
+    return _module
+
+
+def _got(r, where: str):
+    if type(r) is int:
+        raise PerqError(r, where)
+    return r
+
+
 _raw_stream = None
 
 
@@ -268,16 +292,8 @@ def perq_reset_schedule(stream=None) -> None:
 
 def perq_colabs_mean(x, out=None, stream=None):
     """x: CUDA bf16 [M, d] -> CUDA float32 [d]."""
-    import torch
-    M, d, ldx = _check_x(x)
-    lib = load()
-    if out is None:
-        out = torch.empty(d, dtype=torch.float32, device=x.device)
-    nbytes = lib.perq_colabs_mean_workspace_bytes(M, d)
-    ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=x.device)
-    st = lib.perq_colabs_mean(_dev_ptr(x), M, d, ldx, _dev_ptr(out), _dev_ptr(ws), nbytes, _stream_ptr(stream))
-    _check(st, "perq_colabs_mean")
-    return out
+    return _got((_module or _native()).column_statistic(x, out, stream, False), "perq_colabs_mean")
+
 
 
 def perq_colabs_mean_static(x, out, stream=None):
@@ -290,40 +306,21 @@ def perq_colabs_mean_static(x, out, stream=None):
 
 def perq_colabs_absmax(x, out=None, stream=None):
     """x: CUDA bf16 [M, d] -> CUDA float32 [d], max_k |x[k, i]|."""
-    import torch
-    M, d, ldx = _check_x(x)
-    lib = load()
-    if out is None:
-        out = torch.empty(d, dtype=torch.float32, device=x.device)
-    nbytes = lib.perq_colabs_mean_workspace_bytes(M, d)
-    ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=x.device)
-    st = lib.perq_colabs_absmax(_dev_ptr(x), M, d, ldx, _dev_ptr(out), _dev_ptr(ws), nbytes, _stream_ptr(stream))
-    _check(st, "perq_colabs_absmax")
-    return out
+    return _got((_module or _native()).column_statistic(x, out, stream, True), "perq_colabs_absmax")
+
 
 
 def perq_block_diagnostics(x, perm, b: int, out=None, stream=None):
     """x: CUDA bf16 [T, d] -> CUDA float32 [T, 4] = (|x|_inf, |x|_1, max block l1 of xP, |xP R~|_inf)."""
-    import torch
-    T, d, ldx = _check_x(x)
-    if out is None:
-        out = torch.empty((T, 4), dtype=torch.float32, device=x.device)
-    st = load().perq_block_diagnostics(_dev_ptr(x), T, d, ldx, _dev_ptr(perm), int(b), _dev_ptr(out), _stream_ptr(stream))
-    _check(st, "perq_block_diagnostics")
-    return out
+    return _got((_module or _native()).diagnostics(x, perm, b, out, stream), "perq_block_diagnostics")
+
 
 
 def perq_quant_error(y, codes, scales, fmt: str, out=None, stream=None):
     """y: CUDA float32 [T, d]; codes, scales: outputs of perq_permute_rotate_quant for the same input ->
     CUDA float32 [T, 3] = (|y - Q(y)|_2, |y|_2, |y|_inf)."""
-    import torch
-    T, d = y.shape
-    if out is None:
-        out = torch.empty((T, 3), dtype=torch.float32, device=y.device)
-    st = load().perq_quant_error(_dev_ptr(y), T, d, _dev_ptr(codes), _dev_ptr(scales), FMT[fmt], _dev_ptr(out),
-                                 _stream_ptr(stream))
-    _check(st, "perq_quant_error")
-    return out
+    return _got((_module or _native()).quant_error(y, codes, scales, FMT[fmt], out, stream), "perq_quant_error")
+
 
 
 def alloc_outputs(T: int, d: int, fmt: str, device):
@@ -344,73 +341,30 @@ def perq_permute_rotate_quant(x, perm, b: int, fmt: str, codes=None, scales=None
     """x: CUDA bf16 [T, d]; perm: CUDA int32 [d] or None; placement: CUDA uint8 copy of what
     perq_perm_prepare wrote for perm, or None.  Returns (codes, scales) tensors.
     algo "auto" goes by T too; with "mfma" or "butterfly" a row's bits do not depend on the rows beside it."""
-    T, d, ldx = _check_x(x)
-    if codes is None or scales is None:
-        codes, scales = alloc_outputs(T, d, fmt, x.device)
-    lib = load()
-    if placement is not None:
-        if algo != "auto":
-            raise ValueError("a placement goes with algo='auto'")
-        import torch
-        if placement.dtype != torch.uint8 or not placement.is_contiguous() or \
-                placement.numel() != lib.perq_perm_prepared_bytes(d):
-            raise ValueError("placement: not the bytes perq_perm_prepare writes for rows of this width")
-        st = lib.perq_permute_rotate_quant_prepared(_dev_ptr(x), T, d, ldx, _dev_ptr(perm), _dev_ptr(placement), int(b),
-                                                    FMT[fmt], _dev_ptr(codes), _dev_ptr(scales), _stream_ptr(stream))
-    elif algo == "auto":
-        st = lib.perq_permute_rotate_quant(_dev_ptr(x), T, d, ldx, _dev_ptr(perm), int(b), FMT[fmt],
-                                           _dev_ptr(codes), _dev_ptr(scales), _stream_ptr(stream))
-    else:
-        st = lib.perq_permute_rotate_quant_algo(_dev_ptr(x), T, d, ldx, _dev_ptr(perm), int(b), FMT[fmt],
-                                                ALGO[algo], _dev_ptr(codes), _dev_ptr(scales),
-                                                _stream_ptr(stream))
-    _check(st, "perq_permute_rotate_quant")
-    return codes, scales
+    return _got((_module or _native()).apply(x, perm, b, FMT[fmt], codes, scales, stream, ALGO[algo], placement),
+                "perq_permute_rotate_quant")
+
 
 
 def perq_permute_rotate_f32(x, perm, b: int, y=None, stream=None, algo: str = "auto"):
     """Test entry: pre-quantization values, CUDA float32 [T, d]."""
-    import torch
-    T, d, ldx = _check_x(x)
-    if y is None:
-        y = torch.empty((T, d), dtype=torch.float32, device=x.device)
-    st = load().perq_permute_rotate_f32(_dev_ptr(x), T, d, ldx, _dev_ptr(perm), int(b), ALGO[algo],
-                                        _dev_ptr(y), _stream_ptr(stream))
-    _check(st, "perq_permute_rotate_f32")
-    return y
+    return _got((_module or _native()).rotate_f32(x, perm, b, y, stream, ALGO[algo]), "perq_permute_rotate_f32")
+
 
 
 def perq_w4a4_gemm_ref(a_codes, a_scales, w_codes, w_scales, out=None, stream=None):
     """out[t, n] = a_scales[t] * w_scales[n] * <a_codes[t], w_codes[n]> for symmetric INT4 operands
     (CUDA uint8 [T, d/2] / [N, d/2], float32 [T] / [N]); returns CUDA float32 [T, N]."""
-    import torch
-    T, N, d = a_codes.shape[0], w_codes.shape[0], a_codes.shape[1] * 2
-    if w_codes.shape[1] * 2 != d or not a_codes.is_contiguous() or not w_codes.is_contiguous():
-        raise ValueError("a_codes [T, d/2] and w_codes [N, d/2] must be contiguous with the same d")
-    if out is None:
-        out = torch.empty((T, N), dtype=torch.float32, device=a_codes.device)
-    st = load().perq_w4a4_gemm_ref(_dev_ptr(a_codes), _dev_ptr(a_scales), T, _dev_ptr(w_codes), _dev_ptr(w_scales),
-                                   N, d, _dev_ptr(out), out.stride(0) if T else N, _stream_ptr(stream))
-    _check(st, "perq_w4a4_gemm_ref")
-    return out
+    return _got((_module or _native()).product(a_codes, a_scales, w_codes, w_scales, out, stream, False), "perq_w4a4_gemm_ref")
+
 
 
 def perq_w4a4_mxfp4_gemm_ref(a_codes, a_scales, w_codes, w_scales, out=None, stream=None):
     """The same product for MXFP4 operands (CUDA uint8 codes [T, d/2] / [N, d/2], uint8 scale bytes
     [T, d/32] / [N, d/32]); returns CUDA float32 [T, N]."""
-    import torch
-    T, N, d = a_codes.shape[0], w_codes.shape[0], a_codes.shape[1] * 2
-    if w_codes.shape[1] * 2 != d or not a_codes.is_contiguous() or not w_codes.is_contiguous():
-        raise ValueError("a_codes [T, d/2] and w_codes [N, d/2] must be contiguous with the same d")
-    if not a_scales.is_contiguous() or not w_scales.is_contiguous():
-        raise ValueError("scale bytes must be contiguous")
-    if out is None:
-        out = torch.empty((T, N), dtype=torch.float32, device=a_codes.device)
-    st = load().perq_w4a4_mxfp4_gemm_ref(_dev_ptr(a_codes), _dev_ptr(a_scales), T, _dev_ptr(w_codes),
-                                         _dev_ptr(w_scales), N, d, _dev_ptr(out), out.stride(0) if T else N,
-                                         _stream_ptr(stream))
-    _check(st, "perq_w4a4_mxfp4_gemm_ref")
-    return out
+    return _got((_module or _native()).product(a_codes, a_scales, w_codes, w_scales, out, stream, True),
+                "perq_w4a4_mxfp4_gemm_ref")
+
 
 
 def placement_to_device(prepared: np.ndarray, device="cuda"):

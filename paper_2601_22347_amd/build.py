@@ -1,4 +1,4 @@
-"""Builds libperq.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Builds libperq.so (HIP kernels + C ABI) for gfx950 with hipcc, and the Python extension module that calls it, in-tree."""
 from __future__ import annotations
 
 import os
@@ -9,6 +9,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libperq.so")
+MODULE = os.path.join(PKG, "_perq_torch.so")
 
 SOURCES = ["perq_host.cpp", "perq_colabs.hip", "perq_butterfly.hip", "perq_mfma.hip", "perq_api.hip",
            "perq_gemm.hip", "perq_qerr.hip", "perq_npo2.hip", "perq_npo2_12.hip", "perq_npo2_76.hip", "perq_npo2_32.hip"]
@@ -52,7 +53,27 @@ def build(verbose: bool = False) -> str:
     res = subprocess.run(link, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"link failed:\n{res.stdout}")
+    build_module()
     return LIB
+
+
+def build_module() -> str:
+    """Compile the extension module (host code; needs libperq.so to link against)."""
+    import sysconfig
+
+    import torch
+    where = os.path.dirname(torch.__file__)
+    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unknown-pragmas",
+           "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(where, "include"),
+           "-isystem", os.path.join(where, "include", "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
+           "-isystem", sysconfig.get_path("include"), os.path.join(CSRC, "perq_torch.cpp"), "-o", MODULE,
+           "-L", PKG, "-l:libperq.so", "-Wl,-rpath,$ORIGIN", "-L", os.path.join(where, "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"g++ failed on perq_torch.cpp:\n{' '.join(cmd)}\n{res.stdout}")
+    return MODULE
 
 
 def _device_assembly(src: str) -> str:
