@@ -470,45 +470,83 @@ gemm_tile_kernel(GemmParams p) {
     }
 }
 
-// ---- few rows: one 32 x 32 tile per workgroup, the contraction cut among its KW waves --------------
-// Bound by the latency of the loads: nothing is used twice, so the granules go straight to registers,
-// wave k takes the stages k, k + KW, ... and the partial tiles are added in LDS in wave order.  A stage's loads are
-// all issued before its first product (left to itself the compiler puts some behind it: (64, 4096, 8000) INT4
-// 10.4 -> 7.8 us, MXFP4 8.8 -> 8.1).
+// ---- few tiles: one 32 x 32 tile per workgroup, the contraction cut among its KW waves -------------
+// Wave k takes the stages k, k + KW, ...: it brings a stage, a line of every row and column, into 8 KiB of LDS of its own
+// with eight direct loads, reads its operands, asks for its next stage and multiplies; the partial tiles are added in
+// wave order, the only barrier.
+//   Bound by the loads.  Straight to registers, nothing is used twice either, but an instruction then meets 32 rows,
+// which takes the address unit four times as long as eight rows of a line each, and that bound the kernel:
+// INT4 / MXFP4 (3, 517, 28672) 18.8 / 25.2 -> 10.4 / 12.2 us, (64, 4096, 8192) 10.1 / 12.9 -> 6.1 / 7.0, (16, 4096, 4096)
+// 5.0 / 5.4 -> 3.8 / 4.0 (registers, then LDS).  A second buffer per wave leaves one workgroup a CU instead of two: (123, 2665,
+// 12288) INT4 14.4 instead of 11.4; sixteen waves: (64, 4096, 14336) 8.9 instead of 8.2.
 template <bool MX, int KW>
 __global__ void __launch_bounds__(64 * KW)
-gemm_skinny_kernel(GemmParams p) {
-    __shared__ float part_f[KW][16][64];
+gemm_few_kernel(GemmParams p) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    constexpr uint32_t kStage = 64u * kStageBytes;
     const int lane = threadIdx.x & 63, i = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    unsigned char* const mine = lds + (uint32_t)wave * kStage;
     uint32_t tt, tn;
     tile_of_block(p, tt, tn);
-    const int64_t t0 = (int64_t)tt * 32, t = t0 + i < p.T ? t0 + i : p.T - 1;
-    const int32_t n0 = (int32_t)tn * 32, n = n0 + i < p.N ? n0 + i : p.N - 1;
+    const int64_t t0 = (int64_t)tt * 32;
+    const int32_t n0 = (int32_t)tn * 32;
     const uint32_t row_bytes = (uint32_t)p.d >> 1, granules = row_bytes >> 4, nb = (uint32_t)p.d >> 5;
-    const int stages = (int)((granules + 7u) >> 3);
-    const uint8_t* ac = p.a_codes + t * row_bytes;
-    const uint8_t* wc = p.w_codes + (int64_t)n * row_bytes;
-    acc_t<MX> acc = {};
-    for (int s = wave; s < stages; s += KW) {
-        v4i_t a[4], w[4];
-        uint32_t sa = 0, sw = 0;
+    const uint32_t last_t = (uint32_t)(p.T - t0 < 32 ? p.T - t0 : 32) - 1u;
+    const uint32_t last_n = (uint32_t)(p.N - n0 < 32 ? p.N - n0 : 32) - 1u;
+    const rsrc_t abuf = buffer_of(p.a_codes + t0 * row_bytes, (last_t + 1u) * row_bytes);
+    const rsrc_t wbuf = buffer_of(p.w_codes + (int64_t)n0 * row_bytes, (last_n + 1u) * row_bytes);
+    const uint8_t* const as = static_cast<const uint8_t*>(p.a_scales) + (MX ? (t0 + ((uint32_t)i < last_t ? (uint32_t)i : last_t)) * nb : 0);
+    const uint8_t* const ws = static_cast<const uint8_t*>(p.w_scales) + (MX ? (int64_t)(n0 + ((uint32_t)i < last_n ? (uint32_t)i : last_n)) * nb : 0);
+    // a load fills 8 rows: lane l brings the granule of place l & 7 of row l >> 3 (place q of row r holds granule q ^ ((r >> 1) & 7))
+    uint32_t a_row[4], w_row[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t r = 8u * k + ((uint32_t)lane >> 3);
+        a_row[k] = (r < last_t ? r : last_t) * row_bytes;
+        w_row[k] = (r < last_n ? r : last_n) * row_bytes;
+    }
+    const uint32_t gran = ((uint32_t)lane & 7u) ^ ((uint32_t)lane >> 4);
+    uint32_t sa_next = 0, sw_next = 0;
+    // (granules past the end of a row are its last one, cleared in A at use)
+    auto request = [&](int s) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t g = 8u * (uint32_t)s + (gran ^ (4u * (k & 1))), at = 16u * (g < granules ? g : granules - 1u);
+            load_to_lds16(abuf, a_row[k] + at, 0u, mine + 1024 * k);
+            load_to_lds16(wbuf, w_row[k] + at, 0u, mine + 1024 * (4 + k));
+        }
         if constexpr (MX) {
-            const uint8_t* as = static_cast<const uint8_t*>(p.a_scales) + t * nb;
-            const uint8_t* ws = static_cast<const uint8_t*>(p.w_scales) + (int64_t)n * nb;
             uint32_t at = 8u * (uint32_t)s + 4u * (uint32_t)h;
             at = at < nb ? at : nb - 1u;
-            sa = scale_dword(as, at, nb);
-            sw = scale_dword(ws, at, nb);
+            sa_next = scale_dword(as, at, nb);
+            sw_next = scale_dword(ws, at, nb);
         }
+    };
+    acc_t<MX> acc = {};
+    const int stages = (int)((granules + 7u) >> 3);
+    if (wave < stages) request(wave);
+    for (int s = wave; s < stages; s += KW) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        __builtin_amdgcn_sched_barrier(0);
+        const unsigned char* const from = mine + (uint32_t)i * kStageBytes;
+        v4i_t a[4], w[4];
 #pragma unroll
         for (int kc = 0; kc < 4; ++kc) {
-            const uint32_t g = 8u * (uint32_t)s + 4u * (uint32_t)h + kc, gc = g < granules ? g : granules - 1u;
-            a[kc] = *reinterpret_cast<const v4i_t*>(ac + 16u * gc);
-            w[kc] = *reinterpret_cast<const v4i_t*>(wc + 16u * gc);
-            if (g >= granules) a[kc] = v4i_t{0, 0, 0, 0};
+            const uint32_t place = 16u * ((uint32_t)(4 * h + kc) ^ (((uint32_t)i >> 1) & 7u));
+            a[kc] = *reinterpret_cast<const v4i_t*>(from + place);
+            w[kc] = *reinterpret_cast<const v4i_t*>(from + 32u * kStageBytes + place);
         }
-        __builtin_amdgcn_sched_barrier(0);
+        const uint32_t sa = sa_next, sw = sw_next;
+        // every read has landed before the buffer is loaded again
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3])::"memory");
+        if (s + KW < stages) request(s + KW);
+        if (8u * (uint32_t)s + 8u > granules) {
+#pragma unroll
+            for (int kc = 0; kc < 4; ++kc) {
+                if (8u * (uint32_t)s + 4u * (uint32_t)h + (uint32_t)kc >= granules) a[kc] = v4i_t{0, 0, 0, 0};
+            }
+        }
         if constexpr (MX) {
             acc = mx_product<0>(a[0], w[0], acc, sa, sw);
             acc = mx_product<1>(a[1], w[1], acc, sa, sw);
@@ -523,26 +561,23 @@ gemm_skinny_kernel(GemmParams p) {
             }
         }
     }
+    // partial tiles into the waves' own buffers, which nothing is on its way to: [16][64]
+    typedef typename std::conditional<MX, float, int>::type part_t;
+    part_t* const part = reinterpret_cast<part_t*>(mine);
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        if constexpr (MX) part_f[wave][j][lane] = acc[j];
-        else part_f[wave][j][lane] = __int_as_float(acc[j]);
-    }
+    for (int j = 0; j < 16; ++j) part[64 * j + lane] = acc[j];
     __syncthreads();
 #pragma unroll
     for (int jj = 0; jj < 16 / KW; ++jj) {
         const int j = jj * KW + wave;
-        acc_t<MX> sum = {};
+        part_t sum = 0;
 #pragma unroll
-        for (int k = 0; k < KW; ++k) {
-            if constexpr (MX) sum[0] += part_f[k][j][lane];
-            else sum[0] += __float_as_int(part_f[k][j][lane]);
-        }
+        for (int k = 0; k < KW; ++k) sum += reinterpret_cast<const part_t*>(lds + (uint32_t)k * kStage)[64 * j + lane];
         const int64_t row = t0 + 8 * (j >> 2) + 4 * h + (j & 3);
         if (row < p.T && n0 + i < p.N) {
             float v;
-            if constexpr (MX) v = sum[0];
-            else v = (float)sum[0] * 0x1p-8f * static_cast<const float*>(p.a_scales)[row] * static_cast<const float*>(p.w_scales)[n0 + i];
+            if constexpr (MX) v = sum;
+            else v = (float)sum * 0x1p-8f * static_cast<const float*>(p.a_scales)[row] * static_cast<const float*>(p.w_scales)[n0 + i];
             p.out[row * p.ldo + n0 + i] = v;
         }
     }
@@ -657,10 +692,15 @@ hipError_t launch_short(const GemmParams& all, hipStream_t stream) {
 }
 
 template <bool MX, int KW>
-hipError_t launch_skinny(GemmParams p, hipStream_t stream) {
+hipError_t launch_few(GemmParams p, hipStream_t stream) {
+    constexpr uint32_t lds_bytes = KW * 64u * kStageBytes;
     p.tiles_t = (uint32_t)((p.T + 31) / 32);
     p.tiles_n = (uint32_t)(((int64_t)p.N + 31) / 32);
-    hipLaunchKernelGGL((gemm_skinny_kernel<MX, KW>), dim3(p.tiles_t * p.tiles_n), dim3(64 * KW), 0, stream, p);
+    auto kern = gemm_few_kernel<MX, KW>;
+    int per_cu = 0;      // (raises the kernel's limit of dynamic LDS)
+    const hipError_t e = resident_blocks(reinterpret_cast<const void*>(kern), 64 * KW, lds_bytes, &per_cu);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(p.tiles_t * p.tiles_n), dim3(64 * KW), lds_bytes, stream, p);
     return hipGetLastError();
 }
 
@@ -669,12 +709,17 @@ hipError_t launch_skinny(GemmParams p, hipStream_t stream) {
 //   d < 128, MXFP4 also d = 128: no staging and no cut of the contraction, one wave per 32 x 32 tile.
 //     INT4 / MXFP4 (4096, 4096, 64) 14.7 / 12.2 against 19.1 / 15.6 with a trip of the tile through LDS.  At d = 128
 //     against the tiles below: (4096, 4096) 15.9 / 13.2 against 16.3 / 14.4, (300, 14336) 7.7 / 6.7 against 8.2 / 7.6.
-//   up to 256 tiles of 32 x 32: the contraction cut among 8 waves, against 64 x 64 tiles.
-//     INT4: (64, 4096, 4096) 5.9 against 8.1, d = 8192 9.9 against 14.1; 258 tiles: (96, 2752, 4096) 9.4 against 8.7.
-//     MXFP4, where the address unit takes a load of this kernel row by row: up to 16 rows, (1, 4096, 4096) 4.7 against
-//     5.6, (8, 4096, 4096) 5.0 against 5.5, (16, 4096, 4096) 5.6 against 5.6, (24, 4096, 4096) 6.0 against 5.6, (64, 4096, 4096)
-//     6.6 against 5.3; d = 8192 (16, 4096) 9.1 against 8.5.  Up to 32 rows for d <= 2048: (32, 2048, 2048) 4.3 against 4.5.
-//     Rows of scale bytes that are no whole dwords: (64, 4096, 2880) 4.3 against 5.4, (128, 2048, 2880) 4.4 against 5.5.
+//   few tiles of 32 x 32: the contraction cut among 8 waves, against 64 x 64 tiles.
+//     INT4, up to 512, and up to 900 for d >= 2048: (64, 4096, 4096) 4.1 against 8.2, (128, 4096, 4096) 6.0 against 8.5,
+//     (300, 1500, 1088) 4.0 against 5.0, (236, 2696, 6144) 10.5 against 12.4; 1024 tiles: (256, 4096, 4096) 10.2 against 9.2;
+//     800: (160, 5000, 1024) 5.0 against 4.9, (200, 3000, 2048) 5.3 against 5.8.
+//     MXFP4, up to 256: (64, 4096, 4096) 4.5 against 5.5, (64, 4096, 14336) 10.8 against 14.2; 384: (96, 4096, 8192) 10.9
+//     against 9.0; 512: (128, 4096, 4096) 6.7 against 5.8.  Rows of scale bytes that are no whole dwords, up to 512:
+//     (300, 1500, 1088) 3.7 against 4.6.
+//     One row of tiles, which fills half of the others: any number, (16, 65536, 4096) 30.0 / 32.0 against 36.6 / 32.8,
+//     (16, 28672, 8192) 25.5 / 29.5 against 29.4 / 29.3, (32, 65536, 4096) 33.3 / 36.5 against 38.0 / 35.3.
+//     Among 4 waves where there are more than 512 tiles and little to cut: (1, 65536, 2048) 12.3 / 11.8 against 14.2 / 13.6,
+//     (32, 32768, 1024) 6.1 / 5.8 against 7.0 / 6.5, (16, 65536, 4096) 29.7 / 34.5 against 30.0 / 32.0.
 //   up to 128 tiles of 128 x 128: 64 x 64 tiles, which two workgroups a CU hold at once up to there, against
 //     128 x 128.  INT4 / MXFP4 (512, 4096, 4096) 13.7 / 10.7 against 15.5 / 12.5, d = 1024 6.2 / 5.4 against 7.3 / 6.5; the
 //     other way round with 130 tiles, (640, 3328, 4096) 15.5 / 12.1 against 19.1 / 13.7.
@@ -692,8 +737,10 @@ template <bool MX>
 hipError_t launch_gemm(const GemmParams& p, hipStream_t stream) {
     auto tiles = [&](int64_t m, int64_t n) { return ((p.T + m - 1) / m) * (((int64_t)p.N + n - 1) / n); };
     if (p.d <= (MX ? 128 : 96)) return launch_short<MX>(p, stream);
-    const bool few_rows = !MX || (p.d < 8192 && (p.T <= 16 || (p.T <= 32 && p.d <= 2048) || p.d % 128 != 0));
-    if (tiles(32, 32) <= 256 && few_rows) return launch_skinny<MX, 8>(p, stream);
+    const int64_t small = tiles(32, 32);
+    const bool one_row = p.T <= 32 && small <= (int64_t)1 << 22;      // (2^31 lanes; a grid takes less than 2^32)
+    if (small <= 256 || one_row || (small <= 512 && (!MX || p.d % 128 != 0)) || (!MX && small <= 900 && p.d >= 2048))
+        return small > 512 && p.d < 4096 ? launch_few<MX, 4>(p, stream) : launch_few<MX, 8>(p, stream);
     if (tiles(128, 128) <= 128) return launch_tile<MX, 1, 1, 2, 2, 4, 2>(p, stream);
     if (tiles(128, 128) > 256 && (MX || (tiles(128, 128) <= 384 && p.d >= 2880))) return launch_tile<MX, 2, 2, 2, 4, 2, 1>(p, stream);
     if constexpr (MX) return launch_tile<MX, 2, 2, 2, 2, 4, 1>(p, stream);

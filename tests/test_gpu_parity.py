@@ -587,6 +587,14 @@ def test_w4a4_products_over_tiles_and_remainders(T, N, d, fmt):
     assert bool((out[:, N:] == 7.5).all())
 
 
+# few tiles: four and eight waves, one row of tiles and several, rows of one stage, of stages that the waves share unevenly, cut rows
+@pytest.mark.parametrize("T,N,d", [(1, 33, 160), (32, 16500, 288), (32, 16500, 4128), (17, 9000, 2336), (130, 3300, 2080), (130, 3300, 4096),
+                                   (64, 2048, 2304), (33, 100, 2048), (300, 1500, 1088)])
+@pytest.mark.parametrize("fmt", ["int4", "mxfp4"])
+def test_w4a4_products_of_few_tiles(T, N, d, fmt):
+    test_w4a4_products_over_tiles_and_remainders(T, N, d, fmt)
+
+
 # ---- rows that end in several stages of a partial superstage: the waits count the loads that are there ----
 @pytest.mark.parametrize("T,N,d", [(449, 577, 2880), (513, 700, 1312), (1540, 1537, 800), (2177, 2177, 2016),
                                    (1540, 1537, 2880), (1540, 1537, 4096), (2060, 2177, 2880), (2060, 2177, 4096),
