@@ -19,6 +19,8 @@
 #include "perq_device.h"
 #include "perq_launch.h"
 
+#include <type_traits>
+
 namespace perq {
 
 namespace {
@@ -39,7 +41,8 @@ struct BflyGeom {
 // fp32 output is stored by quads of lanes where a row is a multiple of four lanes.  Workgroups of 1024 lanes have 128
 // registers, which both forms of the store in one kernel overflow (d = 17440, T = 9 with a permutation 8.5 -> 9.3 us):
 // there QUADS says which one it is; the others decide at run time.
-template <int OUT, bool PERM, int MAXT, bool QUADS = false>
+//   WAVES: b >= 4096, stages across waves through LDS.  In a kernel of their own: the others have 20 registers less.
+template <int OUT, bool PERM, int MAXT, bool WAVES, bool QUADS = false>
 __global__ void __launch_bounds__(MAXT)
 butterfly_kernel(ApplyParams p, BflyGeom g) {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -56,21 +59,6 @@ butterfly_kernel(ApplyParams p, BflyGeom g) {
 #pragma unroll
     for (int k = 0; k < 6; ++k) sgn[k] = (t >> k) & 1 ? -1.0f : 1.0f;
 
-    // LDS byte address (inside one staged row) of each of this lane's 32 source elements
-    uint32_t src_addr[PERM ? 32 : 1];
-    if constexpr (PERM) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int4 e4 = *reinterpret_cast<const int4*>(p.perm + 32 * (active ? t : 0) + 4 * q);
-            const int e[4] = {e4.x, e4.y, e4.z, e4.w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t ee = (uint32_t)e[j];
-                src_addr[4 * q + j] = (granule_slot(ee >> 3) << 4) | ((ee & 7u) << 1);
-            }
-        }
-    }
-
     const int64_t ngroups = (p.T + g.rows - 1) / g.rows;
     unsigned char* my_row = lds + (uint32_t)r * g.row_bytes;
 
@@ -84,8 +72,35 @@ butterfly_kernel(ApplyParams p, BflyGeom g) {
         }
     };
 
+    // LDS byte address (inside one staged row) of each of this lane's 32 source elements.  Two to a register in
+    // workgroups of more than 256 lanes, which fill a CU's registers with one or two of them: with 32 registers of
+    // addresses those of 512 lanes had 154 registers, one workgroup a CU, and those of 1024 spilled 25 (T = 342, d = 12288,
+    // b = 32 11.3 -> 9.1 us, T = 780, d = 11008, b = 256 19.0 -> 14.9, T = 1000, d = 28672 diagnostics 40.3 -> 28.5).  Up to
+    // 256 lanes the registers saved bring a fourth workgroup, and the work of taking the pairs apart in every row
+    // costs more (T = 2048, d = 8192, b = 32 14.0 -> 14.5).  Read by the workgroup in order and handed over through LDS,
+    // the addresses were 2 % faster to have at d = 4096, 8192 and 13 % slower at d = 2880.
+    constexpr bool kPacked = MAXT > 256;
+    uint32_t src_addr[PERM ? (kPacked ? 16 : 32) : 1];
     uint4 stage[4];
-    if (blockIdx.x < ngroups) load_group(blockIdx.x, stage);
+    if constexpr (PERM) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int4 e4 = *reinterpret_cast<const int4*>(p.perm + 32 * ta + 4 * q);
+            auto address = [](int e) { return (granule_slot((uint32_t)e >> 3) << 4) | (((uint32_t)e & 7u) << 1); };
+            if constexpr (kPacked) {
+                src_addr[2 * q] = address(e4.x) | (address(e4.y) << 16);
+                src_addr[2 * q + 1] = address(e4.z) | (address(e4.w) << 16);
+            } else {
+                src_addr[4 * q] = address(e4.x);
+                src_addr[4 * q + 1] = address(e4.y);
+                src_addr[4 * q + 2] = address(e4.z);
+                src_addr[4 * q + 3] = address(e4.w);
+            }
+        }
+        if (blockIdx.x < ngroups) load_group(blockIdx.x, stage);
+    } else {
+        if (blockIdx.x < ngroups) load_group(blockIdx.x, stage);
+    }
 
     for (int64_t grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
         const int64_t row = grp * g.rows + r;
@@ -105,8 +120,10 @@ butterfly_kernel(ApplyParams p, BflyGeom g) {
         float v[32];
         if constexpr (PERM) {
 #pragma unroll
+            for (int i = 0; i < (kPacked ? 16 : 0); ++i) asm volatile("" : "+v"(src_addr[i]));        // (or they are taken apart ahead of the loop)
+#pragma unroll
             for (int i = 0; i < 32; ++i) {
-                const uint32_t h = *reinterpret_cast<const uint16_t*>(my_row + src_addr[i]);
+                const uint32_t h = *reinterpret_cast<const uint16_t*>(my_row + (!kPacked ? src_addr[PERM ? i : 0] : i & 1 ? src_addr[i >> 1] >> 16 : src_addr[i >> 1] & 0xFFFFu));
                 v[i] = __uint_as_float(h << 16);
             }
         } else {
@@ -147,7 +164,7 @@ butterfly_kernel(ApplyParams p, BflyGeom g) {
         if (b >= 512) lane_stage<8>(v, sgn[3]);
         if (b >= 1024) lane_stage<16>(v, sgn[4]);
         if (b >= 2048) lane_stage<32>(v, sgn[5]);
-        if (b >= 4096) {
+        if constexpr (WAVES) {
             // distances 2048.. : partner lane is in another wave; exchange all 32 values through
             // LDS (aliasing the staged rows, which are dead by now).  Granule j of lane t sits at
             // slot t*8 + (j ^ (t & 7)) so that 8 consecutive lanes cover all banks.
@@ -360,13 +377,18 @@ hipError_t launch_butterfly_out(const ApplyParams& p, hipStream_t stream) {
 
     // register budget follows the workgroup size: 256 threads for rows up to 8192, 512 up to
     // 16384, 1024 beyond
-    auto kern = threads <= 256   ? (p.perm ? butterfly_kernel<OUT, true, 256> : butterfly_kernel<OUT, false, 256>)
-                : threads <= 512 ? (p.perm ? butterfly_kernel<OUT, true, 512> : butterfly_kernel<OUT, false, 512>)
-                                 : (p.perm ? butterfly_kernel<OUT, true, 1024> : butterfly_kernel<OUT, false, 1024>);
-    if constexpr (OUT == OUT_F32) {
-        if (threads > 512 && (g.nt & 3) == 0)
-            kern = p.perm ? butterfly_kernel<OUT, true, 1024, true> : butterfly_kernel<OUT, false, 1024, true>;
-    }
+    auto pick = [&](auto waves) {
+        constexpr bool kWaves = decltype(waves)::value;
+        auto kern = threads <= 256   ? (p.perm ? butterfly_kernel<OUT, true, 256, kWaves> : butterfly_kernel<OUT, false, 256, kWaves>)
+                    : threads <= 512 ? (p.perm ? butterfly_kernel<OUT, true, 512, kWaves> : butterfly_kernel<OUT, false, 512, kWaves>)
+                                     : (p.perm ? butterfly_kernel<OUT, true, 1024, kWaves> : butterfly_kernel<OUT, false, 1024, kWaves>);
+        if constexpr (OUT == OUT_F32) {
+            if (threads > 512 && (g.nt & 3) == 0)
+                kern = p.perm ? butterfly_kernel<OUT, true, 1024, kWaves, true> : butterfly_kernel<OUT, false, 1024, kWaves, true>;
+        }
+        return kern;
+    };
+    auto kern = p.b >= 4096 ? pick(std::true_type{}) : pick(std::false_type{});
     // Persistent grid: as many workgroups as the device keeps resident, each walking the rows.
     int per_cu = 0;
     const hipError_t oe = resident_blocks(reinterpret_cast<const void*>(kern), threads, lds_bytes, &per_cu);
