@@ -181,23 +181,26 @@ npo2_kernel(const ApplyParams p, const Npo2Geom<MB> g) {
 #pragma unroll
             for (int ks = 0; ks < kKS; ++ks)
 #pragma unroll
-                for (int e2 = 0; e2 < 4; ++e2) {
-                    uint32_t pair = 0;
+                for (int q = 0; q < 2; ++q) {
+                    // Four entries a load (read one by one, each instruction meets 64 cache lines, the table was 8 us of a
+                    // short launch: T = 3, d = b = 12288 13.7 -> 8.9 us, T = 2, d = b = 28672 14.9 -> 11.6, T = 2000, d = 6144, b = 1536
+                    // 23.5 -> 16.6).  A base's order is a multiple of four, so four indices
+                    // are inside it or past its end together; past the end they meet zero rows of B and are pointed
+                    // at the a-value's first elements, finite like all input, so that every read below is unconditional.
+                    static_assert(MB % 4 == 0 && kChunkPos % 4 == 0, "groups of four, 16 bytes of perm");
+                    const int r = r_of(ks, 4 * q);
+                    const int4 ch4 = *reinterpret_cast<const int4*>(p.perm + (my_chunk * kChunkPos + a_of(al, ks) * MB + (r < MB ? r : 0)));
+                    const int ch[4] = {ch4.x, ch4.y, ch4.z, ch4.w};
+                    uint32_t off[4];
 #pragma unroll
-                    for (int s = 0; s < 2; ++s) {
-                        // (an index past the end of the base meets a zero row of B: it is pointed at the
-                        //  a-value's first element, finite like all input, so that every read below is
-                        //  unconditional)
-                        const int r = r_of(ks, 2 * e2 + s);
-                        const int pos = my_chunk * kChunkPos + a_of(al, ks) * MB + (r < MB ? r : 0);
-                        const int ch = p.perm[pos];
-                        const uint32_t cl = (uint32_t)(ch % kChunkPos);
+                    for (int s = 0; s < 4; ++s) {
+                        const uint32_t cl = (uint32_t)(ch[s] % kChunkPos);
                         // (in units of two bytes: eight chunks of fp32 pass 64 KiB)
-                        const uint32_t off = (uint32_t)(ch / kChunkPos) * (uint32_t)(kAreaPos * 2) +
-                                             (kSwz ? ((cl >> 5) * 4u + (((cl >> 3) & 3u) ^ ((cl >> 7) & 3u))) * 8u + (cl & 7u) : cl);
-                        pair |= off << (16 * s);
+                        off[s] = (uint32_t)(ch[s] / kChunkPos) * (uint32_t)(kAreaPos * 2) +
+                                 (kSwz ? ((cl >> 5) * 4u + (((cl >> 3) & 3u) ^ ((cl >> 7) & 3u))) * 8u + (cl & 7u) : cl);
                     }
-                    tab[(al * kKS + ks) * 4 + e2] = pair;
+                    tab[(al * kKS + ks) * 4 + 2 * q] = off[0] | (off[1] << 16);
+                    tab[(al * kKS + ks) * 4 + 2 * q + 1] = off[2] | (off[3] << 16);
                 }
     } else {
         tab[0] = 0;
