@@ -1369,8 +1369,9 @@ static int64_t mfma_line(const ApplyParams& p, int out_kind) {
 
     const bool one_tile = p.d <= kTile, two_tiles = p.d > kTile && p.d <= 2 * kTile;
     if (!perm) {
-        // d = 8192, b = 4096: T = 16 5.6 / 9.0, T = 1024 10.8 / 11.1, T = 2048 20.8 / 16.4
-        if (large) return exp2(23);
+        // d = 8192, b = 4096: T = 16 5.6 / 9.0, T = 1024 10.7 / 11.5, T = 2048 20.8 / 16.4; d = 16384, b = 1024, T = 512
+        // 9.4 / 11.7; d = 12288, T = 1024 15.3 / 14.7
+        if (large) return exp2(23) + 1;
         // Two tiles: b = 32, d = 5120, T = 1639 6.8 / 8.6, T = 3277 11.9 / 11.8, T = 4916 14.7 / 14.3; d = 8192, T = 1025
         // 6.5 / 7.5, T = 2049 10.9 / 11.2, T = 4097 18.6 / 18.6 (MXFP4, T = 3072 11.2 / 12.9, T = 4096 14.9 / 15.9: the
         // butterflies keep a group's maximum in the lane).  b = 128: T = 1639 8.8 / 9.7, T = 3277 14.6 / 13.2.
@@ -1378,10 +1379,20 @@ static int64_t mfma_line(const ApplyParams& p, int out_kind) {
         // Ragged rows of more tiles: b = 32, d = 11008, T = 762 7.2 / 7.8, T = 1524 12.6 / 11.7; d = 15904, T = 527
         // 7.4 / 8.4, T = 1054 11.6 / 12.1; b = 128, d = 11008, T = 381 6.7 / 6.8, T = 762 8.7 / 8.3.
         if (ragged && !one_tile) return exp2(small ? 24 : 23);
+        // Three tiles and more.  b = 32: d = 16384, T = 512 6.7 / 7.6, T = 1024 10.5 / 11.4, T = 2048 18.6 / 19.3; d = 14336, T = 1024
+        // 10.2 / 10.6; d = 12288, T = 1365 12.4 / 12.2, T = 2730 19.7 / 18.3; d = 32768, T = 256 7.5 / 8.5, T = 1024 19.3 / 19.2.
+        // b = 128: d = 16384, T = 256 5.5 / 6.4, T = 512 7.6 / 7.9, T = 1024 13.7 / 12.1; d = 14336, T = 512 7.5 / 7.5, T = 1024
+        // 12.7 / 11.4; d = 32768, T = 256 8.4 / 8.9, T = 512 13.1 / 12.1.
+        if (p.d > 2 * kTile) return exp2(small ? ((p.d & (p.d - 1)) == 0 ? 25 : 24) : 23);
         // d = 4096, b = 128, T = 16 3.8 / 4.7, T = 1024 5.1 / 5.2, T = 2048 7.1 / 6.5; b = 16, T = 2048 5.8 / 6.1, T = 8192
         // 17.8 / 16.2; d = 3072, b = 128, T = 32768 74 / 44; d = 2880, b = 32, T = 5832 12.2 / 10.5, T = 32768 56.8 / 41.2
         return exp2(small ? 23 : 22);
     }
+    // fp32 output never has a prepared form.  b = 32: d = 3072, T = 2730 11.7 / 13.8, T = 5461 22.1 / 21.3; d = 8192, T = 2048
+    // 21.0 / 22.0, T = 4096 37.1 / 37.1; d = 14336, T = 585 13.6 / 19.0, T = 2340 38.1 / 38.4, T = 4681 66.3 / 65.9; d = 28672,
+    // T = 2340 69.9 / 73.0.  b = 2048: d = 8192, T = 2048 23.6 / 24.7; d = 14336, T = 585 19.7 / 21.2, T = 1170 27.3 / 25.6.
+    if (out_kind == OUT_F32 && p.d != kTile)
+        return exp2(one_tile ? 24 : large ? (two_tiles ? 25 : 24) : two_tiles ? 25 : p.d <= 4 * kTile ? 26 : 27);
     // T = 512, b = 64 5.3 / 5.7, T = 1024 7.0 / 5.8; b = 4096, T = 16 6.5 / 6.3
     if (p.d == kTile) return large ? 0 : exp2(21) + 1;
     // No prepared form: T = 4096, d = 3072, b = 16 10.9 / 12.3, T = 8192 18.5 / 16.9; b = 128, T = 2048 9.7 / 10.0, T = 4096
@@ -1395,15 +1406,18 @@ static int64_t mfma_line(const ApplyParams& p, int out_kind) {
     if (ragged) return exp2((small ? 24 : 23) + (two_tiles ? 2 : p.d <= 4 * kTile ? 1 : 0));
     // butterflies of workgroups of 1024 lanes: T = 16, d = 28672 11.8 / 9.1
     if (p.d > 4 * kTile) return 0;
-    // d = 6144, b = 2048, T = 256 6.0 / 7.7, T = 512 8.0 / 7.7; d = 16384, b = 4096 9.2 / 9.0
-    if (large) return two_tiles ? exp2(21) + 1 : 0;
+    // Prepared: d = 6144, b = 2048, T = 256 6.4 / 8.0, T = 512 8.4 / 8.1; d = 16384, b = 4096, T = 2 8.8 / 9.0, T = 256 9.8 / 9.8, T = 512
+    // 15.5 / 12.5; d = 12288, b = 1024, T = 256 7.9 / 8.9, T = 512 12.4 / 11.1 (as given 12.0 / 16.3, T = 256 7.9 / 12.2)
+    if (large) return exp2(two_tiles ? 21 : 22) + 1;
     // Two tiles, prepared / as given.  b = 128: d = 8192, T = 513 8.2 / 8.4 / 11.9, T = 1025 10.9 / 10.3 / 13.6.  b = 32: d = 8192,
     // T = 1025 9.9 / 9.8 / 13.4, T = 2049 14.6 / 13.9 / 16.4; d = 7168, T = 2341 14.6 / 13.1 / 15.5; narrower rows leave
     // more of the second tile empty, d = 6144, T = 2731 13.8 / 14.5 / 16.8, T = 4096 17.7 / 17.7 / 20.0, d = 5120,
     // T = 3277 14.3 / 14.4 / 17.7, T = 4916 19.4 / 19.2 / 21.8.
     if (two_tiles) return small ? (p.d <= 6144 ? 3 * exp2(23) : exp2(24)) : exp2(23);
-    // d = 14336, b = 128, T = 256 7.6 / 8.6, T = 1024 17.5 / 13.7
-    return exp2(22);
+    // Three and four tiles, prepared / as given.  b = 32: d = 12288, T = 512 9.6 / 10.0 / 14.5, T = 1024 13.7 / 14.0 / 17.3, T = 1536
+    // 17.3 / 16.4; d = 16384, T = 1024 15.5 / 15.8 / 18.9.  b = 128: d = 14336, T = 256 7.3 / 8.9 / 11.3, T = 512 11.3 / 11.0 /
+    // 15.6, T = 1024 16.8 / 15.5 / 19.1; b = 512, T = 512 12.2 / 11.9.
+    return exp2(small ? 24 : 23);
 }
 
 bool mfma_preferred(const ApplyParams& p, int out_kind) { return p.T * (int64_t)p.d >= mfma_line(p, out_kind); }
