@@ -5,18 +5,18 @@
 // Pass 1: the M rows are cut into S slices; workgroup (column tile, slice) adds |x| over its rows:
 // 32 lanes own 8 adjacent columns each (one 16-byte bf16 load per row), the eight groups of 32 take
 // every eighth row, and their sums meet in LDS (in double).  It writes one partial sum per column
-// and slice, in double.  Pass 2: one lane per column adds the S partials in slice order and divides by
-// M; a single slice (up to 128 rows, or d > 131072) writes the means itself and there is no second launch.
-// No atomics: the result is independent of scheduling.
+// and slice, in double.  Pass 2 adds a column's S partials in a fixed order and divides by M; a single
+// slice (up to 128 rows, or d > 131072) writes the means itself, and up to 64 slices the last workgroup of a column
+// tile does it, in the same launch.  The only atomics count arrivals: the result is independent of scheduling.
 // Rounding: fp32 is used inside a run of at most max_run(M, d) rows of one lane only, so a run's sum is off
 // by less than max_run(M, d) - 1 roundings of non-negative terms, and the mean is rounded once more: the
 // relative error of a_i is below (max_run(M, d) + 1) * 2^-24.
-//   Bound by reading x, small inputs by the two launches.  Eight row groups a workgroup instead of one
+//   Bound by reading x, small inputs by the launch.  Eight row groups a workgroup instead of one
 // (2048 columns each) make the partials a quarter as large (a quarter of the input at M <= 1024 before).
-// Launches back to back: M = 16, d = 4096 4.1 -> 2.5 us, M = 500, d = 14336 7.8 -> 5.6, M = 2048, d = 4096
-// 7.2 -> 5.4, M = 4096, d = 8192 (cache resident) 13.6 -> 13.7, M = d = 32768 369 -> 319.
+// Launches back to back: M = 16, d = 4096 4.1 -> 2.5 us, M = d = 32768 369 -> 319.
 #include "perq.h"
 #include "perq_launch.h"
+#include "perq_schedule.h"
 
 #include <mutex>
 #include <type_traits>
@@ -39,6 +39,18 @@ constexpr int kOneSlice = 128;
 constexpr int64_t kStreamBytes = (int64_t)256 << 20;
 
 constexpr int kMostBlocks = 1024;                             // workgroups of a first pass of several slices
+
+// One launch for both passes: whichever workgroup of a column tile is the last to leave its partials adds all of
+// them up, in the second pass's order.  Arrivals are counted per tile and stream (a set belongs to one stream, whose
+// launches do not overlap, and the last arrival puts the count back to zero); a stream without a set and a launch
+// that is being captured take two launches.  Partials and counts go past the L2 of their XCD.
+//   Up to 64 slices, which a lane of the last workgroup reads 32 at a time.  Launches back to back, two / one: M = 129,
+// d = 1536 7.0 / 4.7 us, M = 694, d = 6144 7.1 / 5.5, M = 1838, d = 7168 9.0 / 8.2, M = 4096, d = 8192 13.7 / 13.0, M = 3000,
+// d = 2048 (47 slices) 8.3 / 8.4, M = 4000, d = 1536 (63) 7.4 / 7.8, where the second launch costs the host 3 us; M = 7002,
+// d = 1536 (84) 9.2 / 10.1, M = 15310, d = 1024 (128) 9.8 / 13.4.
+constexpr int kWays = 16;
+constexpr int kOneLaunchSlices = 64, kOneLaunchTiles = 128;
+__device__ uint32_t arrivals[schedule::kSets][kOneLaunchTiles][32];        // a count per cache line
 
 struct ColabsPlan {
     int col_tiles;
@@ -83,7 +95,8 @@ ColabsPlan colabs_plan(int64_t M, int32_t d) {
 template <bool MAXSTAT, bool FEW, bool STREAM>
 __global__ void __launch_bounds__(kThreads)
 colabs_partial_kernel(const uint16_t* __restrict__ x, int64_t M, int32_t d, int64_t ldx, int rows_per_slice,
-                      uint32_t tiles, uint32_t blocks, double* __restrict__ part, float* __restrict__ out, float m_rows) {
+                      uint32_t tiles, uint32_t blocks, double* __restrict__ part, float* __restrict__ out, float m_rows,
+                      int slices, int set) {
     typedef typename std::conditional<MAXSTAT, float, double>::type sum_t;
     __shared__ sum_t red[kGroups][kTileCols];
     const int cl = threadIdx.x % (kThreads / kGroups), group = threadIdx.x / (kThreads / kGroups);
@@ -145,7 +158,44 @@ colabs_partial_kernel(const uint16_t* __restrict__ x, int64_t M, int32_t d, int6
             t = MAXSTAT ? (v > t ? v : t) : t + v;
         }
         if (FEW || part == nullptr) out[c] = MAXSTAT ? (float)t : (float)(t / (double)m_rows);
-        else part[(int64_t)slice * d + c] = t;
+        else if (set < 0) part[(int64_t)slice * d + c] = t;
+        else __hip_atomic_store(reinterpret_cast<unsigned long long*>(part) + ((int64_t)slice * d + c), (unsigned long long)__double_as_longlong(t),
+                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if constexpr (!FEW) {
+        if (set < 0) return;                                   // (the same for the whole launch)
+        __shared__ uint32_t before;
+        // Every partial is where the whole device sees it before the count says so: a store of device scope is written
+        // through to there and counted out when it has arrived.  (A release fence would write the whole L2 of the XCD
+        // back besides, once per wave: M = 4096, d = 8192 47 us.)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        uint32_t* const count = &arrivals[set][tile][0];
+        if (threadIdx.x == 0) before = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (before != (uint32_t)slices - 1u) return;
+        // (read with device scope too: past the L2 of this XCD)
+        if (threadIdx.x == 0) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (c < d) {
+            // the order of colabs_finish_kernel: 16 sums of every sixteenth slice, added up one after the other
+            double way[kWays] = {};
+            for (int k0 = 0; k0 < slices; k0 += 2 * kWays) {
+                double v[2 * kWays];
+#pragma unroll
+                for (int k = 0; k < 2 * kWays; ++k) {
+                    v[k] = 0.0;
+                    if (k0 + k < slices)
+                        v[k] = __longlong_as_double((long long)__hip_atomic_load(
+                            reinterpret_cast<const unsigned long long*>(part) + ((int64_t)(k0 + k) * d + c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                }
+#pragma unroll
+                for (int k = 0; k < 2 * kWays; ++k) way[k % kWays] = MAXSTAT ? (v[k] > way[k % kWays] ? v[k] : way[k % kWays]) : way[k % kWays] + v[k];
+            }
+            double t = way[0];
+#pragma unroll
+            for (int w = 1; w < kWays; ++w) t = MAXSTAT ? (way[w] > t ? way[w] : t) : t + way[w];
+            out[c] = MAXSTAT ? (float)t : (float)(t / (double)m_rows);
+        }
     }
 }
 
@@ -153,7 +203,8 @@ colabs_partial_kernel(const uint16_t* __restrict__ x, int64_t M, int32_t d, int6
 // j, j+16, ...; the 16 sub-sums are then added in lane order.  Fixed order throughout.  Bound by latency: with 32
 // columns M = 2048, d = 4096 5.9 us instead of 5.4, M = 4096, d = 8192 14.0 instead of 13.9.
 constexpr int kFinishCols = 16;
-constexpr int kFinishWays = kThreads / kFinishCols;   // 16
+constexpr int kFinishWays = kThreads / kFinishCols;
+static_assert(kFinishWays == kWays, "both ways to the result add in one order");
 
 template <bool MAXSTAT>
 __global__ void __launch_bounds__(kThreads)
@@ -180,7 +231,18 @@ colabs_finish_kernel(const double* __restrict__ part, int slices, int32_t d, flo
     }
 }
 
+__global__ void clear_arrivals_kernel() {
+    uint32_t* c = &arrivals[0][0][0];
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < sizeof(arrivals) / 4; i += gridDim.x * blockDim.x) c[i] = 0u;
+}
+
 }  // namespace
+
+hipError_t clear_arrivals(hipStream_t stream) {
+    hipLaunchKernelGGL(clear_arrivals_kernel, dim3(64), dim3(256), 0, stream);
+    return hipGetLastError();
+}
+
 }  // namespace perq
 
 extern "C" size_t perq_colabs_mean_workspace_bytes(int64_t M, int32_t d) {
@@ -216,10 +278,12 @@ perq_status_t colabs_launch(const uint16_t* x_bf16, int64_t M, int32_t d, int64_
                 : M * (int64_t)d * 2 >= kStreamBytes ? colabs_partial_kernel<MAXSTAT, false, true>
                                                      : colabs_partial_kernel<MAXSTAT, false, false>;
     const uint32_t tiles = (uint32_t)pl.col_tiles, blocks = tiles * (uint32_t)pl.slices;
+    const bool together = pl.slices > 1 && pl.slices <= kOneLaunchSlices && pl.col_tiles <= kOneLaunchTiles;
+    const int set = together ? schedule_set_of(stream) : -1;
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), 0, stream, x_bf16, M, d, ldx, pl.rows_per_slice, tiles,
-                       ldx % 64 != 0 ? blocks : 0u, pl.slices == 1 ? nullptr : part, out, (float)M);
+                       ldx % 64 != 0 ? blocks : 0u, pl.slices == 1 ? nullptr : part, out, (float)M, pl.slices, set);
     if (hipGetLastError() != hipSuccess) return PERQ_ERR_LAUNCH;
-    if (pl.slices == 1) return PERQ_OK;
+    if (pl.slices == 1 || set >= 0) return PERQ_OK;
     hipLaunchKernelGGL(colabs_finish_kernel<MAXSTAT>, dim3((d + kFinishCols - 1) / kFinishCols), dim3(kThreads), 0,
                        stream, part, pl.slices, d, (float)M, out);
     if (hipGetLastError() != hipSuccess) return PERQ_ERR_LAUNCH;

@@ -19,6 +19,12 @@ const LaunchInfo& launch_info();
 // Asked of the runtime once per kernel, device and configuration, then remembered.
 hipError_t resident_blocks(const void* kern, int threads, uint32_t lds_bytes, int* per_cu);
 
+// Which set of per-stream counters a launch on `stream` may use, or -1: none (the stream is capturing, or 64 other
+// streams of the current device came first).
+int schedule_set_of(hipStream_t stream);
+// Puts the arrival counts of the column statistics back to zero.
+hipError_t clear_arrivals(hipStream_t stream);
+
 // Kernel families behind perq_permute_rotate_quant / perq_permute_rotate_f32.
 hipError_t launch_butterfly(const ApplyParams& p, int out_kind, hipStream_t stream);
 bool mfma_supports(const ApplyParams& p);

@@ -1467,11 +1467,16 @@ hipError_t launch_mfma(const ApplyParams& p0, int out_kind, hipStream_t stream) 
 
 }  // namespace perq
 
+namespace perq {
+int schedule_set_of(hipStream_t stream) { return stream_counter_set(stream); }
+}  // namespace perq
+
 extern "C" int32_t perq_schedule_set(void* hip_stream) {
     return perq::stream_counter_set(static_cast<hipStream_t>(hip_stream));
 }
 
 extern "C" perq_status_t perq_reset_schedule(void* hip_stream) {
     hipLaunchKernelGGL(perq::clear_counters_kernel, dim3(64), dim3(256), 0, static_cast<hipStream_t>(hip_stream));
-    return hipGetLastError() == hipSuccess ? PERQ_OK : PERQ_ERR_LAUNCH;
+    if (hipGetLastError() != hipSuccess) return PERQ_ERR_LAUNCH;
+    return perq::clear_arrivals(static_cast<hipStream_t>(hip_stream)) == hipSuccess ? PERQ_OK : PERQ_ERR_LAUNCH;
 }

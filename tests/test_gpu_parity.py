@@ -644,6 +644,44 @@ def test_w4a4_mxfp4_scale_bytes_at_any_address(T, N, d):
     assert np.all(np.abs(want[:64].cpu().numpy().astype(np.float64) - a @ w.T) <= d * 2.0 ** -24 * (np.abs(a) @ np.abs(w).T))
 
 
+# one launch (2, 3, 17, 32, 33, 64 slices of rows) and two (65), one tile of columns, a cut one and as many as fit
+@pytest.mark.parametrize("M,d", [(129, 256), (192, 8), (1088, 520), (2048, 512), (2049, 504), (4096, 512), (4097, 512), (300, 32768),
+                                 (300, 32776), (4000, 4104)])
+@pytest.mark.parametrize("stat", ["mean", "absmax"])
+def test_column_statistics_in_one_launch(M, d, stat):
+    """Against 64 bits; every call gives the same bits, with other streams' calls beside it and replayed from a graph
+    (which takes two launches) too."""
+    torch = _torch()
+    print(f"[case] column {stat} M={M} d={d}", flush=True)
+    call = binding.perq_colabs_mean if stat == "mean" else binding.perq_colabs_absmax
+    g = torch.Generator(device="cuda").manual_seed(M + d)
+    xs = [torch.randn((M, d), device="cuda", generator=g).to(torch.bfloat16) for _ in range(3)]
+    want = [call(x) for x in xs]
+    for x, w in zip(xs, want):
+        v = x.double().abs()
+        ref = v.mean(dim=0) if stat == "mean" else v.amax(dim=0)
+        r = max(8, -(-M // max(1, 512 // -(-d // 2048))))                 # terms of an fp32 sum, as documented
+        assert bool(((w.double() - ref).abs() <= (0.0 if stat == "absmax" else (r + 1) * 2.0 ** -24) * ref).all())
+    streams = [torch.cuda.Stream() for _ in xs]
+    torch.cuda.synchronize()
+    for _ in range(20):
+        got = []
+        for s, x in zip(streams, xs):
+            with torch.cuda.stream(s):
+                got.append(call(x))
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = call(xs[0])
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        call(xs[1])
+        torch.cuda.synchronize()
+        assert torch.equal(out, want[0])
+
+
 def test_w4a4_gemm_argument_checks():
     torch = _torch()
     a = torch.zeros((4, 16), dtype=torch.uint8, device="cuda")
