@@ -30,6 +30,23 @@ namespace {
 // one per instruction) then touch 8 distinct 16-byte bank groups per 8 lanes.
 __device__ __forceinline__ uint32_t granule_slot(uint32_t g) { return g ^ ((g >> 3) & 3u); }
 
+// What a launch hands over, 88 bytes.  A launch with up to 96 bytes of arguments takes 2.9 us of the host, one with 128
+// 3.6 and with 512 4.3, and the kernels here are over in 4 - 5 us for a few rows: ApplyParams, the geometry and the hidden
+// arguments that gridDim brings were 408 bytes (T = 1, d = 4096, P = I 4.0 -> 2.8 us of the host for a call of the library, 4.2 -> 3.4 from launch to launch).
+struct BflyArgs {
+    const uint16_t* x;
+    const int32_t* perm;
+    uint8_t* codes;
+    void* out;           // scales, or the fp32 or statistics output
+    int64_t T, ldx;
+    double inv;          // what a row's extent is multiplied by to give its step
+    int32_t d, b;
+    float rsqrt_b, fp4_qmax;
+    int32_t rows;
+    uint32_t red_off, grid;
+};
+static_assert(sizeof(BflyArgs) <= 96, "");
+
 struct BflyGeom {
     int nt;              // lanes per row = d / 32
     int rows;            // rows per workgroup iteration
@@ -44,8 +61,24 @@ struct BflyGeom {
 //   WAVES: b >= 4096, stages across waves through LDS.  In a kernel of their own: the others have 20 registers less.
 template <int OUT, bool PERM, int MAXT, bool WAVES, bool QUADS = false>
 __global__ void __launch_bounds__(MAXT)
-butterfly_kernel(ApplyParams p, BflyGeom g) {
+butterfly_kernel(BflyArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];
+    ApplyParams p;
+    p.x = a.x;
+    p.perm = a.perm;
+    p.codes = a.codes;
+    p.scales = a.out;
+    p.y = static_cast<float*>(a.out);
+    p.T = a.T;
+    p.ldx = a.ldx;
+    p.d = a.d;
+    p.b = a.b;
+    p.rsqrt_b = a.rsqrt_b;
+    p.fp4_qmax = a.fp4_qmax;
+    p.inv_7sqrt_b = p.inv_15sqrt_b = p.inv_fp4sqrt_b = a.inv;
+    p.half_log2b = __builtin_ctz(a.b) >> 1;
+    p.odd_norm = (__builtin_ctz(a.b) & 1) != 0 ? 0x1.6a09e6p-1f : 1.0f;      // fl32(1/sqrt(2))
+    const BflyGeom g = {a.d >> 5, a.rows, ((a.d >> 5) + 63) >> 6, (uint32_t)a.d * 2u, a.red_off};
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int r = tid / g.nt < g.rows ? tid / g.nt : g.rows - 1;   // row slot of this thread
@@ -102,7 +135,7 @@ butterfly_kernel(ApplyParams p, BflyGeom g) {
         if (blockIdx.x < ngroups) load_group(blockIdx.x, stage);
     }
 
-    for (int64_t grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
+    for (int64_t grp = blockIdx.x; grp < ngroups; grp += a.grid) {
         const int64_t row = grp * g.rows + r;
         const bool live = active && row < p.T;
 
@@ -113,7 +146,7 @@ butterfly_kernel(ApplyParams p, BflyGeom g) {
                 *reinterpret_cast<uint4*>(my_row + (granule_slot((uint32_t)(t + k * g.nt)) << 4)) = stage[k];
         }
         __syncthreads();
-        if (grp + gridDim.x < ngroups) load_group(grp + gridDim.x, stage);   // prefetch next rows
+        if (grp + a.grid < ngroups) load_group(grp + a.grid, stage);   // prefetch next rows
 
         // ---- this lane's 32 permuted elements -> fp32 --------------------------------------
         // (lanes past the end of the row read slot 0 and are never stored)
@@ -396,7 +429,10 @@ hipError_t launch_butterfly_out(const ApplyParams& p, hipStream_t stream) {
     const int64_t ngroups = (p.T + g.rows - 1) / g.rows;
     int64_t grid = (int64_t)launch_info().num_cus * per_cu;
     if (grid > ngroups) grid = ngroups;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((unsigned)threads), lds_bytes, stream, p, g);
+    const double inv = OUT == OUT_INT4_ASYM ? p.inv_15sqrt_b : OUT == OUT_FP4_TOKEN ? p.inv_fp4sqrt_b : p.inv_7sqrt_b;
+    const BflyArgs args = {p.x, p.perm, p.codes, OUT == OUT_F32 || OUT == OUT_DIAG ? p.y : p.scales, p.T, p.ldx, inv, p.d, p.b,
+                           p.rsqrt_b, p.fp4_qmax, g.rows, g.red_off, (uint32_t)grid};
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((unsigned)threads), lds_bytes, stream, args);
     return hipGetLastError();
 }
 
