@@ -14,7 +14,7 @@
 // processes.  With one lane per 32 outputs an MXFP4 group is lane-local and each lane stores
 // 16 contiguous bytes of codes.
 //
-// Rows narrower than 8192 are packed several to a 256-thread workgroup when nt is a power of
+// Rows narrower than 8192 are packed several to a workgroup of up to 256 threads when nt is a power of
 // two; otherwise a workgroup of ceil(nt/64) waves handles one row at a time.
 #include "perq_device.h"
 #include "perq_launch.h"
@@ -395,7 +395,14 @@ hipError_t launch_butterfly_out(const ApplyParams& p, hipStream_t stream) {
     int threads;
     if (pow2 && g.nt <= 256) {
         g.rows = 256 / g.nt;
-        threads = 256;
+        // Few rows with a permutation: no more to a workgroup than fill a wave, until every CU has a workgroup.  The waves of
+        // one share an address unit, which takes a lane's entries of the permutation line by line (d = 4096: T = 16 5.2 -> 4.5 us,
+        // T = 256 5.4 -> 4.8; d = 1024, T = 300 5.5 -> 4.5; P = I has nothing of the kind, T = 400 4.4 -> 4.8).
+        const int least = g.nt >= 64 ? 1 : 64 / g.nt;
+        if (p.perm != nullptr) {
+            while (g.rows > least && (p.T + g.rows - 1) / g.rows < launch_info().num_cus) g.rows /= 2;
+        }
+        threads = g.rows * g.nt;
     } else {
         g.rows = 1;
         threads = ((g.nt + 63) / 64) * 64;

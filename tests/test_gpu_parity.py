@@ -644,6 +644,26 @@ def test_w4a4_mxfp4_scale_bytes_at_any_address(T, N, d):
     assert np.all(np.abs(want[:64].cpu().numpy().astype(np.float64) - a @ w.T) <= d * 2.0 ** -24 * (np.abs(a) @ np.abs(w).T))
 
 
+@pytest.mark.parametrize("d,b", [(64, 16), (512, 32), (1024, 512), (2048, 64), (4096, 128), (4096, 4096)])
+@pytest.mark.parametrize("perm", [False, True])
+def test_butterflies_few_rows_to_a_workgroup(d, b, perm):
+    """How many rows a workgroup of the butterflies takes follows from T; a row's bits do not."""
+    torch = _torch()
+    g = torch.Generator(device="cuda").manual_seed(d + b)
+    x = torch.randn((3000, d), device="cuda", generator=g).to(torch.bfloat16)
+    pt = torch.randperm(d, device="cuda", generator=g).to(torch.int32) if perm else None
+    call = lambda v, fmt: binding.perq_permute_rotate_quant(v, pt, b, fmt, algo="butterfly")
+    want = {fmt: call(x, fmt) for fmt in ("int4", "mxfp4", "int4_asym")}
+    y, st = binding.perq_permute_rotate_f32(x, pt, b, algo="butterfly"), binding.perq_block_diagnostics(x, pt, b)
+    for T in (1, 2, 3, 127, 255, 256, 257, 511, 513, 1021, 2049):
+        print(f"[case] butterflies T={T} d={d} b={b}", flush=True)
+        for fmt, (codes, scales) in want.items():
+            c, s = call(x[:T], fmt)
+            assert torch.equal(c, codes[:T]) and torch.equal(s, scales[:T])
+        assert torch.equal(binding.perq_permute_rotate_f32(x[:T], pt, b, algo="butterfly"), y[:T])
+        assert torch.equal(binding.perq_block_diagnostics(x[:T], pt, b), st[:T])
+
+
 # one launch (2, 3, 17, 32, 33, 64 slices of rows) and two (65), one tile of columns, a cut one and as many as fit
 @pytest.mark.parametrize("M,d", [(129, 256), (192, 8), (1088, 520), (2048, 512), (2049, 504), (4096, 512), (4097, 512), (300, 32768),
                                  (300, 32776), (4000, 4104)])
