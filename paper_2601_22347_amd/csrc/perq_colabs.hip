@@ -44,12 +44,14 @@ constexpr int kMostBlocks = 1024;                             // workgroups of a
 // them up, in the second pass's order.  Arrivals are counted per tile and stream (a set belongs to one stream, whose
 // launches do not overlap, and the last arrival puts the count back to zero); a stream without a set and a launch
 // that is being captured take two launches.  Partials and counts go past the L2 of their XCD.
-//   Up to 64 slices, which a lane of the last workgroup reads 32 at a time.  Launches back to back, two / one: M = 129,
+//   Up to 32 slices, which a lane of the last workgroup reads all at once, and up to 64 of a small input, whose second launch
+// takes the host longer than the device.  Launches back to back, two / one: M = 129,
 // d = 1536 7.0 / 4.7 us, M = 694, d = 6144 7.1 / 5.5, M = 1838, d = 7168 9.0 / 8.2, M = 4096, d = 8192 13.7 / 13.0, M = 3000,
 // d = 2048 (47 slices) 8.3 / 8.4, M = 4000, d = 1536 (63) 7.4 / 7.8, where the second launch costs the host 3 us; M = 7002,
-// d = 1536 (84) 9.2 / 10.1, M = 15310, d = 1024 (128) 9.8 / 13.4.
+// d = 1536 (84) 9.2 / 10.1, M = 15310, d = 1024 (128) 9.8 / 13.4; M = 6572, d = 3584 (36) 12.0 / 13.3.
 constexpr int kWays = 16;
 constexpr int kOneLaunchSlices = 64, kOneLaunchTiles = 128;
+constexpr int64_t kOneLaunchSmall = (int64_t)1 << 23;         // elements
 __device__ uint32_t arrivals[schedule::kSets][kOneLaunchTiles][32];        // a count per cache line
 
 struct ColabsPlan {
@@ -278,7 +280,8 @@ perq_status_t colabs_launch(const uint16_t* x_bf16, int64_t M, int32_t d, int64_
                 : M * (int64_t)d * 2 >= kStreamBytes ? colabs_partial_kernel<MAXSTAT, false, true>
                                                      : colabs_partial_kernel<MAXSTAT, false, false>;
     const uint32_t tiles = (uint32_t)pl.col_tiles, blocks = tiles * (uint32_t)pl.slices;
-    const bool together = pl.slices > 1 && pl.slices <= kOneLaunchSlices && pl.col_tiles <= kOneLaunchTiles;
+    const bool together = pl.slices > 1 && pl.col_tiles <= kOneLaunchTiles &&
+                          (pl.slices <= 2 * kWays || (pl.slices <= kOneLaunchSlices && M * (int64_t)d <= kOneLaunchSmall));
     const int set = together ? schedule_set_of(stream) : -1;
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), 0, stream, x_bf16, M, d, ldx, pl.rows_per_slice, tiles,
                        ldx % 64 != 0 ? blocks : 0u, pl.slices == 1 ? nullptr : part, out, (float)M, pl.slices, set);

@@ -4,9 +4,10 @@
 // Measured, T = 2048, N = d = 4096, INT4: 29.8 us; T = N = 2048, d = 8192, MXFP4: 23.9 us.  What bounds both is what the
 // matrix unit draws: with random codes, registers only and nothing else running, it delivers 3.6 POP/s (int8) and 6.0
 // PFLOP/s (fp4) on the whole chip, with zeros 4.7 and 9.4, and one workgroup alone runs its stages 1.4 times as fast
-// as 256 do.  LDS is next: a 128 x 128 stage of MXFP4 moves 96 KiB in and out of it, 0.34 us at 128 bytes a clock, where
-// the products take 0.36; loads from L2 alone 0.31.  Products of 16 x 16 (8 - 12 % more from the unit alone) gave
-// nothing in INT4 and cost MXFP4 18 %: eight scale reads from LDS a stage instead of four.
+// as 256 do.  Past that, loads from L2: 32 KiB, a 128 x 128 stage of MXFP4, take a CU 0.31 us alone, its products 0.36.  LDS
+// is not a bound since its reads have no bank conflicts (INT4 4.4 -> 2.3 M cycles, profiles/products_w4a4.txt).  Products
+// of 16 x 16 (8 - 12 % more from the unit alone) gave nothing in INT4 and cost MXFP4 18 %: eight scale reads from LDS a stage
+// instead of four.
 //
 // With P and the block rotation merged into the weights (Remark "Merging Permutations", Section 4:
 // W~ = R~^T P^T W), the product of the two quantized operands stands for X W.
@@ -632,6 +633,9 @@ gemm_short_kernel(GemmParams p) {
     }
 }
 
+// Rows of the output begin and end with a 128-byte line.
+bool whole_lines(const GemmParams& p) { return p.ldo % 32 == 0 && (reinterpret_cast<uintptr_t>(p.out) & 127u) == 0; }
+
 template <bool MX, int MT, int NT, int WM, int WN, int NBUF, int WGS, bool DWORDS>
 hipError_t launch_tile_as(GemmParams p, hipStream_t stream) {
     constexpr uint32_t lds_bytes = (uint32_t)(32 * MT * WM + 32 * NT * WN) * (kStageBytes * NBUF + (MX ? 0u : 4u)) +
@@ -643,7 +647,7 @@ hipError_t launch_tile_as(GemmParams p, hipStream_t stream) {
     // what stays in L2 is written back at the end of the launch.  INT4 / MXFP4 (2048, 4096, 2048) 22.0 / 20.9 -> 18.8 / 15.2,
     // (2048, 14336, 4096) 112 / 111 -> 103 / 84, (2048, 2048, 1024) 9.5 / 8.8 -> 8.3 / 7.6.  Lines that two rows share:
     // (3000, 3500, 1024) 20.0 / 19.3 -> 22.9 / 22.2, so those keep the plain store.
-    p.stream_out = p.ldo % 32 == 0 && (reinterpret_cast<uintptr_t>(p.out) & 127u) == 0;
+    p.stream_out = whole_lines(p);
     auto kern = gemm_tile_kernel<MX, MT, NT, WM, WN, NBUF, WGS, DWORDS>;
     int per_cu = 0;      // (raises the kernel's limit of dynamic LDS)
     const hipError_t e = resident_blocks(reinterpret_cast<const void*>(kern), 64 * WM * WN, lds_bytes, &per_cu);
@@ -726,7 +730,9 @@ hipError_t launch_few(GemmParams p, hipStream_t stream) {
 //   more than 256 tiles of 128 x 128: 128 x 256, a sixth less to load per product.
 //     MXFP4: (2048, 4096), one round of them for two of 128 x 128, d = 1024 11.2 against 14.1, d = 2048 15.2 against 18.8,
 //     d = 4096 23.5 against 30; (4096, 6144, 2048) 43 against 55, (2048, 14336, 4096) 84 against 88, (4096, 4096, 2048)
-//     36.6 against 34.9; rounds that are not full: (3000, 3500, 2880) 38.5 against 39.6, d = 8192 69 against 67.
+//     36.6 against 34.9; rounds that are not full: (3000, 3500, 2880) 38.5 against 39.6, d = 8192 69 against 67.  Where the
+//     output is not whole lines, from d = 2880 on and up to 512, (2177, 2177, 512) 9.4 against 12.2: (2048, 4000, 1024) 18.2 against 14.0, (3000, 3500, 1024) 19 - 24 against
+//     19.7 (one workgroup a CU stores at the end of its tile with nothing beside it).
 //     INT4, which has two workgroups of 128 x 128 a CU and loads less per product: only where some CUs have one of those
 //     and some two.  (2048, 2560, 4096) 23.4 against 25.3, (2177, 2177, 8192) 42.7 against 45.6, (2048, 3072, 8192) 43.7
 //     against 46.1, d = 4096 25.2 against 25.5, d = 2048 16.1 against 15.6; (2048, 4096, 4096) 31.0 against 29.8,
@@ -742,7 +748,7 @@ hipError_t launch_gemm(const GemmParams& p, hipStream_t stream) {
     if (small <= 256 || one_row || (small <= 512 && (!MX || p.d % 128 != 0)) || (!MX && small <= 900 && p.d >= 2048))
         return small > 512 && p.d < 4096 ? launch_few<MX, 4>(p, stream) : launch_few<MX, 8>(p, stream);
     if (tiles(128, 128) <= 128) return launch_tile<MX, 1, 1, 2, 2, 4, 2>(p, stream);
-    if (tiles(128, 128) > 256 && (MX || (tiles(128, 128) <= 384 && p.d >= 2880))) return launch_tile<MX, 2, 2, 2, 4, 2, 1>(p, stream);
+    if (tiles(128, 128) > 256 && (MX ? p.d >= 2880 || p.d <= 512 || whole_lines(p) : tiles(128, 128) <= 384 && p.d >= 2880)) return launch_tile<MX, 2, 2, 2, 4, 2, 1>(p, stream);
     if constexpr (MX) return launch_tile<MX, 2, 2, 2, 2, 4, 1>(p, stream);
     else return launch_tile<MX, 2, 2, 2, 2, 2, 2>(p, stream);
 }

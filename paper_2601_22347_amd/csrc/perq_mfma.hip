@@ -1383,16 +1383,21 @@ static int64_t mfma_line(const ApplyParams& p, int out_kind) {
         // 10.2 / 10.6; d = 12288, T = 1365 12.4 / 12.2, T = 2730 19.7 / 18.3; d = 32768, T = 256 7.5 / 8.5, T = 1024 19.3 / 19.2.
         // b = 128: d = 16384, T = 256 5.5 / 6.4, T = 512 7.6 / 7.9, T = 1024 13.7 / 12.1; d = 14336, T = 512 7.5 / 7.5, T = 1024
         // 12.7 / 11.4; d = 32768, T = 256 8.4 / 8.9, T = 512 13.1 / 12.1.
-        if (p.d > 2 * kTile) return exp2(small ? ((p.d & (p.d - 1)) == 0 ? 25 : 24) : 23);
+        // A third tile that is filled for a small part: d = 9728, b = 32, T = 1530 10.3 / 9.8, b = 256, T = 791 10.2 / 9.0; d = 8704,
+        // b = 128, T = 512 6.3 / 6.7, T = 1024 11.5 / 9.5.  b = 512: d = 14336, T = 531 10.7 / 10.1.
+        if (p.d > 2 * kTile) {
+            if (small) return p.d < 3 * kTile ? 3 * exp2(22) : exp2((p.d & (p.d - 1)) == 0 ? 25 : 24);
+            return p.d < 3 * kTile || p.b >= 256 ? 3 * exp2(21) : exp2(23);
+        }
         // d = 4096, b = 128, T = 16 3.8 / 4.7, T = 1024 5.1 / 5.2, T = 2048 7.1 / 6.5; b = 16, T = 2048 5.8 / 6.1, T = 8192
         // 17.8 / 16.2; d = 3072, b = 128, T = 32768 74 / 44; d = 2880, b = 32, T = 5832 12.2 / 10.5, T = 32768 56.8 / 41.2
         return exp2(small ? 23 : 22);
     }
     // fp32 output never has a prepared form.  b = 32: d = 3072, T = 2730 11.7 / 13.8, T = 5461 22.1 / 21.3; d = 8192, T = 2048
     // 21.0 / 22.0, T = 4096 37.1 / 37.1; d = 14336, T = 585 13.6 / 19.0, T = 2340 38.1 / 38.4, T = 4681 66.3 / 65.9; d = 28672,
-    // T = 2340 69.9 / 73.0.  b = 2048: d = 8192, T = 2048 23.6 / 24.7; d = 14336, T = 585 19.7 / 21.2, T = 1170 27.3 / 25.6.
+    // T = 2340 69.9 / 73.0.  b = 2048: d = 8192, T = 2048 23.6 / 24.7; d = 14336, T = 585 19.7 / 21.2, T = 1170 27.3 / 25.6 (b = 4096: one stage more).
     if (out_kind == OUT_F32 && p.d != kTile)
-        return exp2(one_tile ? 24 : large ? (two_tiles ? 25 : 24) : two_tiles ? 25 : p.d <= 4 * kTile ? 26 : 27);
+        return exp2((one_tile ? 24 : large ? (two_tiles ? 25 : 24) : two_tiles ? 25 : p.d <= 4 * kTile ? 26 : 27) - (p.b == 4096 ? 1 : 0));
     // T = 512, b = 64 5.3 / 5.7, T = 1024 7.0 / 5.8; b = 4096, T = 16 6.5 / 6.3
     if (p.d == kTile) return large ? 0 : exp2(21) + 1;
     // No prepared form: T = 4096, d = 3072, b = 16 10.9 / 12.3, T = 8192 18.5 / 16.9; b = 128, T = 2048 9.7 / 10.0, T = 4096
@@ -1416,8 +1421,9 @@ static int64_t mfma_line(const ApplyParams& p, int out_kind) {
     if (two_tiles) return small ? (p.d <= 6144 ? 3 * exp2(23) : exp2(24)) : exp2(23);
     // Three and four tiles, prepared / as given.  b = 32: d = 12288, T = 512 9.6 / 10.0 / 14.5, T = 1024 13.7 / 14.0 / 17.3, T = 1536
     // 17.3 / 16.4; d = 16384, T = 1024 15.5 / 15.8 / 18.9.  b = 128: d = 14336, T = 256 7.3 / 8.9 / 11.3, T = 512 11.3 / 11.0 /
-    // 15.6, T = 1024 16.8 / 15.5 / 19.1; b = 512, T = 512 12.2 / 11.9.
-    return exp2(small ? 24 : 23);
+    // 15.6, T = 1024 16.8 / 15.5 / 19.1; b = 512, T = 512 12.2 / 11.9.  A third tile that is filled for a small part: d = 9728,
+    // b = 128, T = 559 13.6 / 11.5.
+    return exp2((small ? 24 : 23) - (p.d < 3 * kTile ? 1 : 0));
 }
 
 bool mfma_preferred(const ApplyParams& p, int out_kind) { return p.T * (int64_t)p.d >= mfma_line(p, out_kind); }
