@@ -3,11 +3,12 @@
 //
 // A call on a small batch is over on the device in 3 - 6 us, so the host's time is the call's time: 16 rows of
 // d = 4096 with a prepared permutation took 9.2 us through ctypes and torch.empty (launch 3.6, two allocations 2.8,
-// the rest conversions) and take 5.4 through here.  The module holds no state and no reference; the interpreter's lock is released around
-// the library call, as ctypes does.  Names and messages of errors are binding.py's.
+// the rest conversions) and take 5.4 through here.  The module holds no state and no reference; the interpreter's
+// lock is released around the library call, as ctypes does.  Names and messages of errors are binding.py's.
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <ATen/ops/empty.h>
+#include <c10/core/StreamGuard.h>
 #include <c10/hip/HIPStream.h>
 
 #include "perq.h"
@@ -46,13 +47,18 @@ void* address(PyObject* o) {
 }
 
 // The stream handed over, or the current one of the current device.
-void* stream_of(PyObject* o) {
-    if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
+struct Stream {
+    void* raw;
+    bool given;
+};
+
+Stream stream_of(PyObject* o) {
+    if (o == Py_None) return {c10::hip::getCurrentHIPStream().stream(), false};
     PyObject* const v = PyObject_GetAttrString(o, "cuda_stream");
     if (v == nullptr) throw PythonError();
     const auto p = static_cast<uintptr_t>(integer(v));
     Py_DECREF(v);
-    return reinterpret_cast<void*>(p);
+    return {reinterpret_cast<void*>(p), true};
 }
 
 struct Rows {
@@ -75,8 +81,21 @@ Rows rows_of(PyObject* o) {
     return {static_cast<const uint16_t*>(x.data_ptr()), x.size(0), x.size(1), x.stride(0), x.device()};
 }
 
-at::Tensor buffer(at::IntArrayRef shape, at::ScalarType type, at::Device device) {
-    return at::empty(shape, at::TensorOptions().dtype(type).device(device));
+// The buffers of a call belong to the stream that it runs on.  The allocator hands a block out again as soon as the
+// work queued so far on the block's own stream allows it, so one that the current stream owned could be written by the
+// call while earlier work of the current stream still used it, and (workspaces, which end with the call) be handed
+// out again while the call still ran.  Results are for the current stream too: freed later, they are not used again
+// before what it has queued by then is done.
+at::Tensor buffer(at::IntArrayRef shape, at::ScalarType type, at::Device device, const Stream& stream, bool is_result) {
+    const auto options = at::TensorOptions().dtype(type).device(device);
+    if (!stream.given || !device.is_cuda()) return at::empty(shape, options);
+    const auto current = c10::hip::getCurrentHIPStream(device.index());
+    if (current.stream() == stream.raw) return at::empty(shape, options);
+    const auto on_device = [&](c10::StreamId id) { return c10::Stream(c10::Stream::UNSAFE, device, id); };
+    const c10::StreamGuard guard(on_device(c10::hip::getStreamFromExternal(static_cast<hipStream_t>(stream.raw), device.index()).id()));
+    at::Tensor t = at::empty(shape, options);
+    if (is_result) t.record_stream(on_device(current.id()));
+    return t;
 }
 
 // The library call without the interpreter's lock.
@@ -97,8 +116,8 @@ PyObject* result(perq_status_t st, PyObject* out) {
 }
 
 // `given`, or a new buffer.
-PyObject* output(PyObject* given, at::IntArrayRef shape, at::ScalarType type, at::Device device) {
-    return given != Py_None ? Py_NewRef(given) : THPVariable_Wrap(buffer(shape, type, device));
+PyObject* output(PyObject* given, at::IntArrayRef shape, at::ScalarType type, at::Device device, const Stream& stream) {
+    return given != Py_None ? Py_NewRef(given) : THPVariable_Wrap(buffer(shape, type, device, stream, true));
 }
 
 struct Held {
@@ -142,11 +161,12 @@ PyObject* apply(PyObject*, PyObject* const* a, Py_ssize_t n) {
             PyErr_SetString(PyExc_ValueError, "a placement goes with algo='auto'");
             throw PythonError();
         }
+        const Stream stream = stream_of(a[6]);
         const bool own = a[4] == Py_None || a[5] == Py_None;
         const int64_t per_row = fmt == PERQ_FMT_MXFP4 ? r.d / 32 : 2, shape[2] = {r.T, per_row};
         const bool one = fmt != PERQ_FMT_MXFP4 && fmt != PERQ_FMT_INT4_ASYM_TOKEN;      // (asymmetric: step and zero point)
-        Held codes(output(own ? Py_None : a[4], {r.T, r.d / 2}, at::kByte, r.device));
-        Held scales(output(own ? Py_None : a[5], at::IntArrayRef(shape, one ? 1 : 2), fmt == PERQ_FMT_MXFP4 ? at::kByte : at::kFloat, r.device));
+        Held codes(output(own ? Py_None : a[4], {r.T, r.d / 2}, at::kByte, r.device, stream));
+        Held scales(output(own ? Py_None : a[5], at::IntArrayRef(shape, one ? 1 : 2), fmt == PERQ_FMT_MXFP4 ? at::kByte : at::kFloat, r.device, stream));
         if (a[8] != Py_None) {
             const at::Tensor& t = tensor(a[8], "placement");
             if (t.scalar_type() != at::kByte || !t.is_contiguous() || (size_t)t.numel() != perq_perm_prepared_bytes(d)) {
@@ -158,10 +178,9 @@ PyObject* apply(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const void* const placement = address(a[8]);
         auto* c = static_cast<uint8_t*>(address(codes.o));
         void* const s = address(scales.o);
-        void* const stream = stream_of(a[6]);
         const perq_status_t st = unlocked([&] {
-            return algo == PERQ_ALGO_AUTO ? perq_permute_rotate_quant_prepared(r.x, r.T, d, r.ldx, perm, placement, b, fmt, c, s, stream)
-                                          : perq_permute_rotate_quant_algo(r.x, r.T, d, r.ldx, perm, b, fmt, algo, c, s, stream);
+            return algo == PERQ_ALGO_AUTO ? perq_permute_rotate_quant_prepared(r.x, r.T, d, r.ldx, perm, placement, b, fmt, c, s, stream.raw)
+                                          : perq_permute_rotate_quant_algo(r.x, r.T, d, r.ldx, perm, b, fmt, algo, c, s, stream.raw);
         });
         if (st != PERQ_OK) return PyLong_FromLong(st);
         PyObject* const both = PyTuple_New(2);
@@ -178,11 +197,11 @@ PyObject* rotate_f32(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const Rows r = rows_of(a[0]);
         const int32_t b = (int32_t)integer(a[2]);
         const auto algo = (perq_algo_t)integer(a[5]);
-        Held y(output(a[3], {r.T, r.d}, at::kFloat, r.device));
+        const Stream stream = stream_of(a[4]);
+        Held y(output(a[3], {r.T, r.d}, at::kFloat, r.device, stream));
         const auto* perm = static_cast<const int32_t*>(address(a[1]));
         auto* out = static_cast<float*>(address(y.o));
-        void* const stream = stream_of(a[4]);
-        const perq_status_t st = unlocked([&] { return perq_permute_rotate_f32(r.x, r.T, (int32_t)r.d, r.ldx, perm, b, algo, out, stream); });
+        const perq_status_t st = unlocked([&] { return perq_permute_rotate_f32(r.x, r.T, (int32_t)r.d, r.ldx, perm, b, algo, out, stream.raw); });
         return result(st, y.release());
     });
 }
@@ -192,11 +211,11 @@ PyObject* diagnostics(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded(n, 5, [&]() -> PyObject* {
         const Rows r = rows_of(a[0]);
         const int32_t b = (int32_t)integer(a[2]);
-        Held out(output(a[3], {r.T, 4}, at::kFloat, r.device));
+        const Stream stream = stream_of(a[4]);
+        Held out(output(a[3], {r.T, 4}, at::kFloat, r.device, stream));
         const auto* perm = static_cast<const int32_t*>(address(a[1]));
         auto* o = static_cast<float*>(address(out.o));
-        void* const stream = stream_of(a[4]);
-        const perq_status_t st = unlocked([&] { return perq_block_diagnostics(r.x, r.T, (int32_t)r.d, r.ldx, perm, b, o, stream); });
+        const perq_status_t st = unlocked([&] { return perq_block_diagnostics(r.x, r.T, (int32_t)r.d, r.ldx, perm, b, o, stream.raw); });
         return result(st, out.release());
     });
 }
@@ -207,13 +226,13 @@ PyObject* column_statistic(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const Rows r = rows_of(a[0]);
         const int32_t d = (int32_t)r.d;
         const bool largest = a[3] == Py_True;
-        Held out(output(a[1], {r.d}, at::kFloat, r.device));
+        const Stream stream = stream_of(a[2]);
+        Held out(output(a[1], {r.d}, at::kFloat, r.device, stream));
         const size_t bytes = perq_colabs_mean_workspace_bytes(r.T, d);
-        const at::Tensor work = buffer({(int64_t)(bytes > 16 ? bytes : 16)}, at::kByte, r.device);
+        const at::Tensor work = buffer({(int64_t)(bytes > 16 ? bytes : 16)}, at::kByte, r.device, stream, false);
         auto* o = static_cast<float*>(address(out.o));
         void* const w = work.data_ptr();
-        void* const stream = stream_of(a[2]);
-        const perq_status_t st = unlocked([&] { return (largest ? perq_colabs_absmax : perq_colabs_mean)(r.x, r.T, d, r.ldx, o, w, bytes, stream); });
+        const perq_status_t st = unlocked([&] { return (largest ? perq_colabs_absmax : perq_colabs_mean)(r.x, r.T, d, r.ldx, o, w, bytes, stream.raw); });
         return result(st, out.release());
     });
 }
@@ -229,13 +248,13 @@ PyObject* quant_error(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int64_t T = y.size(0);
         const auto d = (int32_t)y.size(1);
         const auto fmt = (perq_fmt_t)integer(a[3]);
-        Held out(output(a[4], {T, 3}, at::kFloat, y.device()));
+        const Stream stream = stream_of(a[5]);
+        Held out(output(a[4], {T, 3}, at::kFloat, y.device(), stream));
         const auto* v = static_cast<const float*>(y.data_ptr());
         const auto* c = static_cast<const uint8_t*>(address(a[1]));
         const void* const s = address(a[2]);
         auto* o = static_cast<float*>(address(out.o));
-        void* const stream = stream_of(a[5]);
-        const perq_status_t st = unlocked([&] { return perq_quant_error(v, T, d, c, s, fmt, o, stream); });
+        const perq_status_t st = unlocked([&] { return perq_quant_error(v, T, d, c, s, fmt, o, stream.raw); });
         return result(st, out.release());
     });
 }
@@ -255,15 +274,15 @@ PyObject* product(PyObject*, PyObject* const* a, Py_ssize_t n) {
         }
         const int64_t T = ac.size(0), N = wc.size(0);
         const auto d = (int32_t)(2 * ac.size(1));
-        Held out(output(a[4], {T, N}, at::kFloat, ac.device()));
+        const Stream stream = stream_of(a[5]);
+        Held out(output(a[4], {T, N}, at::kFloat, ac.device(), stream));
         const int64_t ldo = T != 0 ? tensor(out.o, "out").stride(0) : N;
         const auto *pa = static_cast<const uint8_t*>(ac.data_ptr()), *pw = static_cast<const uint8_t*>(wc.data_ptr());
         const void *const sa = address(a[1]), *const sw = address(a[3]);
         auto* o = static_cast<float*>(address(out.o));
-        void* const stream = stream_of(a[5]);
         const perq_status_t st = unlocked([&] {
-            return mx ? perq_w4a4_mxfp4_gemm_ref(pa, static_cast<const uint8_t*>(sa), T, pw, static_cast<const uint8_t*>(sw), (int32_t)N, d, o, ldo, stream)
-                      : perq_w4a4_gemm_ref(pa, static_cast<const float*>(sa), T, pw, static_cast<const float*>(sw), (int32_t)N, d, o, ldo, stream);
+            return mx ? perq_w4a4_mxfp4_gemm_ref(pa, static_cast<const uint8_t*>(sa), T, pw, static_cast<const uint8_t*>(sw), (int32_t)N, d, o, ldo, stream.raw)
+                      : perq_w4a4_gemm_ref(pa, static_cast<const float*>(sa), T, pw, static_cast<const float*>(sw), (int32_t)N, d, o, ldo, stream.raw);
         });
         return result(st, out.release());
     });

@@ -702,6 +702,35 @@ def test_column_statistics_in_one_launch(M, d, stat):
         assert torch.equal(out, want[0])
 
 
+def test_buffers_of_a_call_belong_to_its_stream():
+    """With stream=, outputs and workspaces are blocks of that stream, and of the current one where it is not given:
+    a workspace ends with the call, and a block of another stream could be handed out again while the call still runs."""
+    torch = _torch()
+    x = torch.randn((4096, 2048), device="cuda").to(torch.bfloat16)
+    want = [binding.perq_colabs_mean(x), binding.perq_colabs_absmax(x), *binding.perq_permute_rotate_quant(x, None, 128, "int4"),
+            binding.perq_permute_rotate_f32(x, None, 128), binding.perq_block_diagnostics(x, None, 128)]
+    codes, scales, y = want[2], want[3], want[4]
+    want += [binding.perq_quant_error(y, codes, scales, "int4"), binding.perq_w4a4_gemm_ref(codes[:300], scales[:300], codes[:400], scales[:400])]
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for st in (side, None, torch.cuda.current_stream()):
+        torch.cuda.memory._record_memory_history("all", context=None, max_entries=10000, clear_history=True)
+        try:
+            got = [binding.perq_colabs_mean(x, stream=st), binding.perq_colabs_absmax(x, stream=st),
+                   *binding.perq_permute_rotate_quant(x, None, 128, "int4", stream=st),
+                   binding.perq_permute_rotate_f32(x, None, 128, stream=st), binding.perq_block_diagnostics(x, None, 128, stream=st),
+                   binding.perq_quant_error(y, codes, scales, "int4", stream=st),
+                   binding.perq_w4a4_gemm_ref(codes[:300], scales[:300], codes[:400], scales[:400], stream=st)]
+            trace = torch.cuda.memory._snapshot()["device_traces"][torch.cuda.current_device()]
+        finally:
+            torch.cuda.memory._record_memory_history(None)
+        allocs = [e["stream"] for e in trace if e["action"] == "alloc"]
+        assert len(allocs) == len(got) + 2                                           # two workspaces
+        assert set(allocs) == {(st or torch.cuda.current_stream()).cuda_stream}
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
 def test_w4a4_gemm_argument_checks():
     torch = _torch()
     a = torch.zeros((4, 16), dtype=torch.uint8, device="cuda")
