@@ -15,15 +15,16 @@
  * Conventions
  *   - "device" pointers are HIP device memory on the current device, "host" pointers are
  *     ordinary host memory.  Every buffer is owned by the caller; the library allocates nothing
- *     and frees nothing.  Its only state on a device is a table of counters (64 sets, in device
- *     memory of the library's own): 32 for the run-time row schedule of its main kernel, and the
- *     arrivals at each column tile of the column statistics.  Every launch leaves its counters at
- *     zero, and a set belongs to one stream: the first 64 streams per device that reach one of those
- *     kernels get a set each and keep it for the life of the process.  Launches of one stream never
- *     run side by side, so no two launches draw from one set at the same time, however many streams
- *     overlap.  A launch from a 65th stream, and any launch that is being captured into a graph (a
- *     graph can be replayed beside anything), takes a fixed split of the rows, or two launches for a
- *     column statistic, instead (same results).  See perq_schedule_set / perq_reset_schedule.
+ *     and frees nothing.  Its only state on a device is two tables of counters (64 sets each, in
+ *     device memory of the library's own): 32 per set for the run-time row schedule of its main
+ *     kernel, and the arrivals at each column tile for the column statistics.  Every launch leaves
+ *     its counters at zero, and a set belongs to one stream: in each table the first 64 streams per
+ *     device that use it get a set each and keep it for the life of the process.  Launches of one
+ *     stream never run side by side, so no two launches draw from one set at the same time, however
+ *     many streams overlap.  A launch from a 65th stream, and any launch that is being captured into
+ *     a graph (a graph can be replayed beside anything), takes a fixed split of the rows instead (same
+ *     results; the schedule only balances run time, about 10 % on the largest shapes), or two launches
+ *     for a column statistic (same results; 1 - 2 us).  See perq_schedule_set / perq_reset_schedule.
  *   - bf16 tensors are passed as uint16_t bit patterns, row-major, leading dimension in
  *     elements.
  *   - Device entry points enqueue on `hip_stream` (a hipStream_t, NULL = default stream) and

@@ -3,11 +3,9 @@
 #include "perq_base.h"
 #include "perq_launch.h"
 #include "perq_layout.h"
+#include "perq_schedule.h"
 
 #include <cmath>
-#include <map>
-#include <mutex>
-#include <tuple>
 
 namespace perq {
 
@@ -61,6 +59,24 @@ hipError_t resident_blocks(const void* kern, int threads, uint32_t lds_bytes, in
     known[key] = n;
     *per_cu = n;
     return hipSuccess;
+}
+
+int StreamSets::of(hipStream_t stream) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return -1;
+    }
+    if (cs != hipStreamCaptureStatusNone) return -1;
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    if (dev < 0 || dev >= 64) return -1;
+    const auto key = std::make_tuple(dev, stream, stream == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id());
+    std::lock_guard<std::mutex> lock(mu_);
+    const auto it = sets_.find(key);
+    if (it != sets_.end()) return it->second;
+    if (taken_[dev] >= (int)schedule::kSets) return -1;
+    return sets_[key] = taken_[dev]++;
 }
 
 namespace {

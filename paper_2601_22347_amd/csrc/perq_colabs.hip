@@ -53,6 +53,8 @@ constexpr int kWays = 16;
 constexpr int kOneLaunchSlices = 64, kOneLaunchTiles = 128;
 constexpr int64_t kOneLaunchSmall = (int64_t)1 << 23;         // elements
 __device__ uint32_t arrivals[schedule::kSets][kOneLaunchTiles][32];        // a count per cache line
+// (apart from the row schedule's sets: a stream that only computes statistics takes none of those)
+StreamSets arrival_sets;
 
 struct ColabsPlan {
     int col_tiles;
@@ -282,7 +284,7 @@ perq_status_t colabs_launch(const uint16_t* x_bf16, int64_t M, int32_t d, int64_
     const uint32_t tiles = (uint32_t)pl.col_tiles, blocks = tiles * (uint32_t)pl.slices;
     const bool together = pl.slices > 1 && pl.col_tiles <= kOneLaunchTiles &&
                           (pl.slices <= 2 * kWays || (pl.slices <= kOneLaunchSlices && M * (int64_t)d <= kOneLaunchSmall));
-    const int set = together ? schedule_set_of(stream) : -1;
+    const int set = together ? arrival_sets.of(stream) : -1;
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), 0, stream, x_bf16, M, d, ldx, pl.rows_per_slice, tiles,
                        ldx % 64 != 0 ? blocks : 0u, pl.slices == 1 ? nullptr : part, out, (float)M, pl.slices, set);
     if (hipGetLastError() != hipSuccess) return PERQ_ERR_LAUNCH;

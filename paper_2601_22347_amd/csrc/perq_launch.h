@@ -2,6 +2,11 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <map>
+#include <mutex>
+#include <thread>
+#include <tuple>
+
 #include "perq_device.h"
 
 namespace perq {
@@ -19,9 +24,21 @@ const LaunchInfo& launch_info();
 // Asked of the runtime once per kernel, device and configuration, then remembered.
 hipError_t resident_blocks(const void* kern, int threads, uint32_t lds_bytes, int* per_cu);
 
-// Which set of per-stream counters a launch on `stream` may use, or -1: none (the stream is capturing, or 64 other
-// streams of the current device came first).
-int schedule_set_of(hipStream_t stream);
+// Sets of device counters that belong to streams: the first `schedule::kSets` streams of a device get a set each
+// and keep it for the life of the process.  The per-thread default stream is a different stream in every host
+// thread and is told apart by the thread.
+class StreamSets {
+public:
+    // The set of `stream` on the current device, or -1: the stream is being captured into a graph (which can be replayed
+    // on any stream, beside anything), or every set is taken.
+    int of(hipStream_t stream);
+
+private:
+    std::mutex mu_;
+    std::map<std::tuple<int, hipStream_t, std::thread::id>, int> sets_;
+    int taken_[64] = {};          // sets handed out so far, per device
+};
+
 // Puts the arrival counts of the column statistics back to zero.
 hipError_t clear_arrivals(hipStream_t stream);
 

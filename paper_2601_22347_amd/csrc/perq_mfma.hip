@@ -38,10 +38,6 @@
 #include "perq_layout.h"
 #include "perq_schedule.h"
 
-#include <map>
-#include <mutex>
-#include <thread>
-#include <tuple>
 #include <type_traits>
 
 namespace perq {
@@ -67,51 +63,14 @@ struct MfmaGeom {
 
 // Ticket counters of the run-time row schedule (perq_schedule.h): kSets sets of kQueues counters,
 // each counter on a 256-byte line of its own.  Zero at load; every launch leaves its set at zero.
-// A set belongs to one stream for the life of the process (see stream_counter_set below): launches
+// A set belongs to one stream for the life of the process (see StreamSets): launches
 // of one stream run one after the other, so no two launches ever draw from the same set at the same
 // time, whatever the streams do between them.
 using schedule::kQueues;
 using schedule::kSets;
 __device__ uint32_t work_ctr[kSets][kQueues][64];
 
-// Which set of counters a launch on `stream` draws from, or -1: none, the launch takes the fixed
-// stride.  A stream keeps the set it was given first; a launch being captured into a graph gets
-// none (the graph may be replayed on any stream, beside anything), nor does a stream that comes
-// when every set of its device is taken.  The per-thread default stream is a different stream in
-// every host thread and is told apart by the thread.
-struct StreamKey {
-    int device;
-    hipStream_t stream;
-    std::thread::id thread;
-    bool operator<(const StreamKey& o) const {
-        return std::tie(device, stream, thread) < std::tie(o.device, o.stream, o.thread);
-    }
-};
-std::mutex sched_mu;
-std::map<StreamKey, int> sched_sets;
-int sched_taken[64] = {};          // sets handed out so far, per device
-
-int stream_counter_set(hipStream_t stream) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
-        (void)hipGetLastError();
-        return -1;
-    }
-    if (cs != hipStreamCaptureStatusNone) return -1;
-    StreamKey key;
-    key.device = 0;
-    (void)hipGetDevice(&key.device);
-    if (key.device < 0 || key.device >= 64) return -1;
-    key.stream = stream;
-    key.thread = stream == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id();
-    std::lock_guard<std::mutex> lock(sched_mu);
-    const auto it = sched_sets.find(key);
-    if (it != sched_sets.end()) return it->second;
-    if (sched_taken[key.device] >= (int)kSets) return -1;
-    const int set = sched_taken[key.device]++;
-    sched_sets[key] = set;
-    return set;
-}
+StreamSets row_sets;
 
 __global__ void clear_counters_kernel() {
     uint32_t* c = &work_ctr[0][0][0];
@@ -1274,7 +1233,7 @@ hipError_t launch_mfma_st(const ApplyParams& p, uint32_t fold_mask, hipStream_t 
         const int64_t units = wave_local ? p.T : ngroups;
         g.dynamic = 0;
         if (schedule::queues_usable(grid, workers, units)) {
-            const int set = stream_counter_set(stream);
+            const int set = row_sets.of(stream);
             if (set >= 0) {
                 g.dynamic = 1;
                 g.ctr_set = (uint32_t)set;
@@ -1473,12 +1432,8 @@ hipError_t launch_mfma(const ApplyParams& p0, int out_kind, hipStream_t stream) 
 
 }  // namespace perq
 
-namespace perq {
-int schedule_set_of(hipStream_t stream) { return stream_counter_set(stream); }
-}  // namespace perq
-
 extern "C" int32_t perq_schedule_set(void* hip_stream) {
-    return perq::stream_counter_set(static_cast<hipStream_t>(hip_stream));
+    return perq::row_sets.of(static_cast<hipStream_t>(hip_stream));
 }
 
 extern "C" perq_status_t perq_reset_schedule(void* hip_stream) {

@@ -1090,6 +1090,31 @@ def test_prepared_form_and_chunked_kernel_in_a_graph():
             assert torch.equal(eager[0], ref[0]) and torch.equal(eager[1], ref[1])
 
 
+def test_column_statistics_take_no_set_of_the_row_schedule():
+    """A stream that only computes statistics leaves the 64 sets of the main kernel to others."""
+    torch = _torch()
+    import ctypes
+    hip = ctypes.CDLL("libamdhip64.so")
+    raw = []
+    for _ in range(4):
+        h = ctypes.c_void_p()
+        assert hip.hipStreamCreate(ctypes.byref(h)) == 0
+        raw.append(h)
+    streams = [torch.cuda.ExternalStream(h.value) for h in raw]
+    x = torch.randn((1024, 2048), device="cuda").to(torch.bfloat16)
+    want = binding.perq_colabs_mean(x)
+    torch.cuda.synchronize()
+    first = binding.perq_schedule_set(streams[0])
+    got = [binding.perq_colabs_mean(x, stream=st) for st in streams[1:3]]
+    last = binding.perq_schedule_set(streams[3])
+    torch.cuda.synchronize()
+    assert all(torch.equal(g, want) for g in got)
+    assert first >= 0 and last == first + 1
+    del streams
+    for h in raw:
+        assert hip.hipStreamDestroy(h) == 0
+
+
 def test_run_time_schedule_more_streams_than_counter_sets_and_reset():
     """The 65th stream of a device gets no counter set: its launches take the fixed split.  All
     streams launch at once; every result equals the reference.  perq_reset_schedule leaves the
