@@ -89,16 +89,16 @@ def _device_assembly(src: str) -> str:
         return open(asm).read()
 
 
-def check_product_waits() -> int:
+def check_product_waits() -> set:
     """Compiler check for the counted waits of the products' tile kernels (perq_gemm.hip), about six seconds.
 
     A stage begins with a wait that lets the loads of the stages behind it be on their way, and requests one
     more stage.  The waits may count loads into LDS only, and every one of those has to be there: one wait of
-    NBUF - 1 stages, then a wait of NBUF - 2 stages and a stage of loads each.  Returns the number of
-    kernel variants checked; raises on a mismatch."""
+    NBUF - 1 stages, then a wait of NBUF - 2 stages and a stage of loads each.  Returns the kernel variants
+    checked, (MXFP4, MT, NT, WM, WN, NBUF, scale rows of whole dwords); raises on a mismatch."""
     import re
     text = _device_assembly("perq_gemm.hip")
-    checked = 0
+    checked = set()
     for m in re.finditer(r"\n(_ZN4perq\S*gemm_tile_kernelILb(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)ELi\dELb(\d)\S*): +; @", text):
         mx, mt, nt, wm, wn, nbuf, dwords = (int(v) for v in m.groups()[1:])
         loads = 4 * (mt * wm + nt * wn) // (wm * wn)                 # of a wave and stage
@@ -112,8 +112,8 @@ def check_product_waits() -> int:
         if stages < 12 or sorted(waits) != sorted([loads * (nbuf - 1)] + [loads * (nbuf - 2)] * stages) or \
                 issued != loads * (nbuf + stages) + scales:
             raise RuntimeError(f"{m.group(1)}: {loads} loads a stage, {issued} in all, waits {waits}")
-        checked += 1
-    if checked == 0:
+        checked.add((mx, mt, nt, wm, wn, nbuf, dwords))
+    if not checked:
         raise RuntimeError("no tile kernel found")
     return checked
 
