@@ -118,6 +118,37 @@ def check_product_waits() -> set:
     return checked
 
 
+def check_statistics_order() -> int:
+    """Compiler check for the column statistics in one launch (perq_colabs.hip), a few seconds.
+
+    A workgroup counts itself in when its partial sums are where the whole device sees them, and the last one reads
+    all of them.  What orders this is in the instructions: partials are stored with device scope (sc1), the wave waits
+    for its stores before the barrier ahead of the count, and partials are read with device scope.  Returns the number of
+    kernel variants checked; raises on a mismatch."""
+    import re
+    text = _device_assembly("perq_colabs.hip")
+    checked = 0
+    for m in re.finditer(r"\n(_ZN4perq\S*colabs_partial_kernelILb\dELb0ELb\d\S*): +; @", text):
+        body = [l.split(";")[0].strip() for l in text[m.end():text.index(".Lfunc_end", m.end())].split("\n")]
+        at = [i for i, l in enumerate(body) if l.startswith("global_atomic_add ")]
+        stores = [i for i, l in enumerate(body) if l.startswith("global_store_dwordx2 ") and l.endswith(" sc1")]
+        if len(at) != 1 or len(stores) != 1 or stores[0] > at[0]:
+            raise RuntimeError(f"{m.group(1)}: counts at lines {at}, device-scope stores at lines {stores}")
+        before = [l for l in body[stores[0] + 1:at[0]] if re.match(r"(s_waitcnt|s_barrier|global_|flat_|buffer_)", l)]
+        # (the partial of two launches and the result of a single slice, then: wait, barrier, count)
+        order = [l.split()[0] for l in before if not l.startswith("s_waitcnt lgkmcnt")]
+        last = [l for l in before if l.startswith("s_waitcnt") and "vmcnt(0)" in l][-1:]
+        if order[-2:] != ["s_waitcnt", "s_barrier"] or not last or before.index(last[0]) < max(i for i, l in enumerate(before) if "store" in l):
+            raise RuntimeError(f"{m.group(1)}: between the partial and the count {before}")
+        reads = [l for l in body[at[0]:] if re.match(r"(global|flat|buffer)_load", l)]
+        if len(reads) != 32 or any(not l.startswith("global_load_dwordx2 ") or not l.endswith(" sc1") for l in reads):
+            raise RuntimeError(f"{m.group(1)}: partials read by {reads}")
+        checked += 1
+    if checked == 0:
+        raise RuntimeError("no kernel with arrivals found")
+    return checked
+
+
 def check_table_reads() -> int:
     """Compiler check for the prepared-form reads of the matrix-core kernel (perq_mfma.hip).
 

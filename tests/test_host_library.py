@@ -74,6 +74,11 @@ def test_counted_waits_of_the_products_count_loads_that_are_there():
     assert build.check_product_waits() == tiles
 
 
+def test_partials_of_the_column_statistics_arrive_before_they_are_counted():
+    from paper_2601_22347_amd import build
+    assert build.check_statistics_order() == 4                        # mean and largest, with and without streaming loads
+
+
 def test_statistics_workspace_is_no_larger_than_a_float_per_run_of_rows(lib):
     """A float per column and run of r rows (r as documented); several slices fit the 2 MiB static array."""
     rng = np.random.default_rng(5)
