@@ -131,14 +131,19 @@ _module = None
 def _native():
     global _module
     if _module is None:
-        import importlib
+        import importlib.machinery
+        import importlib.util
 
         import torch  # noqa: F401  (the module links against it)
         load()
         from . import build as _build
-        if not os.path.exists(_build.MODULE):
+        path = _build.module_path()
+        if not os.path.exists(path):
             _build.build_module()
-        _module = importlib.import_module("._perq_torch", __package__)
+        loader = importlib.machinery.ExtensionFileLoader(f"{__package__}._perq_torch", path)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_file_location(loader.name, path, loader=loader))
+        loader.exec_module(module)
+        _module = module
     return _module
 
 
@@ -295,7 +300,6 @@ def perq_colabs_mean(x, out=None, stream=None):
     return _got((_module or _native()).column_statistic(x, out, stream, False), "perq_colabs_mean")
 
 
-
 def perq_colabs_mean_static(x, out, stream=None):
     """x: CUDA bf16 [M, d], out: CUDA float32 [d] (caller's); the call allocates nothing."""
     M, d, ldx = _check_x(x)
@@ -309,18 +313,15 @@ def perq_colabs_absmax(x, out=None, stream=None):
     return _got((_module or _native()).column_statistic(x, out, stream, True), "perq_colabs_absmax")
 
 
-
 def perq_block_diagnostics(x, perm, b: int, out=None, stream=None):
     """x: CUDA bf16 [T, d] -> CUDA float32 [T, 4] = (|x|_inf, |x|_1, max block l1 of xP, |xP R~|_inf)."""
     return _got((_module or _native()).diagnostics(x, perm, b, out, stream), "perq_block_diagnostics")
-
 
 
 def perq_quant_error(y, codes, scales, fmt: str, out=None, stream=None):
     """y: CUDA float32 [T, d]; codes, scales: outputs of perq_permute_rotate_quant for the same input ->
     CUDA float32 [T, 3] = (|y - Q(y)|_2, |y|_2, |y|_inf)."""
     return _got((_module or _native()).quant_error(y, codes, scales, FMT[fmt], out, stream), "perq_quant_error")
-
 
 
 def alloc_outputs(T: int, d: int, fmt: str, device):
@@ -345,11 +346,9 @@ def perq_permute_rotate_quant(x, perm, b: int, fmt: str, codes=None, scales=None
                 "perq_permute_rotate_quant")
 
 
-
 def perq_permute_rotate_f32(x, perm, b: int, y=None, stream=None, algo: str = "auto"):
     """Test entry: pre-quantization values, CUDA float32 [T, d]."""
     return _got((_module or _native()).rotate_f32(x, perm, b, y, stream, ALGO[algo]), "perq_permute_rotate_f32")
-
 
 
 def perq_w4a4_gemm_ref(a_codes, a_scales, w_codes, w_scales, out=None, stream=None):
@@ -358,13 +357,11 @@ def perq_w4a4_gemm_ref(a_codes, a_scales, w_codes, w_scales, out=None, stream=No
     return _got((_module or _native()).product(a_codes, a_scales, w_codes, w_scales, out, stream, False), "perq_w4a4_gemm_ref")
 
 
-
 def perq_w4a4_mxfp4_gemm_ref(a_codes, a_scales, w_codes, w_scales, out=None, stream=None):
     """The same product for MXFP4 operands (CUDA uint8 codes [T, d/2] / [N, d/2], uint8 scale bytes
     [T, d/32] / [N, d/32]); returns CUDA float32 [T, N]."""
     return _got((_module or _native()).product(a_codes, a_scales, w_codes, w_scales, out, stream, True),
                 "perq_w4a4_mxfp4_gemm_ref")
-
 
 
 def placement_to_device(prepared: np.ndarray, device="cuda"):

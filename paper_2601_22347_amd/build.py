@@ -1,15 +1,18 @@
 """Builds libperq.so (HIP kernels + C ABI) for gfx950 with hipcc, and the Python extension module that calls it, in-tree."""
 from __future__ import annotations
 
+import hashlib
+import importlib.util
 import os
 import shutil
 import subprocess
+import sysconfig
+import warnings
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libperq.so")
-MODULE = os.path.join(PKG, "_perq_torch.so")
 
 SOURCES = ["perq_host.cpp", "perq_colabs.hip", "perq_butterfly.hip", "perq_mfma.hip", "perq_api.hip",
            "perq_gemm.hip", "perq_qerr.hip", "perq_npo2.hip", "perq_npo2_12.hip", "perq_npo2_76.hip", "perq_npo2_32.hip"]
@@ -21,6 +24,8 @@ HIP_FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-ffp-contra
              # rewrite of uniform atomics reads the result back at once and stalls on it
              "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
              "-Wall", "-Wno-unused-command-line-argument"]
+MODULE_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unknown-pragmas", "-DUSE_ROCM=1",
+                "-D__HIP_PLATFORM_AMD__=1"]
 
 
 def hipcc() -> str:
@@ -31,7 +36,8 @@ def hipcc() -> str:
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every source and link libperq.so; always recompiles."""
+    """Compile every source and link libperq.so, then the extension module where Python calls can be made at all
+    (module_lacks); always recompiles."""
     objdir = os.path.join(PKG, "_build")
     os.makedirs(objdir, exist_ok=True)
     objs = []
@@ -53,27 +59,65 @@ def build(verbose: bool = False) -> str:
     res = subprocess.run(link, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"link failed:\n{res.stdout}")
-    build_module()
+    lacks = module_lacks()
+    if lacks:
+        warnings.warn(f"libperq.so is built, the extension module for Python is not: no {', no '.join(lacks)}")
+    else:
+        build_module()
     return LIB
+
+
+def _torch_dir() -> str | None:
+    spec = importlib.util.find_spec("torch")
+    return os.path.dirname(spec.origin) if spec and spec.origin else None
+
+
+def module_lacks() -> list[str]:
+    """What the extension module needs beside libperq.so and is not here; the C library needs none of it."""
+    where, lacks = _torch_dir(), []
+    if where is None:
+        lacks.append("PyTorch")
+    elif not os.path.exists(os.path.join(where, "include", "c10", "hip", "HIPStream.h")):
+        lacks.append("PyTorch headers for ROCm")
+    if shutil.which("g++") is None:
+        lacks.append("g++")
+    if not os.path.exists(os.path.join(sysconfig.get_path("include"), "Python.h")):
+        lacks.append("Python headers")
+    return lacks
+
+
+def module_path() -> str:
+    """The extension module's file.  Its name stands for all it was made from, sources and the versions of PyTorch and
+    Python, so that a module that no longer fits is not found, instead of loaded."""
+    import torch
+    made_from = hashlib.sha256(repr((MODULE_FLAGS, torch.__version__, sysconfig.get_config_var("EXT_SUFFIX"))).encode())
+    for path in (os.path.join(CSRC, "perq_torch.cpp"), os.path.join(ROOT, "include", "perq.h")):
+        with open(path, "rb") as f:
+            made_from.update(f.read())
+    return os.path.join(PKG, f"_perq_torch_{made_from.hexdigest()[:12]}.so")
 
 
 def build_module() -> str:
     """Compile the extension module (host code; needs libperq.so to link against)."""
-    import sysconfig
-
     import torch
-    where = os.path.dirname(torch.__file__)
-    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unknown-pragmas",
-           "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+    where, module = _torch_dir(), module_path()
+    # under a name of this process's own, then renamed: another process finds the whole file or none
+    made = f"{module}.{os.getpid()}.tmp"
+    cmd = [shutil.which("g++") or "g++", *MODULE_FLAGS, f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(where, "include"),
            "-isystem", os.path.join(where, "include", "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
-           "-isystem", sysconfig.get_path("include"), os.path.join(CSRC, "perq_torch.cpp"), "-o", MODULE,
+           "-isystem", sysconfig.get_path("include"), os.path.join(CSRC, "perq_torch.cpp"), "-o", made,
            "-L", PKG, "-l:libperq.so", "-Wl,-rpath,$ORIGIN", "-L", os.path.join(where, "lib"),
            "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
-    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if res.returncode != 0:
-        raise RuntimeError(f"g++ failed on perq_torch.cpp:\n{' '.join(cmd)}\n{res.stdout}")
-    return MODULE
+    try:
+        res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        if res.returncode != 0:
+            raise RuntimeError(f"g++ failed on perq_torch.cpp:\n{' '.join(cmd)}\n{res.stdout}")
+        os.replace(made, module)
+    finally:
+        if os.path.exists(made):
+            os.unlink(made)
+    return module
 
 
 def _device_assembly(src: str) -> str:

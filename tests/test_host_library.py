@@ -3,6 +3,7 @@ declares, rejects bad arguments before touching the device, and its greedy match
 import ctypes
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -64,6 +65,69 @@ def test_greedy_rejects_bad_arguments(lib):
     assert lib.perq_massdiff_perm(pa, 64, 16, pp) == binding.PERQ_ERR_INVALID_ARG
     a[3] = -1.0
     assert lib.perq_massdiff_perm(pa, 64, 16, pp) == binding.PERQ_ERR_INVALID_ARG
+
+
+def test_extension_module_loads_and_refuses_what_is_no_device_tensor():
+    import torch
+    native = binding._native()
+    assert native is binding._native()
+    with pytest.raises(ValueError, match="x must be a 2-D CUDA tensor"):
+        binding.perq_permute_rotate_quant(torch.zeros((4, 256), dtype=torch.bfloat16), None, 16, "int4")
+    with pytest.raises(TypeError, match="x must be a tensor"):
+        binding.perq_colabs_mean([1.0])
+    with pytest.raises(TypeError, match="arguments"):
+        native.apply(1, 2)
+
+
+def test_extension_module_appears_whole_and_is_found_by_what_it_was_made_from(monkeypatch, tmp_path):
+    from paper_2601_22347_amd import build
+    csrc = tmp_path / "csrc"
+    csrc.mkdir()
+    (csrc / "perq_torch.cpp").write_text("// one")
+    monkeypatch.setattr(build, "PKG", str(tmp_path))
+    monkeypatch.setattr(build, "CSRC", str(csrc))
+    fail = False
+
+    def compiler(cmd, **kw):
+        made = cmd[cmd.index("-o") + 1]
+        assert made != build.module_path() and os.path.dirname(made) == str(tmp_path)
+        with open(made, "w") as f:
+            f.write("half")
+        assert not os.path.exists(build.module_path())        # what another process would import now
+        return subprocess.CompletedProcess(cmd, int(fail), "no", None)
+
+    monkeypatch.setattr(build.subprocess, "run", compiler)
+    first = build.build_module()
+    assert os.path.exists(first) and first == build.module_path()
+    (csrc / "perq_torch.cpp").write_text("// two")
+    assert not os.path.exists(build.module_path())            # a module of other sources is not taken
+    fail = True
+    with pytest.raises(RuntimeError, match="g\\+\\+ failed"):
+        build.build_module()
+    assert sorted(os.listdir(tmp_path)) == sorted(["csrc", os.path.basename(first)])
+
+
+def test_library_builds_where_the_extension_module_cannot(monkeypatch):
+    """The C library needs neither PyTorch nor a host compiler of its own."""
+    from paper_2601_22347_amd import build
+
+    class Compiler:
+        returncode = 0
+
+        def __init__(self, cmd, **kw):
+            pass
+
+        def communicate(self):
+            return "", None
+
+    monkeypatch.setattr(build.subprocess, "Popen", Compiler)
+    monkeypatch.setattr(build.subprocess, "run", lambda cmd, **kw: subprocess.CompletedProcess(cmd, 0, "", None))
+    monkeypatch.setattr(build, "build_module", lambda: pytest.fail("called"))
+    monkeypatch.setattr(build.importlib.util, "find_spec", lambda name: None)
+    with pytest.warns(UserWarning, match="no PyTorch"):
+        assert build.build() == build.LIB
+    monkeypatch.undo()
+    assert build.module_lacks() == []
 
 
 def test_counted_waits_of_the_products_count_loads_that_are_there():
