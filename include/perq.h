@@ -376,10 +376,13 @@ perq_status_t perq_w4a4_mxfp4_gemm_ref(const uint8_t* a_codes, const uint8_t* a_
  *                        the first call for that stream, by this function or by a launch), or -1
  *                        when such launches take the fixed split: the stream is capturing, or 64
  *                        other streams of the current device came first.
- *   perq_reset_schedule  enqueues a small kernel on `hip_stream` that puts every counter of the
- *                        current device back to zero.  Never needed after launches that ran to
- *                        their end; for a process that goes on after a kernel of the library was
- *                        cut short.  Must not overlap a launch of the fused path on another stream.
+ *   perq_reset_schedule  enqueues small kernels on `hip_stream` that put every counter of the row
+ *                        schedule on the current device, and the arrival counts of the column
+ *                        statistics of this stream, back to zero.  Never needed after launches that
+ *                        ran to their end; for a process that goes on after a kernel of the library
+ *                        was cut short (a column statistic: call it for the stream of that one).
+ *                        Must not overlap a launch of the fused path on another stream; column
+ *                        statistics of other streams are not touched.
  *   perq_schedule_selftest  host only: a model of the schedule on the kernel's own queue
  *                        arithmetic -- n_blocks workgroups of workers_per_block workers each draw
  *                        their units in a seeded random interleaving, `launches` times on the same

@@ -61,7 +61,7 @@ hipError_t resident_blocks(const void* kern, int threads, uint32_t lds_bytes, in
     return hipSuccess;
 }
 
-int StreamSets::of(hipStream_t stream) {
+int StreamSets::of(hipStream_t stream, bool assign) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
         (void)hipGetLastError();
@@ -75,7 +75,7 @@ int StreamSets::of(hipStream_t stream) {
     std::lock_guard<std::mutex> lock(mu_);
     const auto it = sets_.find(key);
     if (it != sets_.end()) return it->second;
-    if (taken_[dev] >= (int)schedule::kSets) return -1;
+    if (!assign || taken_[dev] >= (int)schedule::kSets) return -1;
     return sets_[key] = taken_[dev]++;
 }
 

@@ -235,15 +235,15 @@ colabs_finish_kernel(const double* __restrict__ part, int slices, int32_t d, flo
     }
 }
 
-__global__ void clear_arrivals_kernel() {
-    uint32_t* c = &arrivals[0][0][0];
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < sizeof(arrivals) / 4; i += gridDim.x * blockDim.x) c[i] = 0u;
-}
+__global__ void clear_arrivals_kernel(int set) { arrivals[set][threadIdx.x][0] = 0u; }
 
 }  // namespace
 
+// (of no other stream: a statistic may be running there, and a count that starts over never becomes full)
 hipError_t clear_arrivals(hipStream_t stream) {
-    hipLaunchKernelGGL(clear_arrivals_kernel, dim3(64), dim3(256), 0, stream);
+    const int set = arrival_sets.of(stream, false);
+    if (set < 0) return hipSuccess;
+    hipLaunchKernelGGL(clear_arrivals_kernel, dim3(1), dim3(kOneLaunchTiles), 0, stream, set);
     return hipGetLastError();
 }
 

@@ -30,8 +30,8 @@ hipError_t resident_blocks(const void* kern, int threads, uint32_t lds_bytes, in
 class StreamSets {
 public:
     // The set of `stream` on the current device, or -1: the stream is being captured into a graph (which can be replayed
-    // on any stream, beside anything), or every set is taken.
-    int of(hipStream_t stream);
+    // on any stream, beside anything), every set is taken, or (assign false) it has not been given one.
+    int of(hipStream_t stream, bool assign = true);
 
 private:
     std::mutex mu_;
@@ -39,7 +39,7 @@ private:
     int taken_[64] = {};          // sets handed out so far, per device
 };
 
-// Puts the arrival counts of the column statistics back to zero.
+// Puts the arrival counts of the column statistics of `stream` back to zero.
 hipError_t clear_arrivals(hipStream_t stream);
 
 // Kernel families behind perq_permute_rotate_quant / perq_permute_rotate_f32.

@@ -1115,6 +1115,26 @@ def test_column_statistics_take_no_set_of_the_row_schedule():
         assert hip.hipStreamDestroy(h) == 0
 
 
+def test_reset_leaves_the_column_statistics_of_other_streams_alone():
+    torch = _torch()
+    xs = [torch.randn((4096, 8192), device="cuda").to(torch.bfloat16) for _ in range(2)]
+    want = [binding.perq_colabs_mean(x) for x in xs]
+    st, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    got = []
+    for k in range(60):
+        with torch.cuda.stream(st):
+            got.append(binding.perq_colabs_mean(xs[k % 2]))
+        for _ in range(3):
+            binding.perq_reset_schedule(other)
+    torch.cuda.synchronize()
+    assert all(torch.equal(g, want[k % 2]) for k, g in enumerate(got))
+    # on its own stream a reset comes after what was queued before it
+    with torch.cuda.stream(st):
+        binding.perq_reset_schedule(st)
+        assert torch.equal(binding.perq_colabs_mean(xs[0]), want[0])
+
+
 def test_run_time_schedule_more_streams_than_counter_sets_and_reset():
     """The 65th stream of a device gets no counter set: its launches take the fixed split.  All
     streams launch at once; every result equals the reference.  perq_reset_schedule leaves the
