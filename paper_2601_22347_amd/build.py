@@ -139,12 +139,12 @@ def check_product_waits() -> set:
     A stage begins with a wait that lets the loads of the stages behind it be on their way, and requests one
     more stage.  The waits may count loads into LDS only, and every one of those has to be there: one wait of
     NBUF - 1 stages, then a wait of NBUF - 2 stages and a stage of loads each.  Returns the kernel variants
-    checked, (MXFP4, MT, NT, WM, WN, NBUF, scale rows of whole dwords); raises on a mismatch."""
+    checked, (MXFP4, MT, NT, WM, WN, NBUF, DWORDS, SHORT); raises on a mismatch."""
     import re
     text = _device_assembly("perq_gemm.hip")
     checked = set()
-    for m in re.finditer(r"\n(_ZN4perq\S*gemm_tile_kernelILb(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)ELi\dELb(\d)\S*): +; @", text):
-        mx, mt, nt, wm, wn, nbuf, dwords = (int(v) for v in m.groups()[1:])
+    for m in re.finditer(r"\n(_ZN4perq\S*gemm_tile_kernelILb(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)ELi\dELb(\d)ELb(\d)\S*): +; @", text):
+        mx, mt, nt, wm, wn, nbuf, dwords, short = (int(v) for v in m.groups()[1:])
         loads = 4 * (mt * wm + nt * wn) // (wm * wn)                 # of a wave and stage
         # scale bytes, loaded before the first stage and once in the loop over whole superstages; not counted by the waits
         scales = 2 * -(-(mt * wm + nt * wn) // (wm * wn)) if mx and dwords else 0
@@ -153,10 +153,11 @@ def check_product_waits() -> set:
         waits = [int(re.search(r"vmcnt\((\d+)\)", l).group(1)) for i, l in enumerate(body)
                  if "vmcnt(" in l and any("s_barrier" in k for k in body[i + 1:i + 5])]
         stages = len(waits) - 1
-        if stages < 12 or sorted(waits) != sorted([loads * (nbuf - 1)] + [loads * (nbuf - 2)] * stages) or \
+        # (rows of less than a superstage: the four stages of the partial one, else also whole ones with and without the next)
+        if (stages != 4 if short else stages < 12) or sorted(waits) != sorted([loads * (nbuf - 1)] + [loads * (nbuf - 2)] * stages) or \
                 issued != loads * (nbuf + stages) + scales:
             raise RuntimeError(f"{m.group(1)}: {loads} loads a stage, {issued} in all, waits {waits}")
-        checked.add((mx, mt, nt, wm, wn, nbuf, dwords))
+        checked.add((mx, mt, nt, wm, wn, nbuf, dwords, short))
     if not checked:
         raise RuntimeError("no tile kernel found")
     return checked

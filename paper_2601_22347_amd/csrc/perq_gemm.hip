@@ -108,12 +108,15 @@ __device__ __forceinline__ void tile_of_block(const GemmParams& p, uint32_t& tt,
 // LDS as well, 1 KiB a load for 32 rows, and a lane picks the dword of each stage from there.  Loads of scales
 // straight to the lanes that use them went to every row once per wave, and to spare some of them a stage took two halves
 // of lines, which costs L2 twice the requests.  T = N = 2048, d = 8192 32.1 -> 23.9 us.
-template <bool MX, int MT, int NT, int WM, int WN, int NBUF, int WGS, bool DWORDS>
+//   SHORT: rows of less than a superstage, whose scale bytes need a third of that LDS, so that a CU holds two workgroups and
+// one stores its tile while the other multiplies (T = N = 4096, d = 256 15.4 us; one workgroup of four stages 19.4, of
+// 128 x 256 19.7).
+template <bool MX, int MT, int NT, int WM, int WN, int NBUF, int WGS, bool DWORDS, bool SHORT>
 __global__ void __launch_bounds__(64 * WM * WN, WGS* WM* WN / 4)
 gemm_tile_kernel(GemmParams p) {
     constexpr int kWaves = WM * WN, kBM = 32 * MT * WM, kBN = 32 * NT * WN;
     constexpr int kLoadA = kBM / 8 / kWaves, kLoadW = kBN / 8 / kWaves, kLoads = kLoadA + kLoadW;
-    constexpr int kSc = MX ? MT + NT : 1;
+    constexpr int kSc = MX ? MT + NT : 1, kRest = SHORT ? 0 : 2;         // scale bytes of the partial superstage
     constexpr int kScaleLoads = MX ? (kBM + kBN + 32 * kWaves - 1) / (32 * kWaves) : 1;      // of a wave and superstage
     constexpr uint32_t kBuf = (uint32_t)(kBM + kBN) * kStageBytes, kScaleBuf = (uint32_t)(kScaleLoads * kWaves) * 1024u;
     static_assert(kLoadA * 8 * kWaves == kBM && kLoadW * 8 * kWaves == kBN, "every wave loads whole pieces");
@@ -129,7 +132,7 @@ gemm_tile_kernel(GemmParams p) {
     const int64_t t0 = (int64_t)tt * kBM;
     const int32_t n0 = (int32_t)tn * kBN;
     const uint32_t row_bytes = (uint32_t)p.d >> 1, granules = row_bytes >> 4;
-    const int whole = (int)(granules >> 5);                                         // whole superstages
+    const int whole = SHORT ? 0 : (int)(granules >> 5);                             // whole superstages
     const uint32_t rest = granules & 31u;                                           // granules of the last, partial one
     // rows and columns past the end re-read the last one; their results are not stored
     const uint32_t last_t = (uint32_t)(p.T - t0 < kBM ? p.T - t0 : kBM) - 1u;
@@ -230,7 +233,7 @@ gemm_tile_kernel(GemmParams p) {
 #pragma unroll
             for (uint32_t q = 0; q < 4; ++q) rest_sreg[k].w[q] >>= rest_at(q) < nb - 4u ? 0u : 8u * ((rest_at(q) - (nb - 4u)) & 3u);
         }
-        keep_scales(2, rest_sreg);
+        keep_scales(kRest, rest_sreg);
     };
     // the four scale bytes of this lane's granules in each stage of superstage S
     struct Scales { uint32_t w[kSc][4]; };
@@ -327,7 +330,7 @@ gemm_tile_kernel(GemmParams p) {
                 constexpr bool kScalesNow = kc == 1 && j == 0 && inner;
                 if constexpr (kc == 3) advance();
                 read(j, kc + 1, next);
-                if constexpr (kc == 3 && j == 3 && !tail) read_scales(inner ? (S + 1) & 1 : 2, nxt);
+                if constexpr (kc == 3 && j == 3 && !tail) read_scales(inner ? (S + 1) & 1 : kRest, nxt);
                 if constexpr (!DWORDS && kc == 1 && j == 3 && inner) keep_scales((S + 1) & 1, sreg);
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (kc == 3) request_codes(S, std::integral_constant<int, j + NBUF>{}, inner_const);
@@ -398,7 +401,7 @@ gemm_tile_kernel(GemmParams p) {
         __builtin_amdgcn_s_waitcnt(0x0F70 | (n & 15) | ((n >> 4) << 14));
         workgroup_barrier_lds();
         read(0, 0, r0);
-        read_scales(whole > 0 ? 0 : 2, cur);
+        read_scales(whole > 0 ? 0 : kRest, cur);
         if constexpr (!MX) {
             read(0, 1, r1);
             unpack(r0, u0, whole > 0 ? -1 : live(0, 0));
@@ -636,10 +639,10 @@ gemm_short_kernel(GemmParams p) {
 // Rows of the output begin and end with a 128-byte line.
 bool whole_lines(const GemmParams& p) { return p.ldo % 32 == 0 && (reinterpret_cast<uintptr_t>(p.out) & 127u) == 0; }
 
-template <bool MX, int MT, int NT, int WM, int WN, int NBUF, int WGS, bool DWORDS>
+template <bool MX, int MT, int NT, int WM, int WN, int NBUF, int WGS, bool DWORDS, bool SHORT = false>
 hipError_t launch_tile_as(GemmParams p, hipStream_t stream) {
     constexpr uint32_t lds_bytes = (uint32_t)(32 * MT * WM + 32 * NT * WN) * (kStageBytes * NBUF + (MX ? 0u : 4u)) +
-                                    (MX ? 3u * 1024u * WM * WN * ((MT * WM + NT * WN + WM * WN - 1) / (WM * WN)) : 0u);
+                                    (MX ? (SHORT ? 1u : 3u) * 1024u * WM * WN * ((MT * WM + NT * WN + WM * WN - 1) / (WM * WN)) : 0u);
     static_assert(WGS * lds_bytes <= 160u * 1024u, "LDS of a CU");
     p.tiles_t = (uint32_t)((p.T + 32 * MT * WM - 1) / (32 * MT * WM));
     p.tiles_n = (uint32_t)(((int64_t)p.N + 32 * NT * WN - 1) / (32 * NT * WN));
@@ -648,7 +651,7 @@ hipError_t launch_tile_as(GemmParams p, hipStream_t stream) {
     // (2048, 14336, 4096) 112 / 111 -> 103 / 84, (2048, 2048, 1024) 9.5 / 8.8 -> 8.3 / 7.6.  Lines that two rows share:
     // (3000, 3500, 1024) 20.0 / 19.3 -> 22.9 / 22.2, so those keep the plain store.
     p.stream_out = whole_lines(p);
-    auto kern = gemm_tile_kernel<MX, MT, NT, WM, WN, NBUF, WGS, DWORDS>;
+    auto kern = gemm_tile_kernel<MX, MT, NT, WM, WN, NBUF, WGS, DWORDS, SHORT>;
     int per_cu = 0;      // (raises the kernel's limit of dynamic LDS)
     const hipError_t e = resident_blocks(reinterpret_cast<const void*>(kern), 64 * WM * WN, lds_bytes, &per_cu);
     if (e != hipSuccess) return e;
@@ -737,6 +740,12 @@ hipError_t launch_few(GemmParams p, hipStream_t stream) {
 //     and some two.  (2048, 2560, 4096) 23.4 against 25.3, (2177, 2177, 8192) 42.7 against 45.6, (2048, 3072, 8192) 43.7
 //     against 46.1, d = 4096 25.2 against 25.5, d = 2048 16.1 against 15.6; (2048, 4096, 4096) 31.0 against 29.8,
 //     (2048, 14336, 4096) 108 against 103, (4096, 4096, 8192) 103 against 105.
+//   MXFP4, d < 1024: 128 x 128, two stages and two workgroups a CU, against 128 x 256 (four stages and one):
+//     (4096, 4096) d = 160 15.6 against 20.0 (19.4), d = 320 17.1 against 21.3 (21.4), d = 640 18.4 against 25.4 (26.4),
+//     d = 992 22.2 against 28.5 (29.9); (3000, 3500, 256) 12.6 against 14.4 (16.6), d = 768 15.9 against 18.0 (19.9); (8192, 8192,
+//     512) 57.6 against 68.0 (88.4); (2048, 2048, 256) 6.5 against 7.2 (7.1), d = 992 7.8 against 8.8 (8.6).  One round of 128 x 256
+//     is as fast or faster up to d = 512: (2048, 4096) d = 160 9.4 against 8.7, d = 512 10.6 against 10.0, d = 768 11.3 against 11.3;
+//     (300, 14336, 512) 7.7 against 7.2.
 //   128 x 128: MXFP4 four stages in LDS and one workgroup a CU, against two stages (2048, 2048, 8192) 23.9 against
 //     27.8; INT4, whose stages take twice as long, two and two workgroups, (2048, 2048, 8192) 30.6 against 33.0.
 template <bool MX>
@@ -748,6 +757,10 @@ hipError_t launch_gemm(const GemmParams& p, hipStream_t stream) {
     if (small <= 256 || one_row || (small <= 512 && (!MX || p.d % 128 != 0)) || (!MX && small <= 900 && p.d >= 2048))
         return small > 512 && p.d < 4096 ? launch_few<MX, 4>(p, stream) : launch_few<MX, 8>(p, stream);
     if (tiles(128, 128) <= 128) return launch_tile<MX, 1, 1, 2, 2, 4, 2>(p, stream);
+    if constexpr (MX) {
+        if (p.d < 1024 && !(p.d <= 512 && tiles(128, 128) > 256 && tiles(128, 256) <= 256))
+            return launch_tile_as<MX, 2, 2, 2, 2, 2, 2, false, true>(p, stream);
+    }
     if (tiles(128, 128) > 256 && (MX ? p.d >= 2880 || p.d <= 512 || whole_lines(p) : tiles(128, 128) <= 384 && p.d >= 2880)) return launch_tile<MX, 2, 2, 2, 4, 2, 1>(p, stream);
     if constexpr (MX) return launch_tile<MX, 2, 2, 2, 2, 4, 1>(p, stream);
     else return launch_tile<MX, 2, 2, 2, 2, 2, 2>(p, stream);

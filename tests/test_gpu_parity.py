@@ -595,6 +595,14 @@ def test_w4a4_products_of_few_tiles(T, N, d, fmt):
     test_w4a4_products_over_tiles_and_remainders(T, N, d, fmt)
 
 
+# MXFP4 rows of less than a superstage: one stage to four, whole ones and cut ones, several rounds of tiles; the last one is not
+@pytest.mark.parametrize("T,N,d", [(2700, 3330, 160), (2700, 3330, 256), (1540, 1537, 288), (2700, 3330, 512), (1540, 1537, 544), (1540, 1537, 768),
+                                   (2700, 3330, 992), (1540, 1537, 992), (1540, 1537, 1024)])
+def test_w4a4_mxfp4_products_of_short_rows(T, N, d):
+    test_w4a4_products_over_tiles_and_remainders(T, N, d, "mxfp4")
+    test_w4a4_products_repeat_bit_for_bit(T, N, d, "mxfp4")
+
+
 # ---- rows that end in several stages of a partial superstage: the waits count the loads that are there ----
 @pytest.mark.parametrize("T,N,d", [(449, 577, 2880), (513, 700, 1312), (1540, 1537, 800), (2177, 2177, 2016),
                                    (1540, 1537, 2880), (1540, 1537, 4096), (2060, 2177, 2880), (2060, 2177, 4096),

@@ -133,8 +133,9 @@ def test_library_builds_where_the_extension_module_cannot(monkeypatch):
 def test_counted_waits_of_the_products_count_loads_that_are_there():
     from paper_2601_22347_amd import build
     # the tiles that launch_gemm chooses from; MXFP4 with scale bytes straight into LDS and through registers
-    tiles = {(0, 1, 1, 2, 2, 4, 1), (0, 2, 2, 2, 4, 2, 1), (0, 2, 2, 2, 2, 2, 1)}
-    tiles |= {(1, *shape, dwords) for shape in ((1, 1, 2, 2, 4), (2, 2, 2, 4, 2), (2, 2, 2, 2, 4)) for dwords in (0, 1)}
+    tiles = {(0, *shape, 1, 0) for shape in ((1, 1, 2, 2, 4), (2, 2, 2, 4, 2), (2, 2, 2, 2, 2))}
+    tiles |= {(1, *shape, dwords, 0) for shape in ((1, 1, 2, 2, 4), (2, 2, 2, 4, 2), (2, 2, 2, 2, 4)) for dwords in (0, 1)}
+    tiles |= {(1, 2, 2, 2, 2, 2, 0, 1)}                               # rows of less than a superstage
     assert build.check_product_waits() == tiles
 
 
