@@ -717,53 +717,77 @@ hipError_t launch_few(GemmParams p, hipStream_t stream) {
 //     INT4 / MXFP4 (4096, 4096, 64) 14.7 / 12.2 against 19.1 / 15.6 with a trip of the tile through LDS.  At d = 128
 //     against the tiles below: (4096, 4096) 15.9 / 13.2 against 16.3 / 14.4, (300, 14336) 7.7 / 6.7 against 8.2 / 7.6.
 //   few tiles of 32 x 32: the contraction cut among 8 waves, against 64 x 64 tiles.
-//     INT4, up to 512, and up to 900 for d >= 2048: (64, 4096, 4096) 4.1 against 8.2, (128, 4096, 4096) 6.0 against 8.5,
-//     (300, 1500, 1088) 4.0 against 5.0, (236, 2696, 6144) 10.5 against 12.4; 1024 tiles: (256, 4096, 4096) 10.2 against 9.2;
-//     800: (160, 5000, 1024) 5.0 against 4.9, (200, 3000, 2048) 5.3 against 5.8.
-//     MXFP4, up to 256: (64, 4096, 4096) 4.5 against 5.5, (64, 4096, 14336) 10.8 against 14.2; 384: (96, 4096, 8192) 10.9
-//     against 9.0; 512: (128, 4096, 4096) 6.7 against 5.8.  Rows of scale bytes that are no whole dwords, up to 512:
-//     (300, 1500, 1088) 3.7 against 4.6.
-//     One row of tiles, which fills half of the others: any number, (16, 65536, 4096) 30.0 / 32.0 against 36.6 / 32.8,
-//     (16, 28672, 8192) 25.5 / 29.5 against 29.4 / 29.3, (32, 65536, 4096) 33.3 / 36.5 against 38.0 / 35.3.
-//     Among 4 waves where there are more than 512 tiles and little to cut: (1, 65536, 2048) 12.3 / 11.8 against 14.2 / 13.6,
-//     (32, 32768, 1024) 6.1 / 5.8 against 7.0 / 6.5, (16, 65536, 4096) 29.7 / 34.5 against 30.0 / 32.0.
+//     INT4, up to 512: (64, 4096, 4096) 4.0 against 8.1, (300, 1500, 1088) 4.0 against 5.0; up to 768 (three workgroups on a
+//     CU) from d = 2048 on: (200, 3000, 2048) 5.3 against 5.9, (64, 12288, 4096) 8.7 against 9.2; past that (64, 13000, 4096)
+//     9.6 against 10.4 the other way, (128, 6400, 8192) 14.7 against 15.4.  Up to 900 where 64 x 64 tiles are more than
+//     a CU each: (96, 9568, 4096) 10.9 against 12.3.
+//     MXFP4, up to 256: (64, 4096, 4096) 4.1 against 5.3, (64, 4096, 14336) 10.7 against 14.2; 384: (96, 4096, 4096) 5.9
+//     against 6.3 the other way.  Rows of scale bytes that are no whole dwords, which tiles read through registers,
+//     up to 512 and d = 8192: (300, 1500, 1088) 3.7 against 4.6, d = 4000 6.7 against 7.0, (1848, 148, 7072) 9.6 against
+//     11.5; (300, 1500, 8224) 13.2 against 13.6 the other way, (128, 4000, 14368) 21.0 against 23.2.
+//     One row of tiles, which fills half of a 64 x 64 tile or less.  INT4 any number: (16, 65536, 4096) 30.1 against
+//     36.0, (32, 65536, 8192) 59.5 against 63.1.  MXFP4 has half the products to a load, and loads every row of A once per
+//     32 columns, so it goes by T d: (16, 65536, 4096) 32.1 against 32.6, (24, 65536, 4096) 34.1 against 34.7 the other way,
+//     (32, 65536, 2560) 19.9 against 21.0, (32, 65536, 8192) 60.9 against 74.9; with fewer than 65536 columns later,
+//     (32, 20480, 4096) 9.8 against 10.9, (32, 40960, 4096) 18.6 against 18.9, (24, 28672, 8192) 30.1 against 32.6 the other
+//     way, (16, 20480, 14336) 38.3 against 39.5; 257 .. 384 tiles, (32, 10000, 4096) 6.5 against 7.3, (1, 10000, 8192) 8.9
+//     against 10.3, d = 2048 4.7 against 4.7.  No whole dwords: (16, 65536, 2880) 22.9 against 22.8, (16, 65536, 4000) 33.0
+//     against 36.5 the other way; (16, 14336, 4000) 7.6 against 7.8, (32, 14336, 4000) 8.0 against 8.8 the other way.
+//     Among 4 waves where there are more than 512 tiles and little to cut: (16, 65536, 2048) INT4 13.3 against 14.8, MXFP4
+//     12.6 against 14.1, (16, 65536, 2880) INT4 20.7 against 22.1; no whole dwords, which a wave has more of then, MXFP4 d = 2400
+//     19.2 against 19.7, d = 2880 24.3 against 22.9.
 //   up to 128 tiles of 128 x 128: 64 x 64 tiles, which two workgroups a CU hold at once up to there, against
 //     128 x 128.  INT4 / MXFP4 (512, 4096, 4096) 13.7 / 10.7 against 15.5 / 12.5, d = 1024 6.2 / 5.4 against 7.3 / 6.5; the
 //     other way round with 130 tiles, (640, 3328, 4096) 15.5 / 12.1 against 19.1 / 13.7.
-//   more than 256 tiles of 128 x 128: 128 x 256, a sixth less to load per product.
-//     MXFP4: (2048, 4096), one round of them for two of 128 x 128, d = 1024 11.2 against 14.1, d = 2048 15.2 against 18.8,
-//     d = 4096 23.5 against 30; (4096, 6144, 2048) 43 against 55, (2048, 14336, 4096) 84 against 88, (4096, 4096, 2048)
-//     36.6 against 34.9; rounds that are not full: (3000, 3500, 2880) 38.5 against 39.6, d = 8192 69 against 67.  Where the
-//     output is not whole lines, from d = 2880 on and up to 512, (2177, 2177, 512) 9.4 against 12.2: (2048, 4000, 1024) 18.2 against 14.0, (3000, 3500, 1024) 19 - 24 against
-//     19.7 (one workgroup a CU stores at the end of its tile with nothing beside it).
-//     INT4, which has two workgroups of 128 x 128 a CU and loads less per product: only where some CUs have one of those
-//     and some two.  (2048, 2560, 4096) 23.4 against 25.3, (2177, 2177, 8192) 42.7 against 45.6, (2048, 3072, 8192) 43.7
-//     against 46.1, d = 4096 25.2 against 25.5, d = 2048 16.1 against 15.6; (2048, 4096, 4096) 31.0 against 29.8,
-//     (2048, 14336, 4096) 108 against 103, (4096, 4096, 8192) 103 against 105.
 //   MXFP4, d < 1024: 128 x 128, two stages and two workgroups a CU, against 128 x 256 (four stages and one):
 //     (4096, 4096) d = 160 15.6 against 20.0 (19.4), d = 320 17.1 against 21.3 (21.4), d = 640 18.4 against 25.4 (26.4),
-//     d = 992 22.2 against 28.5 (29.9); (3000, 3500, 256) 12.6 against 14.4 (16.6), d = 768 15.9 against 18.0 (19.9); (8192, 8192,
-//     512) 57.6 against 68.0 (88.4); (2048, 2048, 256) 6.5 against 7.2 (7.1), d = 992 7.8 against 8.8 (8.6).  One round of 128 x 256
-//     is as fast or faster up to d = 512: (2048, 4096) d = 160 9.4 against 8.7, d = 512 10.6 against 10.0, d = 768 11.3 against 11.3;
-//     (300, 14336, 512) 7.7 against 7.2.
+//     d = 992 22.2 against 28.5 (29.9); (3000, 3500, 256) 12.6 against 14.4 (16.6), d = 768 15.9 against 18.0 (19.9);
+//     (8192, 8192, 512) 57.6 against 68.0 (88.4); (2048, 2048, 256) 6.5 against 7.2 (7.1), d = 992 7.8 against 8.8 (8.6).
+//     One round of 128 x 256 is as fast or faster up to d = 512: (2048, 4096) d = 160 9.4 against 8.7, d = 512 10.6 against
+//     10.0, d = 768 11.3 against 11.3; (300, 14336, 512) 7.7 against 7.2.
+//   MXFP4: 128 x 256, a sixth less to load per product, against 128 x 128, both one workgroup a CU, by rounds of 256
+//     tiles.  In eighths of a round of 128 x 128: one that is not full 6 (fewer workgroups share L2 and power), 128 x 256 14
+//     and 10.  One round for two: (2177, 2177, 1024) 10.9 against 12.9, d = 8192 36.9 against 41.4, (2048, 4096, 4096) 25.7
+//     against 29.7; two for three the other way, (3000, 3500, 8192) 69.1 against 73.4, (2304, 4096, 8192) 60.3 against 68.1, (3072,
+//     4096, 2048) 25.0 against 25.2; two for four (4096, 4096, 2048) 33.5 against 34.3, d = 8192 84.3 against 92.4, (3968, 3969,
+//     2880) 43.2 against 52.4; three for five (4096, 5120, 2048) 37.1 against 39.6, (4096, 4097, 8192), as long by this count, 109 against 107;
+//     four for seven (2048, 14336, 4096) 89.9 against 91.8; (36000, 128, 4096), where the other half of a tile is empty, 43.9
+//     against 24.9.
+//   INT4, two workgroups of 128 x 128 a CU, which load less per product than that: 128 x 256 where some CUs have one of
+//     those and some two, the more of these the longer a row has to be, (2048, 2304, 4096) 23.7 against 28.7, (2048, 2560, 2880)
+//     20.9 against 21.8, (2048, 3072, 4096) 26.5 against 29.5, d = 2880 21.9 against 22.1, d = 2048 17.7 against 17.1, (2048,
+//     3584, 4096) 29.1 against 29.2, (2048, 4096, 4096) 32.4 against 31.4, d = 5120 36.0 against 36.1, d = 14336 90.5 against
+//     93.7, but not for up to 64 rows, (64, 65536, 8192) 77.6 against 72.4; and for the longest rows if the rounds are full:
+//     (4096, 4096, 4096) 62.2 against 59.8, d = 6144 82.2 against 82.5, d = 8192 107.2 against 107.9, d = 16384 199 against 204,
+//     (8192, 8192, 8192) 410 against 414; one and a half rounds (2048, 6144, 8192) 91 against 80.
 //   128 x 128: MXFP4 four stages in LDS and one workgroup a CU, against two stages (2048, 2048, 8192) 23.9 against
 //     27.8; INT4, whose stages take twice as long, two and two workgroups, (2048, 2048, 8192) 30.6 against 33.0.
 template <bool MX>
 hipError_t launch_gemm(const GemmParams& p, hipStream_t stream) {
     auto tiles = [&](int64_t m, int64_t n) { return ((p.T + m - 1) / m) * (((int64_t)p.N + n - 1) / n); };
     if (p.d <= (MX ? 128 : 96)) return launch_short<MX>(p, stream);
-    const int64_t small = tiles(32, 32);
+    const int64_t small = tiles(32, 32), square = tiles(128, 128), wide = tiles(128, 256);
+    const bool dwords = p.d % 128 == 0;                               // rows of scale bytes
     const bool one_row = p.T <= 32 && small <= (int64_t)1 << 22;      // (2^31 lanes; a grid takes less than 2^32)
-    if (small <= 256 || one_row || (small <= 512 && (!MX || p.d % 128 != 0)) || (!MX && small <= 900 && p.d >= 2048))
-        return small > 512 && p.d < 4096 ? launch_few<MX, 4>(p, stream) : launch_few<MX, 8>(p, stream);
-    if (tiles(128, 128) <= 128) return launch_tile<MX, 1, 1, 2, 2, 4, 2>(p, stream);
+    bool few = small <= 256;
+    if (!MX) few = few || one_row || small <= 512 || (p.d >= 2048 && small <= (tiles(64, 64) > 256 ? 900 : 768));
+    else if (!one_row) few = few || (small <= 512 && !dwords && p.d <= 8192);
+    else if (!(dwords && small <= 384 && p.d >= 3072))
+        few = few || p.T * p.d < (small >= 2048 ? (dwords ? 5 : 3) : (dwords ? 12 : 7)) << 14;
+    if (few) return small > 512 && p.d < (!MX || dwords ? 4096 : 2560) ? launch_few<MX, 4>(p, stream) : launch_few<MX, 8>(p, stream);
+    if (one_row || square <= 128) return launch_tile<MX, 1, 1, 2, 2, 4, 2>(p, stream);
     if constexpr (MX) {
-        if (p.d < 1024 && !(p.d <= 512 && tiles(128, 128) > 256 && tiles(128, 256) <= 256))
+        if (p.d < 1024 && !(p.d <= 512 && square > 256 && wide <= 256))
             return launch_tile_as<MX, 2, 2, 2, 2, 2, 2, false, true>(p, stream);
+        auto eighths = [](int64_t n, int whole, int part) { return n / 256 * whole + (n % 256 != 0 ? part : 0); };
+        if (eighths(wide, 14, 10) < eighths(square, 8, 6)) return launch_tile<MX, 2, 2, 2, 4, 2, 1>(p, stream);
+        return launch_tile<MX, 2, 2, 2, 2, 4, 1>(p, stream);
+    } else {
+        const int64_t rounds = (wide + 255) / 256;
+        if (square > 256 && (rounds == 1 ? p.T > 64 && p.d >= 9 * square : p.d >= 8192 && 16 * wide >= 15 * 256 * rounds))
+            return launch_tile<MX, 2, 2, 2, 4, 2, 1>(p, stream);
+        return launch_tile<MX, 2, 2, 2, 2, 2, 2>(p, stream);
     }
-    if (tiles(128, 128) > 256 && (MX ? p.d >= 2880 || p.d <= 512 || whole_lines(p) : tiles(128, 128) <= 384 && p.d >= 2880)) return launch_tile<MX, 2, 2, 2, 4, 2, 1>(p, stream);
-    if constexpr (MX) return launch_tile<MX, 2, 2, 2, 2, 4, 1>(p, stream);
-    else return launch_tile<MX, 2, 2, 2, 2, 2, 2>(p, stream);
 }
 
 }  // namespace

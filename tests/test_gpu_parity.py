@@ -595,6 +595,13 @@ def test_w4a4_products_of_few_tiles(T, N, d, fmt):
     test_w4a4_products_over_tiles_and_remainders(T, N, d, fmt)
 
 
+# one row of tiles on either side of the line (MXFP4), three and four of them to a CU (INT4), tiles that columns fill in part
+@pytest.mark.parametrize("T,N,d", [(32, 8224, 3200), (32, 8224, 3616), (32, 8224, 3552), (130, 4900, 2080), (96, 8320, 2080), (33000, 120, 1056)])
+@pytest.mark.parametrize("fmt", ["int4", "mxfp4"])
+def test_w4a4_products_where_the_choice_changes(T, N, d, fmt):
+    test_w4a4_products_over_tiles_and_remainders(T, N, d, fmt)
+
+
 # MXFP4 rows of less than a superstage: one stage to four, whole ones and cut ones, several rounds of tiles; the last one is not
 @pytest.mark.parametrize("T,N,d", [(2700, 3330, 160), (2700, 3330, 256), (1540, 1537, 288), (2700, 3330, 512), (1540, 1537, 544), (1540, 1537, 768),
                                    (2700, 3330, 992), (1540, 1537, 992), (1540, 1537, 1024)])
