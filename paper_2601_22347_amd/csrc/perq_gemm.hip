@@ -701,12 +701,10 @@ hipError_t launch_short(const GemmParams& all, hipStream_t stream) {
 template <bool MX, int KW>
 hipError_t launch_few(GemmParams p, hipStream_t stream) {
     constexpr uint32_t lds_bytes = KW * 64u * kStageBytes;
+    static_assert(lds_bytes <= 64u * 1024u, "what a kernel may ask for as it is");
     p.tiles_t = (uint32_t)((p.T + 31) / 32);
     p.tiles_n = (uint32_t)(((int64_t)p.N + 31) / 32);
     auto kern = gemm_few_kernel<MX, KW>;
-    int per_cu = 0;      // (raises the kernel's limit of dynamic LDS)
-    const hipError_t e = resident_blocks(reinterpret_cast<const void*>(kern), 64 * KW, lds_bytes, &per_cu);
-    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(p.tiles_t * p.tiles_n), dim3(64 * KW), lds_bytes, stream, p);
     return hipGetLastError();
 }
