@@ -301,6 +301,9 @@ perq_status_t perq_permute_rotate_quant_algo(const uint16_t* x_bf16, int64_t T, 
 /*
  * Test entry: the same gather + rotation device code as perq_permute_rotate_quant(_algo),
  * writing the pre-quantization values y = (XP R~)[T, d] as float (normalised by 1/sqrt(b)).
+ *   AUTO takes the kernel that it takes for the quantized call with the same T, d, ldx, b and permutation, so
+ * y is what the codes were made from, bit for bit; only for d = b = 1024 and the formats with one step per
+ * token may it be the other kernel (name one in both calls then).
  *   y   device, float [T, d], 16-byte aligned
  */
 perq_status_t perq_permute_rotate_f32(const uint16_t* x_bf16, int64_t T, int32_t d, int64_t ldx,

@@ -1296,7 +1296,9 @@ static bool folds(const ApplyParams& p, int out_kind) {
 // Which of the two general kernels takes a call: the number of elements from which on it is this one (0: always).
 // The choice must not depend on whether a permutation came with its prepared form (the outputs of the two calls
 // agree bit for bit), so where the form matters the line is that of the prepared call, and calls with the
-// permutation as given, whose table every launch builds, are ahead on the butterflies for some way past it.
+// permutation as given, whose table every launch builds, are ahead on the butterflies for some way past it.  Nor on
+// whether the output is fp32: the values that perq_permute_rotate_f32 gives are those that the codes of the same call
+// were made from (with a line of its own it gained 4 % at T = 2048, d = 8192, b = 32, and was further from the codes).
 // Figures: launches back to back on one GPU, butterfly / this kernel (/ as given) in us, INT4 where no format is
 // named.  What decides: this kernel's set-up (operand tables, two staging buffers) is paid back by long launches
 // only; for b <= 32 the butterflies have five stages fewer; for b >= 1024 its operand addresses cost 3 us.
@@ -1352,11 +1354,6 @@ static int64_t mfma_line(const ApplyParams& p, int out_kind) {
         // 17.8 / 16.2; d = 3072, b = 128, T = 32768 74 / 44; d = 2880, b = 32, T = 5832 12.2 / 10.5, T = 32768 56.8 / 41.2
         return exp2(small ? 23 : 22);
     }
-    // fp32 output never has a prepared form.  b = 32: d = 3072, T = 2730 11.7 / 13.8, T = 5461 22.1 / 21.3; d = 8192, T = 2048
-    // 21.0 / 22.0, T = 4096 37.1 / 37.1; d = 14336, T = 585 13.6 / 19.0, T = 2340 38.1 / 38.4, T = 4681 66.3 / 65.9; d = 28672,
-    // T = 2340 69.9 / 73.0.  b = 2048: d = 8192, T = 2048 23.6 / 24.7; d = 14336, T = 585 19.7 / 21.2, T = 1170 27.3 / 25.6 (b = 4096: one stage more).
-    if (out_kind == OUT_F32 && p.d != kTile)
-        return exp2((one_tile ? 24 : large ? (two_tiles ? 25 : 24) : two_tiles ? 25 : p.d <= 4 * kTile ? 26 : 27) - (p.b == 4096 ? 1 : 0));
     // T = 512, b = 64 5.3 / 5.7, T = 1024 7.0 / 5.8; b = 4096, T = 16 6.5 / 6.3
     if (p.d == kTile) return large ? 0 : exp2(21) + 1;
     // No prepared form: T = 4096, d = 3072, b = 16 10.9 / 12.3, T = 8192 18.5 / 16.9; b = 128, T = 2048 9.7 / 10.0, T = 4096

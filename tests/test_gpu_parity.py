@@ -1006,6 +1006,30 @@ def test_quant_error_of_codes_scales_and_rows_that_are_not_aligned():
             assert torch.equal(got, want)
 
 
+# long and short calls on either side of the lines between the two kernels, rows of one tile, two, three and more, folded, ragged
+@pytest.mark.parametrize("T,d,b", [(2048, 8192, 32), (1024, 14336, 128), (600, 14336, 128), (40, 28672, 64), (1600, 9728, 16), (6000, 3072, 128),
+                                   (900, 16384, 2048), (300, 12288, 1024), (2048, 4096, 64), (4096, 2048, 64), (1500, 11008, 256)])
+@pytest.mark.parametrize("fmt", ["int4", "mxfp4"])
+def test_fp32_output_is_what_the_codes_were_made_from(T, d, b, fmt):
+    """AUTO takes one of the two kernels for both calls of an input."""
+    torch = _torch()
+    print(f"[case] one kernel T={T} d={d} b={b} fmt={fmt}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    x = torch.randn((T, d), device="cuda", generator=g).to(torch.bfloat16)
+    perm = torch.randperm(d, device="cuda", generator=g).to(torch.int32)
+    for p in (perm, None):
+        codes, scales = binding.perq_permute_rotate_quant(x, p, b, fmt)
+        y = binding.perq_permute_rotate_f32(x, p, b)
+        same = []
+        for algo in ("butterfly", "mfma") if d % 512 == 0 else ("butterfly",):
+            c, s = binding.perq_permute_rotate_quant(x, p, b, fmt, algo=algo)
+            same.append((torch.equal(c, codes) and torch.equal(s, scales), torch.equal(binding.perq_permute_rotate_f32(x, p, b, algo=algo), y)))
+        if d % 512 == 0:
+            assert (True, True) in same, same
+        else:                                     # (no explicit call of the other kernel: it is the one that the butterflies are not)
+            assert same[0][0] == same[0][1] or fmt == "mxfp4", same
+
+
 # ---- the ticket counters under concurrency and graph replay ------------------------------------------
 def test_run_time_schedule_on_two_streams_and_in_a_graph():
     """Every stream has a counter set of its own, so launches that overlap on two streams never draw
