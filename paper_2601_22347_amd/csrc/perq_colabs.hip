@@ -6,8 +6,8 @@
 // 32 lanes own 8 adjacent columns each (one 16-byte bf16 load per row), the eight groups of 32 take
 // every eighth row, and their sums meet in LDS (in double).  It writes one partial sum per column
 // and slice, in double.  Pass 2 adds a column's S partials in a fixed order and divides by M; a single
-// slice (up to 128 rows, or d > 131072) writes the means itself, and up to 64 slices the last workgroup of a column
-// tile does it, in the same launch.  The only atomics count arrivals: the result is independent of scheduling.
+// slice (up to 128 rows, or d > 131072) writes the means itself, and up to 48 slices the last workgroup of a column
+// tile may do it, in the same launch.  The only atomics count arrivals: the result is independent of scheduling.
 // Rounding: fp32 is used inside a run of at most max_run(M, d) rows of one lane only, so a run's sum is off
 // by less than max_run(M, d) - 1 roundings of non-negative terms, and the mean is rounded once more: the
 // relative error of a_i is below (max_run(M, d) + 1) * 2^-24.
@@ -44,14 +44,15 @@ constexpr int kMostBlocks = 1024;                             // workgroups of a
 // them up, in the second pass's order.  Arrivals are counted per tile and stream (a set belongs to one stream, whose
 // launches do not overlap, and the last arrival puts the count back to zero); a stream without a set and a launch
 // that is being captured take two launches.  Partials and counts go past the L2 of their XCD.
-//   Up to 32 slices, which a lane of the last workgroup reads all at once, and up to 64 of a small input, whose second launch
-// takes the host longer than the device.  Launches back to back, two / one: M = 129,
-// d = 1536 7.0 / 4.7 us, M = 694, d = 6144 7.1 / 5.5, M = 1838, d = 7168 9.0 / 8.2, M = 4096, d = 8192 13.7 / 13.0, M = 3000,
-// d = 2048 (47 slices) 8.3 / 8.4, M = 4000, d = 1536 (63) 7.4 / 7.8, where the second launch costs the host 3 us; M = 7002,
-// d = 1536 (84) 9.2 / 10.1, M = 15310, d = 1024 (128) 9.8 / 13.4; M = 6572, d = 3584 (36) 12.0 / 13.3.
+//   Up to 32 slices, which a lane of the last workgroup reads all at once, and up to 48 of inputs that are read in less
+// time than the host takes for a second launch (2 - 3 us).  Two launches / one, with the host ahead of the device (back to
+// back): M = 129, d = 8192 5.0 / 4.1 us (6.8 / 4.3), M = 2048, d = 4096 (32 slices) 7.8 / 6.9 (7.6 / 6.6), M = 4096, d = 8192 16.0 /
+// 15.3; M = 2100, d = 512 (33) 5.9 / 5.5 (6.7 / 5.3), M = 3000, d = 1024 (47) 6.3 / 6.2 (6.8 / 6.0), M = 2500, d = 1536 (40) 5.8 / 5.8
+// (6.8 / 5.7).  Past these: M = 4096, d = 1024 (64) 5.9 / 6.6 (6.8 / 6.4), M = 2100, d = 2048 (33) 6.5 / 6.8 (6.8 / 6.5), M = 3000,
+// d = 1536 (47) 7.6 / 7.9 (7.3 / 7.6), M = 3400, d = 2816 (46) 8.4 / 9.3 (8.1 / 9.0), M = 4096, d = 3584 (36) 10.5 / 10.7.
 constexpr int kWays = 16;
-constexpr int kOneLaunchSlices = 64, kOneLaunchTiles = 128;
-constexpr int64_t kOneLaunchSmall = (int64_t)1 << 23;         // elements
+constexpr int kOneLaunchSlices = 48, kOneLaunchTiles = 128;
+constexpr int64_t kOneLaunchSmall = (int64_t)1 << 22;         // elements
 __device__ uint32_t arrivals[schedule::kSets][kOneLaunchTiles][32];        // a count per cache line
 // (apart from the row schedule's sets: a stream that only computes statistics takes none of those)
 StreamSets arrival_sets;
