@@ -1331,8 +1331,8 @@ static int64_t mfma_line(const ApplyParams& p, int out_kind) {
     const bool one_tile = p.d <= kTile, two_tiles = p.d > kTile && p.d <= 2 * kTile;
     if (!perm) {
         // d = 8192, b = 4096: T = 16 5.6 / 9.0, T = 1024 10.7 / 11.5, T = 2048 20.8 / 16.4; d = 16384, b = 1024, T = 512
-        // 9.4 / 11.7; d = 12288, T = 1024 15.3 / 14.7
-        if (large) return exp2(23) + 1;
+        // 9.3 / 11.7, T = 1024 18.2 / 16.5; d = 12288, T = 600 11.4 / 11.9, T = 1033 17.4 / 14.8
+        if (large && p.d <= 4 * kTile) return exp2(23) + 1;
         // Two tiles: b = 32, d = 5120, T = 1639 6.8 / 8.6, T = 3277 11.9 / 11.8, T = 4916 14.7 / 14.3; d = 8192, T = 1025
         // 6.5 / 7.5, T = 2049 10.9 / 11.2, T = 4097 18.6 / 18.6 (MXFP4, T = 3072 11.2 / 12.9, T = 4096 14.9 / 15.9: the
         // butterflies keep a group's maximum in the lane).  b = 128: T = 1639 8.8 / 9.7, T = 3277 14.6 / 13.2.
@@ -1340,15 +1340,38 @@ static int64_t mfma_line(const ApplyParams& p, int out_kind) {
         // Ragged rows of more tiles: b = 32, d = 11008, T = 762 7.2 / 7.8, T = 1524 12.6 / 11.7; d = 15904, T = 527
         // 7.4 / 8.4, T = 1054 11.6 / 12.1; b = 128, d = 11008, T = 381 6.7 / 6.8, T = 762 8.7 / 8.3.
         if (ragged && !one_tile) return exp2(small ? 24 : 23);
-        // Three tiles and more.  b = 32: d = 16384, T = 512 6.7 / 7.6, T = 1024 10.5 / 11.4, T = 2048 18.6 / 19.3; d = 14336, T = 1024
-        // 10.2 / 10.6; d = 12288, T = 1365 12.4 / 12.2, T = 2730 19.7 / 18.3; d = 32768, T = 256 7.5 / 8.5, T = 1024 19.3 / 19.2.
-        // b = 128: d = 16384, T = 256 5.5 / 6.4, T = 512 7.6 / 7.9, T = 1024 13.7 / 12.1; d = 14336, T = 512 7.5 / 7.5, T = 1024
-        // 12.7 / 11.4; d = 32768, T = 256 8.4 / 8.9, T = 512 13.1 / 12.1.
-        // A third tile that is filled for a small part: d = 9728, b = 32, T = 1530 10.3 / 9.8, b = 256, T = 791 10.2 / 9.0; d = 8704,
-        // b = 128, T = 512 6.3 / 6.7, T = 1024 11.5 / 9.5.  b = 512: d = 14336, T = 531 10.7 / 10.1.
+        // Three tiles and more, b = 32 (b = 16; MXFP4, which the butterflies scale without leaving the lane).  How the waves of
+        // both kernels fill a CU changes with the width, and with it the line, which is one for all formats:
+        //   d = 8704, T = 723 7.6 / 7.3 (7.4 / 7.5; 6.6 / 7.0), T = 965 9.5 / 8.5 (9.0 / 8.6; 8.7 / 8.2); d = 10240, T = 820 9.3 / 8.7
+        //     (8.8 / 8.8; 8.5 / 8.4), T = 1230 10.4 / 9.5 (10.2 / 9.7; 9.3 / 8.9)
+        //   d = 11264, T = 745 6.9 / 8.0 (6.7 / 7.6; 6.2 / 7.1), T = 1489 12.0 / 11.6 (11.4 / 11.6; 10.3 / 10.7)
+        //   d = 12288, T = 1365 12.2 / 11.8 (11.9 / 11.8; 10.6 / 10.8), T = 2048 15.5 / 14.6 (14.5 / 14.7; 14.4 / 13.7)
+        //   d = 14336, T = 1170 10.8 / 11.0 (10.3 / 11.1; 9.7 / 10.4), T = 1755 14.3 / 14.3 (13.9 / 14.4; 13.3 / 13.9), T = 2340
+        //     20.1 / 18.1 (19.1 / 18.0; 17.8 / 17.7); d = 13824, T = 1519 12.8 / 13.0 (12.3 / 13.1; 12.0 / 12.6)
+        //   d = 16384, T = 1024 10.0 / 11.1 (9.7 / 11.2; 9.0 / 10.4), T = 2048 18.4 / 18.1 (17.3 / 18.2; 16.5 / 17.9)
+        //   d = 20480, T = 819 13.6 / 13.4 (12.9 / 13.4; 11.7 / 12.8), T = 1638 21.6 / 20.3 (20.8 / 20.5; 19.0 / 20.1)
+        //   d = 22528, T = 932 14.4 / 14.6 (13.7 / 14.5; 13.4 / 13.9), T = 1489 20.1 / 19.5 (19.6 / 19.7; 18.5 / 19.5)
+        //   d = 24576, T = 682 12.0 / 12.4 (11.6 / 12.4; 10.4 / 11.8), T = 1365 21.3 / 19.8 (20.4 / 19.7; 19.0 / 19.4)
+        //   d = 25600, T = 655 13.3 / 12.4 (12.9 / 12.4; 11.2 / 12.0); d = 28672, T = 585 13.8 / 12.5 (13.1 / 12.5; 11.6 / 12.4)
+        //   d = 32768, T = 512 11.0 / 11.4 (10.5 / 11.3; 10.1 / 11.0), T = 1024 19.0 / 18.6 (18.4 / 18.4; 18.0 / 18.5)
+        // b >= 64, by rows: butterflies have a workgroup to a row, so their time goes up in steps of 256 rows, or of 512
+        // where two workgroups share a CU.  T = 512 and 513 (T = 256 and 257 past six tiles):
+        //   d = 9728, b = 64 6.0 / 6.5, 7.5 / 6.9; b = 512 6.9 / 7.6, 9.2 / 8.4
+        //   d = 12288, b = 64 6.7 / 6.9, 7.4 / 7.3; b = 512 8.1 / 8.0, 9.5 / 8.7
+        //   d = 14336, b = 64 7.0 / 7.1, 7.5 / 7.5, T = 858 10.9 / 10.5; b = 128 7.6 / 7.3, 8.2 / 7.8; d = 16384, b = 64 7.2 / 7.7,
+        //     7.6 / 8.0, T = 775 10.6 / 10.7; b = 128 7.6 / 7.8, 8.5 / 8.4
+        //   d = 20480, b = 128 10.0 / 10.1, 12.8 / 11.6; b = 512 11.4 / 12.3, 14.9 / 15.1; b = 1024 12.6 / 13.8, 16.5 / 16.0; b = 4096
+        //     T = 256 9.1 / 11.2, T = 257 14.6 / 14.3, T = 513 21.1 / 17.8
+        //   d = 24576, b = 128 10.6 / 10.8, 13.4 / 12.2; d = 25600, b = 64 7.2 / 7.6, 10.3 / 9.0; b = 512 8.5 / 9.0, 12.9 / 11.7
+        //   d = 32768, b = 64 7.8 / 8.4, 10.8 / 9.9; b = 4096 11.9 / 12.3, 18.7 / 15.3
         if (p.d > 2 * kTile) {
-            if (small) return p.d < 3 * kTile ? 3 * exp2(22) : exp2((p.d & (p.d - 1)) == 0 ? 25 : 24);
-            return p.d < 3 * kTile || p.b >= 256 ? 3 * exp2(21) : exp2(23);
+            if (!small) {
+                if (p.d > 6 * kTile || p.b == 4096) return 257 * (int64_t)p.d;
+                return p.b == 64 && p.d > 3 * kTile && p.d <= 4 * kTile ? 3 * exp2(22) : 513 * (int64_t)p.d;
+            }
+            if (2 * p.d <= 5 * kTile) return exp2(23);
+            if (p.d > 3 * kTile && p.d < 4 * kTile) return 3 * exp2(23);
+            return exp2(p.d == 4 * kTile || p.d == 8 * kTile || (p.d > 5 * kTile && p.d <= 6 * kTile) ? 25 : 24);
         }
         // d = 4096, b = 128, T = 16 3.8 / 4.7, T = 1024 5.1 / 5.2, T = 2048 7.1 / 6.5; b = 16, T = 2048 5.8 / 6.1, T = 8192
         // 17.8 / 16.2; d = 3072, b = 128, T = 32768 74 / 44; d = 2880, b = 32, T = 5832 12.2 / 10.5, T = 32768 56.8 / 41.2
@@ -1365,21 +1388,33 @@ static int64_t mfma_line(const ApplyParams& p, int out_kind) {
     // 27.0 / 24.8; d = 11008, b = 256, T = 762 16.1 / 16.3, T = 16384 212 / 116; b = 128, T = 1524 24.5 / 19.6.  More:
     // b = 32, d = 17440, T = 480 16.6 / 16.2, T = 961 27.3 / 22.2; b = 128, d = 28800, T = 291 24.7 / 18.3.
     if (ragged) return exp2((small ? 24 : 23) + (two_tiles ? 2 : p.d <= 4 * kTile ? 1 : 0));
-    // butterflies of workgroups of 1024 lanes: T = 16, d = 28672 11.8 / 9.1
-    if (p.d > 4 * kTile) return 0;
-    // Prepared: d = 6144, b = 2048, T = 256 6.4 / 8.0, T = 512 8.4 / 8.1; d = 16384, b = 4096, T = 2 8.8 / 9.0, T = 256 9.8 / 9.8, T = 512
-    // 15.5 / 12.5; d = 12288, b = 1024, T = 256 7.9 / 8.9, T = 512 12.4 / 11.1 (as given 12.0 / 16.3, T = 256 7.9 / 12.2)
-    if (large) return exp2(two_tiles ? 21 : 22) + 1;
+    // Five tiles and more, prepared: up to six by rows, as below.  T = 16, 256, 257, 512, 513:
+    //   b = 128: d = 17920 7.8 / 8.5, 9.0 / 9.5, 12.0 / 11.4, 13.2 / 12.7, 16.0 / 14.5; d = 24576 8.7 / 9.0, 10.4 / 10.1, 13.5 / 12.4;
+    //     d = 25600 9.9 / 9.1, 11.4 / 10.2, 15.4 / 12.6; d = 28672 10.1 / 9.2
+    //   b = 32: d = 17920 7.1 / 8.2, 8.2 / 9.1, 10.5 / 10.7, 11.4 / 12.0, 13.9 / 13.6; d = 24576 8.2 / 8.8, 9.6 / 9.7, 12.0 / 11.8, 13.6 /
+    //     13.6, 16.0 / 14.9; d = 25600 9.1 / 8.8, 10.4 / 9.8, 13.6 / 12.0
+    //   b = 1024: d = 20480 9.4 / 9.3, 10.9 / 10.2, 15.1 / 12.3
+    if (p.d > 4 * kTile) return p.d > 6 * kTile || large ? 0 : (small ? 513 : 257) * (int64_t)p.d;
+    // Three and four, by rows: the butterflies' time goes up at 257 and 513 rows as above.  A line lies where the
+    // prepared call gains enough to set against the 4 us that a call as given loses.  T = 256, 257, 512, 513, prepared:
+    //   b = 1024: d = 10240 7.8 / 8.7, 9.6 / 9.3, 10.5 / 10.4, 14.2 / 11.0; d = 12288 8.0 / 8.9, 11.0 / 9.6, 12.4 / 11.0,
+    //     14.2 / 11.4 (as given T = 256 12.2, T = 512 16.3); d = 16384 8.7 / 9.4, 12.4 / 10.5, 13.9 / 12.0, 15.6 / 12.5; b = 4096 9.9 / 9.9, 14.5 / 11.0
+    //   b = 128: d = 9728 6.8 / 8.2, 8.2 / 8.9, 9.0 / 9.8, 12.1 / 10.2; d = 12288 7.0 / 8.4, 9.3 / 9.3, 10.4 / 10.2,
+    //     11.6 / 10.6; d = 14336 7.4 / 8.7, 10.0 / 9.8, 11.4 / 10.9 (as given 15.6), 12.4 / 11.5; b = 512 8.1 / 9.4, 10.8 / 10.4, 12.2 / 11.9, 13.5 / 12.6
+    //   b = 32: d = 9728 6.2 / 7.9, 7.4 / 8.8, 8.1 / 9.5, 10.8 / 9.8; d = 12288 6.5 / 8.2, 8.2 / 9.0, 9.6 / 10.0, 10.1 / 10.3, T = 690
+    //     11.0 / 11.3, T = 1033 14.4 / 13.7; d = 16384 7.2 / 8.7, 9.7 / 9.8, 11.2 / 11.0, 11.6 / 11.6, T = 775 15.5 / 14.4, T = 1031
+    //     16.9 / 15.7 (T = 1024 15.5 / 15.8, as given 18.9)
+    // Two tiles: d = 6144, b = 2048, T = 256 6.4 / 8.0, T = 512 8.4 / 8.1
+    if (!two_tiles) {
+        const bool a_little = 2 * p.d <= 5 * kTile;              // of the third tile
+        return (large && !a_little ? 257 : small && !a_little ? 1025 : 513) * (int64_t)p.d;
+    }
+    if (large) return exp2(21) + 1;
     // Two tiles, prepared / as given.  b = 128: d = 8192, T = 513 8.2 / 8.4 / 11.9, T = 1025 10.9 / 10.3 / 13.6.  b = 32: d = 8192,
     // T = 1025 9.9 / 9.8 / 13.4, T = 2049 14.6 / 13.9 / 16.4; d = 7168, T = 2341 14.6 / 13.1 / 15.5; narrower rows leave
     // more of the second tile empty, d = 6144, T = 2731 13.8 / 14.5 / 16.8, T = 4096 17.7 / 17.7 / 20.0, d = 5120,
     // T = 3277 14.3 / 14.4 / 17.7, T = 4916 19.4 / 19.2 / 21.8.
-    if (two_tiles) return small ? (p.d <= 6144 ? 3 * exp2(23) : exp2(24)) : exp2(23);
-    // Three and four tiles, prepared / as given.  b = 32: d = 12288, T = 512 9.6 / 10.0 / 14.5, T = 1024 13.7 / 14.0 / 17.3, T = 1536
-    // 17.3 / 16.4; d = 16384, T = 1024 15.5 / 15.8 / 18.9.  b = 128: d = 14336, T = 256 7.3 / 8.9 / 11.3, T = 512 11.3 / 11.0 /
-    // 15.6, T = 1024 16.8 / 15.5 / 19.1; b = 512, T = 512 12.2 / 11.9.  A third tile that is filled for a small part: d = 9728,
-    // b = 128, T = 559 13.6 / 11.5.
-    return exp2((small ? 24 : 23) - (p.d < 3 * kTile ? 1 : 0));
+    return small ? (p.d <= 6144 ? 3 * exp2(23) : exp2(24)) : exp2(23);
 }
 
 bool mfma_preferred(const ApplyParams& p, int out_kind) { return p.T * (int64_t)p.d >= mfma_line(p, out_kind); }

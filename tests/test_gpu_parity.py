@@ -428,6 +428,16 @@ def test_few_rows_and_many_take_either_kernel(d, b, rows, with_perm, fmt):
                 assert torch.equal(p, q)
 
 
+# the lines of rows of three tiles and more
+@pytest.mark.parametrize("d,b,rows,with_perm", [(12288, 1024, 257, True), (14336, 128, 513, True), (9728, 64, 513, True), (9728, 16, 513, True),
+                                                (12288, 16, 1025, True), (14336, 256, 513, False), (16384, 64, 768, False), (9728, 32, 863, False),
+                                                (22528, 2048, 513, False), (28672, 64, 257, False), (20480, 4096, 257, False), (25600, 32, 656, False),
+                                                (17920, 64, 257, True), (24576, 32, 513, True), (20480, 1024, 3, True), (25600, 16, 3, True)])
+@pytest.mark.parametrize("fmt", ["int4", "mxfp4"])
+def test_few_wide_rows_and_many_take_either_kernel(d, b, rows, with_perm, fmt):
+    test_few_rows_and_many_take_either_kernel(d, b, rows, with_perm, fmt)
+
+
 # ---- a kernel chosen by the caller: a row's bits do not depend on how many rows come with it ------------
 @pytest.mark.parametrize("d,b", [(1024, 64), (2048, 2048), (3072, 32), (4096, 128), (4096, 4096), (8192, 32), (14336, 512), (20480, 16)])
 @pytest.mark.parametrize("algo", ["butterfly", "mfma"])
