@@ -44,15 +44,17 @@ constexpr int kMostBlocks = 1024;                             // workgroups of a
 // them up, in the second pass's order.  Arrivals are counted per tile and stream (a set belongs to one stream, whose
 // launches do not overlap, and the last arrival puts the count back to zero); a stream without a set and a launch
 // that is being captured take two launches.  Partials and counts go past the L2 of their XCD.
-//   Up to 32 slices, which a lane of the last workgroup reads all at once, and up to 48 of inputs that are read in less
-// time than the host takes for a second launch (2 - 3 us).  Two launches / one, with the host ahead of the device (back to
-// back): M = 129, d = 8192 5.0 / 4.1 us (6.8 / 4.3), M = 2048, d = 4096 (32 slices) 7.8 / 6.9 (7.6 / 6.6), M = 4096, d = 8192 16.0 /
-// 15.3; M = 2100, d = 512 (33) 5.9 / 5.5 (6.7 / 5.3), M = 3000, d = 1024 (47) 6.3 / 6.2 (6.8 / 6.0), M = 2500, d = 1536 (40) 5.8 / 5.8
-// (6.8 / 5.7).  Past these: M = 4096, d = 1024 (64) 5.9 / 6.6 (6.8 / 6.4), M = 2100, d = 2048 (33) 6.5 / 6.8 (6.8 / 6.5), M = 3000,
-// d = 1536 (47) 7.6 / 7.9 (7.3 / 7.6), M = 3400, d = 2816 (46) 8.4 / 9.3 (8.1 / 9.0), M = 4096, d = 3584 (36) 10.5 / 10.7.
+//   Up to 32 slices, which a lane of the last workgroup reads all at once, and of inputs that are read in about the
+// time that the host takes for a second launch (2 - 3 us) up to 48, or 40 of few columns.  Two launches / one, us with the
+// host ahead of the device (back to back):
+//   M = 129, d = 8192 (3 slices) 5.0 / 4.1 (6.8 / 4.3), M = 2048, d = 4096 (32) 7.8 / 6.9 (7.6 / 6.6), M = 4096, d = 8192 (16)
+//   16.0 / 15.3; M = 2500, d = 768 (40) 5.5 / 5.6 (6.2 / 5.4), M = 2900, d = 1568 (46) 6.1 / 6.2 (7.0 / 5.9), M = 2500,
+//   d = 2304 (40) 6.7 / 6.6 (7.3 / 6.4), M = 2900, d = 2816 (46) 8.0 / 8.0 (7.8 / 7.8), M = 2500, d = 3072 (40) 7.6 / 7.4;
+//   past these M = 3072, d = 768 (48) 5.6 / 6.0 (6.2 / 5.7), M = 4096, d = 1024 (64) 6.0 / 6.7 (7.1 / 6.4), M = 4096, d = 2304
+//   (56) 8.7 / 9.4 (8.4 / 9.1), M = 3400, d = 2816 (46) 8.4 / 9.2 (8.1 / 8.8), M = 4096, d = 3584 (36) 10.5 / 10.8.
 constexpr int kWays = 16;
-constexpr int kOneLaunchSlices = 48, kOneLaunchTiles = 128;
-constexpr int64_t kOneLaunchSmall = (int64_t)1 << 22;         // elements
+constexpr int kOneLaunchTiles = 128;
+int one_launch_slices(int64_t M, int32_t d) { return M * (int64_t)d > ((int64_t)1 << 23) ? 2 * kWays : d >= 1536 ? 48 : 40; }
 __device__ uint32_t arrivals[schedule::kSets][kOneLaunchTiles][32];        // a count per cache line
 // (apart from the row schedule's sets: a stream that only computes statistics takes none of those)
 StreamSets arrival_sets;
@@ -283,8 +285,7 @@ perq_status_t colabs_launch(const uint16_t* x_bf16, int64_t M, int32_t d, int64_
                 : M * (int64_t)d * 2 >= kStreamBytes ? colabs_partial_kernel<MAXSTAT, false, true>
                                                      : colabs_partial_kernel<MAXSTAT, false, false>;
     const uint32_t tiles = (uint32_t)pl.col_tiles, blocks = tiles * (uint32_t)pl.slices;
-    const bool together = pl.slices > 1 && pl.col_tiles <= kOneLaunchTiles &&
-                          (pl.slices <= 2 * kWays || (pl.slices <= kOneLaunchSlices && M * (int64_t)d <= kOneLaunchSmall));
+    const bool together = pl.slices > 1 && pl.slices <= one_launch_slices(M, d) && pl.col_tiles <= kOneLaunchTiles;
     const int set = together ? arrival_sets.of(stream) : -1;
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), 0, stream, x_bf16, M, d, ldx, pl.rows_per_slice, tiles,
                        ldx % 64 != 0 ? blocks : 0u, pl.slices == 1 ? nullptr : part, out, (float)M, pl.slices, set);

@@ -689,9 +689,9 @@ def test_butterflies_few_rows_to_a_workgroup(d, b, perm):
         assert torch.equal(binding.perq_block_diagnostics(x[:T], pt, b), st[:T])
 
 
-# one launch (2, 3, 17, 32, 33, 48 slices of rows) and two (49, 64, 65), one tile of columns, a cut one and as many as fit
-@pytest.mark.parametrize("M,d", [(129, 256), (192, 8), (1088, 520), (2048, 512), (2049, 504), (3072, 520), (3073, 520), (4096, 512), (4097, 512),
-                                 (300, 32768), (300, 32776), (4000, 4104), (2060, 2040)])
+# one launch (2, 3, 17, 32, 33, 40, 48 slices of rows) and two (41, 49, 64, 65), one tile of columns, a cut one and as many as fit
+@pytest.mark.parametrize("M,d", [(129, 256), (192, 8), (1088, 520), (2048, 512), (2049, 504), (2560, 520), (2561, 520), (3072, 1544), (3073, 1544),
+                                 (4096, 512), (4097, 512), (300, 32768), (300, 32776), (4000, 4104), (2200, 3840)])
 @pytest.mark.parametrize("stat", ["mean", "absmax"])
 def test_column_statistics_in_one_launch(M, d, stat):
     """Against 64 bits; every call gives the same bits, with other streams' calls beside it and replayed from a graph
