@@ -31,8 +31,9 @@ namespace {
 __device__ __forceinline__ uint32_t granule_slot(uint32_t g) { return g ^ ((g >> 3) & 3u); }
 
 // What a launch hands over, 88 bytes.  A launch with up to 96 bytes of arguments takes 2.9 us of the host, one with 128
-// 3.6 and with 512 4.3, and the kernels here are over in 4 - 5 us for a few rows: ApplyParams, the geometry and the hidden
-// arguments that gridDim brings were 408 bytes (T = 1, d = 4096, P = I 4.0 -> 2.8 us of the host for a call of the library, 4.2 -> 3.4 from launch to launch).
+// 3.6 and with 512 4.3, and the kernels here are over in 4 - 5 us for a few rows: ApplyParams, the geometry and the
+// hidden arguments that gridDim brings were 408 bytes (T = 1, d = 4096, P = I 4.0 -> 2.8 us of the host for a call of the
+// library, 4.2 -> 3.4 from launch to launch).
 struct BflyArgs {
     const uint16_t* x;
     const int32_t* perm;
@@ -130,10 +131,8 @@ butterfly_kernel(BflyArgs a) {
                 src_addr[4 * q + 3] = address(e4.w);
             }
         }
-        if (blockIdx.x < ngroups) load_group(blockIdx.x, stage);
-    } else {
-        if (blockIdx.x < ngroups) load_group(blockIdx.x, stage);
     }
+    if (blockIdx.x < ngroups) load_group(blockIdx.x, stage);
 
     for (int64_t grp = blockIdx.x; grp < ngroups; grp += a.grid) {
         const int64_t row = grp * g.rows + r;
@@ -395,8 +394,8 @@ hipError_t launch_butterfly_out(const ApplyParams& p, hipStream_t stream) {
     int threads;
     if (pow2 && g.nt <= 256) {
         g.rows = 256 / g.nt;
-        // Few rows with a permutation: no more to a workgroup than fill a wave, until every CU has a workgroup.  The waves of
-        // one share an address unit, which takes a lane's entries of the permutation line by line (d = 4096: T = 16 5.2 -> 4.5 us,
+        // Few rows with a permutation: no more to a workgroup than fill a wave, until every CU has a workgroup.  The waves
+        // of one share an address unit, which takes a lane's entries of the permutation line by line (d = 4096: T = 16 5.2 -> 4.5 us,
         // T = 256 5.4 -> 4.8; d = 1024, T = 300 5.5 -> 4.5; P = I has nothing of the kind, T = 400 4.4 -> 4.8).
         const int least = g.nt >= 64 ? 1 : 64 / g.nt;
         if (p.perm != nullptr) {

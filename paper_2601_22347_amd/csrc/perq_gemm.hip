@@ -481,8 +481,8 @@ gemm_tile_kernel(GemmParams p) {
 //   Bound by the loads.  Straight to registers, nothing is used twice either, but an instruction then meets 32 rows,
 // which takes the address unit four times as long as eight rows of a line each, and that bound the kernel:
 // INT4 / MXFP4 (3, 517, 28672) 18.8 / 25.2 -> 10.4 / 12.2 us, (64, 4096, 8192) 10.1 / 12.9 -> 6.1 / 7.0, (16, 4096, 4096)
-// 5.0 / 5.4 -> 3.8 / 4.0 (registers, then LDS).  A second buffer per wave leaves one workgroup a CU instead of two: (123, 2665,
-// 12288) INT4 14.4 instead of 11.4; sixteen waves: (64, 4096, 14336) 8.9 instead of 8.2.
+// 5.0 / 5.4 -> 3.8 / 4.0 (registers, then LDS).  A second buffer per wave leaves one workgroup a CU instead of two:
+// (123, 2665, 12288) INT4 14.4 instead of 11.4; sixteen waves: (64, 4096, 14336) 8.9 instead of 8.2.
 template <bool MX, int KW>
 __global__ void __launch_bounds__(64 * KW)
 gemm_few_kernel(GemmParams p) {
@@ -502,7 +502,8 @@ gemm_few_kernel(GemmParams p) {
     const rsrc_t wbuf = buffer_of(p.w_codes + (int64_t)n0 * row_bytes, (last_n + 1u) * row_bytes);
     const uint8_t* const as = static_cast<const uint8_t*>(p.a_scales) + (MX ? (t0 + ((uint32_t)i < last_t ? (uint32_t)i : last_t)) * nb : 0);
     const uint8_t* const ws = static_cast<const uint8_t*>(p.w_scales) + (MX ? (int64_t)(n0 + ((uint32_t)i < last_n ? (uint32_t)i : last_n)) * nb : 0);
-    // a load fills 8 rows: lane l brings the granule of place l & 7 of row l >> 3 (place q of row r holds granule q ^ ((r >> 1) & 7))
+    // a load fills 8 rows: lane l brings the granule of place l & 7 of row l >> 3 (place q of row r holds granule
+    // q ^ ((r >> 1) & 7))
     uint32_t a_row[4], w_row[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -709,57 +710,55 @@ hipError_t launch_few(GemmParams p, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// Which kernel and tile.  Measured on both sides of every line, one GPU, launches back to back, us (T, N, d), the
-// kernel that is taken first:
+// Which kernel and tile.  Measured on both sides of every line, one GPU, launches back to back, us at (T, N, d): the
+// kernel that a paragraph is about / the other one.
 //   d < 128, MXFP4 also d = 128: no staging and no cut of the contraction, one wave per 32 x 32 tile.
-//     INT4 / MXFP4 (4096, 4096, 64) 14.7 / 12.2 against 19.1 / 15.6 with a trip of the tile through LDS.  At d = 128
-//     against the tiles below: (4096, 4096) 15.9 / 13.2 against 16.3 / 14.4, (300, 14336) 7.7 / 6.7 against 8.2 / 7.6.
-//   few tiles of 32 x 32: the contraction cut among 8 waves, against 64 x 64 tiles.
-//     INT4, up to 512: (64, 4096, 4096) 4.0 against 8.1, (300, 1500, 1088) 4.0 against 5.0; up to 768 (three workgroups on a
-//     CU) from d = 2048 on: (200, 3000, 2048) 5.3 against 5.9, (64, 12288, 4096) 8.7 against 9.2; past that (64, 13000, 4096)
-//     9.6 against 10.4 the other way, (128, 6400, 8192) 14.7 against 15.4.  Up to 900 where 64 x 64 tiles are more than
-//     a CU each: (96, 9568, 4096) 10.9 against 12.3.
-//     MXFP4, up to 256: (64, 4096, 4096) 4.1 against 5.3, (64, 4096, 14336) 10.7 against 14.2; 384: (96, 4096, 4096) 5.9
-//     against 6.3 the other way.  Rows of scale bytes that are no whole dwords, which tiles read through registers,
-//     up to 512 and d = 8192: (300, 1500, 1088) 3.7 against 4.6, d = 4000 6.7 against 7.0, (1848, 148, 7072) 9.6 against
-//     11.5; (300, 1500, 8224) 13.2 against 13.6 the other way, (128, 4000, 14368) 21.0 against 23.2.
-//     One row of tiles, which fills half of a 64 x 64 tile or less.  INT4 any number: (16, 65536, 4096) 30.1 against
-//     36.0, (32, 65536, 8192) 59.5 against 63.1.  MXFP4 has half the products to a load, and loads every row of A once per
-//     32 columns, so it goes by T d: (16, 65536, 4096) 32.1 against 32.6, (24, 65536, 4096) 34.1 against 34.7 the other way,
-//     (32, 65536, 2560) 19.9 against 21.0, (32, 65536, 8192) 60.9 against 74.9; with fewer than 65536 columns later,
-//     (32, 20480, 4096) 9.8 against 10.9, (32, 40960, 4096) 18.6 against 18.9, (24, 28672, 8192) 30.1 against 32.6 the other
-//     way, (16, 20480, 14336) 38.3 against 39.5; 257 .. 384 tiles, (32, 10000, 4096) 6.5 against 7.3, (1, 10000, 8192) 8.9
-//     against 10.3, d = 2048 4.7 against 4.7.  No whole dwords: (16, 65536, 2880) 22.9 against 22.8, (16, 65536, 4000) 33.0
-//     against 36.5 the other way; (16, 14336, 4000) 7.6 against 7.8, (32, 14336, 4000) 8.0 against 8.8 the other way.
-//     Among 4 waves where there are more than 512 tiles and little to cut: (16, 65536, 2048) INT4 13.3 against 14.8, MXFP4
-//     12.6 against 14.1, (16, 65536, 2880) INT4 20.7 against 22.1; no whole dwords, which a wave has more of then, MXFP4 d = 2400
-//     19.2 against 19.7, d = 2880 24.3 against 22.9.
-//   up to 128 tiles of 128 x 128: 64 x 64 tiles, which two workgroups a CU hold at once up to there, against
-//     128 x 128.  INT4 / MXFP4 (512, 4096, 4096) 13.7 / 10.7 against 15.5 / 12.5, d = 1024 6.2 / 5.4 against 7.3 / 6.5; the
-//     other way round with 130 tiles, (640, 3328, 4096) 15.5 / 12.1 against 19.1 / 13.7.
-//   MXFP4, d < 1024: 128 x 128, two stages and two workgroups a CU, against 128 x 256 (four stages and one):
-//     (4096, 4096) d = 160 15.6 against 20.0 (19.4), d = 320 17.1 against 21.3 (21.4), d = 640 18.4 against 25.4 (26.4),
-//     d = 992 22.2 against 28.5 (29.9); (3000, 3500, 256) 12.6 against 14.4 (16.6), d = 768 15.9 against 18.0 (19.9);
-//     (8192, 8192, 512) 57.6 against 68.0 (88.4); (2048, 2048, 256) 6.5 against 7.2 (7.1), d = 992 7.8 against 8.8 (8.6).
-//     One round of 128 x 256 is as fast or faster up to d = 512: (2048, 4096) d = 160 9.4 against 8.7, d = 512 10.6 against
-//     10.0, d = 768 11.3 against 11.3; (300, 14336, 512) 7.7 against 7.2.
-//   MXFP4: 128 x 256, a sixth less to load per product, against 128 x 128, both one workgroup a CU, by rounds of 256
-//     tiles.  In eighths of a round of 128 x 128: one that is not full 6 (fewer workgroups share L2 and power), 128 x 256 14
-//     and 10.  One round for two: (2177, 2177, 1024) 10.9 against 12.9, d = 8192 36.9 against 41.4, (2048, 4096, 4096) 25.7
-//     against 29.7; two for three the other way, (3000, 3500, 8192) 69.1 against 73.4, (2304, 4096, 8192) 60.3 against 68.1, (3072,
-//     4096, 2048) 25.0 against 25.2; two for four (4096, 4096, 2048) 33.5 against 34.3, d = 8192 84.3 against 92.4, (3968, 3969,
-//     2880) 43.2 against 52.4; three for five (4096, 5120, 2048) 37.1 against 39.6, (4096, 4097, 8192), as long by this count, 109 against 107;
-//     four for seven (2048, 14336, 4096) 89.9 against 91.8; (36000, 128, 4096), where the other half of a tile is empty, 43.9
-//     against 24.9.
-//   INT4, two workgroups of 128 x 128 a CU, which load less per product than that: 128 x 256 where some CUs have one of
-//     those and some two, the more of these the longer a row has to be, (2048, 2304, 4096) 23.7 against 28.7, (2048, 2560, 2880)
-//     20.9 against 21.8, (2048, 3072, 4096) 26.5 against 29.5, d = 2880 21.9 against 22.1, d = 2048 17.7 against 17.1, (2048,
-//     3584, 4096) 29.1 against 29.2, (2048, 4096, 4096) 32.4 against 31.4, d = 5120 36.0 against 36.1, d = 14336 90.5 against
-//     93.7, but not for up to 64 rows, (64, 65536, 8192) 77.6 against 72.4; and for the longest rows if the rounds are full:
-//     (4096, 4096, 4096) 62.2 against 59.8, d = 6144 82.2 against 82.5, d = 8192 107.2 against 107.9, d = 16384 199 against 204,
-//     (8192, 8192, 8192) 410 against 414; one and a half rounds (2048, 6144, 8192) 91 against 80.
-//   128 x 128: MXFP4 four stages in LDS and one workgroup a CU, against two stages (2048, 2048, 8192) 23.9 against
-//     27.8; INT4, whose stages take twice as long, two and two workgroups, (2048, 2048, 8192) 30.6 against 33.0.
+//     INT4 (4096, 4096, 64) 14.7 / 19.1, MXFP4 12.2 / 15.6 against a trip of the tile through LDS; d = 128 against the tiles
+//     below (4096, 4096) 15.9 / 16.3 and 13.2 / 14.4, (300, 14336) 7.7 / 8.2 and 6.7 / 7.6.
+//   Few tiles of 32 x 32: the contraction cut among 8 waves, against 64 x 64 tiles.
+//     INT4, up to 512 (64, 4096, 4096) 4.0 / 8.1, (300, 1500, 1088) 4.0 / 5.0; up to 768 (three workgroups on a CU) from
+//     d = 2048 on (200, 3000, 2048) 5.3 / 5.9, (64, 12288, 4096) 8.7 / 9.2, past that (64, 13000, 4096) 10.4 / 9.6,
+//     (128, 6400, 8192) 15.4 / 14.7; up to 900 where the 64 x 64 tiles are more than one a CU (96, 9568, 4096) 10.9 / 12.3.
+//     MXFP4, up to 256 (64, 4096, 4096) 4.1 / 5.3, (64, 4096, 14336) 10.7 / 14.2, past that (96, 4096, 4096) 6.3 / 5.9; rows
+//     of scale bytes that are no whole dwords, which tiles read through registers, up to 512 and d = 8192
+//     (300, 1500, 1088) 3.7 / 4.6, d = 4000 6.7 / 7.0, (1848, 148, 7072) 9.6 / 11.5, past that (300, 1500, 8224) 13.6 / 13.2,
+//     (128, 4000, 14368) 23.2 / 21.0.
+//   One row of tiles, which fills half of a 64 x 64 tile or less: the same, any number of them.
+//     INT4 (16, 65536, 4096) 30.1 / 36.0, (32, 65536, 8192) 59.5 / 63.1.
+//     MXFP4 has half the products to a load, and all of A is loaded again every 32 columns, so it goes by T d:
+//     (16, 65536, 4096) 32.1 / 32.6, (24, 65536, 4096) 34.7 / 34.1, (32, 65536, 2560) 21.0 / 19.9, (32, 65536, 8192) 74.9 /
+//     60.9; below 65536 columns (32, 20480, 4096) 9.8 / 10.9, (32, 40960, 4096) 18.6 / 18.9, (24, 28672, 8192) 32.6 / 30.1,
+//     (16, 20480, 14336) 39.5 / 38.3; 257 .. 384 tiles (32, 10000, 4096) 7.3 / 6.5, (1, 10000, 8192) 10.3 / 8.9,
+//     d = 2048 4.7 / 4.7; no whole dwords (16, 65536, 2880) 22.9 / 22.8, (16, 65536, 4000) 36.5 / 33.0,
+//     (16, 14336, 4000) 7.6 / 7.8, (32, 14336, 4000) 8.8 / 8.0.
+//     Among 4 waves instead of 8 where there are more than 512 tiles and little to cut: (16, 65536, 2048) INT4
+//     13.3 / 14.8, MXFP4 12.6 / 14.1, (16, 65536, 2880) INT4 20.7 / 22.1; no whole dwords, of which a wave then reads more,
+//     MXFP4 d = 2400 19.2 / 19.7, d = 2880 24.3 / 22.9.
+//   Up to 128 tiles of 128 x 128: 64 x 64 tiles, which two workgroups a CU hold at once up to there, against 128 x 128.
+//     INT4 (512, 4096, 4096) 13.7 / 15.5, d = 1024 6.2 / 7.3, past that (640, 3328, 4096) 19.1 / 15.5; MXFP4 10.7 / 12.5,
+//     5.4 / 6.5 and 13.7 / 12.1.
+//   MXFP4, d < 1024: 128 x 128, two stages and two workgroups a CU, against 128 x 256 (/ four stages and one).
+//     (4096, 4096) d = 160 15.6 / 20.0 / 19.4, d = 320 17.1 / 21.3 / 21.4, d = 640 18.4 / 25.4 / 26.4, d = 992 22.2 / 28.5 /
+//     29.9; (3000, 3500, 256) 12.6 / 14.4 / 16.6, d = 768 15.9 / 18.0 / 19.9; (8192, 8192, 512) 57.6 / 68.0 / 88.4;
+//     (2048, 2048, 256) 6.5 / 7.2 / 7.1, d = 992 7.8 / 8.8 / 8.6.  One round of 128 x 256 is as fast or faster up to d = 512:
+//     (2048, 4096) d = 160 9.4 / 8.7, d = 512 10.6 / 10.0, d = 768 11.3 / 11.3; (300, 14336, 512) 7.7 / 7.2.
+//   MXFP4, longer rows: 128 x 256, a sixth less to load per product, against 128 x 128, both one workgroup a CU, by rounds
+//     of 256 tiles.  In eighths of a round of 128 x 128: a round that is not full 6 (fewer workgroups share L2 and power),
+//     of 128 x 256 14 and 10.
+//     One round for two (2177, 2177, 1024) 10.9 / 12.9, d = 8192 36.9 / 41.4, (2048, 4096, 4096) 25.7 / 29.7; two for three
+//     (3000, 3500, 8192) 73.4 / 69.1, (2304, 4096, 8192) 68.1 / 60.3, (3072, 4096, 2048) 25.2 / 25.0; two for four
+//     (4096, 4096, 2048) 33.5 / 34.3, d = 8192 84.3 / 92.4, (3968, 3969, 2880) 43.2 / 52.4; three for five
+//     (4096, 5120, 2048) 37.1 / 39.6, but (4096, 4097, 8192) 109 / 107; four for seven (2048, 14336, 4096) 89.9 / 91.8;
+//     (36000, 128, 4096), where half of every tile is empty, 43.9 / 24.9.
+//   INT4: 128 x 256 against two workgroups of 128 x 128 a CU, which load less per product.
+//     Where some CUs have one of those and some two; the more have two, the longer a row has to be: (2048, 2304, 4096)
+//     23.7 / 28.7, (2048, 2560, 2880) 20.9 / 21.8, (2048, 3072, 4096) 26.5 / 29.5, d = 2880 21.9 / 22.1, d = 2048 17.7 / 17.1,
+//     (2048, 3584, 4096) 29.1 / 29.2, (2048, 4096, 4096) 32.4 / 31.4, d = 5120 36.0 / 36.1, d = 14336 90.5 / 93.7; not for up
+//     to 64 rows, (64, 65536, 8192) 77.6 / 72.4.
+//     The longest rows, if the rounds are full: (4096, 4096, 4096) 62.2 / 59.8, d = 6144 82.2 / 82.5, d = 8192 107.2 /
+//     107.9, d = 16384 199 / 204, (8192, 8192, 8192) 410 / 414; one round and a half (2048, 6144, 8192) 91 / 80.
+//   128 x 128: MXFP4 four stages in LDS and one workgroup a CU, against two stages (2048, 2048, 8192) 23.9 / 27.8; INT4,
+//     whose stages take twice as long, two and two workgroups, against four and one 30.6 / 33.0.
 template <bool MX>
 hipError_t launch_gemm(const GemmParams& p, hipStream_t stream) {
     auto tiles = [&](int64_t m, int64_t n) { return ((p.T + m - 1) / m) * (((int64_t)p.N + n - 1) / n); };

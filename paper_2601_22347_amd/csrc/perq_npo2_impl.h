@@ -182,10 +182,10 @@ npo2_kernel(const ApplyParams p, const Npo2Geom<MB> g) {
             for (int ks = 0; ks < kKS; ++ks)
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
-                    // Four entries a load (read one by one, each instruction meets 64 cache lines, the table was 8 us of a
-                    // short launch: T = 3, d = b = 12288 13.7 -> 8.9 us, T = 2, d = b = 28672 14.9 -> 11.6, T = 2000, d = 6144, b = 1536
-                    // 23.5 -> 16.6).  A base's order is a multiple of four, so four indices
-                    // are inside it or past its end together; past the end they meet zero rows of B and are pointed
+                    // Four entries a load (read one by one, each instruction meets 64 cache lines, the table was 8 us of
+                    // a short launch: T = 3, d = b = 12288 13.7 -> 8.9 us, T = 2, d = b = 28672 14.9 -> 11.6, T = 2000,
+                    // d = 6144, b = 1536 23.5 -> 16.6).  A base's order is a multiple of four, so four indices are
+                    // inside it or past its end together; past the end they meet zero rows of B and are pointed
                     // at the a-value's first elements, finite like all input, so that every read below is unconditional.
                     static_assert(MB % 4 == 0 && kChunkPos % 4 == 0, "groups of four, 16 bytes of perm");
                     const int r = r_of(ks, 4 * q);
