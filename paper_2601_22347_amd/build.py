@@ -63,7 +63,10 @@ def build(verbose: bool = False) -> str:
     if lacks:
         warnings.warn(f"libperq.so is built, the extension module for Python is not: no {', no '.join(lacks)}")
     else:
-        build_module()
+        module = build_module()
+        for name in os.listdir(PKG):                       # modules made from earlier sources
+            if name.startswith("_perq_torch") and name.endswith(".so") and name != os.path.basename(module):
+                os.unlink(os.path.join(PKG, name))
     return LIB
 
 
