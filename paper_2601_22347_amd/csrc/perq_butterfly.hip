@@ -1,5 +1,5 @@
-// Shuffle-butterfly kernel for X -> quantize(XP R~): every shape the C ABI accepts.  AUTO takes it for b >= 4096, for rows of
-// 32 and for short launches whose long ones are mfma_kernel's (route_of in perq_mfma.hip).
+// Shuffle-butterfly kernel for X -> quantize(XP R~): every shape the C ABI accepts.  AUTO takes it for
+// short launches and for widths that the matrix cores do not get at any length (matrix_core_line in perq_mfma.hip).
 //
 // Layout.  A row of d = 32*nt elements is spread over nt lanes; lane t owns the 32 contiguous
 // positions [32t, 32t+32) of the permuted row.  Index bits 0..4 are therefore in registers,

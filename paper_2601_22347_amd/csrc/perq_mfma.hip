@@ -1296,7 +1296,7 @@ static bool block_always(const ApplyParams& p) {
     return p.d < (p.b == 128 ? 3 * kTile : 4 * kTile + 1);
 }
 
-// b <= 64: the number of elements from which on a call is this kernel's.
+// b <= 64: the number of elements from which on a call of the matrix cores is this kernel's.
 //   d = 2560, T = 52428, b = 32 58.3 / 65.1 (T = 13107 21.0 / 21.4, MXFP4 of d = 3072, T = 43690 59.6 / 55.0), d = 2880, T = 46603 58.9 / 59.4,
 //   T = 93206 109.6 / 116.2: block_kernel's waves are filled to 63 - 87 % there.  Prepared, more than 8192: d = 14336, b = 64, T = 2340
 //   21.7 / 20.9, T = 4681 34.5 / 36.1; d = 28672, T = 1170 24.3 / 24.4, T = 2340 39.3 / 42.1; whole tiles, d = 12288, T = 5461 36.7 / 36.9,
@@ -1310,66 +1310,152 @@ static int64_t small_block_line(const ApplyParams& p, int out_kind) {
     return (int64_t)1 << (p.d % kTile == 0 ? 27 : 26);
 }
 
-// The rest, between this kernel and the butterflies: b >= 128 with a permutation where it is not block_kernel's, b = 4096.
-// The choice must not depend on the prepared form here either, so a line is that of the prepared call, and calls with the
-// permutation as given, whose table every launch builds, are ahead on the butterflies for some way past it.  Butterflies /
-// this kernel (/ as given); what decides is that the set-up (operand tables, two staging buffers) is paid back by long
-// launches only.
-static int64_t large_line(const ApplyParams& p) {
-    if (!mfma_supports(p)) return kNever;
+// Rows of 512, 1024 and 2048 stored back to back, whose lines are their own (this kernel took several to a tile); the formats with
+// one scale per token from b = 1024 on only at 2048.
+static bool packs(const ApplyParams& p, int out_kind) {
+    const bool per_token = out_kind == OUT_INT4 || out_kind == OUT_INT4_ASYM || out_kind == OUT_FP4_TOKEN;
+    if (per_token && p.b > 512 && p.d != 2048) return false;
+    return p.d >= 512 && p.d < kTile && kTile % p.d == 0 && p.ldx == p.d && p.T >= kTile / p.d;
+}
+
+// The number of elements from which on AUTO takes the matrix cores; below it the butterflies have the call.
+//   The line is the one between the butterflies and this file's kernel: the matrix unit cuts every term of a sum of eight off at
+// half an ulp of the largest, the butterflies round each sum to nearest, so the error of the first is the larger one (relative
+// 2-norm of the fp32 output against 64 bits, 13 widths from 512 to 28672, heavy tails and outlier channels, mean ratio of the two: b = 16
+// 1.13, b = 32 1.008, b = 64 1.09, b = 128 - 256 1.005 - 1.011, b = 512 - 2048 1.001 - 1.005).  block_kernel would be the faster one for some
+// way below it too (d = 1536, b = 256, T = 25080 37.8 / 22.9 us, d = 8192, b = 16, T = 1442 13.1 / 11.1, d = 14336, b = 512, T = 365 12.4 / 10.1), at that
+// price; it may be named.
+//   The choice must not depend on whether a permutation came with its prepared form (the outputs of the two calls
+// agree bit for bit), so where the form matters the line is that of the prepared call, and calls with the
+// permutation as given, whose table every launch builds, are ahead on the butterflies for some way past it.  Nor on
+// whether the output is fp32: the values that perq_permute_rotate_f32 gives are those that the codes of the same call
+// were made from.  Figures: launches back to back on one GPU, butterfly / this kernel (/ as given) in us, INT4 where no format
+// is named, from before block_kernel took most of the calls past the line.  What decides: the set-up (operand tables, two staging
+// buffers) is paid back by long launches only; for b <= 32 the butterflies have five stages fewer; for b >= 1024 this kernel's
+// operand addresses cost 3 us.
+static int64_t matrix_core_line(const ApplyParams& p, int out_kind) {
+    const bool ragged = mfma_takes_ragged(p), perm = p.perm != nullptr, packed = packs(p, out_kind);
+    const bool small = p.b <= 32, large = p.b >= 1024;
     auto exp2 = [](int k) { return (int64_t)1 << k; };
-    if (p.perm == nullptr) {        // b = 4096
-        // d = 8192: T = 16 5.6 / 9.0, T = 1024 10.7 / 11.5, T = 2048 20.8 / 16.4; d = 12288, T = 600 11.4 / 11.9, T = 1033 17.4 / 14.8; past four
-        // tiles by rows, the butterflies have a workgroup to a row: d = 20480, T = 256 9.1 / 11.2, T = 257 14.6 / 14.3, T = 513 21.1 / 17.8; d = 32768
-        // 11.9 / 12.3, 18.7 / 15.3
-        return p.d <= 4 * kTile ? exp2(23) + 1 : 257 * (int64_t)p.d;
+    if (!mfma_supports(p) && !ragged) return kNever;
+
+    if (packed) {           // rows of 512, 1024, 2048
+        // Rows left over take a second launch of 4 us, 6 us with a permutation: d = 1024, T = 16385, b = 64 11.8 / 14.1,
+        // T = 65537 36.4 / 34.5; b = 128, T = 8193 7.3 / 10.8, T = 32769 21.6 / 21.5; permutation, T = 4097 7.8 / 13.1,
+        // T = 32769 25.2 / 27.9.
+        if (p.T % (kTile / p.d) != 0 && !large) return small ? exp2(27) : perm ? exp2(26) : 3 * exp2(24);
+        // d = 2048, T = 16384 17.6 / 17.2, with a permutation and MXFP4 20.3 / 20.5; T = 32768 31.9 / 30.4, 37.2 / 34.4
+        if (small) return exp2(26);
+        // d = 2048, T = 8192 11.8 / 10.3; permutation, d = 1024, T = 16384 13.2 / 13.6, T = 32768 22.7 / 21.0; d = 512,
+        // T = 65536 20.4 / 17.1
+        if (p.b == 64) return perm ? 3 * exp2(23) : exp2(24);
+        // P = I: d = 1024, T = 4096 5.3 / 5.6, T = 16384 13.0 / 11.1
+        if (!perm) return large ? exp2(23) : 3 * exp2(21);
+        // a permutation: the table is built once for four waves, as at d = 4096
+        return large ? 0 : exp2(21) + 1;
     }
-    // folded (d = 2048) and d = 4096: the table is built once for four waves; b = 4096, T = 16 6.5 / 6.3
-    if (folds(p) || p.d == kTile) return 0;
-    if (p.d < 2560) return p.d == 2048 ? exp2(25) : kNever;         // (rows that lie apart; T = 32768 59 / 47)
-    if (p.d < kTile) return exp2(23);                               // d = 3072, b = 1024
-    // Five tiles and more, prepared: up to six by rows.  T = 16, 256, 257: b = 128, d = 17920 7.8 / 8.5, 9.0 / 9.5, 12.0 / 11.4; d = 24576 8.7 / 9.0,
-    // 10.4 / 10.1, 13.5 / 12.4; d = 25600 9.9 / 9.1, 11.4 / 10.2, 15.4 / 12.6; d = 28672 10.1 / 9.2; b = 1024, d = 20480 9.4 / 9.3, 10.9 / 10.2
-    if (p.d > 4 * kTile) return p.d > 6 * kTile || p.b >= 1024 ? 0 : 257 * (int64_t)p.d;
-    // Three and four, by rows: the butterflies' time goes up at 257 and 513 rows.  A line lies where the prepared call gains
-    // enough to set against the 4 us that a call as given loses.  T = 256, 257, 512, 513, prepared:
+    // Narrow rows that cannot be folded leave too much of the tile empty (d = 2048, b = 128: 39 / 37, d = 1024:
+    // 21 / 31), but for the large blocks of d = 2048 (T = 32768, b = 2048: 59 / 47).
+    if (p.d < 2560) return p.d == 2048 && large ? exp2(25) : kNever;
+
+    const bool one_tile = p.d <= kTile, two_tiles = p.d > kTile && p.d <= 2 * kTile;
+    if (!perm) {
+        // d = 8192, b = 4096: T = 16 5.6 / 9.0, T = 1024 10.7 / 11.5, T = 2048 20.8 / 16.4; d = 16384, b = 1024, T = 512
+        // 9.3 / 11.7, T = 1024 18.2 / 16.5; d = 12288, T = 600 11.4 / 11.9, T = 1033 17.4 / 14.8
+        if (large && p.d <= 4 * kTile) return exp2(23) + 1;
+        // Two tiles: b = 32, d = 5120, T = 1639 6.8 / 8.6, T = 3277 11.9 / 11.8, T = 4916 14.7 / 14.3; d = 8192, T = 1025
+        // 6.5 / 7.5, T = 2049 10.9 / 11.2, T = 4097 18.6 / 18.6 (MXFP4, T = 3072 11.2 / 12.9, T = 4096 14.9 / 15.9: the
+        // butterflies keep a group's maximum in the lane).  b = 128: T = 1639 8.8 / 9.7, T = 3277 14.6 / 13.2.
+        if (two_tiles) return 3 * exp2(small ? 23 : 22);
+        // Ragged rows of more tiles: b = 32, d = 11008, T = 762 7.2 / 7.8, T = 1524 12.6 / 11.7; d = 15904, T = 527
+        // 7.4 / 8.4, T = 1054 11.6 / 12.1; b = 128, d = 11008, T = 381 6.7 / 6.8, T = 762 8.7 / 8.3.
+        if (ragged && !one_tile) return exp2(small ? 24 : 23);
+        // Three tiles and more, b = 32 (b = 16; MXFP4, which the butterflies scale without leaving the lane).  How the waves of
+        // both kernels fill a CU changes with the width, and with it the line, which is one for all formats:
+        //   d = 8704, T = 723 7.6 / 7.3 (7.4 / 7.5; 6.6 / 7.0), T = 965 9.5 / 8.5 (9.0 / 8.6; 8.7 / 8.2); d = 10240, T = 820 9.3 / 8.7
+        //     (8.8 / 8.8; 8.5 / 8.4), T = 1230 10.4 / 9.5 (10.2 / 9.7; 9.3 / 8.9)
+        //   d = 11264, T = 745 6.9 / 8.0 (6.7 / 7.6; 6.2 / 7.1), T = 1489 12.0 / 11.6 (11.4 / 11.6; 10.3 / 10.7)
+        //   d = 12288, T = 1365 12.2 / 11.8 (11.9 / 11.8; 10.6 / 10.8), T = 2048 15.5 / 14.6 (14.5 / 14.7; 14.4 / 13.7)
+        //   d = 14336, T = 1170 10.8 / 11.0 (10.3 / 11.1; 9.7 / 10.4), T = 1755 14.3 / 14.3 (13.9 / 14.4; 13.3 / 13.9), T = 2340
+        //     20.1 / 18.1 (19.1 / 18.0; 17.8 / 17.7); d = 13824, T = 1519 12.8 / 13.0 (12.3 / 13.1; 12.0 / 12.6)
+        //   d = 16384, T = 1024 10.0 / 11.1 (9.7 / 11.2; 9.0 / 10.4), T = 2048 18.4 / 18.1 (17.3 / 18.2; 16.5 / 17.9)
+        //   d = 20480, T = 819 13.6 / 13.4 (12.9 / 13.4; 11.7 / 12.8), T = 1638 21.6 / 20.3 (20.8 / 20.5; 19.0 / 20.1)
+        //   d = 22528, T = 932 14.4 / 14.6 (13.7 / 14.5; 13.4 / 13.9), T = 1489 20.1 / 19.5 (19.6 / 19.7; 18.5 / 19.5)
+        //   d = 24576, T = 682 12.0 / 12.4 (11.6 / 12.4; 10.4 / 11.8), T = 1365 21.3 / 19.8 (20.4 / 19.7; 19.0 / 19.4)
+        //   d = 25600, T = 655 13.3 / 12.4 (12.9 / 12.4; 11.2 / 12.0); d = 28672, T = 585 13.8 / 12.5 (13.1 / 12.5; 11.6 / 12.4)
+        //   d = 32768, T = 512 11.0 / 11.4 (10.5 / 11.3; 10.1 / 11.0), T = 1024 19.0 / 18.6 (18.4 / 18.4; 18.0 / 18.5)
+        // b >= 64, by rows: butterflies have a workgroup to a row, so their time goes up in steps of 256 rows, or of 512
+        // where two workgroups share a CU.  T = 512 and 513 (T = 256 and 257 past six tiles):
+        //   d = 9728, b = 64 6.0 / 6.5, 7.5 / 6.9; b = 512 6.9 / 7.6, 9.2 / 8.4
+        //   d = 12288, b = 64 6.7 / 6.9, 7.4 / 7.3; b = 512 8.1 / 8.0, 9.5 / 8.7
+        //   d = 14336, b = 64 7.0 / 7.1, 7.5 / 7.5, T = 858 10.9 / 10.5; b = 128 7.6 / 7.3, 8.2 / 7.8; d = 16384, b = 64 7.2 / 7.7,
+        //     7.6 / 8.0, T = 775 10.6 / 10.7; b = 128 7.6 / 7.8, 8.5 / 8.4
+        //   d = 20480, b = 128 10.0 / 10.1, 12.8 / 11.6; b = 512 11.4 / 12.3, 14.9 / 15.1; b = 1024 12.6 / 13.8, 16.5 / 16.0; b = 4096
+        //     T = 256 9.1 / 11.2, T = 257 14.6 / 14.3, T = 513 21.1 / 17.8
+        //   d = 24576, b = 128 10.6 / 10.8, 13.4 / 12.2; d = 25600, b = 64 7.2 / 7.6, 10.3 / 9.0; b = 512 8.5 / 9.0, 12.9 / 11.7
+        //   d = 32768, b = 64 7.8 / 8.4, 10.8 / 9.9; b = 4096 11.9 / 12.3, 18.7 / 15.3
+        if (p.d > 2 * kTile) {
+            if (!small) {
+                if (p.d > 6 * kTile || p.b == 4096) return 257 * (int64_t)p.d;
+                return p.b == 64 && p.d > 3 * kTile && p.d <= 4 * kTile ? 3 * exp2(22) : 513 * (int64_t)p.d;
+            }
+            if (2 * p.d <= 5 * kTile) return exp2(23);
+            if (p.d > 3 * kTile && p.d < 4 * kTile) return 3 * exp2(23);
+            return exp2(p.d == 4 * kTile || p.d == 8 * kTile || (p.d > 5 * kTile && p.d <= 6 * kTile) ? 25 : 24);
+        }
+        // d = 4096, b = 128, T = 16 3.8 / 4.7, T = 1024 5.1 / 5.2, T = 2048 7.1 / 6.5; b = 16, T = 2048 5.8 / 6.1, T = 8192
+        // 17.8 / 16.2; d = 3072, b = 128, T = 32768 74 / 44; d = 2880, b = 32, T = 5832 12.2 / 10.5, T = 32768 56.8 / 41.2
+        return exp2(small ? 23 : 22);
+    }
+    // T = 512, b = 64 5.3 / 5.7, T = 1024 7.0 / 5.8; b = 4096, T = 16 6.5 / 6.3
+    if (p.d == kTile) return large ? 0 : exp2(21) + 1;
+    // No prepared form: T = 4096, d = 3072, b = 16 10.9 / 12.3, T = 8192 18.5 / 16.9; b = 128, T = 2048 9.7 / 10.0, T = 4096
+    // 13.6 / 12.4, T = 32768 83 / 51; asymmetric INT4, T = 4001 14.7 / 13.0.  Ragged: d = 2880, b = 32, T = 2912 11.4 / 10.9,
+    // T = 5825 16.2 / 15.3; b = 64, MXFP4, T = 32768 69.1 / 51.2
+    if (one_tile) return exp2(small ? 24 : 23);
+    // Ragged, no prepared form.  Two tiles: b = 16, d = 5152, T = 6512 23.6 / 25.2, b = 32, T = 16384 64.5 / 57.3; b = 256,
+    // d = 7424, T = 2259 18.6 / 17.7, T = 4519 31.5 / 26.2.  Three and four: b = 16, d = 15904, T = 1054 17.2 / 18.3, T = 2109
+    // 27.0 / 24.8; d = 11008, b = 256, T = 762 16.1 / 16.3, T = 16384 212 / 116; b = 128, T = 1524 24.5 / 19.6.  More:
+    // b = 32, d = 17440, T = 480 16.6 / 16.2, T = 961 27.3 / 22.2; b = 128, d = 28800, T = 291 24.7 / 18.3.
+    if (ragged) return exp2((small ? 24 : 23) + (two_tiles ? 2 : p.d <= 4 * kTile ? 1 : 0));
+    // Five tiles and more, prepared: up to six by rows, as below.  T = 16, 256, 257, 512, 513:
+    //   b = 128: d = 17920 7.8 / 8.5, 9.0 / 9.5, 12.0 / 11.4, 13.2 / 12.7, 16.0 / 14.5; d = 24576 8.7 / 9.0, 10.4 / 10.1, 13.5 / 12.4;
+    //     d = 25600 9.9 / 9.1, 11.4 / 10.2, 15.4 / 12.6; d = 28672 10.1 / 9.2
+    //   b = 32: d = 17920 7.1 / 8.2, 8.2 / 9.1, 10.5 / 10.7, 11.4 / 12.0, 13.9 / 13.6; d = 24576 8.2 / 8.8, 9.6 / 9.7, 12.0 / 11.8, 13.6 /
+    //     13.6, 16.0 / 14.9; d = 25600 9.1 / 8.8, 10.4 / 9.8, 13.6 / 12.0
+    //   b = 1024: d = 20480 9.4 / 9.3, 10.9 / 10.2, 15.1 / 12.3
+    if (p.d > 4 * kTile) return p.d > 6 * kTile || large ? 0 : (small ? 513 : 257) * (int64_t)p.d;
+    // Three and four, by rows: the butterflies' time goes up at 257 and 513 rows as above.  A line lies where the
+    // prepared call gains enough to set against the 4 us that a call as given loses.  T = 256, 257, 512, 513, prepared:
     //   b = 1024: d = 10240 7.8 / 8.7, 9.6 / 9.3, 10.5 / 10.4, 14.2 / 11.0; d = 12288 8.0 / 8.9, 11.0 / 9.6, 12.4 / 11.0,
     //     14.2 / 11.4 (as given T = 256 12.2, T = 512 16.3); d = 16384 8.7 / 9.4, 12.4 / 10.5, 13.9 / 12.0, 15.6 / 12.5; b = 4096 9.9 / 9.9, 14.5 / 11.0
-    //   b = 128: d = 12288 7.0 / 8.4, 9.3 / 9.3, 10.4 / 10.2, 11.6 / 10.6; d = 14336 7.4 / 8.7, 10.0 / 9.8, 11.4 / 10.9 (as given 15.6), 12.4 / 11.5
-    if (p.d > 2 * kTile) return (p.b >= 1024 && 2 * p.d > 5 * kTile ? 257 : 513) * (int64_t)p.d;
-    return exp2(21) + 1;            // two tiles, b = 4096
+    //   b = 128: d = 9728 6.8 / 8.2, 8.2 / 8.9, 9.0 / 9.8, 12.1 / 10.2; d = 12288 7.0 / 8.4, 9.3 / 9.3, 10.4 / 10.2,
+    //     11.6 / 10.6; d = 14336 7.4 / 8.7, 10.0 / 9.8, 11.4 / 10.9 (as given 15.6), 12.4 / 11.5; b = 512 8.1 / 9.4, 10.8 / 10.4, 12.2 / 11.9, 13.5 / 12.6
+    //   b = 32: d = 9728 6.2 / 7.9, 7.4 / 8.8, 8.1 / 9.5, 10.8 / 9.8; d = 12288 6.5 / 8.2, 8.2 / 9.0, 9.6 / 10.0, 10.1 / 10.3, T = 690
+    //     11.0 / 11.3, T = 1033 14.4 / 13.7; d = 16384 7.2 / 8.7, 9.7 / 9.8, 11.2 / 11.0, 11.6 / 11.6, T = 775 15.5 / 14.4, T = 1031
+    //     16.9 / 15.7 (T = 1024 15.5 / 15.8, as given 18.9)
+    // Two tiles: d = 6144, b = 2048, T = 256 6.4 / 8.0, T = 512 8.4 / 8.1
+    if (!two_tiles) {
+        const bool a_little = 2 * p.d <= 5 * kTile;              // of the third tile
+        return (large && !a_little ? 257 : small && !a_little ? 1025 : 513) * (int64_t)p.d;
+    }
+    if (large) return exp2(21) + 1;
+    // Two tiles, prepared / as given.  b = 128: d = 8192, T = 513 8.2 / 8.4 / 11.9, T = 1025 10.9 / 10.3 / 13.6.  b = 32: d = 8192,
+    // T = 1025 9.9 / 9.8 / 13.4, T = 2049 14.6 / 13.9 / 16.4; d = 7168, T = 2341 14.6 / 13.1 / 15.5; narrower rows leave
+    // more of the second tile empty, d = 6144, T = 2731 13.8 / 14.5 / 16.8, T = 4096 17.7 / 17.7 / 20.0, d = 5120,
+    // T = 3277 14.3 / 14.4 / 17.7, T = 4916 19.4 / 19.2 / 21.8.
+    return small ? (p.d <= 6144 ? 3 * exp2(23) : exp2(24)) : exp2(23);
 }
 
-// b = 128 and 256 on rows of no multiple of 512, where no caller can name this kernel: long launches keep the bits that they
-// have had from it, and with a permutation the short ones those of the butterflies.  With P = I d = 11008, b = 256, T = 762
-// takes 8.7 there and 7.9 from block_kernel.
-static Route ragged_route(const ApplyParams& p) {
-    const int line = p.perm == nullptr || p.d > 4 * kTile ? 23 : p.d > kTile && p.d <= 2 * kTile ? 25 : 24;
-    return p.T * (int64_t)p.d >= (int64_t)1 << line ? Route::mfma : p.perm == nullptr ? Route::block : Route::butterfly;
-}
-
-// Rows of up to 1024 through a permutation, b <= 32, where block_kernel's waves have two units and a rest: butterflies / block_kernel,
-// as given, d = 512, b = 32, T = 8195 6.8 / 6.6, T = 16387 8.3 / 8.9, T = 20155 8.8 / 9.6, T = 23173 10.5 / 10.0; d = 1024, T = 8195 8.0 / 8.6,
-// T = 11588 10.1 / 9.4; d = 256, T = 32771 8.7 / 9.7, T = 46343 11.3 / 11.3; b = 64 and d = 2048 within 2 - 4 %.
-static bool short_of_units(const ApplyParams& p) {
-    const int64_t elements = p.T * (int64_t)p.d;
-    return p.perm != nullptr && p.d <= 1024 && p.b <= 32 && elements > (int64_t)3 << 21 && elements <= (int64_t)21 << 19;
+// Past the line, and where a caller names the matrix cores: which of the two kernels.  b = 128 and 256 on rows of no multiple of 512,
+// where no caller can name this kernel, keep the bits that they have had from it.
+Route matrix_core_route(const ApplyParams& p, int out_kind) {
+    if (p.b <= 64 && block_supports(p)) return p.T * (int64_t)p.d >= small_block_line(p, out_kind) ? Route::mfma : Route::block;
+    return block_always(p) ? Route::block : Route::mfma;
 }
 
 Route route_of(const ApplyParams& p, int out_kind) {
-    const int64_t elements = p.T * (int64_t)p.d;
-    if (p.b > 64 && mfma_takes_ragged(p)) return ragged_route(p);
-    if (p.b <= 64 && block_supports(p)) {
-        if (out_kind != OUT_DIAG && short_of_units(p)) return Route::butterfly;
-        return elements >= small_block_line(p, out_kind) ? Route::mfma : Route::block;
-    }
-    if (block_always(p)) return Route::block;
-    return elements >= large_line(p) ? Route::mfma : Route::butterfly;
-}
-
-Route matrix_core_route(const ApplyParams& p, int out_kind) {
-    if (p.b <= 64 && block_supports(p)) return short_of_units(p) ? Route::block : route_of(p, out_kind);
-    return block_always(p) ? Route::block : Route::mfma;
+    return p.T * (int64_t)p.d >= matrix_core_line(p, out_kind) ? matrix_core_route(p, out_kind) : Route::butterfly;
 }
 
 hipError_t launch_mfma(const ApplyParams& p0, int out_kind, hipStream_t stream) {

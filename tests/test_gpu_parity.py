@@ -1487,10 +1487,10 @@ def test_chunked_kernels_more_rows_than_one_pass_of_the_grid(d, b, fmt, with_per
 
 
 # ---- the matrix-core kernel of half the tile ---------------------------------------------------------
-# rows that share a wave (64, 512), leave a pair or a wave part empty (96, 2080, 11008), are packed several to a unit from 512
-# units on (1536, 3072), fill one, two, three, four, eight and sixteen waves; every number of stages
-@pytest.mark.parametrize("T,d,b", [(70, 64, 16), (33, 96, 32), (9, 2080, 32), (11, 512, 128), (2051, 1536, 512), (1027, 3072, 256), (19, 2048, 2048),
-                                   (7, 4096, 64), (9, 5120, 1024), (3, 6144, 2048), (4, 8192, 128), (3, 11008, 256), (2, 16384, 512), (2, 28672, 1024), (2, 32768, 2048)])
+# rows that share a wave (512), are packed several to a unit from 512 units on (1536, 3072), leave a wave part empty (2880, which only
+# AUTO takes, from 2^22 elements on), fill one, two, three, four, eight and sixteen waves; every number of stages
+@pytest.mark.parametrize("T,d,b", [(70, 512, 16), (33, 1024, 32), (1457, 2880, 64), (11, 512, 128), (2051, 1536, 512), (1027, 3072, 256), (19, 1024, 1024),
+                                   (7, 4096, 64), (9, 5120, 1024), (3, 6144, 2048), (4, 8192, 128), (3, 11264, 256), (2, 16384, 512), (2, 28672, 512), (2, 32768, 512)])
 @pytest.mark.parametrize("fmt", ["int4", "mxfp4", "int4_asym", "fp4_token"])
 def test_half_tile_kernel_at_the_edges_of_its_shapes(T, d, b, fmt):
     rng = np.random.default_rng(T + d + b)
@@ -1498,8 +1498,8 @@ def test_half_tile_kernel_at_the_edges_of_its_shapes(T, d, b, fmt):
     x[:, rng.choice(d, size=max(1, d // 100), replace=False)] *= 50
     x[T // 2] *= 2.0 ** -115                                   # a row whose step leaves the usual range
     bits = synth.f64_to_bf16_bits(x)
-    for perm in (None, rng.permutation(d).astype(np.int32)):
-        assert_parity(bits, perm, b, fmt, label="half tile")
+    for perm in (None, rng.permutation(d).astype(np.int32)) if d % 512 == 0 else (None,):
+        assert_parity(bits, perm, b, fmt, algo="mfma" if d % 512 == 0 else "auto", label="half tile")
 
 
 # as above, in launches long enough for the run-time schedule (units of two and more to every workgroup) and its limit on
@@ -1515,29 +1515,51 @@ def test_half_tile_kernel_long_and_short_launches_give_the_same_bits(T, d, b, fm
     perm = torch.randperm(d, device="cuda", generator=g).to(torch.int32)
     form = binding.placement_to_device(binding.perq_perm_prepare(perm.cpu().numpy(), b)[0]) if "p" in perms else None
     for kind in perms:
-        p, placement = None if kind == "n" else perm, form if kind == "p" else None
-        codes, scales = binding.perq_permute_rotate_quant(x, p, b, fmt, placement=placement)
-        y, stats = binding.perq_permute_rotate_f32(x, p, b), binding.perq_block_diagnostics(x, p, b)
+        # (a prepared form is AUTO's, which these numbers of rows take to the matrix cores)
+        p, how = None if kind == "n" else perm, {"placement": form} if kind == "p" else {"algo": "mfma"}
+        codes, scales = binding.perq_permute_rotate_quant(x, p, b, fmt, **how)
+        y, stats = binding.perq_permute_rotate_f32(x, p, b, algo="mfma"), binding.perq_block_diagnostics(x, p, b)
         for at in (slice(0, 3), slice(T // 2, T // 2 + 5), slice(T - 7, T)):
-            c, s = binding.perq_permute_rotate_quant(x[at].contiguous(), p, b, fmt)
+            c, s = binding.perq_permute_rotate_quant(x[at].contiguous(), p, b, fmt, algo="mfma")
             assert torch.equal(c, codes[at]) and torch.equal(s, scales[at]), (kind, at)
-            assert torch.equal(binding.perq_permute_rotate_f32(x[at], p, b), y[at]), (kind, at)
+            assert torch.equal(binding.perq_permute_rotate_f32(x[at], p, b, algo="mfma"), y[at]), (kind, at)
             assert torch.equal(binding.perq_block_diagnostics(x[at], p, b), stats[at]), (kind, at)
 
 
-# short rows with a permutation, on either side of the two lines between which AUTO takes the butterflies; a named kernel
-# keeps its bits
-@pytest.mark.parametrize("T,d,b", [(6144, 1024, 32), (6145, 1024, 32), (21504, 512, 16), (21505, 512, 16)])
-def test_short_rows_on_either_side_of_the_butterflies_lines(T, d, b):
+# ---- AUTO's line between the butterflies and the matrix cores ------------------------------------------
+# The matrix unit cuts every term of a sum of eight off at half an ulp of the largest, which butterflies do not: below the line
+# AUTO's outputs are the butterflies', bit for bit, and above it those of the matrix cores.  (T, d, b, pad, permutation, which):
+# each class of the line from both sides where it has two, with rows that it never takes (widths below 2560 that do not pack
+# into 4096, rows that lie apart), short rows through a permutation between 6.3 and 11 million elements, and one row.
+@pytest.mark.parametrize("T,d,b,pad,perm,which", [
+    (70, 64, 16, 0, True, "butterfly"), (333, 96, 32, 0, False, "butterfly"), (2051, 1536, 512, 0, False, "butterfly"),
+    (2051, 1536, 256, 0, True, "butterfly"), (3001, 2048, 128, 64, True, "butterfly"), (5, 2048, 64, 0, False, "butterfly"),
+    (6145, 1024, 32, 0, True, "butterfly"), (65536, 1024, 32, 0, True, "mfma"), (20155, 512, 16, 0, True, "butterfly"),
+    (8191, 2048, 64, 0, False, "butterfly"), (8192, 2048, 64, 0, False, "mfma"), (512, 4096, 64, 0, True, "butterfly"),
+    (513, 4096, 64, 0, True, "mfma"), (16, 4096, 128, 0, True, "butterfly"), (1023, 4096, 256, 0, False, "butterfly"),
+    (1024, 4096, 256, 0, False, "mfma"), (2730, 3072, 128, 0, True, "butterfly"), (2731, 3072, 128, 0, True, "mfma"),
+    (1024, 8192, 32, 0, True, "butterfly"), (2048, 8192, 32, 0, True, "mfma"), (1, 14336, 2048, 0, False, "butterfly"),
+    (512, 14336, 512, 0, True, "butterfly"), (513, 14336, 512, 0, True, "mfma"), (256, 28672, 64, 0, False, "butterfly"),
+    (257, 28672, 64, 0, False, "mfma"), (1, 28672, 64, 0, True, "mfma"), (1500, 2880, 64, 0, False, "mfma"),
+    (1400, 2880, 64, 0, False, "butterfly"), (700, 11008, 256, 0, False, "butterfly"), (16, 8192, 4096, 0, False, "butterfly")])
+def test_auto_takes_the_butterflies_below_its_line(T, d, b, pad, perm, which):
     torch = _torch()
-    print(f"[case] short rows T={T} d={d} b={b}", flush=True)
-    g = torch.Generator(device="cuda").manual_seed(T + d)
-    x = torch.randn((T, d), device="cuda", generator=g).to(torch.bfloat16)
-    perm = torch.randperm(d, device="cuda", generator=g).to(torch.int32)
-    y = binding.perq_permute_rotate_f32(x, perm, b)
-    algo = "butterfly" if 6144 * 1024 < T * d <= 21 << 19 else "mfma"
-    assert torch.equal(y, binding.perq_permute_rotate_f32(x, perm, b, algo=algo))
-    codes, scales = binding.perq_permute_rotate_quant(x, perm, b, "int4")
-    c, s = binding.perq_permute_rotate_quant(x, perm, b, "int4", algo=algo)
-    assert torch.equal(c, codes) and torch.equal(s, scales)
-    assert torch.equal(binding.perq_permute_rotate_f32(x[:5], perm, b, algo="mfma"), binding.perq_permute_rotate_f32(x, perm, b, algo="mfma")[:5])
+    print(f"[case] line T={T} d={d} b={b} pad={pad} perm={perm} {which}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + d + b)
+    x = torch.randn((T, d + pad), device="cuda", generator=g)
+    x[:, torch.randperm(d, device="cuda", generator=g)[:max(1, d // 100)]] *= 1000.0        # (sums that round)
+    x = x.to(torch.bfloat16)[:, :d]
+    p = torch.randperm(d, device="cuda", generator=g).to(torch.int32) if perm else None
+    y = binding.perq_permute_rotate_f32(x, p, b)
+    butterflies = binding.perq_permute_rotate_f32(x, p, b, algo="butterfly")
+    if which == "butterfly":
+        assert torch.equal(y, butterflies)
+    else:
+        assert not torch.equal(y, butterflies)
+        if d % 512 == 0:
+            assert torch.equal(y, binding.perq_permute_rotate_f32(x, p, b, algo="mfma"))
+    for fmt in ("int4", "mxfp4"):
+        codes, scales = binding.perq_permute_rotate_quant(x, p, b, fmt)
+        if which == "butterfly" or d % 512 == 0:
+            c, s = binding.perq_permute_rotate_quant(x, p, b, fmt, algo=which)
+            assert torch.equal(codes, c) and torch.equal(scales, s), fmt
