@@ -257,6 +257,10 @@ extern "C" perq_status_t perq_block_diagnostics(const uint16_t* x_bf16, int64_t 
     if ((reinterpret_cast<uintptr_t>(out) & 15u) != 0) return PERQ_ERR_UNSUPPORTED;
     if (!perq::is_pow2(b)) return PERQ_ERR_UNSUPPORTED;
     p.y = out;
-    const auto launch = perq::block_supports(p) ? perq::launch_block : perq::launch_butterfly;
+    // The half-tile kernel where its sums cost nothing: of the four, the largest rotated value is the one that sees the matrix
+    // unit (error against 64 bits, this kernel / butterflies: b = 16 1.10, b = 64 1.04, b = 128 - 2048 1.000 - 1.002; b = 32 and other
+    // odd powers 0.82 - 0.94, scaled in 64 bits; the sums of a block 0.35 - 1.0).
+    const bool half_tile = perq::block_supports(p) && b != 16 && b != 64;
+    const auto launch = half_tile ? perq::launch_block : perq::launch_butterfly;
     return launch(p, perq::OUT_DIAG, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? PERQ_OK : PERQ_ERR_LAUNCH;
 }
