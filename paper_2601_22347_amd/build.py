@@ -197,33 +197,79 @@ def check_statistics_order() -> int:
     return checked
 
 
-def check_ticket_register(src: str = "perq_block.hip") -> int:
-    """Compiler check for the run-time row schedule's tickets (perq_block.hip, perq_mfma.hip), a minute or two.
+def _built_kernels(name: str):
+    """(symbol, instructions) of every kernel in libperq.so whose name holds `name` (an expression), from its disassembly."""
+    import re
+    import tempfile
+    llvm = os.path.join(os.path.dirname(os.path.dirname(hipcc())), "llvm", "bin", "llvm-objdump")
+    run = lambda *args, **kw: subprocess.run([llvm, *args], check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, **kw).stdout
+    with tempfile.TemporaryDirectory() as tmp:
+        lib = shutil.copy(LIB, tmp)
+        run("--offloading", lib, cwd=tmp)
+        for part in sorted(os.listdir(tmp)):
+            with open(os.path.join(tmp, part), "rb") as f:
+                if not part.endswith("gfx950") or not re.search(name.encode(), f.read()):
+                    continue
+            for m in re.finditer(rf"\n[0-9a-f]+ <(\S*{name}\S*)>:\n((?:.+\n)*)", run("-d", os.path.join(tmp, part))):
+                yield m.group(1), [l.split("//")[0].strip() for l in m.group(2).split("\n") if l.startswith("\t")]
+
+
+def check_ticket_register() -> int:
+    """Check of the built library for the run-time row schedule's tickets (perq_block.hip, perq_mfma.hip), a few seconds.
 
     A ticket is on its way into a register of its own while the compiler's code runs, so no other instruction may
     name that register (as a part of a tuple neither), and every kernel has to have it.  Returns the number of kernel
     variants checked; raises on a mismatch.  `python -m paper_2601_22347_amd.build --check-ticket-register`."""
     import re
-    number = {"perq_block.hip": 127, "perq_mfma.hip": 255}[src]
-    text = _device_assembly(src)
     checked = 0
-    for m in re.finditer(r"\n(_ZN4perq\S*(?:block|mfma)_kernel\S*): +; @", text):
-        drawn = 0
-        for line in text[m.end():text.index(".Lfunc_end", m.end())].split("\n"):
-            line = line.split(";")[0].strip()
-            if line.startswith("."):
+    for kernel, number in (("block_kernel", 127), ("mfma_kernel", 255)):
+        found = 0
+        for symbol, body in _built_kernels(rf"perq\S*\d{kernel}I"):
+            drawn = 0
+            for line in body:
+                if re.match(rf"(global_atomic_add v{number}, |v_readfirstlane_b32 s\d+, v{number}$)", line):
+                    drawn += line.startswith("global_atomic_add")
+                    continue
+                used = [int(v) for v in re.findall(r"\bv(\d+)\b", line)] + [int(v) for v in re.findall(r"\bv\[\d+:(\d+)\]", line)]
+                if any(v >= number for v in used):
+                    raise RuntimeError(f"{symbol}: {line}")
+            if drawn < 2:
+                raise RuntimeError(f"{symbol}: {drawn} draws")
+            found += 1
+        if found == 0:
+            raise RuntimeError(f"no {kernel} found")
+        checked += found
+    return checked
+
+
+def check_lane_stages() -> int:
+    """Check of the built library for the butterflies across lanes of block_kernel, a few seconds.
+
+    They are instructions that the compiler does not look into: it keeps no distance between them and what it puts around
+    them.  A vector instruction's result may be read through DPP, and by a swap of half-waves or rows of lanes, two wait states
+    later.  Returns the number of stages' instructions and swaps checked; raises on a mismatch."""
+    import re
+    checked = 0
+    for symbol, body in _built_kernels(r"perq\S*\d+block_kernelI"):
+        for i, line in enumerate(body):
+            if line.startswith("v_fmac_f32_dpp "):
+                reads = {int(re.match(r"v_fmac_f32_dpp v\d+, v(\d+),", line).group(1))}
+            elif line.startswith("v_permlane"):
+                reads = {int(v) for v in re.findall(r"\bv(\d+)\b", line)}
+            else:
                 continue
-            if re.match(rf"(global_atomic_add v{number}, |v_readfirstlane_b32 s\d+, v{number}$)", line):
-                drawn += line.startswith("global_atomic_add")
-                continue
-            used = [int(v) for v in re.findall(r"\bv(\d+)\b", line)] + [int(v) for v in re.findall(r"\bv\[\d+:(\d+)\]", line)]
-            if any(v >= number for v in used):
-                raise RuntimeError(f"{m.group(1)}: {line}")
-        if drawn < 2:
-            raise RuntimeError(f"{m.group(1)}: {drawn} draws")
-        checked += 1
+            checked += 1
+            states = 0
+            for before in reversed(body[max(0, i - 2):i]):
+                nop = re.match(r"s_nop (\d+)", before)
+                if states < 2 and not nop and before.startswith("v_fmac_f32_dpp" if line.startswith("v_permlane") else "v_"):
+                    first = re.match(r"\S+ v(\d+|\[\d+:\d+\])", before)
+                    ends = [int(v) for v in re.findall(r"\d+", first.group(1))] if first else []
+                    if ends and reads & set(range(ends[0], ends[-1] + 1)):
+                        raise RuntimeError(f"{symbol}: {before} | {line}")
+                states += int(nop.group(1)) + 1 if nop else 1
     if checked == 0:
-        raise RuntimeError("no kernel with tickets found")
+        raise RuntimeError("no stage across lanes found")
     return checked
 
 
@@ -262,6 +308,6 @@ if __name__ == "__main__":
     if "--check-table-reads" in sys.argv:
         print(check_table_reads(), "kernel variants checked")
     elif "--check-ticket-register" in sys.argv:
-        print(sum(check_ticket_register(src) for src in ("perq_block.hip", "perq_mfma.hip")), "kernel variants checked")
+        print(check_ticket_register(), "kernel variants checked")
     else:
         print(build(verbose=True))

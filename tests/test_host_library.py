@@ -144,6 +144,31 @@ def test_partials_of_the_column_statistics_arrive_before_they_are_counted():
     assert build.check_statistics_order() == 4                        # mean and largest, with and without streaming loads
 
 
+def test_nothing_but_tickets_touches_the_ticket_register(monkeypatch):
+    from paper_2601_22347_amd import build
+    assert build.check_ticket_register() == 180 + 147                 # block_kernel, mfma_kernel
+    draw = ["global_atomic_add v127, v[2:3], v1, off sc0", "v_readfirstlane_b32 s4, v127"] * 2
+    for wrong in ("v_add_f32_e32 v127, v1, v2", "global_load_dwordx4 v[124:127], v[2:3], off"):
+        monkeypatch.setattr(build, "_built_kernels", lambda name: [("block", draw + [wrong])])
+        with pytest.raises(RuntimeError, match="block"):
+            build.check_ticket_register()
+
+
+def test_stages_across_lanes_keep_their_distances(monkeypatch):
+    from paper_2601_22347_amd import build
+    # 60 kernels with stages across lanes, each two buffers of four stages on 32 values, and their swaps
+    assert build.check_lane_stages() > 60 * 2 * 4 * 32
+    stage = "v_fmac_f32_dpp v5, v5, v9 row_ror:8 row_mask:0xf bank_mask:0xf"
+    for wrong in ([stage, "v_permlane16_swap_b32_e32 v4, v5"], [stage, "s_nop 0", "v_permlane16_swap_b32_e32 v5, v4"],
+                  ["v_add_f32_e32 v5, v1, v2", "v_mov_b32_e32 v1, 0", stage], ["v_lshl_add_u64 v[4:5], v[0:1], 2, v[2:3]", "s_nop 0", stage]):
+        monkeypatch.setattr(build, "_built_kernels", lambda name: [("block", wrong)])
+        with pytest.raises(RuntimeError, match="block"):
+            build.check_lane_stages()
+    for right in ([stage, "s_nop 1", "v_permlane16_swap_b32_e32 v4, v5"], ["v_add_f32_e32 v5, v1, v2", "s_nop 1", stage]):
+        monkeypatch.setattr(build, "_built_kernels", lambda name: [("block", right)])
+        assert build.check_lane_stages() > 0
+
+
 def test_statistics_workspace_is_no_larger_than_a_float_per_run_of_rows(lib):
     """A float per column and run of r rows (r as documented); several slices fit the 2 MiB static array."""
     rng = np.random.default_rng(5)
