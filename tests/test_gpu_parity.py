@@ -116,11 +116,11 @@ SHAPES = [
     (19, 1024, [16, 32, 256, 512, 1024]),
     (13, 3072, [16, 32, 64, 1024]),          # nt = 96: not a power of two
     (21, 2048, [32, 2048]),
-    (24, 2048, [32, 128, 1024, 2048]),       # rows of d < 4096 stored back to back: folded into 4096-wide ones
+    (24, 2048, [32, 128, 1024, 2048]),       # rows of d < 4096 stored back to back: several to a wave
     (40, 1024, [16, 64, 1024]),
     (64, 512, [32, 512]),
-    (69, 512, [32, 512]),                    # 8 rows fold into one; the last 5 take a launch of their own
-    (27, 2048, [32, 2048]),
+    (69, 512, [32, 512]),                    # rows left over: a wave that is not full
+    (27, 2048, [32, 2048]),                  # (b >= 1024 with a permutation: a launch of its own for the last row)
     (9, 8192, [16, 32, 64, 128, 2048, 4096, 8192]),
     (5, 14336, [32, 128, 512, 1024, 2048]),
     (6, 20480, [256, 1024, 4096]),           # 8-wave groups, ragged last tile
@@ -219,20 +219,25 @@ def test_colabs_mean(M, d):
     assert np.array_equal(got, (1 + np.arange(d) % 7).astype(np.float32))
 
 
-# ---- enough rows for the run-time schedule of the matrix-core kernel --------------------------
-# With at least two units per worker (a wave for d <= 4096, else a workgroup) the kernel deals its
+# ---- enough rows for the run-time schedule of the matrix-core kernels --------------------------
+# With at least two units per worker (a workgroup; in mfma_kernel with d <= 4096 a wave) they deal their
 # rows through ticket counters; every row is checked against the oracle, ragged tails included.
 DYNAMIC_SHAPES = [
     # (T, d, b, fmt, perm)
-    (4099, 4096, 128, "int4", True),      # a wave per row, shared address table
+    # block_kernel: two waves a row, one, four, eight
+    (4099, 4096, 128, "int4", True),
     (4099, 4096, 32, "mxfp4", False),
-    (4500, 4096, 4096, "int4", True),
-    (4611, 2048, 64, "mxfp4", True),      # a wave per row, half tiles
-    (8200, 2048, 64, "mxfp4", True),      # two rows folded into one tile
+    (4611, 2048, 64, "mxfp4", True),
+    (8200, 2048, 64, "mxfp4", True),
     (8200, 2048, 2048, "mxfp4", False),
-    (2051, 8192, 32, "mxfp4", True),      # two rows per workgroup
-    (1030, 14336, 128, "int4", True),     # one row per workgroup, ragged last tile, row maximum across waves
+    (2051, 8192, 32, "mxfp4", True),
     (1030, 14336, 2048, "int4", False),
+    # mfma_kernel
+    (4500, 4096, 4096, "int4", True),     # a wave per row, shared address table
+    (4500, 4096, 2048, "int4", True),
+    (8201, 2048, 2048, "mxfp4", True),    # two rows folded into one tile, the last one by itself
+    (2051, 8192, 4096, "mxfp4", True),    # two rows per workgroup
+    (1030, 14336, 128, "int4", True),     # one row per workgroup, ragged last tile, row maximum across waves
     (530, 20480, 1024, "int4", True),     # eight-wave workgroups, one staging buffer
 ]
 
@@ -249,22 +254,45 @@ def test_run_time_schedule_all_rows(T, d, b, fmt, with_perm):
     assert rep.ok(), (rep.summary(), rep.notes[:5])
 
 
-def test_run_time_schedule_counters_come_back_to_zero():
+# (block_kernel, mfma_kernel with a wave and with a workgroup as worker)
+@pytest.mark.parametrize("T,d,b", [(4200, 4096, 128), (4200, 4096, 2048), (1100, 14336, 128)])
+def test_run_time_schedule_counters_come_back_to_zero(T, d, b):
     """Many launches in a row on one stream, i.e. on one set of ticket counters: a counter that a
     launch left non-zero would hand the next launch the wrong rows."""
     torch = _torch()
-    T, d = 4200, 4096
+    print(f"[case] counters T={T} d={d} b={b}", flush=True)
     rng = np.random.default_rng(99)
     x = binding.bits_to_device(synth.f64_to_bf16_bits(rng.standard_normal((T, d))))
     perm = torch.from_numpy(rng.permutation(d).astype(np.int32)).cuda()
     ref = None
     for i in range(150):
-        codes, scales = binding.perq_permute_rotate_quant(x, perm, 128, "int4", algo="mfma")
+        codes, scales = binding.perq_permute_rotate_quant(x, perm, b, "int4", algo="mfma")
         if ref is None:
             ref = (codes.clone(), scales.clone())
         elif i % 10 == 9 or i >= 140:
             assert torch.equal(codes, ref[0]) and torch.equal(scales, ref[1]), f"launch {i} differs"
     torch.cuda.synchronize()
+
+
+def test_run_time_schedule_both_kernels_in_turn_on_one_stream():
+    """block_kernel and mfma_kernel draw from the counters of their stream alike, with grids, workers and numbers of
+    tickets of their own: every launch finds them at zero, whichever came before."""
+    torch = _torch()
+    rng = np.random.default_rng(98)
+    calls = []
+    for T, d, b, fmt, with_perm in ((4200, 4096, 128, "int4", True), (4300, 4096, 2048, "int4", True), (9000, 3072, 128, "int4_asym", True),
+                                    (1100, 14336, 128, "mxfp4", True), (1500, 14336, 512, "fp4_token", False), (2100, 8192, 4096, "int4", True)):
+        x = binding.bits_to_device(synth.f64_to_bf16_bits(rng.standard_normal((T, d))))
+        perm = torch.from_numpy(rng.permutation(d).astype(np.int32)).cuda() if with_perm else None
+        x3 = x[:3].contiguous()                    # (too few units to draw for)
+        calls.append((x, perm, b, fmt, binding.perq_permute_rotate_quant(x, perm, b, fmt, algo="mfma")))
+        few = binding.perq_permute_rotate_quant(x3, perm, b, fmt, algo="mfma")
+        assert torch.equal(few[0], calls[-1][4][0][:3]) and torch.equal(few[1], calls[-1][4][1][:3])
+    order = [int(k) for k in rng.integers(0, len(calls), size=120)]
+    got = [binding.perq_permute_rotate_quant(*calls[k][:4], algo="mfma") for k in order]
+    torch.cuda.synchronize()
+    for i, k in enumerate(order):
+        assert torch.equal(got[i][0], calls[k][4][0]) and torch.equal(got[i][1], calls[k][4][1]), f"launch {i}, call {k}"
 
 
 # ---- the two per-token formats of Appendix B: asymmetric INT4, FP4 with a real scale -------------
@@ -277,12 +305,12 @@ TOKEN_FORMAT_SHAPES = [
     (7, 8192, [32, 2048, 8192]),
     (5, 14336, [128, 2048]),                 # ragged last tile: absent sub-blocks must not enter min / max
     (4, 20480, [256, 4096]),
-    # narrow rows stored back to back, T a multiple of 4096 / d: folded into 4096-wide ones for b <= 512
-    # (the row extremes are then exchanged inside 4, 8 or 16 lanes of a half-wave pair), not folded above
+    # narrow rows stored back to back, T a multiple of 4096 / d: several to a wave, the row extremes then exchanged inside 8 or 16
+    # lanes of a half-wave pair (block_kernel), and rows of 2048 two to a 4096-wide one for b >= 1024 with a permutation (mfma_kernel)
     (24, 2048, [32, 128, 512, 1024, 2048]),
     (40, 1024, [16, 64, 256, 1024]),
     (64, 512, [32, 128, 512]),
-    # the same with rows left over that do not fill a folded row (they take a second launch)
+    # the same with rows left over that do not fill the last wave, or 4096-wide row (a second launch)
     (25, 2048, [128, 2048]),
     (43, 1024, [64]),
     (67, 512, [32]),
@@ -462,10 +490,11 @@ def test_rows_alone_and_among_others(d, b, algo):
 # period of 32, and a row's output does not depend on its place: the first 32 go to the oracle, the others
 # have to equal them bit for bit.
 @pytest.mark.parametrize("d,b,with_perm", [
-    (2592, 32, True), (2880, 64, True), (2880, 32, False), (3040, 16, True), (3552, 32, True),   # a row per wave
-    (5152, 32, True), (7648, 16, False), (7424, 256, True),                                       # two rows a group
-    (11008, 256, True), (11008, 64, False), (15904, 32, True),                                    # one row, four tiles
-    (17440, 32, True), (28800, 128, True), (31776, 16, True),                                     # eight waves
+    # (block_kernel up to b = 64, mfma_kernel above)
+    (2592, 32, True), (2880, 64, True), (2880, 32, False), (3040, 16, True), (3552, 32, True),   # two waves a row
+    (5152, 32, True), (7648, 16, False), (7424, 256, True),                                       # three and four; two rows a group
+    (11008, 256, True), (11008, 64, False), (15904, 32, True),                                    # one row of four tiles; six and eight
+    (17440, 32, True), (28800, 128, True), (31776, 16, True),                                     # nine to sixteen; eight waves
     (4064, 32, True), (8160, 32, True), (16352, 16, False), (32736, 32, True)])                   # no room for the zeros: butterflies
 @pytest.mark.parametrize("fmt", ["int4", "mxfp4", "int4_asym", "fp4_token"])
 def test_ragged_rows_in_bulk(d, b, with_perm, fmt):
@@ -1073,14 +1102,18 @@ def test_fp32_output_is_what_the_codes_were_made_from(T, d, b, fmt):
 
 
 # ---- the ticket counters under concurrency and graph replay ------------------------------------------
-def test_run_time_schedule_on_two_streams_and_in_a_graph():
+# (block_kernel, mfma_kernel with a wave and with a workgroup as worker, one of each)
+@pytest.mark.parametrize("shapes", [((6000, 4096, 128, "int4"), (2100, 8192, 32, "mxfp4")), ((6000, 4096, 2048, "int4"), (1100, 14336, 128, "int4")),
+                                    ((4300, 4096, 4096, "int4"), (1500, 14336, 512, "mxfp4"))])
+def test_run_time_schedule_on_two_streams_and_in_a_graph(shapes):
     """Every stream has a counter set of its own, so launches that overlap on two streams never draw
     from the same counters; a launch that is being captured takes the fixed split and can be replayed
     beside eager launches: every result equals the eager one."""
     torch = _torch()
     rng = np.random.default_rng(123)
     cases = []
-    for T, d, b, fmt in ((6000, 4096, 128, "int4"), (2100, 8192, 32, "mxfp4")):
+    for T, d, b, fmt in shapes:
+        print(f"[case] two streams T={T} d={d} b={b} fmt={fmt}", flush=True)
         x = binding.bits_to_device(synth.f64_to_bf16_bits(rng.standard_normal((T, d))))
         perm = torch.from_numpy(rng.permutation(d).astype(np.int32)).cuda()
         ref = binding.perq_permute_rotate_quant(x, perm, b, fmt, algo="mfma")
@@ -1216,13 +1249,14 @@ def test_reset_leaves_the_column_statistics_of_other_streams_alone():
         assert torch.equal(binding.perq_colabs_mean(xs[0]), want[0])
 
 
-def test_run_time_schedule_more_streams_than_counter_sets_and_reset():
+@pytest.mark.parametrize("b", [128, 2048])          # (block_kernel, mfma_kernel)
+def test_run_time_schedule_more_streams_than_counter_sets_and_reset(b):
     """The 65th stream of a device gets no counter set: its launches take the fixed split.  All
     streams launch at once; every result equals the reference.  perq_reset_schedule leaves the
     counters usable."""
     torch = _torch()
     rng = np.random.default_rng(321)
-    T, d, b, fmt = 4300, 4096, 128, "int4"
+    T, d, fmt = 4300, 4096, "int4"
     x = binding.bits_to_device(synth.f64_to_bf16_bits(rng.standard_normal((T, d))))
     perm = torch.from_numpy(rng.permutation(d).astype(np.int32)).cuda()
     ref = binding.perq_permute_rotate_quant(x, perm, b, fmt, algo="mfma")
@@ -1259,12 +1293,13 @@ def test_run_time_schedule_more_streams_than_counter_sets_and_reset():
 
 
 # ---- edges of the run-time schedule: exactly two units per worker, one more, strided rows, long T ----
+@pytest.mark.parametrize("b", [64, 2048])          # (block_kernel, mfma_kernel)
 @pytest.mark.parametrize("T", [4095, 4096, 4097, 4160])
-def test_run_time_schedule_threshold_edges(T):
-    """d = 4096 runs 2048 waves: T = 4096 is the first size on the ticket path (no row left to draw),
-    T = 4095 the last on the fixed stride."""
+def test_run_time_schedule_threshold_edges(T, b):
+    """d = 4096 has room for 2048 workers (of two waves, of one): T = 4096 is the first size on the ticket path (mfma_kernel:
+    no row left to draw), T = 4095 the last on the fixed stride."""
     rng = np.random.default_rng(T)
-    d, b = 4096, 64
+    d = 4096
     x = synth.f64_to_bf16_bits(rng.standard_normal((T, d)) * np.exp(rng.uniform(-1, 1, size=(T, 1))))
     perm = rng.permutation(d).astype(np.int32)
     for fmt in ("int4", "mxfp4"):
@@ -1274,21 +1309,23 @@ def test_run_time_schedule_threshold_edges(T):
             assert rep.ok(), (T, fmt, rep.summary(), rep.notes[:5])
 
 
-def test_run_time_schedule_with_a_row_stride():
+@pytest.mark.parametrize("b", [128, 4096])         # (block_kernel, mfma_kernel)
+def test_run_time_schedule_with_a_row_stride(b):
     rng = np.random.default_rng(5)
     T, d = 2300, 8192
     x = synth.f64_to_bf16_bits(rng.standard_normal((T, d)))
     perm = rng.permutation(d).astype(np.int32)
-    codes, scales, _y = run_gpu(x, perm, 128, "int4", "mfma", want_y=False, ldx=d + 512)
-    rep = parity.compare_apply(x, perm, 128, "int4", codes, scales, None)
+    codes, scales, _y = run_gpu(x, perm, b, "int4", "mfma", want_y=False, ldx=d + 512)
+    rep = parity.compare_apply(x, perm, b, "int4", codes, scales, None)
     assert rep.ok(), (rep.summary(), rep.notes[:5])
 
 
-def test_long_launch_sampled_rows():
-    """T = 131072 rows of 4096 (the largest launch timed in the design notes): 64 tickets per wave;
-    sampled rows against the oracle, every row's scale against the identity |y|_inf = |scale| * 7 <= |x|_2."""
+@pytest.mark.parametrize("b", [128, 2048])         # (block_kernel, mfma_kernel)
+def test_long_launch_sampled_rows(b):
+    """T = 131072 rows of 4096, 60 and more tickets to a worker: sampled rows against the oracle, every row's scale against
+    the identity |y|_inf = |scale| * 7 <= |x|_2."""
     torch = _torch()
-    T, d, b = 131072, 4096, 128
+    T, d = 131072, 4096
     g = torch.Generator(device="cuda"); g.manual_seed(11)
     x = torch.randn((T, d), generator=g, device="cuda").to(torch.bfloat16)
     perm = np.random.default_rng(12).permutation(d).astype(np.int32)
@@ -1595,3 +1632,62 @@ def test_auto_takes_the_butterflies_below_its_line(T, d, b, pad, perm, which):
         if which == "butterfly" or d % 512 == 0:
             c, s = binding.perq_permute_rotate_quant(x, p, b, fmt, algo=which)
             assert torch.equal(codes, c) and torch.equal(scales, s), fmt
+
+
+# ---- the lines between the two matrix-core kernels: the same bits on either side ------------------------
+# Up to b = 64 they form the same sums in the same order, so the number of rows may decide.  (T: the first number of rows that is
+# mfma_kernel's; rows of 2560 .. 4095, also of no multiple of 512, of no whole tile and of whole tiles past 8192.)
+@pytest.mark.parametrize("T,d", [(39322, 2560), (34953, 2880), (32768, 3072), (28087, 3584), (4682, 14336), (2341, 28672), (10923, 12288), (8192, 16384)])
+@pytest.mark.parametrize("b,fmt", [(16, "int4"), (32, "int4_asym"), (64, "fp4_token"), (32, "mxfp4")])
+def test_the_same_bits_on_either_side_of_the_matrix_core_kernels_lines(T, d, b, fmt):
+    torch = _torch()
+    print(f"[case] same bits T={T} d={d} b={b} fmt={fmt}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + d + b)
+    x = torch.randn((T, d), device="cuda", generator=g)
+    x[:, torch.randperm(d, device="cuda", generator=g)[:max(1, d // 100)]] *= 1000.0        # (sums that round)
+    x = x.to(torch.bfloat16)
+    perm = torch.randperm(d, device="cuda", generator=g).to(torch.int32)
+    long = binding.perq_permute_rotate_quant(x, perm, b, fmt)
+    short = binding.perq_permute_rotate_quant(x[:T - 1], perm, b, fmt)
+    assert torch.equal(long[0][:-1], short[0]) and torch.equal(long[1][:-1], short[1])
+    if d >= 4096:
+        form = binding.placement_to_device(binding.perq_perm_prepare(perm.cpu().numpy(), b)[0])
+        for n in (T - 1, T):
+            codes, scales = binding.perq_permute_rotate_quant(x[:n], perm, b, fmt, placement=form)
+            assert torch.equal(codes, long[0][:n]) and torch.equal(scales, long[1][:n])
+    del long, short
+    y = binding.perq_permute_rotate_f32(x, perm, b)
+    assert torch.equal(y[:-1], binding.perq_permute_rotate_f32(x[:T - 1], perm, b))
+
+
+# ---- how far the matrix cores' sums are from 64 bits -----------------------------------------------------
+# perq.h gives the mean ratio to the butterflies' error by block size and the range of the means of a width; `most` is the top of the
+# range.  Single inputs scatter further (b = 16: 1.0 to 3, few sums round at all), the mean of these 24 by a fifth of that.
+@pytest.mark.parametrize("b,most", [(16, 1.36), (32, 1.03), (64, 1.24), (128, 1.08), (512, 1.08), (2048, 1.08)])
+def test_error_of_the_matrix_cores_stays_where_the_header_has_it(b, most):
+    torch = _torch()
+    ratios = []
+    for d in (4096, 8192, 14336):
+        for seed in range(4):
+            g = torch.Generator(device="cuda").manual_seed(d + b + 7 * seed)
+            T = (1 << 23) // d
+            x = torch.randn((T, d), device="cuda", generator=g)
+            x /= torch.stack([torch.randn((T, d), device="cuda", generator=g) for _ in range(3)]).square().mean(dim=0).clamp(min=1e-6).sqrt()
+            x[:, torch.randperm(d, device="cuda", generator=g)[:max(1, d // 100)]] *= 50.0
+            x = x.clamp(-1e4, 1e4).to(torch.bfloat16)
+            perm = torch.randperm(d, device="cuda", generator=g).to(torch.int32)
+            for p in (None, perm):
+                v = x.double() if p is None else x.double()[:, p.long()]
+                h = 1
+                while h < b:
+                    v = v.reshape(-1, 2, h)
+                    v = torch.stack((v[:, 0] + v[:, 1], v[:, 0] - v[:, 1]), dim=1)
+                    h *= 2
+                want = v.reshape(T, d) / b ** 0.5
+                error = [float((binding.perq_permute_rotate_f32(x, p, b, algo=algo).double() - want).norm() / want.norm()) for algo in ("mfma", "butterfly")]
+                print(f"[case] error d={d} b={b} perm={p is not None}: {error[0]:.3e}, butterflies {error[1]:.3e}", flush=True)
+                # (each of log2(b) stages and the scale round to 2^-24 of a norm that they keep)
+                assert error[0] < (math.log2(b) + 1) * 2.0 ** -24
+                ratios.append(error[0] / error[1])
+    print("       mean ratio", sum(ratios) / len(ratios), min(ratios), max(ratios), flush=True)
+    assert sum(ratios) / len(ratios) <= most
