@@ -89,12 +89,12 @@ Rows rows_of(PyObject* o) {
 // out again while the call still ran.  Results are for the current stream too: freed later, they are not used again
 // before what it has queued by then is done.
 //   Through the dispatcher (at::empty) a buffer takes 0.8 us of the host, from the function that it comes to 0.55: 0.4 us
-// of a small call's 5.4 (two buffers; calls of 16 rows 5.42 -> 5.03). Where a mode of the dispatcher is on (fake tensors,
-// functorch, functionalization), the mode has to see the allocation, as it always did.
+// of a small call's 5.4 (two buffers; calls of 16 rows 5.42 -> 5.03).  Where a mode of the dispatcher is on (fake tensors,
+// functorch, functionalization, tracing), the mode has to see the allocation, as it always did.
 at::Tensor buffer(at::IntArrayRef shape, at::ScalarType type, at::Device device, const Stream& stream, bool is_result) {
     const auto empty = [&]() -> at::Tensor {
-        const c10::DispatchKeySet modes({c10::DispatchKey::Python, c10::DispatchKey::PythonTLSSnapshot,
-                                         c10::DispatchKey::Functionalize, c10::DispatchKey::FuncTorchDynamicLayerFrontMode});
+        const c10::DispatchKeySet modes({c10::DispatchKey::Python, c10::DispatchKey::PythonTLSSnapshot, c10::DispatchKey::PythonDispatcher,
+                                         c10::DispatchKey::Functionalize, c10::DispatchKey::FuncTorchDynamicLayerFrontMode, c10::DispatchKey::Tracer});
         if (!device.is_cuda() || c10::impl::tls_local_dispatch_key_set().included_.has_any(modes))
             return at::empty(shape, at::TensorOptions().dtype(type).device(device));
         return at::detail::empty_cuda(shape, type, device, std::nullopt);

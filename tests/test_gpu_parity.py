@@ -1691,3 +1691,28 @@ def test_error_of_the_matrix_cores_stays_where_the_header_has_it(b, most):
                 ratios.append(error[0] / error[1])
     print("       mean ratio", sum(ratios) / len(ratios), min(ratios), max(ratios), flush=True)
     assert sum(ratios) / len(ratios) <= most
+
+
+# ---- outputs under a mode of the dispatcher ---------------------------------------------------------------
+def test_a_mode_of_the_dispatcher_sees_the_buffers_of_a_call():
+    torch = _torch()
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Seen(TorchDispatchMode):
+        def __init__(self):
+            super().__init__()
+            self.ops = []
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            self.ops.append(str(func))
+            return func(*args, **(kwargs or {}))
+
+    x = torch.randn((40, 512), device="cuda").to(torch.bfloat16)
+    want = binding.perq_permute_rotate_quant(x, None, 32, "int4")
+    with Seen() as seen:
+        got = binding.perq_permute_rotate_quant(x, None, 32, "int4")
+        stats = binding.perq_block_diagnostics(x, None, 32)
+    assert seen.ops.count("aten.empty.memory_format") == 3, seen.ops
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and torch.equal(stats, binding.perq_block_diagnostics(x, None, 32))
+    traced = torch.jit.trace(lambda t: binding.perq_permute_rotate_quant(t, None, 32, "int4")[0], x, check_trace=False)
+    assert "aten::empty" in str(traced.graph)
