@@ -15,9 +15,10 @@
  * Conventions
  *   - "device" pointers are HIP device memory on the current device, "host" pointers are
  *     ordinary host memory.  Every buffer is owned by the caller; the library allocates nothing
- *     and frees nothing.  Its only state on a device is two tables of counters (64 sets each, in
- *     device memory of the library's own): 32 per set for the run-time row schedule of its main
- *     kernel, and the arrivals at each column tile for the column statistics.  Every launch leaves
+ *     and frees nothing.  Its only state on a device is three tables of counters (64 sets each, in
+ *     device memory of the library's own): 32 per set for the run-time row schedule of the fused path,
+ *     as many for that of the block statistics, and the arrivals at each column tile for the column
+ *     statistics.  Every launch leaves
  *     its counters at zero, and a set belongs to one stream: in each table the first 64 streams per
  *     device that use it get a set each and keep it for the life of the process.  Launches of one
  *     stream never run side by side, so no two launches draw from one set at the same time, however
@@ -379,18 +380,18 @@ perq_status_t perq_w4a4_mxfp4_gemm_ref(const uint8_t* a_codes, const uint8_t* a_
                                        float* out, int64_t ldo, void* hip_stream);
 
 /*
- * The run-time row schedule of the main kernel (see "Conventions" above).
+ * The run-time row schedule of the fused path (see "Conventions" above).
  *   perq_schedule_set    the counter set launches on `hip_stream` draw from, 0 .. 63 (assigned at
  *                        the first call for that stream, by this function or by a launch), or -1
  *                        when such launches take the fixed split: the stream is capturing, or 64
  *                        other streams of the current device came first.
  *   perq_reset_schedule  enqueues small kernels on `hip_stream` that put every counter of the row
- *                        schedule on the current device, and the arrival counts of the column
- *                        statistics of this stream, back to zero.  Never needed after launches that
- *                        ran to their end; for a process that goes on after a kernel of the library
- *                        was cut short (a column statistic: call it for the stream of that one).
- *                        Must not overlap a launch of the fused path on another stream; column
- *                        statistics of other streams are not touched.
+ *                        schedule on the current device, and the counters of the block statistics and
+ *                        of the column statistics of this stream, back to zero.  Never needed after
+ *                        launches that ran to their end; for a process that goes on after a kernel of
+ *                        the library was cut short (a statistic: call it for the stream of that one).
+ *                        Must not overlap a launch of the fused path on another stream; statistics of
+ *                        other streams are not touched.
  *   perq_schedule_selftest  host only: a model of the schedule on the kernel's own queue
  *                        arithmetic -- n_blocks workgroups of workers_per_block workers each draw
  *                        their units in a seeded random interleaving, `launches` times on the same

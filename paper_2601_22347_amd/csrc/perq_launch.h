@@ -52,8 +52,8 @@ Route route_of(const ApplyParams& p, int out_kind);
 Route matrix_core_route(const ApplyParams& p, int out_kind);
 hipError_t launch_mfma(const ApplyParams& p, int out_kind, hipStream_t stream);
 // Ticket counters of the row schedule for launches on `stream` (perq_schedule.h: kQueues, 256 bytes apart, all zero), or
-// nullptr: the launch takes a fixed split.
-uint32_t* row_counters(hipStream_t stream);
+// nullptr: the launch takes a fixed split.  The block statistics have counters of their own.
+uint32_t* row_counters(hipStream_t stream, bool statistics);
 // The matrix-core kernel of half the tile, b <= 2048: launches of few rows to a CU and rows that do not fill the tiles
 // of the other one.
 bool block_supports(const ApplyParams& p);

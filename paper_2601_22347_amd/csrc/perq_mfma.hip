@@ -72,13 +72,18 @@ struct MfmaGeom {
 using schedule::kQueues;
 using schedule::kSets;
 __device__ uint32_t work_ctr[kSets][kQueues][64];
+// ... and those of the block statistics, which are no part of the fused path: they take none of its sets, and a reset on another
+// stream leaves them alone.
+__device__ uint32_t statistics_ctr[kSets][kQueues][64];
 
-StreamSets row_sets;
+StreamSets row_sets, statistics_sets;
 
 __global__ void clear_counters_kernel() {
     uint32_t* c = &work_ctr[0][0][0];
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < kSets * kQueues * 64u; i += gridDim.x * blockDim.x) c[i] = 0u;
 }
+
+__global__ void clear_statistics_counters_kernel(int set) { statistics_ctr[set][threadIdx.x][0] = 0u; }
 
 using layout::granule_slot;      // granule -> slot inside a staged row
 using layout::hk_pos;            // high-K mode: position inside the tile of row m, contraction index K
@@ -1504,19 +1509,21 @@ hipError_t launch_mfma(const ApplyParams& p0, int out_kind, hipStream_t stream) 
 }  // namespace perq
 
 namespace perq {
-uint32_t* row_counters(hipStream_t stream) {
-    static std::atomic<uint32_t*> base[64];
-    const int set = row_sets.of(stream);
+uint32_t* row_counters(hipStream_t stream, bool statistics) {
+    static std::atomic<uint32_t*> base[2][64];
+    const int set = (statistics ? statistics_sets : row_sets).of(stream);
     if (set < 0) return nullptr;
     int dev = 0;
     (void)hipGetDevice(&dev);                       // (below 64, or there was no set)
-    uint32_t* p = base[dev].load(std::memory_order_relaxed);
+    uint32_t* p = base[statistics][dev].load(std::memory_order_relaxed);
     if (p == nullptr) {
-        if (hipGetSymbolAddress(reinterpret_cast<void**>(&p), HIP_SYMBOL(work_ctr)) != hipSuccess) {
+        const hipError_t e = statistics ? hipGetSymbolAddress(reinterpret_cast<void**>(&p), HIP_SYMBOL(statistics_ctr))
+                                        : hipGetSymbolAddress(reinterpret_cast<void**>(&p), HIP_SYMBOL(work_ctr));
+        if (e != hipSuccess) {
             (void)hipGetLastError();
             return nullptr;
         }
-        base[dev].store(p, std::memory_order_relaxed);
+        base[statistics][dev].store(p, std::memory_order_relaxed);
     }
     return p + (size_t)set * kQueues * 64u;
 }
@@ -1527,7 +1534,10 @@ extern "C" int32_t perq_schedule_set(void* hip_stream) {
 }
 
 extern "C" perq_status_t perq_reset_schedule(void* hip_stream) {
-    hipLaunchKernelGGL(perq::clear_counters_kernel, dim3(64), dim3(256), 0, static_cast<hipStream_t>(hip_stream));
+    const auto stream = static_cast<hipStream_t>(hip_stream);
+    hipLaunchKernelGGL(perq::clear_counters_kernel, dim3(64), dim3(256), 0, stream);
+    const int set = perq::statistics_sets.of(stream, false);
+    if (set >= 0) hipLaunchKernelGGL(perq::clear_statistics_counters_kernel, dim3(1), dim3(perq::kQueues), 0, stream, set);
     if (hipGetLastError() != hipSuccess) return PERQ_ERR_LAUNCH;
-    return perq::clear_arrivals(static_cast<hipStream_t>(hip_stream)) == hipSuccess ? PERQ_OK : PERQ_ERR_LAUNCH;
+    return perq::clear_arrivals(stream) == hipSuccess ? PERQ_OK : PERQ_ERR_LAUNCH;
 }

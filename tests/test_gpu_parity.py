@@ -1205,7 +1205,7 @@ def test_prepared_form_and_chunked_kernel_in_a_graph():
 
 
 def test_column_statistics_take_no_set_of_the_row_schedule():
-    """A stream that only computes statistics leaves the 64 sets of the main kernel to others."""
+    """A stream that only computes statistics, of columns or of blocks, leaves the 64 sets of the fused path to others."""
     torch = _torch()
     import ctypes
     hip = ctypes.CDLL("libamdhip64.so")
@@ -1220,6 +1220,10 @@ def test_column_statistics_take_no_set_of_the_row_schedule():
     torch.cuda.synchronize()
     first = binding.perq_schedule_set(streams[0])
     got = [binding.perq_colabs_mean(x, stream=st) for st in streams[1:3]]
+    many = torch.zeros((20000, 2048), device="cuda", dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    for st in streams[1:3]:
+        binding.perq_block_diagnostics(many, None, 128, stream=st)
     last = binding.perq_schedule_set(streams[3])
     torch.cuda.synchronize()
     assert all(torch.equal(g, want) for g in got)
@@ -1247,6 +1251,29 @@ def test_reset_leaves_the_column_statistics_of_other_streams_alone():
     with torch.cuda.stream(st):
         binding.perq_reset_schedule(st)
         assert torch.equal(binding.perq_colabs_mean(xs[0]), want[0])
+
+
+def test_reset_leaves_the_block_statistics_of_other_streams_alone():
+    """A launch whose counters went back to zero under it would leave them off zero, and the next one would skip rows."""
+    torch = _torch()
+    x = torch.randn((30000, 4096), device="cuda").to(torch.bfloat16)
+    want = binding.perq_block_diagnostics(x, None, 128)
+    st, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    got = []
+    for k in range(40):
+        out = torch.full_like(want, -1.0)
+        st.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(st):
+            got.append(binding.perq_block_diagnostics(x, None, 128, out=out))
+        for _ in range(6):
+            binding.perq_reset_schedule(other)
+    torch.cuda.synchronize()
+    assert all(torch.equal(g, want) for g in got)
+    with torch.cuda.stream(st):
+        binding.perq_reset_schedule(st)
+        assert torch.equal(binding.perq_block_diagnostics(x, None, 128), want)
+    torch.cuda.synchronize()
 
 
 @pytest.mark.parametrize("b", [128, 2048])          # (block_kernel, mfma_kernel)
