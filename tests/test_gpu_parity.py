@@ -1622,6 +1622,26 @@ def test_half_tile_kernel_long_and_short_launches_give_the_same_bits(T, d, b, fm
             assert torch.equal(binding.perq_block_diagnostics(x[at], p, b), stats[at]), (kind, at)
 
 
+# a permutation as given, launches of a unit to every workgroup that fits and of one less or more than that or than half of it:
+# the same bits as in two calls, which have other workgroups
+@pytest.mark.parametrize("T,d,b", [(1024, 4096, 32), (1025, 4096, 128), (2047, 4096, 64), (2048, 4096, 512), (2049, 4096, 32), (8193, 512, 128),
+                                   (16384, 512, 128), (16389, 512, 32), (513, 8192, 128), (1024, 8192, 2048), (512, 14336, 512), (257, 28672, 64)])
+def test_half_tile_kernel_launches_of_one_unit_to_a_workgroup(T, d, b):
+    torch = _torch()
+    print(f"[case] one unit to a workgroup T={T} d={d} b={b}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + d + b)
+    x = torch.randn((T, d), device="cuda", generator=g)
+    x[:, torch.randperm(d, device="cuda", generator=g)[:max(1, d // 100)]] *= 1000.0        # (sums that round)
+    x = x.to(torch.bfloat16)
+    perm = torch.randperm(d, device="cuda", generator=g).to(torch.int32)
+    calls = [lambda v, fmt=fmt: binding.perq_permute_rotate_quant(v, perm, b, fmt, algo="mfma") for fmt in ("int4", "mxfp4", "int4_asym")]
+    calls += [lambda v: (binding.perq_permute_rotate_f32(v, perm, b, algo="mfma"),), lambda v: (binding.perq_block_diagnostics(v, perm, b),)]
+    cut = T // 3
+    for call in calls:
+        for whole, head, tail in zip(call(x), call(x[:cut]), call(x[cut:])):
+            assert torch.equal(whole[:cut], head) and torch.equal(whole[cut:], tail)
+
+
 # ---- AUTO's line between the butterflies and the matrix cores ------------------------------------------
 # The matrix unit cuts every term of a sum of eight off at half an ulp of the largest, which butterflies do not: below the line
 # AUTO's outputs are the butterflies', bit for bit, and above it those of the matrix cores.  (T, d, b, pad, permutation, which):
