@@ -1643,6 +1643,23 @@ def test_half_tile_kernel_launches_of_one_unit_to_a_workgroup(T, d, b):
             assert torch.equal(whole[:cut], head) and torch.equal(whole[cut:], tail)
 
 
+# the prepared form of rows wider than 8192 in launches of a unit or two to a workgroup: read, and the bits of the plain call
+@pytest.mark.parametrize("T,d,b", [(520, 9728, 64), (600, 9728, 512), (513, 14336, 512), (700, 14336, 64), (100, 28672, 32), (257, 28672, 512), (64, 32768, 16)])
+@pytest.mark.parametrize("fmt", ["int4", "mxfp4"])
+def test_half_tile_kernel_reads_the_prepared_form_of_few_wide_rows(T, d, b, fmt):
+    torch = _torch()
+    print(f"[case] few wide rows, prepared T={T} d={d} b={b} fmt={fmt}", flush=True)
+    rng = np.random.default_rng(T + d + b)
+    x = binding.bits_to_device(synth.f64_to_bf16_bits(rng.standard_t(4, size=(T, d))))
+    perm = rng.permutation(d).astype(np.int32)
+    perm_t = torch.from_numpy(perm).cuda()
+    form, other = (binding.placement_to_device(binding.perq_perm_prepare(p, b)[0]) for p in (perm, np.roll(perm, 1)))
+    want = binding.perq_permute_rotate_quant(x, perm_t, b, fmt, algo="mfma")
+    got = binding.perq_permute_rotate_quant(x, perm_t, b, fmt, placement=form)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    assert not torch.equal(binding.perq_permute_rotate_quant(x, perm_t, b, fmt, placement=other)[0], want[0])
+
+
 # ---- AUTO's line between the butterflies and the matrix cores ------------------------------------------
 # The matrix unit cuts every term of a sum of eight off at half an ulp of the largest, which butterflies do not: below the line
 # AUTO's outputs are the butterflies', bit for bit, and above it those of the matrix cores.  (T, d, b, pad, permutation, which):
