@@ -196,10 +196,11 @@ perq_status_t quant_entry(const uint16_t* x_bf16, int64_t T, int32_t d, int64_t 
     // 8192: + 1 - 1.5 %), so those stay in the fixed layout (layout::placement_applies, which the
     // tables follow).
     if (prepared != nullptr && perm != nullptr && algo == PERQ_ALGO_AUTO && d >= 4096 && d % 512 == 0 && is_pow2(b) && b >= 16 && b <= 4096) {
-        const Route route = route_of(p, out_kind);
         // [int32 place of the channel of every position][uint16 granule of every slot][uint16 lane tables]
         const int32_t* places = static_cast<const int32_t*>(prepared);
-        if (route != Route::butterfly) p.lane_table = reinterpret_cast<const uint16_t*>(places + d) + d / 8;
+        p.lane_table = reinterpret_cast<const uint16_t*>(places + d) + d / 8;
+        const Route route = route_of(p, out_kind);
+        if (route == Route::butterfly) p.lane_table = nullptr;
         if (route == Route::mfma && layout::placement_applies(d)) {
             p.perm = places;
             p.place = reinterpret_cast<const uint16_t*>(places + d);

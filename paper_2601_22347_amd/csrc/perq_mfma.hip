@@ -1306,12 +1306,15 @@ static bool block_always(const ApplyParams& p) {
 //   T = 93206 109.6 / 116.2: block_kernel's waves are filled to 63 - 87 % there.  Prepared, more than 8192: d = 14336, b = 64, T = 2340
 //   21.7 / 20.9, T = 4681 34.5 / 36.1; d = 28672, T = 1170 24.3 / 24.4, T = 2340 39.3 / 42.1; whole tiles, d = 12288, T = 5461 36.7 / 36.9,
 //   T = 10922 61.2 / 65.0; d = 16384, T = 4096 34.2 / 35.1 (b = 16 34.2 / 32.4), T = 8192 59.3 / 64.1; d = 32768, T = 2048 38.8 / 39.2, T = 4096
-//   66.5 / 69.8.  As given: d = 28672, T = 4681 79.2 / 75.3.  d = 9728, T = 13797 70.0 / 66.0.
+//   66.5 / 69.8.  As given: d = 28672, T = 4681 79.2 / 75.3.  d = 9728, T = 13797 70.0 / 66.0.  Asymmetric INT4 on the 13 and 14 waves of a
+//   row of seven tiles, prepared: d = 28672, b = 16, T = 1500 29.0 / 29.7, T = 2000 35.8 / 37.8, T = 3000 49.2 / 52.6, T = 4500 69.7 / 75.3 (d = 24576, T = 3500
+//   51.2 / 50.4, d = 32768, T = 3200 56.1 / 57.3, T = 1600 33.7 / 33.1; as given d = 28672, T = 3000 58.5 / 55.3).
 constexpr int64_t kNever = INT64_MAX;
 static int64_t small_block_line(const ApplyParams& p, int out_kind) {
     if (p.perm == nullptr) return kNever;
     if (p.d >= 2560 && p.d < kTile) return out_kind != OUT_MXFP4 && (mfma_supports(p) || mfma_takes_ragged(p)) ? (int64_t)3 << 25 : kNever;
     if (p.d < 3 * kTile || !mfma_supports(p)) return kNever;
+    if (out_kind == OUT_INT4_ASYM && p.lane_table != nullptr && p.d > 6 * kTile && p.d < 8 * kTile) return (int64_t)3 << 24;
     return (int64_t)1 << (p.d % kTile == 0 ? 27 : 26);
 }
 

@@ -1701,8 +1701,8 @@ def test_auto_takes_the_butterflies_below_its_line(T, d, b, pad, perm, which):
 
 # ---- the lines between the two matrix-core kernels: the same bits on either side ------------------------
 # Up to b = 64 they form the same sums in the same order, so the number of rows may decide.  (T: the first number of rows that is
-# mfma_kernel's; rows of 2560 .. 4095, also of no multiple of 512, of no whole tile and of whole tiles past 8192.)
-@pytest.mark.parametrize("T,d", [(39322, 2560), (34953, 2880), (32768, 3072), (28087, 3584), (4682, 14336), (2341, 28672), (10923, 12288), (8192, 16384)])
+# mfma_kernel's for some format; rows of 2560 .. 4095, also of no multiple of 512, of no whole tile and of whole tiles past 8192.)
+@pytest.mark.parametrize("T,d", [(39322, 2560), (34953, 2880), (32768, 3072), (28087, 3584), (4682, 14336), (2341, 28672), (1756, 28672), (10923, 12288), (8192, 16384)])
 @pytest.mark.parametrize("b,fmt", [(16, "int4"), (32, "int4_asym"), (64, "fp4_token"), (32, "mxfp4")])
 def test_the_same_bits_on_either_side_of_the_matrix_core_kernels_lines(T, d, b, fmt):
     torch = _torch()
