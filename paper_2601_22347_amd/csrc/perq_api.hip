@@ -261,7 +261,10 @@ extern "C" perq_status_t perq_block_diagnostics(const uint16_t* x_bf16, int64_t 
     // The half-tile kernel where its sums cost nothing: of the four, the largest rotated value is the one that sees the matrix
     // unit (error against 64 bits, this kernel / butterflies: b = 16 1.10, b = 64 1.04, b = 128 - 2048 1.000 - 1.002; b = 32 and other
     // odd powers 0.82 - 0.94, scaled in 64 bits; the sums of a block 0.35 - 1.0).
-    const bool half_tile = perq::block_supports(p) && b != 16 && b != 64;
+    //   Rows of 64 and 128 through a permutation are the butterflies' too: 32 and 16 of them lie in a wave there, and its element reads
+    // meet in the same banks (butterflies / the other, b = 32, 2^23 elements: d = 64 14.0 / 18.3 us, d = 128 10.4 / 11.7, d = 256 9.0 / 9.45, 2^25:
+    // 43.1 / 61.7, 27.9 / 34.0, 25.4 / 22.3; P = I d = 64 24.8 / 16.4; d = 96, a row to a wave, 71.2 / 44.4).
+    const bool half_tile = perq::block_supports(p) && b != 16 && b != 64 && !(perm != nullptr && (d == 64 || d == 128));
     const auto launch = half_tile ? perq::launch_block : perq::launch_butterfly;
     return launch(p, perq::OUT_DIAG, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? PERQ_OK : PERQ_ERR_LAUNCH;
 }
