@@ -1288,15 +1288,21 @@ static bool folds(const ApplyParams& p) { return p.d == kTile / 2 && p.b >= 1024
 //   P = I          d = 9728, b = 512, T = 3449 27.3 / 19.0, T = 13797 89.5 / 62.0; d = 4096, b = 128, T = 32768 55.3 / 53.7; d = 8192, b = 2048,
 //                  T = 2048 15.9 / 11.9, T = 16384 64.7 / 59.6; d = 28672, b = 1024, T = 292 14.3 / 9.9, T = 4681 73.1 / 64.3
 //   a permutation  d = 4096, b = 512, T = 32768 64.2 / 60.9, prepared 65.9 / 60.3; d = 8192, b = 128, T = 1024 13.4 / 8.6, T = 16384 64.5 / 57.3,
-//                  prepared 62.5 / 57.3; d = 8192, b = 2048, T = 1024 14.9 / 10.2, T = 16384 68.9 / 65.9; d = 9728, b = 128, T = 13797
-//                  80.8 / 71.1, prepared 76.1 / 71.2; d = 14336, b = 512, T = 9362 88.9 / 70.6, prepared 84.1 / 70.4
+//                  prepared 62.5 / 57.3; d = 9728, b = 128, T = 13797 80.8 / 71.1, prepared 76.1 / 71.2; d = 14336, b = 512, T = 9362 88.9 / 70.6,
+//                  prepared 84.1 / 70.4
 //   and not        d = 4096, b = 2048, T = 2048 8.1 / 9.9, T = 32768 57.8 / 67.6; d = 3072, b = 1024, T = 43690 64.0 / 69.5;
 //                  prepared: d = 12288, b = 128, T = 10922 67.0 / 69.3; d = 14336, b = 128, T = 9362 62.7 / 67.7, b = 2048 67.4 / 79.3; d = 28672,
 //                  b = 256, T = 4681 77.9 / 83.9 (its prepared placement is made for this kernel's reads)
+// From b = 1024 on with a permutation none but d = 1024 is, though d = 8192, b = 2048 would gain (T = 1024 14.9 / 10.2, T = 16384 68.9 / 65.9).  This kernel
+// contracts the middle bits of a position first and adds sub-blocks of 16 last; where a block begins with its largest channels, as
+// the calibrated permutations fill it, large values then meet in the last four roundings only, and in all but five of eleven there:
+// error against 64 bits of a row's step 4.7e-8 / 5.7e-8 (d = 5120, b = 1024 4.4 / 5.0), of the fp32 output 5.98 / 6.08 (4.34 / 4.37).  With P = I and rows
+// in the order that the model has them both errors are equal (ratio of that kernel to this one 0.98 - 1.006); rows that come
+// permuted already have the ratios of the permutation there too, 1.10 - 1.27 for the step.
 static bool block_always(const ApplyParams& p) {
     if (!block_supports(p) || p.b <= 64 || mfma_takes_ragged(p)) return false;
     if (p.perm == nullptr) return true;
-    if (p.b >= 1024) return p.d <= 1024 || (p.d > kTile && p.d <= 2 * kTile);
+    if (p.b >= 1024) return p.d <= 1024;
     if (p.b == 512) return true;
     return p.d < (p.b == 128 ? 3 * kTile : 4 * kTile + 1);
 }
