@@ -61,7 +61,7 @@ struct MfmaGeom {
     uint32_t ctr_set;    // which set of ticket counters this launch draws from
     uint32_t dynamic;    // 1: units dealt at run time through the ticket counters; 0: fixed stride
     uint32_t fold_mask;  // rows folded into 4096-wide ones: width of a real row - 1; else all ones
-    int32_t row_per_half; // 1: folded rows of 2048 in the high-K modes, one real row per half-wave
+    int32_t row_per_half; // 1: folded rows, for the extremes of a row: one real row (of 2048) per half-wave
 };
 
 // Ticket counters of the run-time row schedule (perq_schedule.h): kSets sets of kQueues counters,
@@ -1189,7 +1189,7 @@ hipError_t launch_mfma_st(const ApplyParams& p, uint32_t fold_mask, hipStream_t 
     g.ctr_set = 0;
     g.dynamic = 0;
     g.fold_mask = fold_mask;
-    g.row_per_half = fold_mask != 0xFFFFFFFFu;          // (rows of 2048, see folds())
+    g.row_per_half = fold_mask != 0xFFFFFFFFu;          // (formats that ask for extremes fold rows of 2048 only, see folds())
 
     const int64_t ngroups = (p.T + g.rows - 1) / g.rows;
     // (one of each of the forms that launch_mfma's callers reach: route_of, matrix_core_route)
@@ -1273,9 +1273,12 @@ static bool mfma_takes_ragged(const ApplyParams& p) {
 
 // Rows of 2048 stored back to back are folded into 4096-wide ones (a wave's tile is 4096 wide whatever d is): codes, e8m0
 // bytes and fp32 outputs of consecutive rows are contiguous, so only the operand addresses through `perm` know about it, and
-// the extremes of a row, which is one half-wave.  A last row that does not fill a 4096-wide one takes a second, unfolded
-// launch.
-static bool folds(const ApplyParams& p) { return p.d == kTile / 2 && p.b >= 1024 && p.ldx == p.d && p.T >= 2; }
+// the extremes of a row, which is one half-wave.  So are rows of 1024 where nobody asks for extremes.  Last rows that do not fill
+// a 4096-wide one take a second, unfolded launch.
+static bool folds(const ApplyParams& p, int out_kind) {
+    if (p.b < 1024 || p.ldx != p.d || p.T < kTile / p.d) return false;
+    return p.d == kTile / 2 || (p.d == kTile / 4 && (out_kind == OUT_MXFP4 || out_kind == OUT_F32));
+}
 
 // ---- which kernel takes a call -----------------------------------------------------------------------
 // Launches back to back on one GPU, INT4 where no format is named, us; "prepared" where a permutation came with its form.
@@ -1293,16 +1296,16 @@ static bool folds(const ApplyParams& p) { return p.d == kTile / 2 && p.b >= 1024
 //   and not        d = 4096, b = 2048, T = 2048 8.1 / 9.9, T = 32768 57.8 / 67.6; d = 3072, b = 1024, T = 43690 64.0 / 69.5;
 //                  prepared: d = 12288, b = 128, T = 10922 67.0 / 69.3; d = 14336, b = 128, T = 9362 62.7 / 67.7, b = 2048 67.4 / 79.3; d = 28672,
 //                  b = 256, T = 4681 77.9 / 83.9 (its prepared placement is made for this kernel's reads)
-// From b = 1024 on with a permutation none but d = 1024 is, though d = 8192, b = 2048 would gain (T = 1024 14.9 / 10.2, T = 16384 68.9 / 65.9).  This kernel
+// From b = 1024 on with a permutation none is, though d = 8192, b = 2048 would gain (T = 1024 14.9 / 10.2, T = 16384 68.9 / 65.9).  This kernel
 // contracts the middle bits of a position first and adds sub-blocks of 16 last; where a block begins with its largest channels, as
 // the calibrated permutations fill it, large values then meet in the last four roundings only, and in all but five of eleven there:
-// error against 64 bits of a row's step 4.7e-8 / 5.7e-8 (d = 5120, b = 1024 4.4 / 5.0), of the fp32 output 5.98 / 6.08 (4.34 / 4.37).  With P = I and rows
+// error against 64 bits of a row's step 4.7e-8 / 5.7e-8 (d = 5120, b = 1024 4.4 / 5.0), of the fp32 output 5.98 / 6.08 (4.34 / 4.37; d = b = 1024 1.009 times).  With P = I and rows
 // in the order that the model has them both errors are equal (ratio of that kernel to this one 0.98 - 1.006); rows that come
 // permuted already have the ratios of the permutation there too, 1.10 - 1.27 for the step.
 static bool block_always(const ApplyParams& p) {
     if (!block_supports(p) || p.b <= 64 || mfma_takes_ragged(p)) return false;
     if (p.perm == nullptr) return true;
-    if (p.b >= 1024) return p.d <= 1024;
+    if (p.b >= 1024) return false;
     if (p.b == 512) return true;
     return p.d < (p.b == 128 ? 3 * kTile : 4 * kTile + 1);
 }
@@ -1475,7 +1478,7 @@ Route route_of(const ApplyParams& p, int out_kind) {
 hipError_t launch_mfma(const ApplyParams& p0, int out_kind, hipStream_t stream) {
     ApplyParams p = p0;
     uint32_t fold_mask = 0xFFFFFFFFu;
-    if (folds(p)) {
+    if (folds(p, out_kind)) {
         const int64_t per_tile = kTile / p.d, rest = p.T % per_tile;
         if (rest != 0) {
             // the last rows, too few for a 4096-wide one: a launch of their own, unfolded (folds() says no

@@ -1787,6 +1787,23 @@ def test_large_blocks_that_begin_with_their_largest_channels(d, b):
     assert error["auto"] == error["mfma"] <= 1.03 * 0.91 * error["butterfly"]
 
 
+# d = b = 1024 with a permutation: four rows to a 4096-wide one for MXFP4 and fp32 output, one to a tile for the formats with a step
+# per token, rows left over and rows that lie apart; one kernel by name for all of them
+@pytest.mark.parametrize("T,pad", [(1, 0), (3, 0), (4, 0), (5, 0), (1027, 0), (9, 64)])
+def test_rows_of_one_block_of_1024_folded_and_not(T, pad):
+    torch = _torch()
+    rng = np.random.default_rng(T + pad)
+    bits = synth.f64_to_bf16_bits(rng.standard_t(4, size=(T, 1024)))
+    perm = rng.permutation(1024).astype(np.int32)
+    for fmt in ("int4", "mxfp4", "int4_asym", "fp4_token"):
+        assert_parity(bits, perm, 1024, fmt, algo="mfma", ldx=1024 + pad if pad else None, label="one block of 1024")
+    x, p = binding.bits_to_device(bits), torch.from_numpy(perm).cuda()
+    y = binding.perq_permute_rotate_f32(x, p, 1024, algo="mfma")
+    assert torch.equal(binding.perq_permute_rotate_f32(x[T // 2:], p, 1024, algo="mfma"), y[T // 2:])
+    if T >= 4:
+        assert torch.equal(binding.perq_permute_rotate_f32(x, p, 1024), y) and torch.equal(*(binding.perq_permute_rotate_quant(x, p, 1024, "mxfp4", algo=a)[0] for a in ("auto", "mfma")))
+
+
 # ---- outputs under a mode of the dispatcher ---------------------------------------------------------------
 def test_a_mode_of_the_dispatcher_sees_the_buffers_of_a_call():
     torch = _torch()
