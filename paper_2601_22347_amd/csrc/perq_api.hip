@@ -259,7 +259,7 @@ extern "C" perq_status_t perq_block_diagnostics(const uint16_t* x_bf16, int64_t 
     if (!perq::is_pow2(b)) return PERQ_ERR_UNSUPPORTED;
     p.y = out;
     // The half-tile kernel where its sums cost nothing: of the four, the largest rotated value is the one that sees the matrix
-    // unit (error against 64 bits, this kernel / butterflies: b = 16 1.10, b = 64 1.04, b = 128 - 2048 1.000 - 1.002; b = 32 and other
+    // unit (error against 64 bits, this kernel / butterflies: b = 16 1.10, b = 64 1.04, b = 256 1.003, b = 1024 1.001; b = 32 and other
     // odd powers 0.82 - 0.94, scaled in 64 bits; the sums of a block 0.35 - 1.0).
     //   Rows of 64 and 128 through a permutation are the butterflies' too: 32 and 16 of them lie in a wave there, and its element reads
     // meet in the same banks (butterflies / the other, b = 32, 2^23 elements: d = 64 14.0 / 18.3 us, d = 128 10.4 / 11.7, d = 256 9.0 / 9.45, 2^25:

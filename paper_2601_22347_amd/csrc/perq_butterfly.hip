@@ -1,5 +1,6 @@
 // Shuffle-butterfly kernel for X -> quantize(XP R~): every shape the C ABI accepts.  AUTO takes it for
-// short launches and for widths that the matrix cores do not get at any length (matrix_core_line in perq_mfma.hip).
+// short launches and for widths that the matrix cores do not get at any length (matrix_core_line in perq_mfma.hip); the block
+// statistics take it for b = 16, 64 and from 4096 on (perq_api.hip).
 //
 // Layout.  A row of d = 32*nt elements is spread over nt lanes; lane t owns the 32 contiguous
 // positions [32t, 32t+32) of the permuted row.  Index bits 0..4 are therefore in registers,

@@ -1,4 +1,4 @@
-// Matrix-core kernel for X -> quantize(XP R~) with tiles of 4096: large blocks (b = 1024 .. 4096), long launches through a
+// Matrix-core kernel for X -> quantize(XP R~) with tiles of 4096: large blocks (b = 1024 and 2048 with a permutation, 4096), long launches through a
 // permutation on rows wider than 8192, some on 2560 .. 4095 and on ragged rows (staged at a pitch of whole load
 // instructions); block_kernel (perq_block.hip), with half the tile, has the rest.  Which takes what: route_of below.
 //
