@@ -1601,7 +1601,7 @@ def test_half_tile_kernel_at_the_edges_of_its_shapes(T, d, b, fmt):
 
 # as above, in launches long enough for the run-time schedule (units of two and more to every workgroup) and its limit on
 # waves, against launches of a few rows: (.., 14336, 64) is the other matrix-core kernel's from 2^26 elements on, same bits
-@pytest.mark.parametrize("T,d,b,fmt,perms", [(70001, 512, 128, "int4", "ni"), (14001, 3072, 32, "int4_asym", "ni"), (2101, 14336, 64, "int4", "ni"),
+@pytest.mark.parametrize("T,d,b,fmt,perms", [(70001, 512, 128, "int4", "ni"), (14001, 3072, 32, "int4_asym", "ni"), (2101, 14336, 64, "int4", "ni"), (1537, 16384, 64, "int4", "ni"),
                                              (50003, 1536, 512, "int4_asym", "ni"), (14001, 3072, 64, "mxfp4", "ni"),
                                              (9001, 4096, 512, "fp4_token", "nip"), (5003, 8192, 2048, "mxfp4", "nip"), (4001, 8192, 32, "int4", "nip"),
                                              (1501, 16384, 512, "int4", "nip"), (4701, 14336, 64, "int4", "ip"), (1101, 28672, 512, "mxfp4", "nip")])
